@@ -142,14 +142,28 @@ def group_matrix_bytes(m, V):
     return -(-m // 4096) * (1 << bits) * 4
 
 
+def entry_format(n, V, kb):
+    """(bytes, keys held) of the table's probe index entries: for 32-bit keys
+    a field of bit_length((2^32 - 1) // V) bits per key beside a 4-bit code, in
+    4 bytes if they hold 2 + 2n/V keys, else 8; 64-bit keys 16 bytes, 1 key."""
+    if kb == 8:
+        return 16, 1
+    qb = max(((1 << 32) - 1) // V, 1).bit_length()
+    cap = min(28 // qb, 13)
+    if cap >= 3 and (cap - 2) * V >= 2 * n:
+        return 4, cap
+    return 8, min(60 // qb, 13)
+
+
 def index_bytes(name, n, m, V, kb, sum_tail):
     """Bytes the kernels move with the per-bucket probe index: the probe reads
-    one 16-byte entry per query and only the keys the entry does not account
-    for (sum_tail); the per-bin build also writes 16 bytes per bucket."""
+    one entry per query and only the keys the entry does not account for
+    (sum_tail); the per-bin build also writes an entry per bucket."""
+    eb, _ = entry_format(n, V, kb)
     if name == "probe_count":
-        return m * kb + m * 16 + kb * sum_tail + m * 4
+        return m * kb + m * eb + kb * sum_tail + m * 4
     if name == "v2_local_build":
-        return 2 * n * (kb + 4) + (V + 1) * 4 + V * 16
+        return 2 * n * (kb + 4) + (V + 1) * 4 + V * eb
     return None
 
 
@@ -538,19 +552,25 @@ def main():
     offl = off.to(torch.int64) & 0xFFFFFFFF
     blen = offl[h + 1] - offl[h]
     sum_len = int(blen.sum().item())
-    # a bucket of up to 3 keys is held whole in its index entry; a longer one
-    # holds its first key, that key's count and a 24-bit filter of its other
-    # keys: a query equal to the first key, or whose filter bit no other key
-    # of the bucket sets, needs nothing more; other queries read the rest of
-    # the bucket (a bucket of more than 32 keys is counted as read whole)
+    # a bucket of up to `cap` keys is held whole in its index entry; a longer
+    # one holds its first key, that key's count and a filter of its other keys'
+    # quotients: a query equal to the first key, or whose filter bit no other
+    # key of the bucket sets, needs nothing more; other queries read the rest
+    # of the bucket (a bucket of more than 32 keys is counted as read whole)
+    ebytes, cap = entry_format(n, V, kb)
+    qbits = max(((1 << 32) - 1) // V, 1).bit_length()
+    nf = min(8 * ebytes - 12 - qbits, 32)
     eku = ek.to(torch.int64) & 0xFFFFFFFF
     qu = dq.to(torch.int64) & 0xFFFFFFFF
     first = eku[offl[h].clamp(max=n - 1)]
-    reads = (blen > 3) & (qu != first)
+    reads = (blen > cap) & (qu != first)
     sel = torch.nonzero(reads).squeeze(1)
     if sel.numel():
-        def fbit(x):  # the entry's filter bit of a key (multiplicative hash)
-            return (((x * 0x9E3779B1) & 0xFFFFFFFF) * 24) >> 32
+        def fbit(x):  # the entry's filter bit of a key's quotient
+            x = ((x ^ (x >> 16)) * 0x85EBCA6B) & 0xFFFFFFFF
+            x = ((x ^ (x >> 13)) * 0xC2B2AE35) & 0xFFFFFFFF
+            x = (x ^ (x >> 16)) // V
+            return (((x * 0x9E3779B1) & 0xFFFFFFFF) * nf) >> 32
         st, ln = offl[h[sel]], blen[sel]
         pos = st[:, None] + torch.arange(1, int(ln.max().item()), device=st.device)[None, :]
         kk = eku[pos.clamp(max=n - 1)]

@@ -68,26 +68,25 @@ typedef struct hg_build_opts {
                           choose from N and V.                                 */
     uint32_t block;    /* V1: threads per block, 0 = 256                        */
     int32_t no_index;  /* V2 also writes a probe index beside the CSR arrays:
-                          one 16-byte entry per bucket holding its length and
-                          either all its keys (up to three 32-bit keys) or its
-                          start and first key (32-bit keys: with that key's
-                          count in the bucket and a 24-bit filter of the
-                          bucket's other keys; 64-bit keys: a filter of all
-                          keys in place of the first key when the bucket
-                          holds two or more), so most probes take one
-                          random read.  Buckets of more than 32 entries get a
-                          key-run summary instead (distinct keys ascending,
-                          each with the end of its group of ids), so probes
-                          and intersections of skewed tables cost a binary
-                          search instead of a scan.  The whole index is built
-                          on the device, in stream order: the build never
-                          waits for it.  Its arrays (16 bytes per bucket of
-                          the range capacity, and key + 8 bytes per entry of
-                          the key capacity for the summary) are allocated by
-                          hg_table_create, or by hg_build when it writes the
-                          index.  1 = skip the index (probes then read
-                          offsets and scan the edge array).  Results are
-                          identical either way.  V1 never writes it.         */
+                          one entry per bucket (32-bit keys: 4 or 8 bytes,
+                          chosen from N and V, that identify every key of all
+                          but the longest buckets by its hash quotient;
+                          64-bit keys: 16 bytes, the bucket's length, start
+                          and its key or, of two or more, a filter), so most
+                          probes take one random read.  Buckets of more than
+                          32 entries get a key-run summary as well (distinct
+                          keys ascending, each with the end of its group of
+                          ids), so probes and intersections of skewed tables
+                          cost a binary search instead of a scan.  The whole
+                          index is built on the device, in stream order: the
+                          build never waits for it.  Its arrays (8 or, 64-bit
+                          keys, 16 bytes per bucket of the range capacity, and
+                          key + 8 bytes per entry of the key capacity for the
+                          summary) are allocated by hg_table_create, or by
+                          hg_build when it writes the index.  1 = skip the
+                          index (probes then read offsets and scan the edge
+                          array).  Results are identical either way.  V1 never
+                          writes it.                                         */
     int32_t any_order; /* V2: 1 = the order of ids inside a bucket is
                           unspecified (as in the paper), which lets the
                           partition passes rank without ballots and skips the

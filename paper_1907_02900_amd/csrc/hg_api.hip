@@ -32,7 +32,8 @@ struct hg_table {
     uint32_t* offsets = nullptr;
     uint32_t* ids = nullptr;
     void* keys = nullptr;
-    uint4* head = nullptr;  // V_cap per-bucket probe index entries
+    void* head = nullptr;   // V_cap per-bucket probe index entries
+    HeadFmt fmt{};          // of the last build that wrote head
     bool has_head = false;  // the last build wrote head
     RunsDev runs{};         // key runs of long buckets: n_cap entries per array
     // erasing keys: live entries per bucket, scratch flags, live entry count
@@ -85,18 +86,19 @@ hg_status read_u64(const uint64_t* d, uint64_t* h, hipStream_t s) {
         if (st__ != HG_OK) return st__;      \
     } while (0)
 
-// The probe index (16 bytes per bucket of the range capacity) and the key-run
-// arrays of long buckets (sized for the worst case: every entry in a long
+// The probe index (up to 8 bytes per bucket of the range capacity, 64-bit keys
+// 16) and the key-run arrays of long buckets (sized for the worst case: every entry in a long
 // bucket), allocated once per table.
 hg_status ensure_index(hg_table* t) {
     if (t->head) return HG_OK;
     const size_t nc = t->n_cap ? t->n_cap : 1;
     const size_t ks = key_size(t->key_bits);
-    HG_CALL(hipMalloc((void**)&t->head, t->V_cap * sizeof(uint4)));
+    const size_t hb = t->V_cap * head_bytes_max(t->key_bits);
+    HG_CALL(hipMalloc(&t->head, hb));
     HG_CALL(hipMalloc(&t->runs.run_key, nc * ks));
     HG_CALL(hipMalloc((void**)&t->runs.run_end, nc * 4));
     HG_CALL(hipMalloc((void**)&t->runs.kperm, nc * 4));
-    t->bytes += t->V_cap * sizeof(uint4) + nc * (ks + 8);
+    t->bytes += hb + nc * (ks + 8);
     return HG_OK;
 }
 
@@ -149,6 +151,7 @@ hg_status build_into(hg_table* t, const void* keys, uint64_t n, uint64_t V, uint
     t->seed = seed;
     t->variant = variant;
     t->has_head = want_head;
+    t->fmt = ix.fmt;
     t->has_len = false;
     t->live = n;
     return HG_OK;
@@ -198,7 +201,10 @@ TableDev dev_view(const hg_table* t) {
     d.V = t->V;
     d.seed = t->seed;
     d.head = t->has_head ? t->head : nullptr;
-    if (t->has_head) d.runs = t->runs;
+    if (t->has_head) {
+        d.runs = t->runs;
+        d.fmt = t->fmt;
+    }
     if (t->has_len) d.len = t->len;
     return d;
 }
@@ -215,7 +221,7 @@ hg_status check_pairs_args(const hg_table* t, const void* d_queries, uint64_t m,
 }
 
 // Probe-Standard pairs in two passes over a workspace of probe_ws_bytes(m)
-// (plus m bytes with `held`): per-query counts, their exclusive scan (64-bit
+// (plus 2m bytes with `held`): per-query counts, their exclusive scan (64-bit
 // positions), the total read back, then each query writes its pairs at its
 // position.  With `held` the counting pass also leaves, per query, the
 // matching keys of a bucket held whole in its index entry, so the pairs pass
@@ -228,7 +234,7 @@ hg_status probe_pairs_into(const hg_table* t, const void* d_queries, uint64_t m,
     uint32_t* counts = c.take<uint32_t>(m);
     uint64_t* pos = c.take<uint64_t>(m + 1);
     void* scan_ws = c.take<char>(scan_ws_bytes(m));
-    uint8_t* held = with_held && t->key_bits == 32 && t->has_head ? c.take<uint8_t>(m) : nullptr;
+    uint16_t* held = with_held && t->key_bits == 32 && t->has_head ? c.take<uint16_t>(m) : nullptr;
     TableDev d = dev_view(t);
     hipError_t e = t->key_bits == 32
                        ? run_probe_counts<uint32_t>(d, (const uint32_t*)d_queries, m, counts, nullptr, stream, held)
@@ -849,7 +855,7 @@ hg_status hg_probe_pairs(const hg_table* t, const void* d_queries, uint64_t m,
         return HG_OK;
     }
     Workspace ws(stream);
-    HG_CALL(ws.get(probe_ws_bytes(m) + align_up(m, 256)));
+    HG_CALL(ws.get(probe_ws_bytes(m) + align_up(2 * m, 256)));
     return probe_pairs_into(t, d_queries, m, d_build_ids, d_probe_ids, capacity, h_total, ws.p,
                             stream, true);
 }

@@ -250,12 +250,12 @@ __device__ __forceinline__ void bin_range(const BTable<Key>* __restrict__ tabs, 
     }
 }
 
-template <typename Key>
+template <typename Key, bool ANY>
 __global__ __launch_bounds__(kLocalThreads) void k_blocal(
     const BTable<Key>* __restrict__ tabs, BPrefix pre, uint32_t bins,
     const uint32_t* __restrict__ mat, const Key* __restrict__ rkeys,
     const uint32_t* __restrict__ rids, uint32_t* __restrict__ heavy_list,
-    uint32_t* __restrict__ heavy_count, bool any_order) {
+    uint32_t* __restrict__ heavy_count) {
     extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t gb = blockIdx.x;
     if (gb >= bins) return;
@@ -271,11 +271,12 @@ __global__ __launch_bounds__(kLocalThreads) void k_blocal(
     const uint32_t NB = 1u << tb.k, v0 = lb << tb.k;
     const uint32_t nb = (tb.V - v0 < NB) ? tb.V - v0 : NB;
     if (tb.kind == kPartitioned)
-        light_bin_body<Key>(rkeys + start, rids + start, 0u, L, start - tb.key_base, v0, tb.k, nb,
-                            tb.hp, tb.offsets, IndexOut{}, tb.ids, tb.ekeys, smem, any_order);
+        light_bin_body<Key, ANY, 0>(rkeys + start, rids + start, 0u, L, start - tb.key_base, v0,
+                                    tb.k, nb, tb.hp, tb.offsets, IndexOut{}, tb.ids, tb.ekeys,
+                                    smem);
     else
-        light_bin_body<Key>(tb.keys, nullptr, 0u, L, 0u, v0, tb.k, nb, tb.hp, tb.offsets, IndexOut{},
-                            tb.ids, tb.ekeys, smem, any_order);
+        light_bin_body<Key, ANY, 0>(tb.keys, nullptr, 0u, L, 0u, v0, tb.k, nb, tb.hp, tb.offsets,
+                                    IndexOut{}, tb.ids, tb.ekeys, smem);
 }
 
 template <typename Key>
@@ -553,10 +554,11 @@ struct BatchPlan : BatchPlanBase {
             HG_TRY(part_items == 8 ? enqueue_partition<8>(pre, s) : enqueue_partition<16>(pre, s));
         }
         if (bins) {
-            hipLaunchKernelGGL(k_blocal<Key>, dim3(bins), dim3(kLocalThreads),
+            const auto local = any_order ? k_blocal<Key, true> : k_blocal<Key, false>;
+            hipLaunchKernelGGL(local, dim3(bins), dim3(kLocalThreads),
                                light_smem<Key>(max_k), s, (const BTable<Key>*)d_tabs, pre, bins,
                                (const uint32_t*)d_mat, (const Key*)d_rkeys,
-                               (const uint32_t*)d_rids, d_heavy, heavy_count, any_order);
+                               (const uint32_t*)d_rids, d_heavy, heavy_count);
             HG_TRY(hipGetLastError());
             const uint32_t hgrid = bins < 256 ? bins : 256;
             hipLaunchKernelGGL(k_bheavy<Key>, dim3(hgrid), dim3(kLocalThreads),
@@ -646,7 +648,9 @@ static hipError_t set_batch_smem() {
                                    hipFuncAttributeMaxDynamicSharedMemorySize, lim));
         HG_TRY(hipFuncSetAttribute((const void*)k_bhist<Key, 8>,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, lim));
-        HG_TRY(hipFuncSetAttribute((const void*)k_blocal<Key>,
+        HG_TRY(hipFuncSetAttribute((const void*)k_blocal<Key, true>,
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, lim));
+        HG_TRY(hipFuncSetAttribute((const void*)k_blocal<Key, false>,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, lim));
         HG_TRY(hipFuncSetAttribute((const void*)k_bheavy<Key>,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, lim));
@@ -951,7 +955,7 @@ struct STable {
     uint32_t* offsets = nullptr;
     uint32_t* ids = nullptr;
     void* keys = nullptr;
-    uint4* head = nullptr;   // probe index (tables built by a launch of their own)
+    void* head = nullptr;    // probe index (tables built by a launch of their own)
     RunsDev runs{};          // key runs of long buckets (with head)
     bool has_index = false;
     uint64_t bytes = 0;
@@ -1067,7 +1071,7 @@ struct Server {
         t.ids = c.take<uint32_t>(nn);
         t.keys = c.take<char>(nn * ks);
         if (t.has_index) {
-            t.head = c.take<uint4>(t.V);
+            t.head = c.take<char>(t.V * head_fmt(t.n, t.V, t.key_bits).bytes);
             t.runs.run_key = c.take<char>(nn * ks);
             t.runs.run_end = c.take<uint32_t>(nn);
             t.runs.kperm = c.take<uint32_t>(nn);
@@ -1379,6 +1383,7 @@ struct Server {
                 TableDev d{t.offsets, t.ids, t.keys, t.n, t.V, t.seed};
                 if (t.has_index) {
                     d.head = t.head;
+                    d.fmt = head_fmt(t.n, t.V, kb);
                     d.runs = t.runs;
                 }
                 e = kb == 32 ? run_probe_counts<uint32_t>(d, (const uint32_t*)rq0.data, rq0.count,

@@ -160,9 +160,9 @@ __global__ __launch_bounds__(kLocalThreads) void k_coll_groups(
     }
     __syncthreads();
     const uint32_t k = NBk <= 1 ? 0u : 32u - __clz(NBk - 1);
-    light_bin_body_by<Key>(
+    light_bin_body_by<Key, false, 0>(
         keys + key0, nullptr, key0, L, key0, 0u, k, NBk,
-        [&](Key key, uint32_t e) {
+        [&](Key key, uint32_t e, uint32_t&) {
             uint32_t a = 0, b = ns;  // the last set of the window starting at or before e
             while (b - a > 1) {
                 const uint32_t m = (a + b) >> 1;
@@ -174,7 +174,7 @@ __global__ __launch_bounds__(kLocalThreads) void k_coll_groups(
             const uint32_t V = (uint32_t)gbkt[a + 1] - gbkt[a];
             return (uint32_t)gbkt[a] + (set_hash<Key>(key, seed) & (V - 1u));
         },
-        offsets + B0, IndexOut{}, ids, ekeys, smem, false);
+        offsets + B0, IndexOut{}, ids, ekeys, smem);
 }
 
 template <typename Key>

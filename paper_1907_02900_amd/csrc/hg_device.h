@@ -27,7 +27,7 @@ struct HashParams {
     uint64_t seed;   // low 32 bits are XOR-ed into the key
     uint32_t range;  // V = d, 1 <= V < 2^32
     uint32_t magic;  // m - 2^32
-    uint32_t shift;  // l - 1
+    uint32_t shift;  // l - 1 (log2 V when V is a power of two)
     uint32_t pow2;   // V is a power of two (V = 1 included): a mod V = a & (V - 1)
 };
 
@@ -42,6 +42,19 @@ __host__ __device__ __forceinline__ uint32_t mod_u32(uint32_t a, const HashParam
     // floor((a + t) / 2^l) without overflowing 32 bits (t <= a)
     const uint32_t q = (((a - t) >> 1) + t) >> p.shift;
     return a - q * p.range;
+}
+
+// floor(a / d) and a mod d
+__host__ __device__ __forceinline__ uint32_t divmod_u32(uint32_t a, const HashParams& p,
+                                                        uint32_t& r) {
+    if (p.pow2) {
+        r = a & (p.range - 1u);
+        return a >> p.shift;
+    }
+    const uint32_t t = mulhi32(a, p.magic);
+    const uint32_t q = (((a - t) >> 1) + t) >> p.shift;
+    r = a - q * p.range;
+    return q;
 }
 
 __host__ __device__ __forceinline__ uint32_t fmix32(uint32_t x) {
@@ -85,6 +98,7 @@ inline HashParams make_hash_params(uint64_t range, uint64_t seed) {
     p.range = (uint32_t)range;
     if ((range & (range - 1)) == 0) {
         p.pow2 = 1;
+        while ((1ull << p.shift) < range) ++p.shift;
         return p;
     }
     uint32_t l = 0;
@@ -125,6 +139,12 @@ struct KeyTraits<uint32_t> {
     static inline Params make(uint64_t range, uint64_t seed) { return make_hash_params(range, seed); }
     __host__ __device__ static __forceinline__ uint32_t bucket(uint32_t k, const Params& p) {
         return mod_u32(fmix32(k ^ (uint32_t)p.seed), p);
+    }
+    // bucket h and quotient floor(fmix32(k ^ seed) / V): fmix32 is a
+    // bijection, so the pair identifies the key
+    __host__ __device__ static __forceinline__ uint32_t quotient(uint32_t k, const Params& p,
+                                                                 uint32_t& h) {
+        return divmod_u32(fmix32(k ^ (uint32_t)p.seed), p, h);
     }
 };
 

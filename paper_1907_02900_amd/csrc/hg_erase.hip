@@ -12,8 +12,8 @@
 //      stays stable: ids keep their order inside the bucket), sets its new
 //      length and rewrites its probe index entry.  A bucket still longer
 //      than kRunBucket loses its key runs (R = 0 in its entry) and is scanned by probes.
-// Readers take the length into account: the index entry carries the live end,
-// intersections skip stale slots of the walked table, and an export writes the
+// Readers take the length into account: probes that go past the index entry
+// bound the bucket by it, intersections skip stale slots of the walked table, and an export writes the
 // compacted CSR of the live entries.
 #include "hg_v2_device.h"
 
@@ -62,7 +62,7 @@ __device__ __forceinline__ uint32_t compact_bucket(uint64_t h, const uint32_t* _
                                                    Key* __restrict__ ekeys,
                                                    uint32_t* __restrict__ ids,
                                                    uint8_t* __restrict__ dead,
-                                                   uint4* __restrict__ head) {
+                                                   const IndexOut& ix) {
     const uint32_t lo = off[h], L = len[h];
     uint32_t w = lo;
     for (uint32_t p = lo; p < lo + L; ++p) {
@@ -78,12 +78,10 @@ __device__ __forceinline__ uint32_t compact_bucket(uint64_t h, const uint32_t* _
     }
     const uint32_t nl = w - lo;
     len[h] = nl;
-    uint4 e = head_entry<Key>(lo, w, ekeys + lo);
-    if (nl > kRunBucket) {  // no key runs any more (R = 0): probes scan the bucket
-        e.z = 0;
-        e.w = 0;
-    }
-    head[h] = e;
+    if (nl > kRunBucket)  // no key runs any more (R = 0): probes scan the bucket
+        put_long<Key>(ix, (uint32_t)h, nl, lo, 0u, ekeys[lo], 0u);
+    else
+        put_short<Key>(ix, (uint32_t)h, lo, w, ekeys + lo);
     return L - nl;
 }
 
@@ -99,7 +97,7 @@ __global__ __launch_bounds__(kT) void k_erase_compact(uint64_t V, const uint32_t
                                                       uint32_t* __restrict__ ids,
                                                       uint8_t* __restrict__ dead,
                                                       uint8_t* __restrict__ touched,
-                                                      uint4* __restrict__ head,
+                                                      IndexOut ix,
                                                       unsigned long long* __restrict__ removed) {
     __shared__ unsigned long long red[kT / kWave];
     unsigned long long gone = 0;
@@ -113,13 +111,13 @@ __global__ __launch_bounds__(kT) void k_erase_compact(uint64_t V, const uint32_t
         const uint32_t word[4] = {f.x, f.y, f.z, f.w};
         for (int i = 0; i < 16; ++i)
             if ((word[i >> 2] >> (8 * (i & 3))) & 0xffu)
-                gone += compact_bucket<Key>(g * 16 + i, off, len, ekeys, ids, dead, head);
+                gone += compact_bucket<Key>(g * 16 + i, off, len, ekeys, ids, dead, ix);
     }
     // the last V % 16 buckets one by one
     for (uint64_t h = groups * 16 + t0; h < V; h += stride) {
         if (!touched[h]) continue;
         touched[h] = 0;
-        gone += compact_bucket<Key>(h, off, len, ekeys, ids, dead, head);
+        gone += compact_bucket<Key>(h, off, len, ekeys, ids, dead, ix);
     }
     gone = wave_sum64(gone);
     if (lane_id() == 0) red[threadIdx.x / kWave] = gone;
@@ -159,7 +157,7 @@ hipError_t init_lengths(const uint32_t* offsets, uint64_t V, uint32_t* len, hipS
 
 template <typename Key>
 hipError_t run_erase(const TableDev& t, uint32_t* len, uint8_t* dead, uint8_t* touched,
-                     uint4* head, const Key* del, uint64_t m, unsigned long long* d_removed,
+                     void* head, const Key* del, uint64_t m, unsigned long long* d_removed,
                      hipStream_t s) {
     auto hp = KeyTraits<Key>::make(t.V, t.seed);
     if (m) {
@@ -169,10 +167,14 @@ hipError_t run_erase(const TableDev& t, uint32_t* len, uint8_t* dead, uint8_t* t
         HG_TRY(hipGetLastError());
     }
     HG_PROF("erase_compact", s);
+    IndexOut ix{};
+    ix.head = head;
+    ix.fmt = t.fmt;
+    ix.hp = make_hash_params(t.V, t.seed);
     const uint32_t g16 = grid_of(ceil_div(t.V, 16));
     const uint32_t cb = g16 < kCompactBlocks ? g16 : kCompactBlocks;
     hipLaunchKernelGGL(k_erase_compact<Key>, dim3(cb), dim3(kT), 0, s, t.V, t.offsets,
-                       len, (Key*)t.keys, (uint32_t*)t.ids, dead, touched, head, d_removed);
+                       len, (Key*)t.keys, (uint32_t*)t.ids, dead, touched, ix, d_removed);
     return hipGetLastError();
 }
 
@@ -187,7 +189,7 @@ hipError_t run_export_live(const TableDev& t, const uint32_t* len, const uint32_
 }
 
 #define HG_ERASE_INST(Key)                                                                      \
-    template hipError_t run_erase<Key>(const TableDev&, uint32_t*, uint8_t*, uint8_t*, uint4*, \
+    template hipError_t run_erase<Key>(const TableDev&, uint32_t*, uint8_t*, uint8_t*, void*, \
                                        const Key*, uint64_t, unsigned long long*, hipStream_t); \
     template hipError_t run_export_live<Key>(const TableDev&, const uint32_t*, const uint32_t*, \
                                              uint32_t*, Key*, hipStream_t);

@@ -205,16 +205,113 @@ hipError_t run_build_v1(const Key* keys, uint64_t n, uint64_t V, uint64_t seed, 
 // key-grouped copy of the bucket's ids.
 constexpr uint32_t kRunBucket = 32;
 
-// A 32-bit-key bucket of 4..kRunBucket entries keeps, beside its first key and
-// that key's count (low 8 bits of the entry's w), a 24-bit filter of its other
-// keys (w's high 24 bits): bit filter_bit(k) is set for every key k of the
-// bucket that differs from the first.  A query whose bit is clear matches
-// nothing past the first key, so the edge array is not read.  The bit comes
-// from a multiplicative hash of the key, not from the bucket hash, so keys of
-// one bucket spread over the 24 bits.
-constexpr uint32_t kFilterBits = 24;
-__host__ __device__ inline uint32_t filter_bit(uint32_t k) {
-    return (uint32_t)(((uint64_t)(k * 0x9E3779B1u) * kFilterBits) >> 32);
+// Index entries of 32-bit keys.  fmix32 is a bijection, so inside bucket
+// h = fmix32(k ^ seed) mod V a key is identified by its quotient
+// floor(fmix32(k ^ seed) / V), which takes only `qb` bits: 4 at V = 2^28.  An
+// entry of 4 or 8 bytes therefore holds every key of all but the longest
+// buckets, exactly: its low 4 bits are a code, the fields above it depend on
+// the code.
+//   0..13   the bucket's length (at most cap); field i (qb bits, from bit 4)
+//           is the quotient of its i-th key, unused fields are 0
+//   14      a bucket of cap + 1 .. kRunBucket entries: how many of them equal
+//           the first one (8 bits), the first one's quotient (qb bits) and an
+//           nf-bit filter over the other keys' quotients (filter_bit)
+//   15      a bucket of more than kRunBucket entries: bit 4: they all equal
+//           the first one; bit 5: it has no key runs (after an erase) and is
+//           scanned; then the first one's quotient and how many equal it (0:
+//           more than the remaining bits hold)
+// Codes 14 and 15 find the bucket through the offsets when the entry does not
+// settle a query.
+// (The entries were 16 bytes, {len, key0, key1, key2}: at 2^28 buckets 4 GiB
+// of the build's writes, and windows of the grouped probe twice an XCD's L2.)
+// `one` has bit 0 of every field set, `low` all but the top bit of every
+// field and `high` the top bits: they compare all fields with a quotient at
+// once (held_matches).
+struct HeadFmt {
+    uint32_t bytes = 0;  // 4 or 8; 16: 64-bit keys
+    uint32_t qb = 0, cap = 0, nf = 0;
+    uint64_t one = 0, low = 0, high = 0;
+};
+constexpr uint32_t kCodeMedium = 14, kCodeLong = 15, kMaxHeld = 13;
+
+// Four bytes when they hold the buckets that matter: a query that hits sees
+// a bucket of 1 + Poisson(n / V) keys, of which a capacity of 2 + 2n/V leaves
+// out at most 2% at loads 0.25 to 8; else eight.
+inline HeadFmt head_fmt(uint64_t n, uint64_t V, int key_bits) {
+    HeadFmt f;
+    if (key_bits == 64) {
+        f.bytes = 16;
+        return f;
+    }
+    const uint32_t q = (uint32_t)(0xffffffffull / V);
+    while (f.qb < 32 && (q >> f.qb)) ++f.qb;
+    if (f.qb == 0) f.qb = 1;
+    const uint32_t c4 = 28 / f.qb < kMaxHeld ? 28 / f.qb : kMaxHeld;
+    f.bytes = (c4 >= 3 && (uint64_t)(c4 - 2) * V >= 2 * n) ? 4 : 8;
+    const uint32_t bits = 8 * f.bytes;
+    f.cap = (bits - 4) / f.qb < kMaxHeld ? (bits - 4) / f.qb : kMaxHeld;
+    f.nf = bits - 12 - f.qb < 32 ? bits - 12 - f.qb : 32;
+    for (uint32_t i = 0; i < f.cap; ++i) {
+        const uint64_t field = ((1ull << f.qb) - 1) << (i * f.qb);
+        f.one |= 1ull << (i * f.qb);
+        f.high |= 1ull << (i * f.qb + f.qb - 1);
+        f.low |= field;
+    }
+    f.low &= ~f.high;
+    return f;
+}
+
+// Bytes of index memory per bucket that any build of these keys may need.
+inline size_t head_bytes_max(int key_bits) { return key_bits == 64 ? 16 : 8; }
+
+// Filter bit (of nf) of a quotient.
+__host__ __device__ inline uint32_t filter_bit(uint32_t q, uint32_t nf) {
+    return (uint32_t)(((uint64_t)(q * 0x9E3779B1u) * nf) >> 32);
+}
+
+// Probe index entry of a 32-bit-key bucket of len <= kRunBucket entries whose
+// i-th key has the quotient quot(i) (HeadFmt).
+template <typename Quot>
+__host__ __device__ __forceinline__ uint64_t short_word(const HeadFmt& f, uint32_t len, Quot quot) {
+    if (len <= f.cap) {
+        uint64_t w = len;
+        for (uint32_t i = 0; i < len; ++i) w |= (uint64_t)quot(i) << (4 + i * f.qb);
+        return w;
+    }
+    const uint32_t q0 = quot(0);
+    uint32_t c0 = 1, filt = 0;
+    for (uint32_t i = 1; i < len; ++i) {
+        const uint32_t q = quot(i);
+        if (q == q0) ++c0;
+        else filt |= 1u << filter_bit(q, f.nf);
+    }
+    return (uint64_t)kCodeMedium | (uint64_t)c0 << 4 | (uint64_t)q0 << 12 |
+           (uint64_t)filt << (12 + f.qb);
+}
+
+// Fields of an entry of c <= cap keys that equal the quotient q, as the top
+// bits of those fields: all fields at once -- a field of x is zero exactly
+// when neither its low part plus all ones carries into its top bit nor that
+// bit is set.
+template <typename T>
+__host__ __device__ __forceinline__ T held_matches(T e, uint32_t c, uint32_t q, const HeadFmt& f) {
+    const T x = (e >> 4) ^ ((T)q * (T)f.one);
+    const T nonzero = ((x & (T)f.low) + (T)f.low) | x;
+    return ~nonzero & (T)f.high & (((T)1 << (c * f.qb)) - 1);
+}
+
+template <typename T>
+__host__ __device__ __forceinline__ uint32_t popcount(T x) {
+    return (uint32_t)(sizeof(T) == 8 ? __builtin_popcountll(x) : __builtin_popcount((uint32_t)x));
+}
+
+// held_matches as a mask over the bucket's keys.
+template <typename T>
+__host__ __device__ __forceinline__ uint32_t held_mask(T m, uint32_t c, const HeadFmt& f) {
+    uint32_t mask = 0;
+    for (uint32_t i = 0; i < c; ++i)
+        mask |= (uint32_t)((m >> (i * f.qb + f.qb - 1)) & 1) << i;
+    return mask;
 }
 
 // A 64-bit-key bucket of 2..kRunBucket entries keeps a 64-bit filter of all
@@ -233,9 +330,10 @@ __host__ __device__ inline uint64_t filter_bits64(uint64_t k) {
 // from st: runs are cumulative), and kperm[st .. st + len) lists the bucket's
 // ids grouped by key in run order, in bucket order inside each group.  A
 // bucket of one repeated key (R = 1) writes no kperm: its ids are the edge
-// array's own.  The bucket's probe index entry is {len, st, R, key} with key
-// the (32-bit) key when R = 1, else 0; R = 0 marks a long bucket without runs
-// (after an erase): probes then scan it.
+// array's own.  64-bit keys: the bucket's probe index entry is {len, st, R, 0},
+// and R = 0 marks a long bucket without runs (after an erase), which probes
+// scan.  32-bit keys (HeadFmt): run_end[st + len - 1] is R for R > 1 (when
+// R = len that is the last run's end, else the place is free).
 struct RunsDev {
     void* run_key = nullptr;     // Key[n]
     uint32_t* run_end = nullptr; // [n]
@@ -253,9 +351,12 @@ __host__ __device__ inline uint32_t gen_region(uint32_t bin_start, uint32_t g) {
 inline uint64_t gen_list_cap(uint64_t n, uint64_t bins) { return n / (kRunBucket + 1) + bins + 1; }
 
 // Where a V2 build writes its probe index (head == null: none) and the
-// key-run summary of its long buckets.  k and bins are set by the build.
+// key-run summary of its long buckets.  k, bins, fmt and hp are set by the
+// build.
 struct IndexOut {
-    uint4* head = nullptr;
+    void* head = nullptr;  // fmt.bytes per bucket
+    HeadFmt fmt{};
+    HashParams hp{};       // 32-bit keys: for the quotients
     RunsDev runs{};
     uint32_t* gen_list = nullptr;
     uint32_t* gen_cnt = nullptr;  // [bins]
@@ -274,8 +375,8 @@ hipError_t run_key_runs(const uint32_t* offsets, const uint32_t* ids, const Key*
                         uint64_t n, const uint32_t* bin_start, uint32_t bins, const IndexOut& ix,
                         Key* rkeys, uint32_t* rids, uint32_t* ctr, void* ws, hipStream_t s);
 
-// ix.head (may be null): V 16-byte probe index entries, one per bucket, and
-// the key-run summary of long buckets (IndexOut).  stable: ids ascend inside
+// ix.head (may be null): V probe index entries (head_fmt(n, V, key width)), one
+// per bucket, and the key-run summary of long buckets (IndexOut).  stable: ids ascend inside
 // every bucket (otherwise their order there is unspecified).
 template <typename Key>
 hipError_t run_build_v2(const Key* keys, uint64_t n, uint64_t V, uint64_t seed, uint32_t* offsets,
@@ -288,7 +389,8 @@ struct TableDev {
     const uint32_t* ids;
     const void* keys;
     uint64_t n, V, seed;
-    const uint4* head = nullptr;  // per-bucket probe index, when the build wrote one
+    const void* head = nullptr;   // per-bucket probe index, when the build wrote one
+    HeadFmt fmt{};                // its entries
     RunsDev runs{};               // key-run summary of long buckets (with head)
     const uint32_t* len = nullptr;  // live entries per bucket, after an erase (n = slots)
 };
@@ -302,7 +404,7 @@ hipError_t init_lengths(const uint32_t* offsets, uint64_t V, uint32_t* len, hipS
 // table's probe index; *d_removed (device, zeroed) gets the number removed.
 template <typename Key>
 hipError_t run_erase(const TableDev& t, uint32_t* len, uint8_t* dead, uint8_t* touched,
-                     uint4* head, const Key* del, uint64_t m, unsigned long long* d_removed,
+                     void* head, const Key* del, uint64_t m, unsigned long long* d_removed,
                      hipStream_t s);
 
 // Compacted ids / keys of the live entries at new_off (the exclusive scan of
@@ -315,7 +417,7 @@ size_t probe_ws_bytes(uint64_t m);
 
 // counts (may be null) and/or the total (may be null: else a buffer of
 // probe_total_slots(m) uint64, the total lands in slot 0).  held (may be
-// null; 32-bit keys with the probe index): per query, 0x80 | the mask of the
+// null; 32-bit keys with the probe index): per query, 0x8000 | the mask of the
 // matching keys when its bucket is held whole in its index entry, else 0 --
 // what the pairs pass needs instead of that entry.
 // xcd_order: query tiles are dealt out per XCD (xcd_tile), for queries that
@@ -324,7 +426,7 @@ size_t probe_ws_bytes(uint64_t m);
 template <typename Key>
 hipError_t run_probe_counts(const TableDev& t, const Key* queries, uint64_t m, uint32_t* counts,
                             unsigned long long* d_total, hipStream_t s,
-                            uint8_t* held = nullptr, bool xcd_order = false,
+                            uint16_t* held = nullptr, bool xcd_order = false,
                             const uint32_t* gate = nullptr, const Key* q_in = nullptr,
                             uint32_t* counts_in = nullptr);
 
@@ -346,7 +448,7 @@ hipError_t run_probe_grouped(const TableDev& t, const Key* queries, uint64_t m, 
 template <typename Key>
 hipError_t run_probe_pairs(const TableDev& t, const Key* queries, uint64_t m,
                            const uint64_t* positions, uint32_t* build_ids, uint32_t* probe_ids,
-                           hipStream_t s, const uint8_t* held = nullptr);
+                           hipStream_t s, const uint16_t* held = nullptr);
 
 // Intersection over b's edges: per-edge counts (edge order) and, optionally,
 // counts scattered to b's input order.

@@ -1,5 +1,5 @@
 // Random-transaction micro-roofline.  The probe of Sec. 3.4 makes one random
-// 16-byte read per query (its bucket's index entry) and V1 (Alg. 1) one random
+// read per query (its bucket's index entry, 4 to 16 bytes) and V1 (Alg. 1) one random
 // atomic add per key, so their ceilings are not the streaming bandwidth but
 // the rate of independent random transactions the memory system sustains.
 // These kernels measure that rate over a power-of-two footprint: every thread

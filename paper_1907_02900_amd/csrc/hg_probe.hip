@@ -3,18 +3,20 @@
 // HashGraph-Probe-Standard: each query is hashed with Eq. 1, the bucket's
 // segment [offsets[h], offsets[h+1]) of the edge array is scanned, and every
 // entry with an equal key is counted (all instances, not the first).  When
-// the V2 build wrote the per-bucket probe index, the segment bounds and the
-// bucket's first keys come from one 16-byte entry instead, so a query into a
-// bucket of at most two 32-bit keys (one 64-bit key) costs one random read.  Each
-// thread owns several queries (coalesced, strided by the block) and issues
-// all their offset loads before scanning, to keep many random reads in
-// flight.  Pairs are written in a second pass at positions given by an
-// exclusive scan of the counts, so pairs are grouped by query id.
+// the V2 build wrote the per-bucket probe index, one entry of 4 or 8 bytes
+// (64-bit keys: 16) answers most queries instead (HeadFmt), so they cost one
+// random read.  Each thread owns several queries (coalesced, strided by the
+// block) and issues all their entry or offset loads before using any, to keep
+// many random reads in flight.  Pairs are written in a second pass at
+// positions given by an exclusive scan of the counts, so pairs are grouped by
+// query id.
 //
 // HashGraph-Probe-New (Alg. 3): both inputs are built into HashGraphs with the
 // same hash and V, and bucket x of A is intersected with bucket x of B for
 // every x.  B's edges are walked in edge order, so the buckets of A are read
 // in increasing order (streaming, cache-friendly) instead of at random.
+#include <type_traits>
+
 #include "hg_internal.h"
 
 namespace hg {
@@ -48,36 +50,6 @@ __device__ __forceinline__ uint32_t count_in_bucket(const Key* __restrict__ ekey
     return c;
 }
 
-// What a probe index entry holds (x = the bucket's length; see head_entry):
-// 32-bit keys: all keys of a bucket of at most three in y, z, w, else the
-// start in y, the first key in z and, in w, the number of entries equal to it
-// (low 8 bits) and the filter of the bucket's other keys (high 24 bits);
-// 64-bit keys: the start in y and in z, w the key of a one-key bucket or the
-// filter of a longer bucket's keys.  A bucket longer than kRunBucket has its
-// key-run summary in z, w instead.
-template <typename Key>
-struct HeadKeys;
-
-template <>
-struct HeadKeys<uint32_t> {
-    static constexpr uint32_t full = 3;  // buckets this short keep every key, no start
-    __device__ static bool has_start(uint32_t len) { return len > full; }
-    __device__ static uint32_t stored(uint32_t len) { return len <= full ? len : 1u; }
-    __device__ static uint32_t key(const uint4& e, uint32_t len, uint32_t i) {
-        if (len <= full) return i == 0 ? e.y : (i == 1 ? e.z : e.w);
-        return e.z;
-    }
-};
-
-template <>
-struct HeadKeys<uint64_t> {
-    __device__ static bool has_start(uint32_t) { return true; }
-    __device__ static uint32_t stored(uint32_t len) { return len == 1 ? 1u : 0u; }
-    __device__ static uint64_t key(const uint4& e, uint32_t, uint32_t) {
-        return (uint64_t)e.z | ((uint64_t)e.w << 32);
-    }
-};
-
 // Key-run summary of the long buckets (see hg_runs.hip and RunsDev): runs
 // of a bucket starting at edge position st are at [st, st + R) of key / end.
 template <typename Key>
@@ -87,10 +59,42 @@ struct Runs {
     const uint32_t* kperm;  // ids grouped by key (buckets of several keys)
 };
 
+// A table as the kernels below read it.
 template <typename Key>
-Runs<Key> runs_of(const TableDev& t) {
-    return Runs<Key>{(const Key*)t.runs.run_key, t.runs.run_end, t.runs.kperm};
+struct View {
+    const uint32_t* off;
+    const uint32_t* len;  // live entries per bucket after an erase, else null
+    const void* head;     // probe index, or null
+    const Key* keys;
+    const uint32_t* ids;
+    Runs<Key> runs;
+    HeadFmt f;
+    typename KeyTraits<Key>::Params hp;
+
+    __device__ __forceinline__ uint32_t bucket_end(uint32_t h, uint32_t lo) const {
+        return len ? lo + len[h] : off[h + 1];
+    }
+};
+
+template <typename Key>
+View<Key> view_of(const TableDev& t) {
+    return View<Key>{t.offsets, t.len, t.head, (const Key*)t.keys, t.ids,
+                     Runs<Key>{(const Key*)t.runs.run_key, t.runs.run_end, t.runs.kperm}, t.fmt,
+                     KeyTraits<Key>::make(t.V, t.seed)};
 }
+
+// The template parameter W of the kernels: bytes of an index entry (4 or 8:
+// 32-bit keys, 16: 64-bit keys), 0 without the index.
+template <int W>
+struct EntryOf;
+template <>
+struct EntryOf<0> { using T = uint2; };  // offsets[h], end
+template <>
+struct EntryOf<4> { using T = uint32_t; };
+template <>
+struct EntryOf<8> { using T = uint64_t; };
+template <>
+struct EntryOf<16> { using T = uint4; };
 
 // Run of q among runs [r0, r0 + d) (keys ascending), or ~0u if q is absent.
 template <typename Key>
@@ -105,94 +109,138 @@ __device__ __forceinline__ uint32_t find_run(const Key* __restrict__ rk, uint32_
     return (lo < r0 + d && rk[lo] == q) ? lo : ~0u;
 }
 
-// Group [*b, *e) (offsets from the bucket start) of q in a long bucket whose
-// index entry is e = {len, st, R, key}; false if q is not in the bucket.  A
-// bucket of one key (R = 1) is answered from its entry (32-bit keys) or its
-// single run key.
-template <typename Key>
-__device__ __forceinline__ bool run_group(const uint4& e, const Runs<Key>& runs, Key q,
-                                          uint32_t* gb, uint32_t* ge) {
-    const uint32_t st = e.y, R = e.z;
-    if (R == 1) {
-        const bool hit = sizeof(Key) == 4 ? (uint32_t)q == e.w : runs.key[st] == q;
-        *gb = 0;
-        *ge = e.x;
-        return hit;
+// A long bucket: `runs` key runs (0: none, the bucket is scanned), of which
+// one holds its single key.
+struct LongRef {
+    uint32_t st, end, runs;
+};
+
+template <typename Key, int W>
+__device__ __forceinline__ LongRef long_ref(const View<Key>& t, uint32_t h,
+                                            const typename EntryOf<W>::T& e) {
+    LongRef r;
+    if constexpr (W == 16) {
+        r.st = e.y;
+        r.end = e.y + e.x;
+        r.runs = e.z;
+    } else {
+        r.st = t.off[h];
+        r.end = t.bucket_end(h, r.st);
+        r.runs = (e >> 5) & 1 ? 0u : (e >> 4) & 1 ? 1u : t.runs.end[r.end - 1];
     }
-    const uint32_t r = find_run(runs.key, st, R, q);
-    if (r == ~0u) return false;
-    *gb = r > st ? runs.end[r - 1] : 0u;
-    *ge = runs.end[r];
+    return r;
+}
+
+// Group [*gb, *ge) (offsets from the bucket start) of q in a long bucket with
+// key runs; false if q is not in it.
+template <typename Key>
+__device__ __forceinline__ bool run_group(const LongRef& r, const Runs<Key>& runs, Key q,
+                                          uint32_t* gb, uint32_t* ge) {
+    if (r.runs == 1) {
+        *gb = 0;
+        *ge = r.end - r.st;
+        return runs.key[r.st] == q;
+    }
+    const uint32_t i = find_run(runs.key, r.st, r.runs, q);
+    if (i == ~0u) return false;
+    *gb = i > r.st ? runs.end[i - 1] : 0u;
+    *ge = runs.end[i];
     return true;
 }
 
-// Matches of q in a bucket described by its index entry: the keys held in the
-// entry are compared directly, the edge array is read only past them; a long
-// bucket's entry points at its key runs instead (R = 0: no runs, scanned).
 template <typename Key>
-__device__ __forceinline__ uint32_t count_with_head(const uint4& e, const Key* __restrict__ ekeys,
-                                                    const Runs<Key>& runs, Key q) {
-    using HK = HeadKeys<Key>;
-    const uint32_t len = e.x;
-    if (len > kRunBucket) {
-        if (e.z == 0) return count_in_bucket(ekeys, e.y, e.y + len, q);  // runs dropped by an erase
-        uint32_t gb, ge;
-        return run_group(e, runs, q, &gb, &ge) ? ge - gb : 0u;
+__device__ __forceinline__ uint32_t count_long(const View<Key>& t, const LongRef& r, Key q) {
+    if (r.runs == 0) return count_in_bucket(t.keys, r.st, r.end, q);
+    uint32_t gb, ge;
+    return run_group(r, t.runs, q, &gb, &ge) ? ge - gb : 0u;
+}
+
+// Bucket (and, 32-bit keys, quotient) of a query.
+template <typename Key>
+__device__ __forceinline__ uint32_t locate(const View<Key>& t, Key q, uint32_t& quot) {
+    if constexpr (sizeof(Key) == 4) {
+        uint32_t h;
+        quot = KeyTraits<uint32_t>::quotient(q, t.hp, h);
+        return h;
+    } else {
+        quot = 0;
+        return KeyTraits<Key>::bucket(q, t.hp);
     }
-    if (sizeof(Key) == 4 && len > HeadKeys<uint32_t>::full) {
-        // {len, start, first key, its count | filter}: the first key's
-        // matches are counted in the entry; the rest of the bucket is read
-        // only when the query is not the first key and its filter bit is set
-        // (a clear bit: no other key of the bucket equals q)
-        if ((uint32_t)q == e.z) return e.w & 0xffu;
-        if (!((e.w >> (8 + filter_bit((uint32_t)q))) & 1u)) return 0u;
-        return count_in_bucket(ekeys, e.y + 1, e.y + len, q);
+}
+
+template <typename Key, int W>
+__device__ __forceinline__ typename EntryOf<W>::T entry_at(const View<Key>& t, uint32_t h) {
+    if constexpr (W == 0) {
+        const uint32_t lo = t.off[h];
+        return make_uint2(lo, t.bucket_end(h, lo));
+    } else {
+        return ((const typename EntryOf<W>::T*)t.head)[h];
     }
-    if (sizeof(Key) == 8 && len > 1) {
+}
+
+// Matches of q in the bucket whose entry is e, if the entry settles them;
+// else kUnsettled (counts stay below 2^32 - 1: so do the entries).
+constexpr uint32_t kUnsettled = 0xffffffffu;
+
+template <typename Key, int W>
+__device__ __forceinline__ uint32_t count_settled(const View<Key>& t,
+                                                  const typename EntryOf<W>::T& e, Key q,
+                                                  uint32_t quot) {
+    if constexpr (W == 16) {
+        const uint32_t len = e.x;
+        const uint64_t f = (uint64_t)e.z | ((uint64_t)e.w << 32);
+        if (len <= 1) return len == 1 && f == (uint64_t)q ? 1u : 0u;
         // {len, start, filter of the bucket's keys}: read the bucket only
         // when both of q's filter bits are set
-        const uint64_t f = (uint64_t)e.z | ((uint64_t)e.w << 32), b = filter_bits64((uint64_t)q);
-        if ((f & b) != b) return 0u;
-        return count_in_bucket(ekeys, e.y, e.y + len, q);
+        const uint64_t b = filter_bits64((uint64_t)q);
+        return len <= kRunBucket && (f & b) != b ? 0u : kUnsettled;
+    } else {
+        const uint32_t code = (uint32_t)e & 15u;
+        if (code <= kMaxHeld) return popcount(held_matches(e, code, quot, t.f));
+        // the first key's matches are counted in the entry; the rest of the
+        // bucket is read only when the query is not the first key and (medium)
+        // its filter bit is set, (long) there are other keys
+        const bool medium = code == kCodeMedium;
+        const uint32_t qmask = (uint32_t)((1ull << t.f.qb) - 1);
+        const bool lead = ((uint32_t)(e >> (medium ? 12 : 6)) & qmask) == quot;
+        const uint32_t n = medium ? (uint32_t)(e >> 4) & 0xffu : (uint32_t)(e >> (6 + t.f.qb));
+        if (lead) return n ? n : kUnsettled;  // (0: not held)
+        const bool others = medium ? (uint32_t)(e >> (12 + t.f.qb + filter_bit(quot, t.f.nf))) & 1u
+                                   : !((uint32_t)(e >> 4) & 1u);
+        return others ? kUnsettled : 0u;
     }
-    const uint32_t n = HK::stored(len);
-    uint32_t c = 0;
-#pragma unroll
-    for (uint32_t i = 0; i < 3; ++i) c += (i < n && HK::key(e, len, i) == q) ? 1u : 0u;
-    if (len > n) c += count_in_bucket(ekeys, e.y + n, e.y + len, q);  // the start is stored
-    return c;
 }
 
-// For the pairs pass: 0x80 | the mask of the entry's keys equal to q when the
-// bucket (1-3 32-bit keys) is held whole in its entry, else 0.
-template <typename Key>
-__device__ __forceinline__ uint8_t held_code(const uint4& e, Key q) {
-    using HK = HeadKeys<uint32_t>;
-    const uint32_t len = e.x;
-    if (len == 0 || len > HK::full) return 0;
-    uint32_t mask = 0;
-#pragma unroll
-    for (uint32_t i = 0; i < HK::full; ++i)
-        mask |= (i < len && HK::key(e, len, i) == (uint32_t)q) ? 1u << i : 0u;
-    return (uint8_t)(0x80u | mask);
+// Matches of q in bucket h, whose entry e does not settle them.
+template <typename Key, int W>
+__device__ __forceinline__ uint32_t count_unsettled(const View<Key>& t,
+                                                    const typename EntryOf<W>::T& e, Key q,
+                                                    uint32_t h) {
+    if constexpr (W == 16) {
+        if (e.x > kRunBucket) return count_long(t, long_ref<Key, W>(t, h, e), q);
+        return count_in_bucket(t.keys, e.y, e.y + e.x, q);
+    } else {
+        if (((uint32_t)e & 15u) == kCodeLong) return count_long(t, long_ref<Key, W>(t, h, e), q);
+        const uint32_t lo = t.off[h];
+        return count_in_bucket(t.keys, lo + 1, t.bucket_end(h, lo), q);
+    }
 }
 
-// Probe-Standard counts.  HEAD: each query reads its bucket's 16-byte index
-// entry (one random access for buckets of up to three 32-bit keys or one
-// 64-bit key); otherwise it reads
-// offsets[h], offsets[h+1] and scans the edge array.  xcd_tiles = 0: block b
+// Probe-Standard counts.  W: each query reads its bucket's index entry (one
+// random access when the entry settles it); W = 0: it reads offsets[h],
+// offsets[h+1] and scans the edge array.  xcd_tiles = 0: block b
 // takes query tile b; else the grid has 8 * ceil(xcd_tiles / 8) blocks and
 // tiles are dealt out by xcd_tile, so that each XCD walks one contiguous run
 // of queries (queries grouped by bucket range then read one L2-sized window
 // of the index per XCD at a time).  gate (may be null): when *gate == 0 the
 // launch probes q_in into counts_in instead, block b taking tile b (the
 // grouped probe decides on the device whether its queries were grouped).
-template <typename Key, bool HEAD>
+// held (32-bit keys): per query 0x8000 | the mask of the bucket's keys equal
+// to it when it has matches and its entry holds the bucket whole, else 0.
+template <typename Key, int W>
 __global__ __launch_bounds__(kProbeThreads) void k_probe_count(
-    const Key* __restrict__ q, uint64_t m, typename KeyTraits<Key>::Params hp,
-    const uint32_t* __restrict__ off, const uint4* __restrict__ head, Runs<Key> runs,
-    const Key* __restrict__ ekeys, uint32_t* __restrict__ counts,
-    unsigned long long* __restrict__ total, uint8_t* __restrict__ held, uint32_t xcd_tiles,
+    const Key* __restrict__ q, uint64_t m, View<Key> t, uint32_t* __restrict__ counts,
+    unsigned long long* __restrict__ total, uint16_t* __restrict__ held, uint32_t xcd_tiles,
     const uint32_t* __restrict__ gate, const Key* __restrict__ q_in,
     uint32_t* __restrict__ counts_in) {
     __shared__ uint64_t red[kProbeThreads / kWave + 1];
@@ -204,7 +252,8 @@ __global__ __launch_bounds__(kProbeThreads) void k_probe_count(
     }
     const uint64_t base = (uint64_t)tile * (kProbeThreads * kProbeItems) + threadIdx.x;
     Key qq[kProbeItems];
-    uint4 e[kProbeItems];
+    uint32_t quot[kProbeItems];
+    typename EntryOf<W>::T e[kProbeItems];
 #pragma unroll
     for (int r = 0; r < kProbeItems; ++r) {
         const uint64_t j = base + (uint64_t)r * kProbeThreads;
@@ -213,26 +262,32 @@ __global__ __launch_bounds__(kProbeThreads) void k_probe_count(
 #pragma unroll
     for (int r = 0; r < kProbeItems; ++r) {
         const uint64_t j = base + (uint64_t)r * kProbeThreads;
-        if (j < m) {
-            const uint32_t h = KeyTraits<Key>::bucket(qq[r], hp);
-            if (HEAD) {
-                e[r] = head[h];
-            } else {
-                e[r].x = off[h];
-                e[r].y = off[h + 1];
-            }
-        } else {
-            e[r] = make_uint4(0u, 0u, 0u, 0u);
-        }
+        quot[r] = 0;
+        e[r] = typename EntryOf<W>::T{};
+        if (j < m) e[r] = entry_at<Key, W>(t, locate(t, qq[r], quot[r]));
     }
     uint64_t sum = 0;
 #pragma unroll
     for (int r = 0; r < kProbeItems; ++r) {
         const uint64_t j = base + (uint64_t)r * kProbeThreads;
-        const uint32_t c = HEAD ? count_with_head(e[r], ekeys, runs, qq[r])
-                                : count_in_bucket(ekeys, e[r].x, e[r].y, qq[r]);
+        uint32_t c;
+        if constexpr (W == 0) {
+            c = count_in_bucket(t.keys, e[r].x, e[r].y, qq[r]);
+        } else {
+            c = count_settled<Key, W>(t, e[r], qq[r], quot[r]);
+            if (c == kUnsettled)  // (not for j >= m: their entry is empty)
+                c = count_unsettled<Key, W>(t, e[r], qq[r], KeyTraits<Key>::bucket(qq[r], t.hp));
+        }
         if (j < m && counts) counts[j] = c;
-        if (HEAD && sizeof(Key) == 4 && held && j < m) held[j] = held_code(e[r], qq[r]);
+        if constexpr (W == 4 || W == 8) {
+            if (held && j < m) {
+                const uint32_t code = (uint32_t)e[r] & 15u;
+                held[j] = (uint16_t)(c && code <= kMaxHeld
+                                         ? 0x8000u | held_mask(held_matches(e[r], code, quot[r], t.f),
+                                                               code, t.f)
+                                         : 0u);
+            }
+        }
         sum += c;
     }
     if (total) {
@@ -242,164 +297,163 @@ __global__ __launch_bounds__(kProbeThreads) void k_probe_count(
     }
 }
 
-template <typename Key, bool HEAD>
+// Writes a query's pairs: its output range [positions[j], positions[j+1]) is
+// known from the counting pass, and a query whose range is empty reads
+// nothing more.  Each thread first loads what its kProbeItems queries need --
+// with the counting pass's codes (held) only the bucket's start -- so that
+// their random reads overlap.
+template <typename Key, int W>
 __global__ __launch_bounds__(kProbeThreads) void k_probe_pairs(
-    const Key* __restrict__ q, uint64_t m, typename KeyTraits<Key>::Params hp,
-    const uint32_t* __restrict__ off, const uint4* __restrict__ head, Runs<Key> runs,
-    const Key* __restrict__ ekeys, const uint32_t* __restrict__ eids,
-    const uint64_t* __restrict__ positions, uint32_t* __restrict__ build_ids,
-    uint32_t* __restrict__ probe_ids, const uint8_t* __restrict__ held) {
-    using HK = HeadKeys<Key>;
-    // as in k_probe_count: every thread first loads the index entries (or
-    // offsets) of its kProbeItems queries, so that their random reads overlap;
-    // a query whose output range [positions[j], positions[j+1]) is empty has
-    // no match and reads nothing more
+    const Key* __restrict__ q, uint64_t m, View<Key> t, const uint64_t* __restrict__ positions,
+    uint32_t* __restrict__ build_ids, uint32_t* __restrict__ probe_ids,
+    const uint16_t* __restrict__ held) {
     const uint64_t base = (uint64_t)blockIdx.x * (kProbeThreads * kProbeItems) + threadIdx.x;
-    // (with the counting pass's codes, a query whose bucket is held whole in
-    // its entry skips the entry: it knows its matching keys and reads only
-    // the bucket's start)
     Key qq[kProbeItems];
-    uint32_t hh[kProbeItems];
-    uint4 e[kProbeItems];
-    uint64_t pend[kProbeItems];
-    bool none[kProbeItems];
-    uint32_t code[kProbeItems];
+    uint32_t hh[kProbeItems], st[kProbeItems];
+    typename EntryOf<W>::T e[kProbeItems];
+    uint64_t pos[kProbeItems], pend[kProbeItems];
+    uint32_t mask[kProbeItems];  // the bucket's matching keys, when known from its entry
 #pragma unroll
     for (int r = 0; r < kProbeItems; ++r) {
         const uint64_t j = base + (uint64_t)r * kProbeThreads;
         qq[r] = (j < m) ? q[j] : (Key)0;
+        pos[r] = (j < m) ? positions[j] : 0ull;
         pend[r] = (j < m) ? positions[j + 1] : 0ull;
-        none[r] = j >= m || positions[j] == pend[r];
-        code[r] = (HEAD && held && j < m) ? held[j] : 0u;
+        mask[r] = (W && held && j < m) ? held[j] & 0x7fffu : 0u;
     }
 #pragma unroll
     for (int r = 0; r < kProbeItems; ++r) {
-        hh[r] = KeyTraits<Key>::bucket(qq[r], hp);
-        if (none[r] || code[r]) {
-            e[r] = make_uint4(0u, 0u, 0u, 0u);
-        } else if (HEAD) {
-            e[r] = head[hh[r]];
-        } else {
-            e[r].x = off[hh[r]];
-            e[r].y = off[hh[r] + 1];
-        }
-    }
-    // where each query's bucket starts (a bucket whose keys are all in its
-    // entry needs offsets[h], read only when one of those keys matches), and
-    // how many leading keys the entry holds; the loads overlap across queries
-    uint32_t st[kProbeItems], nn[kProbeItems];
-    bool skip[kProbeItems], via_runs[kProbeItems];
-#pragma unroll
-    for (int r = 0; r < kProbeItems; ++r) {
-        const uint4 er = e[r];
-        skip[r] = none[r];
-        via_runs[r] = false;
-        nn[r] = 0;
-        st[r] = er.x;
-        if (HEAD && !skip[r] && code[r]) {
-            st[r] = off[hh[r]];
-        } else if (HEAD && !skip[r]) {
-            const uint32_t len = er.x;
-            const bool longb = len > kRunBucket;
-            via_runs[r] = longb && er.z != 0u;
-            nn[r] = longb ? 0u : HK::stored(len);
-            if (HK::has_start(len)) {
-                st[r] = er.y;
-            } else {
-                bool any = false;
-                for (uint32_t i = 0; i < nn[r]; ++i) any |= HK::key(er, len, i) == qq[r];
-                skip[r] = !any;
-                st[r] = any ? off[hh[r]] : 0u;
-            }
-        }
+        uint32_t quot;
+        hh[r] = locate(t, qq[r], quot);
+        e[r] = typename EntryOf<W>::T{};
+        st[r] = 0;
+        if (pos[r] == pend[r]) continue;
+        if (!mask[r]) e[r] = entry_at<Key, W>(t, hh[r]);
+        if (W == 4 || W == 8) st[r] = t.off[hh[r]];
     }
 #pragma unroll
     for (int r = 0; r < kProbeItems; ++r) {
-        if (skip[r]) continue;
-        const uint64_t j = base + (uint64_t)r * kProbeThreads;
+        if (pos[r] == pend[r]) continue;
+        const uint32_t j = (uint32_t)(base + (uint64_t)r * kProbeThreads);
         const Key k = qq[r];
-        const uint4 er = e[r];
-        uint64_t pos = positions[j];
-        if (code[r]) {
-#pragma unroll
-            for (uint32_t i = 0; i < 3; ++i)
-                if (((code[r] >> i) & 1u) && pos < pend[r]) {
-                    build_ids[pos] = eids[st[r] + i];
-                    probe_ids[pos] = (uint32_t)j;
-                    ++pos;
+        uint64_t o = pos[r];
+        uint32_t lo = st[r], hi = lo, mk = mask[r];
+        if constexpr (W == 0) {
+            lo = e[r].x;
+            hi = e[r].y;
+        } else {
+            bool longb;
+            if constexpr (W == 16) {
+                lo = e[r].y;
+                hi = lo + e[r].x;
+                longb = e[r].x > kRunBucket;
+            } else {
+                const uint32_t code = (uint32_t)e[r] & 15u;
+                if (!mk && code <= kMaxHeld) {
+                    uint32_t quot;
+                    locate(t, k, quot);
+                    mk = held_mask(held_matches(e[r], code, quot, t.f), code, t.f);
                 }
-            continue;
-        }
-        if (via_runs[r]) {
-            // the ids of q's group, in bucket order: the edge array's own for
-            // a bucket of one key, else its group in kperm
-            uint32_t gb, ge;
-            if (run_group(er, runs, k, &gb, &ge)) {
-                const uint32_t* src = er.z == 1 ? eids + er.y : runs.kperm + er.y;
-                for (uint32_t t = gb; t < ge && pos < pend[r]; ++t) {
-                    build_ids[pos] = src[t];
-                    probe_ids[pos] = (uint32_t)j;
-                    ++pos;
+                longb = !mk && code == kCodeLong;
+                if (!mk) hi = t.bucket_end(hh[r], lo);
+            }
+            if (longb) {
+                const LongRef ref = long_ref<Key, W>(t, hh[r], e[r]);
+                if (ref.runs) {
+                    // the ids of q's group, in bucket order: the edge array's own
+                    // for a bucket of one key, else its group in kperm
+                    uint32_t gb, ge;
+                    if (run_group(ref, t.runs, k, &gb, &ge)) {
+                        const uint32_t* src = (ref.runs == 1 ? t.ids : t.runs.kperm) + ref.st;
+                        for (uint32_t x = gb; x < ge && o < pend[r]; ++x, ++o) {
+                            build_ids[o] = src[x];
+                            probe_ids[o] = j;
+                        }
+                    }
+                    continue;
                 }
             }
-            continue;
         }
-        const uint32_t start = st[r], len = HEAD ? er.x : er.y - er.x, n = nn[r];
-        for (uint32_t p = start; p < start + len && pos < pend[r]; ++p)
-            if ((p - start < n ? HK::key(er, len, p - start) : ekeys[p]) == k) {
-                build_ids[pos] = eids[p];
-                probe_ids[pos] = (uint32_t)j;
-                ++pos;
+        for (; mk && o < pend[r]; mk &= mk - 1, ++o) {
+            build_ids[o] = t.ids[lo + __builtin_ctz(mk)];
+            probe_ids[o] = j;
+        }
+        for (uint32_t p = lo; p < hi && o < pend[r]; ++p)
+            if (t.keys[p] == k) {
+                build_ids[o] = t.ids[p];
+                probe_ids[o] = j;
+                ++o;
             }
     }
 }
 
 // Alg. 3 over B's edges p: count the entries of A's bucket h(key_p) equal to
-// key_p.  A and B share hash parameters, so h is recomputed from B's key.
-// Matches of k in A's bucket h: a scan, or A's key runs when the bucket is
-// long and A has them (a_head not null).
-template <typename Key>
-__device__ __forceinline__ uint32_t count_in_a(const uint32_t* __restrict__ a_off,
-                                               const uint32_t* __restrict__ a_len,
-                                               const uint4* __restrict__ a_head,
-                                               const Runs<Key>& runs,
-                                               const Key* __restrict__ a_keys, uint32_t h,
-                                               Key k) {
-    const uint32_t lo = a_off[h], hi = a_len ? lo + a_len[h] : a_off[h + 1];
-    if (a_head && hi - lo > kRunBucket) {
-        const uint4 e = a_head[h];
-        uint32_t gb, ge;
-        if (e.z != 0) return run_group(e, runs, k, &gb, &ge) ? ge - gb : 0u;
+// key_p.  A and B share hash parameters, so h is recomputed from B's key.  A's
+// buckets come in increasing order, so its index entries (W) are streamed:
+// they are smaller than its offsets and keys together.  (64-bit keys: 16 bytes
+// per bucket would cost more than the offsets; the index is read for long
+// buckets only.)
+template <typename Key, int W, int WE>
+__device__ __forceinline__ uint32_t count_in_a(const View<Key>& a,
+                                               const typename EntryOf<WE>::T& e, Key k,
+                                               uint32_t quot) {
+    if constexpr (W == 16) {
+        if (e.y - e.x > kRunBucket) {
+            const uint32_t h = KeyTraits<Key>::bucket(k, a.hp);
+            return count_long(a, long_ref<Key, 16>(a, h, ((const uint4*)a.head)[h]), k);
+        }
     }
-    return count_in_bucket(a_keys, lo, hi, k);
+    if constexpr (WE == 0) {
+        return count_in_bucket(a.keys, e.x, e.y, k);
+    } else {
+        const uint32_t c = count_settled<Key, WE>(a, e, k, quot);
+        return c != kUnsettled ? c : count_unsettled<Key, WE>(a, e, k, KeyTraits<Key>::bucket(k, a.hp));
+    }
 }
 
-// B's stale slots (behind a bucket's live entries after an erase) are skipped:
-// they get edge count 0 and write no count by input.
+// Whether slot p of B, holding key k, is stale (behind its bucket's live
+// entries after an erase): such slots get edge count 0 and no count by input.
 template <typename Key>
+__device__ __forceinline__ bool stale(const View<Key>& b, uint64_t p, Key k) {
+    if (!b.len) return false;
+    const uint32_t h = KeyTraits<Key>::bucket(k, b.hp);
+    return p - b.off[h] >= b.len[h];
+}
+
+template <typename Key, int W>
 __global__ __launch_bounds__(kProbeThreads) void k_intersect_count(
-    const uint32_t* __restrict__ a_off, const uint32_t* __restrict__ a_len,
-    const uint4* __restrict__ a_head, Runs<Key> runs, const Key* __restrict__ a_keys,
-    const uint32_t* __restrict__ b_off, const uint32_t* __restrict__ b_len,
-    const Key* __restrict__ b_keys, const uint32_t* __restrict__ b_ids, uint64_t nb,
-    typename KeyTraits<Key>::Params hp, uint32_t* __restrict__ edge_counts,
+    View<Key> a, View<Key> b, uint64_t nb, uint32_t* __restrict__ edge_counts,
     uint32_t* __restrict__ counts_by_input, unsigned long long* __restrict__ total) {
     __shared__ uint64_t red[kProbeThreads / kWave + 1];
     uint64_t sum = 0;
     const uint64_t base = (uint64_t)blockIdx.x * (kProbeThreads * kProbeItems) + threadIdx.x;
+    Key kk[kProbeItems];
+    uint32_t quot[kProbeItems];
+    constexpr int WE = W == 16 ? 0 : W;  // 64-bit keys read the offsets (see above)
+    typename EntryOf<WE>::T e[kProbeItems];
+#pragma unroll
+    for (int r = 0; r < kProbeItems; ++r) {
+        const uint64_t p = base + (uint64_t)r * kProbeThreads;
+        kk[r] = p < nb ? b.keys[p] : (Key)0;
+    }
+#pragma unroll
+    for (int r = 0; r < kProbeItems; ++r) {
+        const uint64_t p = base + (uint64_t)r * kProbeThreads;
+        quot[r] = 0;
+        e[r] = typename EntryOf<WE>::T{};
+        if (p < nb) e[r] = entry_at<Key, WE>(a, locate(a, kk[r], quot[r]));
+    }
 #pragma unroll
     for (int r = 0; r < kProbeItems; ++r) {
         const uint64_t p = base + (uint64_t)r * kProbeThreads;
         if (p < nb) {
-            const Key k = b_keys[p];
-            const uint32_t h = KeyTraits<Key>::bucket(k, hp);
-            if (b_len && p - b_off[h] >= b_len[h]) {
+            if (stale(b, p, kk[r])) {
                 if (edge_counts) edge_counts[p] = 0;
                 continue;
             }
-            const uint32_t c = count_in_a(a_off, a_len, a_head, runs, a_keys, h, k);
+            const uint32_t c = count_in_a<Key, W, WE>(a, e[r], kk[r], quot[r]);
             if (edge_counts) edge_counts[p] = c;
-            if (counts_by_input) counts_by_input[b_ids[p]] = c;
+            if (counts_by_input) counts_by_input[b.ids[p]] = c;
             sum += c;
         }
     }
@@ -410,15 +464,10 @@ __global__ __launch_bounds__(kProbeThreads) void k_intersect_count(
     }
 }
 
-template <typename Key>
+template <typename Key, int W>
 __global__ __launch_bounds__(kProbeThreads) void k_intersect_pairs(
-    const uint32_t* __restrict__ a_off, const uint32_t* __restrict__ a_len,
-    const uint4* __restrict__ a_head, Runs<Key> runs, const Key* __restrict__ a_keys,
-    const uint32_t* __restrict__ a_ids, const uint32_t* __restrict__ b_off,
-    const uint32_t* __restrict__ b_len, const Key* __restrict__ b_keys,
-    const uint32_t* __restrict__ b_ids, uint64_t nb, typename KeyTraits<Key>::Params hp,
-    const uint64_t* __restrict__ positions, uint32_t* __restrict__ out_a,
-    uint32_t* __restrict__ out_b) {
+    View<Key> a, View<Key> b, uint64_t nb, const uint64_t* __restrict__ positions,
+    uint32_t* __restrict__ out_a, uint32_t* __restrict__ out_b) {
     uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const uint64_t st = (uint64_t)gridDim.x * blockDim.x;
     for (; p < nb; p += st) {
@@ -427,29 +476,30 @@ __global__ __launch_bounds__(kProbeThreads) void k_intersect_pairs(
         uint64_t pos = positions[p];
         const uint64_t pend = positions[p + 1];
         if (pos == pend) continue;
-        const Key k = b_keys[p];
-        const uint32_t h = KeyTraits<Key>::bucket(k, hp);
-        if (b_len && p - b_off[h] >= b_len[h]) continue;  // stale slot of B
-        const uint32_t lo = a_off[h], hi = a_len ? lo + a_len[h] : a_off[h + 1];
-        const uint32_t bid = b_ids[p];
-        if (a_head && hi - lo > kRunBucket) {
-            const uint4 e = a_head[h];
-            if (e.z != 0) {
-                uint32_t gb, ge;
-                if (run_group(e, runs, k, &gb, &ge)) {
-                    const uint32_t* src = e.z == 1 ? a_ids + e.y : runs.kperm + e.y;
-                    for (uint32_t t = gb; t < ge && pos < pend; ++t) {
-                        out_a[pos] = src[t];
-                        out_b[pos] = bid;
-                        ++pos;
+        const Key k = b.keys[p];
+        const uint32_t h = KeyTraits<Key>::bucket(k, a.hp);
+        const uint32_t lo = a.off[h], hi = a.bucket_end(h, lo);
+        const uint32_t bid = b.ids[p];
+        if constexpr (W != 0) {
+            if (hi - lo > kRunBucket) {
+                const LongRef ref = long_ref<Key, W>(a, h, entry_at<Key, W>(a, h));
+                if (ref.runs != 0) {
+                    uint32_t gb, ge;
+                    if (run_group(ref, a.runs, k, &gb, &ge)) {
+                        const uint32_t* src = (ref.runs == 1 ? a.ids : a.runs.kperm) + ref.st;
+                        for (uint32_t x = gb; x < ge && pos < pend; ++x) {
+                            out_a[pos] = src[x];
+                            out_b[pos] = bid;
+                            ++pos;
+                        }
                     }
+                    continue;
                 }
-                continue;
             }
         }
         for (uint32_t i = lo; i < hi && pos < pend; ++i)
-            if (a_keys[i] == k) {
-                out_a[pos] = a_ids[i];
+            if (a.keys[i] == k) {
+                out_a[pos] = a.ids[i];
                 out_b[pos] = bid;
                 ++pos;
             }
@@ -473,28 +523,31 @@ uint64_t probe_total_slots(uint64_t m) {
     return 1 + (m ? 8 * (((uint64_t)grid_for(m, kProbeThreads * kProbeItems) + 7) / 8) : 0);
 }
 
+// Calls f with the bytes of t's index entries (0: no index) as a constant.
+template <typename Key, typename F>
+void with_entry(const TableDev& t, F&& f) {
+    if (!t.head) f(std::integral_constant<int, 0>{});
+    else if constexpr (sizeof(Key) == 8) f(std::integral_constant<int, 16>{});
+    else if (t.fmt.bytes == 4) f(std::integral_constant<int, 4>{});
+    else f(std::integral_constant<int, 8>{});
+}
+
 template <typename Key>
 hipError_t run_probe_counts(const TableDev& t, const Key* queries, uint64_t m, uint32_t* counts,
-                            unsigned long long* d_total, hipStream_t s, uint8_t* held,
+                            unsigned long long* d_total, hipStream_t s, uint16_t* held,
                             bool xcd_order, const uint32_t* gate, const Key* q_in,
                             uint32_t* counts_in) {
     if (m == 0) return d_total ? fill_u32((uint32_t*)d_total, 2, 0u, s) : hipSuccess;
-    auto hp = KeyTraits<Key>::make(t.V, t.seed);
     const uint32_t tiles = grid_for(m, kProbeThreads * kProbeItems);
     const uint32_t xt = xcd_order ? tiles : 0u;
     const dim3 grid(xcd_order ? 8 * ((tiles + 7) / 8) : tiles);
     {
         HG_PROF("probe_count", s);
-        if (t.head)
-            hipLaunchKernelGGL((k_probe_count<Key, true>), grid, dim3(kProbeThreads), 0, s,
-                               queries, m, hp, t.offsets, t.head, runs_of<Key>(t),
-                               (const Key*)t.keys, counts, d_total, held, xt, gate, q_in,
-                               counts_in);
-        else
-            hipLaunchKernelGGL((k_probe_count<Key, false>), grid, dim3(kProbeThreads), 0, s,
-                               queries, m, hp, t.offsets, t.head, runs_of<Key>(t),
-                               (const Key*)t.keys, counts, d_total, (uint8_t*)nullptr, xt,
-                               gate, q_in, counts_in);
+        with_entry<Key>(t, [&](auto w) {
+            hipLaunchKernelGGL((k_probe_count<Key, decltype(w)::value>), grid,
+                               dim3(kProbeThreads), 0, s, queries, m, view_of<Key>(t), counts,
+                               d_total, held, xt, gate, q_in, counts_in);
+        });
     }
     HG_TRY(hipGetLastError());
     return d_total ? sum_u64(d_total + 1, grid.x, d_total, s) : hipSuccess;
@@ -503,22 +556,16 @@ hipError_t run_probe_counts(const TableDev& t, const Key* queries, uint64_t m, u
 template <typename Key>
 hipError_t run_probe_pairs(const TableDev& t, const Key* queries, uint64_t m,
                            const uint64_t* positions, uint32_t* build_ids, uint32_t* probe_ids,
-                           hipStream_t s, const uint8_t* held) {
+                           hipStream_t s, const uint16_t* held) {
     if (m == 0) return hipSuccess;
-    auto hp = KeyTraits<Key>::make(t.V, t.seed);
     const uint32_t g = grid_for(m, kProbeThreads * kProbeItems);
     {
         HG_PROF("probe_pairs", s);
-        if (t.head)
-            hipLaunchKernelGGL((k_probe_pairs<Key, true>), dim3(g), dim3(kProbeThreads), 0, s,
-                               queries, m, hp, t.offsets, t.head, runs_of<Key>(t),
-                               (const Key*)t.keys, t.ids, positions, build_ids, probe_ids,
-                               sizeof(Key) == 4 ? held : nullptr);
-        else
-            hipLaunchKernelGGL((k_probe_pairs<Key, false>), dim3(g), dim3(kProbeThreads), 0, s,
-                               queries, m, hp, t.offsets, t.head, runs_of<Key>(t),
-                               (const Key*)t.keys, t.ids, positions, build_ids, probe_ids,
-                               (const uint8_t*)nullptr);
+        with_entry<Key>(t, [&](auto w) {
+            hipLaunchKernelGGL((k_probe_pairs<Key, decltype(w)::value>), dim3(g),
+                               dim3(kProbeThreads), 0, s, queries, m, view_of<Key>(t), positions,
+                               build_ids, probe_ids, held);
+        });
     }
     return hipGetLastError();
 }
@@ -528,14 +575,14 @@ hipError_t run_intersect_counts(const TableDev& a, const TableDev& b, uint32_t* 
                                 uint32_t* counts_by_input, unsigned long long* d_total,
                                 hipStream_t s) {
     if (b.n == 0) return d_total ? fill_u32((uint32_t*)d_total, 2, 0u, s) : hipSuccess;
-    auto hp = KeyTraits<Key>::make(a.V, a.seed);
     const uint32_t grid = grid_for(b.n, kProbeThreads * kProbeItems);
     {
         HG_PROF("intersect_count", s);
-        hipLaunchKernelGGL(k_intersect_count<Key>, dim3(grid),
-                           dim3(kProbeThreads), 0, s, a.offsets, a.len, a.head, runs_of<Key>(a),
-                           (const Key*)a.keys, b.offsets, b.len, (const Key*)b.keys, b.ids, b.n,
-                           hp, edge_counts, counts_by_input, d_total);
+        with_entry<Key>(a, [&](auto w) {
+            hipLaunchKernelGGL((k_intersect_count<Key, decltype(w)::value>), dim3(grid),
+                               dim3(kProbeThreads), 0, s, view_of<Key>(a), view_of<Key>(b), b.n,
+                               edge_counts, counts_by_input, d_total);
+        });
     }
     HG_TRY(hipGetLastError());
     return d_total ? sum_u64(d_total + 1, grid, d_total, s) : hipSuccess;
@@ -545,25 +592,26 @@ template <typename Key>
 hipError_t run_intersect_pairs(const TableDev& a, const TableDev& b, const uint64_t* positions,
                                uint32_t* a_ids, uint32_t* b_ids, hipStream_t s) {
     if (b.n == 0) return hipSuccess;
-    auto hp = KeyTraits<Key>::make(a.V, a.seed);
     uint32_t g = grid_for(b.n, kProbeThreads);
     if (g > 8192) g = 8192;
     {
         HG_PROF("intersect_pairs", s);
-        hipLaunchKernelGGL(k_intersect_pairs<Key>, dim3(g), dim3(kProbeThreads), 0, s, a.offsets,
-                           a.len, a.head, runs_of<Key>(a), (const Key*)a.keys, a.ids, b.offsets,
-                           b.len, (const Key*)b.keys, b.ids, b.n, hp, positions, a_ids, b_ids);
+        with_entry<Key>(a, [&](auto w) {
+            hipLaunchKernelGGL((k_intersect_pairs<Key, decltype(w)::value>), dim3(g),
+                               dim3(kProbeThreads), 0, s, view_of<Key>(a), view_of<Key>(b), b.n,
+                               positions, a_ids, b_ids);
+        });
     }
     return hipGetLastError();
 }
 
 #define HG_PINST(Key)                                                                           \
     template hipError_t run_probe_counts<Key>(const TableDev&, const Key*, uint64_t, uint32_t*, \
-                                              unsigned long long*, hipStream_t, uint8_t*, bool,  \
+                                              unsigned long long*, hipStream_t, uint16_t*, bool, \
                                               const uint32_t*, const Key*, uint32_t*);           \
     template hipError_t run_probe_pairs<Key>(const TableDev&, const Key*, uint64_t,             \
                                              const uint64_t*, uint32_t*, uint32_t*,             \
-                                             hipStream_t, const uint8_t*);                      \
+                                             hipStream_t, const uint16_t*);                     \
     template hipError_t run_intersect_counts<Key>(const TableDev&, const TableDev&, uint32_t*,  \
                                                   uint32_t*, unsigned long long*, hipStream_t); \
     template hipError_t run_intersect_pairs<Key>(const TableDev&, const TableDev&,              \

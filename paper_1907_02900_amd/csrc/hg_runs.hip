@@ -59,11 +59,6 @@ constexpr uint32_t small_cap() {
     return light_cap<Key>();
 }
 
-template <typename Key>
-__device__ __forceinline__ uint32_t key32(Key k) {
-    return sizeof(Key) == 4 ? (uint32_t)k : 0u;
-}
-
 // LDS of the per-bucket kernels: sort buffer, radix counters, scan temporaries.
 template <typename Key>
 struct BucketLds {
@@ -222,7 +217,7 @@ __device__ void emit_runs(const Key* sk, const uint32_t* sp, uint32_t O, Key lea
         const uint32_t rl = m.sh[1];
         rkey[st + rl] = lead;
         rend[st + rl] = nless + clead;
-        ix.head[b] = make_uint4(len, st, runs + 1, 0u);
+        put_long<Key>(ix, b, len, st, runs + 1, lead, clead);
     }
     __syncthreads();
 }
@@ -233,7 +228,7 @@ __device__ __forceinline__ void single_run(const IndexOut& ix, uint32_t b, uint3
                                            uint32_t len, Key lead) {
     ((Key*)ix.runs.run_key)[st] = lead;
     ix.runs.run_end[st] = len;
-    ix.head[b] = make_uint4(len, st, 1u, key32(lead));
+    put_long<Key>(ix, b, len, st, 1u, lead, len);
 }
 
 struct G2 {

@@ -23,6 +23,8 @@
 // Stable ranking (rank_stable) finds equal digits in a round of 64 items with
 // one ballot per digit bit and keeps per-wave running counts in LDS, updated
 // with non-returning atomics so that rounds do not wait on each other.
+#include <type_traits>
+
 #include "hg_v2_device.h"
 
 namespace hg {
@@ -776,7 +778,7 @@ __global__ __launch_bounds__(kLocalThreads) void k_huge_index(
             if (hi - lo > kRunBucket)
                 ix.gen_list[gen_region(bs, b) + atomicAdd(&nlisted, 1u)] = v0 + v;
             else
-                ix.head[v0 + v] = head_entry<Key>(lo, hi, ekeys + lo);
+                put_short<Key>(ix, v0 + v, lo, hi, ekeys + lo);
         }
         __syncthreads();
         if (threadIdx.x == 0) ix.gen_cnt[b] = nlisted;
@@ -786,12 +788,15 @@ __global__ __launch_bounds__(kLocalThreads) void k_huge_index(
 
 // One workgroup per final bin g (buckets [g*2^k, min((g+1)*2^k, V))) that
 // holds at most light_cap<Key>() keys.
-template <typename Key>
-__global__ __launch_bounds__(kLocalThreads) void k_local_light(
+// ANY: any order inside a bucket; W: bytes of an index entry (0: none).
+// Both are constants so that an any-order bin carries no sorting network: with
+// them as arguments the kernel took 146 VGPRs, one workgroup per CU.
+template <typename Key, bool ANY, int W>
+__global__ __launch_bounds__(kLocalThreads, 4) void k_local_light(
     const Key* __restrict__ src_keys, const uint32_t* __restrict__ src_ids,
     const uint32_t* __restrict__ bin_start, typename KeyTraits<Key>::Params hp, uint32_t k,
     uint32_t* __restrict__ offsets, IndexOut ix, uint32_t* __restrict__ ids,
-    Key* __restrict__ ekeys, bool any_order) {
+    Key* __restrict__ ekeys) {
     extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t g = blockIdx.x;
     const uint32_t start = bin_start[g], end = bin_start[g + 1];
@@ -799,8 +804,21 @@ __global__ __launch_bounds__(kLocalThreads) void k_local_light(
     if (L > light_cap<Key>()) return;  // oversize bins go to k_local_heavy
     const uint32_t NB = 1u << k, v0 = g << k, V = hp.range;
     const uint32_t nb = (V - v0 < NB) ? V - v0 : NB;
-    light_bin_body<Key>(src_keys + start, src_ids + start, 0u, L, start, v0, k, nb, hp, offsets,
-                        ix, ids, ekeys, smem, any_order);
+    light_bin_body<Key, ANY, W>(src_keys + start, src_ids + start, 0u, L, start, v0, k, nb, hp,
+                                offsets, ix, ids, ekeys, smem);
+}
+
+// Calls f with any_order and the index entry's bytes as constants.
+template <typename Key, typename F>
+void with_layout(bool any_order, const IndexOut& ix, F&& f) {
+    auto by_width = [&](auto any) {
+        if (!ix.head) f(any, std::integral_constant<int, 0>{});
+        else if constexpr (sizeof(Key) == 8) f(any, std::integral_constant<int, 16>{});
+        else if (ix.fmt.bytes == 4) f(any, std::integral_constant<int, 4>{});
+        else f(any, std::integral_constant<int, 8>{});
+    };
+    if (any_order) by_width(std::true_type{});
+    else by_width(std::false_type{});
 }
 
 // Oversize bins (from the device list), one workgroup per bin.
@@ -1070,8 +1088,19 @@ hipError_t set_smem_limits() {
                                    hipFuncAttributeMaxDynamicSharedMemorySize, lim));
         HG_TRY(hipFuncSetAttribute((const void*)k_tile_partition<Key, false, false, false, true>,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, lim));
-        HG_TRY(hipFuncSetAttribute((const void*)k_local_light<Key>,
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, lim));
+        hipError_t le = hipSuccess;
+        IndexOut ix{};
+        for (int i = 0; i < 6; ++i) {  // every layout and entry width
+            ix.head = i / 2 ? &le : nullptr;
+            ix.fmt.bytes = i / 2 == 1 ? 4 : 8;
+            with_layout<Key>(i & 1, ix, [&](auto any, auto width) {
+                const hipError_t e = hipFuncSetAttribute(
+                    (const void*)k_local_light<Key, decltype(any)::value, decltype(width)::value>,
+                    hipFuncAttributeMaxDynamicSharedMemorySize, lim);
+                if (e != hipSuccess) le = e;
+            });
+        }
+        HG_TRY(le);
         HG_TRY(hipFuncSetAttribute((const void*)k_local_heavy<Key>,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, lim));
         HG_TRY(hipFuncSetAttribute((const void*)k_huge_place<Key>,
@@ -1103,12 +1132,15 @@ hipError_t run_build_v2(const Key* keys, uint64_t n, uint64_t V, uint64_t seed, 
     ix.k = 0;
     ix.bins = 0;
     if (n == 0) {
-        if (ix.head) HG_TRY(fill_u32((uint32_t*)ix.head, 4 * V, 0u, s));
+        ix.fmt = head_fmt(0, V, sizeof(Key) * 8);
+        if (ix.head) HG_TRY(fill_u32((uint32_t*)ix.head, ix.fmt.bytes / 4 * V, 0u, s));
         return fill_u32(offsets, V + 1, 0u, s);
     }
     const V2Plan p = plan_v2(n, V, sizeof(Key) * 8, bins_hint);
     ix.k = p.k;
     ix.bins = p.bins;
+    ix.fmt = head_fmt(n, V, sizeof(Key) * 8);
+    ix.hp = make_hash_params(V, seed);
     V2Ws w;
     layout_v2(ws, p, sizeof(Key), &w);
     ix.gen_list = w.gen_list;
@@ -1157,11 +1189,13 @@ hipError_t run_build_v2(const Key* keys, uint64_t n, uint64_t V, uint64_t seed, 
     HG_TRY(hipGetLastError());
     {
         HG_PROF("v2_local_build", s);
-        hipLaunchKernelGGL(k_local_light<Key>, dim3(p.bins), dim3(kLocalThreads),
-                           ix.head ? light_smem_index<Key>(p.k) : light_smem<Key>(p.k), s,
-                           (const Key*)rkeys, (const uint32_t*)w.rids,
-                           (const uint32_t*)w.bin_start, hp, p.k, offsets, ix, ids, ekeys,
-                           !stable);
+        with_layout<Key>(!stable, ix, [&](auto any, auto width) {
+            hipLaunchKernelGGL((k_local_light<Key, decltype(any)::value, decltype(width)::value>),
+                               dim3(p.bins), dim3(kLocalThreads),
+                               ix.head ? light_smem_index<Key>(p.k) : light_smem<Key>(p.k), s,
+                               (const Key*)rkeys, (const uint32_t*)w.rids,
+                               (const uint32_t*)w.bin_start, hp, p.k, offsets, ix, ids, ekeys);
+        });
     }
     HG_TRY(hipGetLastError());
     {

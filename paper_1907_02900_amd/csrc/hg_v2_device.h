@@ -10,7 +10,7 @@ namespace v2dev {
 
 constexpr int W_PART = kPartThreads / kWave;
 constexpr int W_LOCAL = kLocalThreads / kWave;
-constexpr uint32_t kFixMax = 16;  // longest bucket the insertion-sort path handles
+constexpr uint32_t kFixMax = 16;  // longest bucket whose ids are ranked by counting
 
 // ------------------------------------------------------------ ranking -----
 
@@ -186,43 +186,6 @@ __device__ __forceinline__ void sort_chunk_by_bucket(Key (&kk)[ITEMS], uint32_t 
         }
 }
 
-// Put the s <= 8 entries of one bucket in LDS (ids[0..s), keys[0..s)) in
-// ascending id order, in registers: load them, run Batcher's odd-even merge
-// network for 8 (19 compare-exchanges; empty places hold id 0xffffffff,
-// above every real id, and sort last), store them back.  Unlike an insertion
-// sort in LDS it has no chain of dependent LDS reads.
-template <typename Key>
-__device__ __forceinline__ void sort8_by_id(uint32_t* ids, Key* keys, uint32_t s) {
-    uint32_t a[8];
-    Key k[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        a[j] = (uint32_t)j < s ? ids[j] : 0xffffffffu;
-        k[j] = (uint32_t)j < s ? keys[j] : Key(0);
-    }
-    auto cx = [&](int i, int j) {
-        const bool sw = a[j] < a[i];
-        const uint32_t ai = sw ? a[j] : a[i], aj = sw ? a[i] : a[j];
-        const Key ki = sw ? k[j] : k[i], kj = sw ? k[i] : k[j];
-        a[i] = ai;
-        a[j] = aj;
-        k[i] = ki;
-        k[j] = kj;
-    };
-    cx(0, 1); cx(2, 3); cx(4, 5); cx(6, 7);
-    cx(0, 2); cx(1, 3); cx(4, 6); cx(5, 7);
-    cx(1, 2); cx(5, 6);
-    cx(0, 4); cx(1, 5); cx(2, 6); cx(3, 7);
-    cx(2, 4); cx(3, 5);
-    cx(1, 2); cx(3, 4); cx(5, 6);
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-        if ((uint32_t)j < s) {
-            ids[j] = a[j];
-            keys[j] = k[j];
-        }
-}
-
 // Exclusive scan of cnt[0..NB) in place (NB a power of two); returns via
 // cnt; *total gets the sum.  All threads must call it.
 __device__ __forceinline__ void scan_counts(uint32_t* cnt, uint32_t NB, uint32_t base,
@@ -293,51 +256,17 @@ inline size_t heavy_smem(uint32_t k) {
            (2 * W_LOCAL + 2) * 4 + 64;
 }
 
-// Probe index entry of one bucket, x = its length.  32-bit keys: a bucket of
-// at most three keys holds them all in y, z, w (its start is not needed to
-// count matches); a longer one holds {len, start, first key, c0 | filter << 8}
-// with c0 the entries equal to the first key and the filter of the other keys
-// (filter_bit), so a query equal to the first key, any query against a bucket
-// of one repeated key, and most queries matching no other key are answered
-// without reading the edge array.  64-bit keys: {len, start, low and high
-// half of the key} for a bucket of at most one key, {len, start, filter of
-// all its keys (filter_bits64), low and high half} for a longer one, so that
-// most queries matching none of its keys skip the edge array.  Unused key
-// slots are 0.  A bucket longer than kRunBucket later gets its key-run
-// summary in z, w.  `k` points at the bucket's first key.
-template <typename Key>
-__device__ __forceinline__ uint4 head_entry(uint32_t start, uint32_t end, const Key* k);
-
-template <>
-__device__ __forceinline__ uint4 head_entry<uint32_t>(uint32_t start, uint32_t end,
-                                                      const uint32_t* k) {
-    const uint32_t len = end - start;
-    if (len <= 3)
-        return make_uint4(len, len >= 1 ? k[0] : 0u, len >= 2 ? k[1] : 0u, len >= 3 ? k[2] : 0u);
-    const uint32_t k0 = k[0];
-    uint32_t c0 = 0, filt = 0;  // long buckets get their key runs in z, w instead
-    if (len <= kRunBucket) {
-        c0 = 1;
-        // four keys per round, so that their loads overlap
-#pragma unroll 1
-        for (uint32_t i = 1; i < len; i += 4) {
-            uint32_t kv[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) kv[j] = i + j < len ? k[i + j] : k0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (i + j >= len) continue;
-                if (kv[j] == k0) ++c0;
-                else filt |= 1u << filter_bit(kv[j]);
-            }
-        }
-    }
-    return make_uint4(len, start, k0, c0 | filt << 8);
+__device__ __forceinline__ void store_word(const IndexOut& ix, uint32_t bucket, uint64_t w) {
+    if (ix.fmt.bytes == 4) ((uint32_t*)ix.head)[bucket] = (uint32_t)w;
+    else ((uint64_t*)ix.head)[bucket] = w;
 }
 
-template <>
-__device__ __forceinline__ uint4 head_entry<uint64_t>(uint32_t start, uint32_t end,
-                                                      const uint64_t* k) {
+// 64-bit keys: {len, start, low and high half of the key} for a bucket of at
+// most one key, {len, start, filter of all its keys (filter_bits64), low and
+// high half} for a longer one, so that most queries matching none of its keys
+// skip the edge array.  A bucket longer than kRunBucket later gets its
+// key-run summary in z.  `k` points at the bucket's first key.
+__device__ __forceinline__ uint4 head_entry64(uint32_t start, uint32_t end, const uint64_t* k) {
     const uint32_t len = end - start;
     uint64_t z = len == 1 ? k[0] : 0ull;
     if (len >= 2 && len <= kRunBucket) {
@@ -351,6 +280,40 @@ __device__ __forceinline__ uint4 head_entry<uint64_t>(uint32_t start, uint32_t e
         }
     }
     return make_uint4(len, start, (uint32_t)z, (uint32_t)(z >> 32));
+}
+
+// Writes the index entry of a bucket of at most kRunBucket entries, edge
+// positions [start, end), whose first key is at k (LDS or global).
+template <typename Key>
+__device__ __forceinline__ void put_short(const IndexOut& ix, uint32_t bucket, uint32_t start,
+                                          uint32_t end, const Key* k) {
+    if constexpr (sizeof(Key) == 4) {
+        store_word(ix, bucket, short_word(ix.fmt, end - start, [&](uint32_t i) {
+                       uint32_t h;
+                       return KeyTraits<uint32_t>::quotient(k[i], ix.hp, h);
+                   }));
+    } else {
+        ((uint4*)ix.head)[bucket] = head_entry64(start, end, k);
+    }
+}
+
+// Writes the index entry of a long bucket of R key runs (R = 0: none), whose
+// first key `lead` clead entries equal, and (32-bit keys) R itself behind the
+// runs.
+template <typename Key>
+__device__ __forceinline__ void put_long(const IndexOut& ix, uint32_t bucket, uint32_t len,
+                                         uint32_t start, uint32_t R, Key lead, uint32_t clead) {
+    if constexpr (sizeof(Key) == 4) {
+        uint32_t h;
+        const uint32_t room = 8 * ix.fmt.bytes - 6 - ix.fmt.qb;  // at least 17 bits
+        uint64_t w = (uint64_t)KeyTraits<uint32_t>::quotient(lead, ix.hp, h) << 6 |
+                     (R == 0 ? 32u : R == 1 ? 16u : 0u) | kCodeLong;
+        if (R && (room >= 32 || clead >> room == 0)) w |= (uint64_t)clead << (6 + ix.fmt.qb);
+        store_word(ix, bucket, w);
+        if (R > 1) ix.runs.run_end[start + len - 1] = R;
+    } else {
+        ((uint4*)ix.head)[bucket] = make_uint4(len, start, R, 0u);
+    }
 }
 
 // LDS of the per-bin key runs (after light_smem's layout, 16-byte aligned):
@@ -379,10 +342,22 @@ struct LongLds {
 
 __host__ __device__ inline size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
 
-// LDS bytes of a light bin that also builds its key runs.
+// Most medium buckets a bin can list (lengths above head_lane_max).
+template <typename Key>
+__host__ __device__ constexpr uint32_t medium_cap() {
+    return light_cap<Key>() / (sizeof(Key) == 4 ? 9 : 17) + 1;
+}
+
+// LDS bytes of a light bin that also builds its index entries and key runs:
+// beside light_smem, the long buckets and, where the bucket sort's scratch
+// was, the medium buckets and (32-bit keys) one entry word per bucket.  At 2^12
+// buckets 77.6 KB: two workgroups per CU.
 template <typename Key>
 __host__ __device__ inline size_t light_smem_index(uint32_t k) {
-    return align16(light_smem<Key>(k)) + LongLds<Key>::bytes();
+    const size_t scratch = light_cap<Key>() * 2;
+    const size_t words = 4 * medium_cap<Key>() + (sizeof(Key) == 4 ? (size_t)4 << k : 0);
+    return align16(light_smem<Key>(k) - scratch) + LongLds<Key>::bytes() + 16 +
+           (words > scratch ? words : scratch) + 16;
 }
 
 // Sort the 64 lanes' (key, position) pairs ascending (bitonic network over
@@ -407,35 +382,33 @@ __device__ __forceinline__ void wave_sort_pairs(Key& k, uint32_t& p) {
     }
 }
 
-// Buckets whose index entry is built by one lane: up to 16 entries (rounds
-// of four overlapped LDS reads).  Longer ones up to kRunBucket entries --
-// common only when keys repeat many times -- are listed and built by groups
-// of 32 lanes (bin_medium_heads) instead of one lane walking them in up to
-// eight rounds.  (Groups of 16 lanes for buckets of 9-16 entries were faster
-// only when keys repeat about 16 times, and slower below that.)
+// Buckets whose index entry one lane builds key by key (32-bit keys: those
+// past the entry's capacity, whose quotients it hashes again).  Longer ones up
+// to kRunBucket entries -- common only when keys repeat many times -- are
+// listed and built by groups of 32 lanes (bin_medium_heads) instead of one
+// lane walking them.
 template <typename Key>
-constexpr uint32_t head_lane_max() { return 16u; }
+__host__ __device__ constexpr uint32_t head_lane_max() { return sizeof(Key) == 4 ? 8u : 16u; }
 
-// A bucket's probe index entry, or its place in one of the bin's lists: the
-// long buckets (more than kRunBucket entries; their entries are written with
-// their key runs) and the medium ones (their entries are written by lane
-// groups), med[] packing lo | len << 13 | v << 19 (v = local bucket).  k
-// points at the bucket's first key in LDS.
+// Lists a bucket whose index entry is not one lane's work: the long buckets
+// (more than kRunBucket entries; their entries are written with their key
+// runs) and the medium ones (their entries are written by lane groups), med[]
+// packing lo | len << 13 | v << 19 (v = local bucket).  False: neither.
 template <typename Key>
-__device__ __forceinline__ void note_bucket(const IndexOut& ix, const LongLds<Key>& lr,
-                                            uint32_t* med, uint32_t v0, uint32_t v,
-                                            uint32_t out, uint32_t lo, uint32_t hi,
-                                            const Key* k) {
+__device__ __forceinline__ bool list_bucket(const LongLds<Key>& lr, uint32_t* med, uint32_t v0,
+                                            uint32_t v, uint32_t lo, uint32_t hi) {
     const uint32_t len = hi - lo;
     if (len > kRunBucket) {
         const uint32_t t = atomicAdd(&lr.cnt[0], 1u);
         lr.lohi[t] = lo | (hi << 16);
         lr.bkt[t] = v0 + v;
-    } else if (len > head_lane_max<Key>()) {
-        med[atomicAdd(&lr.cnt[2], 1u)] = lo | (len << 13) | (v << 19);
-    } else {
-        ix.head[v0 + v] = head_entry<Key>(out + lo, out + hi, k);
+        return true;
     }
+    if (len > head_lane_max<Key>()) {
+        med[atomicAdd(&lr.cnt[2], 1u)] = lo | (len << 13) | (v << 19);
+        return true;
+    }
+    return false;
 }
 
 // OR over each row of 16 lanes, left in the row's last lane (lanes 15, 31,
@@ -465,7 +438,7 @@ __device__ __forceinline__ uint32_t group_or(uint32_t f, uint32_t g) {
 // Index entries of the medium buckets in list[0, n), whose lengths are at
 // most G: each wave takes 64 / G buckets at a time, lane s of group g holding
 // key s of its bucket; the first key's count is a ballot and the filter an
-// OR over the group -- the same entry head_entry builds with one lane.
+// OR over the group -- the same entry put_short builds with one lane.
 template <typename Key, uint32_t G>
 __device__ __forceinline__ void medium_heads_by(const IndexOut& ix, const uint32_t* list,
                                                 uint32_t n, const Key* skeys, uint32_t out,
@@ -482,15 +455,21 @@ __device__ __forceinline__ void medium_heads_by(const IndexOut& ix, const uint32
         const Key k0 = skeys[lo];
         const Key kx = in ? skeys[lo + s] : k0;
         if constexpr (sizeof(Key) == 4) {
+            // (listed buckets are longer than an entry's capacity)
             const uint64_t eq = ballot(in && kx == k0);
             const uint32_t c0 = (uint32_t)__popcll((eq >> (g * G)) & ((1ull << G) - 1ull));
+            uint32_t h;
+            const uint32_t q = KeyTraits<uint32_t>::quotient(kx, ix.hp, h);
             const uint32_t f =
-                group_or<G>((in && kx != k0) ? (1u << filter_bit((uint32_t)kx)) : 0u, g);
-            if (have && s == 0) ix.head[v0 + v] = make_uint4(len, out + lo, (uint32_t)k0, c0 | f << 8);
+                group_or<G>((in && kx != k0) ? (1u << filter_bit(q, ix.fmt.nf)) : 0u, g);
+            if (have && s == 0)  // lane 0's key is the first one
+                store_word(ix, v0 + v,
+                           (uint64_t)kCodeMedium | (uint64_t)c0 << 4 | (uint64_t)q << 12 |
+                               (uint64_t)f << (12 + ix.fmt.qb));
         } else {
             const uint64_t z = in ? filter_bits64((uint64_t)kx) : 0ull;
             const uint32_t zl = group_or<G>((uint32_t)z, g), zh = group_or<G>((uint32_t)(z >> 32), g);
-            if (have && s == 0) ix.head[v0 + v] = make_uint4(len, out + lo, zl, zh);
+            if (have && s == 0) ((uint4*)ix.head)[v0 + v] = make_uint4(len, out + lo, zl, zh);
         }
     }
 }
@@ -542,7 +521,7 @@ __device__ __forceinline__ bool wave_bucket_runs(const IndexOut& ix, const Key* 
         if (lane == 0) {
             rkey[st] = lead;
             rend[st] = len;
-            ix.head[b] = make_uint4(len, st, 1u, sizeof(Key) == 4 ? (uint32_t)lead : 0u);
+            put_long<Key>(ix, b, len, st, 1u, lead, len);
         }
         return true;
     }
@@ -571,7 +550,7 @@ __device__ __forceinline__ bool wave_bucket_runs(const IndexOut& ix, const Key* 
     if (lane == 0) {
         rkey[st + rl] = lead;
         rend[st + rl] = nless + clead;
-        ix.head[b] = make_uint4(len, st, (uint32_t)__popcll(fb) + 1u, 0u);
+        put_long<Key>(ix, b, len, st, (uint32_t)__popcll(fb) + 1u, lead, clead);
     }
     // the lead key's ids, in bucket order, after the smaller keys' runs
     uint32_t done = 0;
@@ -612,20 +591,85 @@ __device__ __forceinline__ void bin_long_runs(const IndexOut& ix, const LongLds<
     if (threadIdx.x == 0) ix.gen_cnt[g] = lr.cnt[1];
 }
 
+// Index entries of a bin's buckets (32-bit keys).  Entry words are put together
+// key by key, not bucket by bucket: each ORs its quotient into its bucket's
+// word in LDS (`or_part(f, high)`: the lower or upper 32 bits of every key),
+// one atomic a key and no divergence, then each thread adds the code and
+// stores the word.  A lane walking its bucket's keys would run as long as the
+// longest bucket of its wave, about five rounds at load 1.  Entries of eight
+// bytes take a second round for their upper halves, so that the words need 4
+// bytes of LDS per bucket either way.  words[] is zero on entry; cnt[v] = start
+// of bucket v in the bin, cnt[NB] = its end.  Whole workgroup; barriers.
+template <int W, typename OrPart>
+__device__ __forceinline__ void words_of_bin(OrPart or_part, uint32_t* words, const uint32_t* skeys,
+                                             uint32_t out, uint32_t v0, uint32_t nb,
+                                             const uint32_t* cnt, uint32_t* __restrict__ offsets,
+                                             const IndexOut& ix, const LongLds<uint32_t>& lr,
+                                             uint32_t* med) {
+    constexpr uint32_t PER = (1u << kMaxLocalBits) / kLocalThreads;
+    const HeadFmt& f = ix.fmt;
+    or_part(words, false);
+    __syncthreads();
+    uint32_t lo32[PER];
+    if constexpr (W == 8) {
+#pragma unroll
+        for (uint32_t j = 0; j < PER; ++j) {
+            const uint32_t v = threadIdx.x + j * kLocalThreads;
+            if (v < nb) {
+                lo32[j] = words[v];
+                words[v] = 0;
+            }
+        }
+        __syncthreads();
+        or_part(words, true);
+        __syncthreads();
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < PER; ++j) {
+        const uint32_t v = threadIdx.x + j * kLocalThreads;
+        if (v >= nb) continue;
+        const uint32_t lo = cnt[v], hi = cnt[v + 1], len = hi - lo;
+        offsets[v0 + v] = out + lo;
+        if (len <= f.cap) {
+            if constexpr (W == 8)
+                ((uint64_t*)ix.head)[v0 + v] = (uint64_t)words[v] << 32 | lo32[j] | len;
+            else
+                ((uint32_t*)ix.head)[v0 + v] = words[v] | len;
+        } else if (!list_bucket<uint32_t>(lr, med, v0, v, lo, hi)) {
+            put_short<uint32_t>(ix, v0 + v, out + lo, out + hi, skeys + lo);
+        }
+    }
+}
+
+// The part (lower or upper 32 bits) of an entry that the i-th key of its
+// bucket, with quotient q, fills.
+__device__ __forceinline__ void or_field(uint32_t* word, const HeadFmt& f, uint32_t i, uint32_t q,
+                                         bool high) {
+    const uint32_t sh = 4 + i * f.qb;
+    if (i >= f.cap) return;
+    if (!high) {
+        if (sh < 32) atomicOr(word, q << sh);
+    } else if (sh + f.qb > 32) {
+        atomicOr(word, sh < 32 ? q >> (32 - sh) : q << (sh - 32));
+    }
+}
+
 // Build one bin of L <= light_cap<Key>() keys whose buckets are [v0, v0 + nb) with
 // nb <= 2^k.  Entry e (e < L) of the bin is src_keys[e], with id src_ids[e]
 // (or id_base + e when src_ids is null).  The bin's keys and ids go to
 // ekeys/ids[out + p] for p < L, sorted by bucket with ids ascending inside a
 // bucket, and offsets[v0 + v] = out + (start of bucket v in the bin).
 // Usual case (every bucket of the bin holds at most kFixMax keys, or any order
-// is allowed): LDS
-// counting sort with atomic cursors, then an insertion sort by id inside each
-// bucket (skipped with any_order: order inside a bucket is then unspecified).
-// Otherwise the bin (in id order) is stably ranked by local bucket.
-// When ix.head is not null it also receives each bucket's probe index entry.
-// `bucket_of(key, e)` gives the local bucket (< nb) of entry e.
+// is allowed): an LDS counting sort -- the counting atomic returns each key's
+// arrival rank in its bucket, so that placing it takes no second one -- and, in
+// the stable layout, its rank by id counted over the bucket.  Otherwise the bin (in id order) is stably ranked by local
+// bucket.
+// With W > 0, ix.head also receives each bucket's probe index entry.
+// `bucket_of(key, e, q)` gives the local bucket (< nb) of entry e and, where an
+// index is written, sets q to its quotient (32-bit keys).
 // Called by a whole workgroup of kLocalThreads threads.
-template <typename Key, typename BucketOf>
+// ANY: any order inside a bucket; W: bytes of an index entry (0: no index).
+template <typename Key, bool ANY, int W, typename BucketOf>
 __device__ __forceinline__ void light_bin_body_by(const Key* __restrict__ src_keys,
                                                   const uint32_t* __restrict__ src_ids,
                                                   uint32_t id_base, uint32_t L, uint32_t out,
@@ -633,24 +677,27 @@ __device__ __forceinline__ void light_bin_body_by(const Key* __restrict__ src_ke
                                                   BucketOf bucket_of,
                                                   uint32_t* __restrict__ offsets,
                                                   const IndexOut& ix, uint32_t* __restrict__ ids,
-                                                  Key* __restrict__ ekeys, unsigned char* smem,
-                                                  bool any_order) {
+                                                  Key* __restrict__ ekeys, unsigned char* smem) {
     constexpr int IT = light_items<Key>();
     constexpr uint32_t kLightCap = light_cap<Key>();
     const uint32_t NB = 1u << k;
     Key* skeys = (Key*)smem;
     uint32_t* sids = (uint32_t*)(skeys + kLightCap);
-    uint16_t* sb = (uint16_t*)(sids + kLightCap);
-    // the bucket sort's scratch holds the list of medium buckets afterwards
-    // (at most kLightCap / (head_lane_max + 1) of them; room for kLightCap / 2)
+    uint32_t* cnt = sids + kLightCap;              // NB + 1 (in light_smem's padding)
+    uint32_t* wcnt = cnt + NB + 1;                 // W * 64
+    uint32_t* dstart = wcnt + W_LOCAL * 64;        // 64
+    uint32_t* tmp = dstart + 64;                   // 2 * W + 2
+    // the bin's long buckets, when the probe index is written, then the
+    // bucket sort's scratch, whose place the lists of medium buckets and the
+    // entry words take (stable layout: afterwards)
+    const size_t front = align16(light_smem<Key>(k) - 2 * kLightCap);
+    const LongLds<Key> lr(smem + front);
+    uint16_t* sb = W ? (uint16_t*)(smem + align16(front + LongLds<Key>::bytes()))
+                     : (uint16_t*)(tmp + 2 * W_LOCAL + 2);
     static_assert(kLightCap <= 8192u, "a medium-list entry holds lo in 13 bits");
     uint32_t* med = (uint32_t*)sb;
-    uint32_t* cnt = (uint32_t*)(sb + kLightCap);  // NB
-    uint32_t* wcnt = cnt + NB;                     // W * 64
-    uint32_t* dstart = wcnt + W_LOCAL * 64;        // 64
-    uint32_t* tmp = dstart + 64;
-    // the bin's long buckets, when the probe index is written
-    const LongLds<Key> lr(smem + align16(light_smem<Key>(k)));
+    uint32_t* words = med + medium_cap<Key>();
+    constexpr bool by_key = W == 4 || W == 8;  // entry words put together key by key
     const uint32_t w = threadIdx.x / kWave, lane = lane_id();
     // balance the bin over the waves in whole rounds of 64
     const uint32_t wchunk = (((L + W_LOCAL - 1) / W_LOCAL) + kWave - 1) & ~(uint32_t)(kWave - 1);
@@ -659,7 +706,9 @@ __device__ __forceinline__ void light_bin_body_by(const Key* __restrict__ src_ke
     const uint32_t rounds = (mylen + kWave - 1) / kWave;
 
     Key kk[IT];
-    uint32_t id[IT], b[IT];
+    // br: the local bucket, and above it the rank in the bucket
+    uint32_t id[IT], br[IT], qt[IT];
+    constexpr uint32_t kNone = ~0u, kBktMask = (1u << (kMaxLocalBits + 1)) - 1;
 #pragma unroll
     for (int r = 0; r < IT; ++r) {
         const uint32_t e = wb + r * kWave + lane;
@@ -672,89 +721,110 @@ __device__ __forceinline__ void light_bin_body_by(const Key* __restrict__ src_ke
         }
     }
     for (uint32_t i = threadIdx.x; i < NB; i += kLocalThreads) cnt[i] = 0;
-    if (ix.head && threadIdx.x < 3) lr.cnt[threadIdx.x] = 0;
-    if (threadIdx.x == 0) dstart[0] = 0;  // list of multi-entry buckets (stable path)
+    if (by_key)
+        for (uint32_t i = threadIdx.x; i < NB; i += kLocalThreads) words[i] = 0;
+    if (W && threadIdx.x < 3) lr.cnt[threadIdx.x] = 0;
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < IT; ++r) {
+        br[r] = kNone;
+        qt[r] = 0;
         if ((uint32_t)r < rounds && r * kWave + lane < mylen) {
-            b[r] = bucket_of(kk[r], wb + r * kWave + lane);
-            atomicAdd(&cnt[b[r]], 1u);
-        } else {
-            b[r] = NB;
+            const uint32_t b = bucket_of(kk[r], wb + r * kWave + lane, qt[r]);
+            br[r] = b | atomicAdd(&cnt[b], 1u) << (kMaxLocalBits + 1);
         }
     }
     __syncthreads();
     // bucket starts (in place) and the largest bucket of the bin
     const uint32_t maxc = scan_counts_max(cnt, NB, tmp);
-    if (maxc <= kFixMax || any_order) {
+    if (threadIdx.x == 0) cnt[NB] = L;
+    // whether br holds every key's place in its bucket
+    const bool ranked = ANY || maxc <= kFixMax;
+    if (ranked) {
+        if constexpr (!ANY) {
+            // a key's place in its bucket is the number of the bucket's ids
+            // below its own, counted by every key over the ids placed in the
+            // order of arrival.  (One lane per bucket sorting it in registers
+            // took 122 VGPRs and a list of the buckets to sort.)
+#pragma unroll
+            for (int r = 0; r < IT; ++r)
+                if (br[r] != kNone)
+                    sids[cnt[br[r] & kBktMask] + (br[r] >> (kMaxLocalBits + 1))] = id[r];
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < IT; ++r) {
+                if (br[r] == kNone) continue;
+                const uint32_t v = br[r] & kBktMask;
+                const uint32_t lo = cnt[v], hi = cnt[v + 1];
+                uint32_t below = 0;
+                if (hi - lo > 1)
+                    for (uint32_t i = lo; i < hi; ++i) below += sids[i] < id[r] ? 1u : 0u;
+                br[r] = v | below << (kMaxLocalBits + 1);
+            }
+            __syncthreads();
+        }
 #pragma unroll
         for (int r = 0; r < IT; ++r) {
-            if (b[r] < NB) {
-                const uint32_t slot = atomicAdd(&cnt[b[r]], 1u);
+            if (br[r] != kNone) {
+                const uint32_t slot = cnt[br[r] & kBktMask] + (br[r] >> (kMaxLocalBits + 1));
                 skeys[slot] = kk[r];
                 sids[slot] = id[r];
             }
         }
         __syncthreads();
-        // cnt[v] is now the end of bucket v; ids are put back in ascending
-        // order inside each (short) bucket unless any order is allowed.  The
-        // buckets of two or more entries are listed first (in the bucket
-        // sort's scratch, unused on this path: at most L / 2 of them, packed
-        // lo | len << 16), so that every lane of the sorting pass has one.
-        if (!any_order) {
-            uint32_t* multi = (uint32_t*)sb;
-            for (uint32_t v = threadIdx.x; v < NB; v += kLocalThreads) {
-                const uint32_t lo = v ? cnt[v - 1] : 0u, hi = cnt[v];
-                if (hi - lo >= 2) multi[atomicAdd(&dstart[0], 1u)] = lo | ((hi - lo) << 16);
-            }
-            __syncthreads();
-            const uint32_t nmulti = dstart[0];
-            for (uint32_t j = threadIdx.x; j < nmulti; j += kLocalThreads) {
-                const uint32_t lo = multi[j] & 0xffffu, len = multi[j] >> 16, hi = lo + len;
-                if (len <= 8) {
-                    sort8_by_id<Key>(sids + lo, skeys + lo, len);
-                    continue;
-                }
-                for (uint32_t i = lo + 1; i < hi; ++i) {
-                    const uint32_t idv = sids[i];
-                    const Key kv = skeys[i];
-                    uint32_t j2 = i;
-                    while (j2 > lo && sids[j2 - 1] > idv) {
-                        sids[j2] = sids[j2 - 1];
-                        skeys[j2] = skeys[j2 - 1];
-                        --j2;
-                    }
-                    sids[j2] = idv;
-                    skeys[j2] = kv;
-                }
-            }
-        }
-        __syncthreads();
-        for (uint32_t v = threadIdx.x; v < nb; v += kLocalThreads) {
-            const uint32_t lo = v ? cnt[v - 1] : 0u, hi = cnt[v];
-            offsets[v0 + v] = out + lo;
-            if (ix.head) note_bucket<Key>(ix, lr, med, v0, v, out, lo, hi, skeys + lo);
-        }
     } else {
-        sort_chunk_by_bucket<Key, IT>(kk, id, b, rounds, L, wchunk, k, skeys, sids, sb, wcnt,
-                                      dstart, tmp);
-        __syncthreads();
+        if constexpr (!ANY) {
+            uint32_t b[IT];
+#pragma unroll
+            for (int r = 0; r < IT; ++r) {
+                b[r] = br[r] == kNone ? NB : br[r] & kBktMask;
+                br[r] = kNone;  // (not kept in registers over the sort)
+                qt[r] = 0;
+            }
+            sort_chunk_by_bucket<Key, IT>(kk, id, b, rounds, L, wchunk, k, skeys, sids, sb, wcnt,
+                                          dstart, tmp);
+            __syncthreads();
+        }
+    }
+    if constexpr (by_key) {
+        if (!ranked) {  // the words' place held the bucket sort's scratch
+            for (uint32_t i = threadIdx.x; i < NB; i += kLocalThreads) words[i] = 0;
+            __syncthreads();
+        }
+        words_of_bin<W>(
+            [&](uint32_t* wd, bool high) {
+                if (ranked) {  // from registers
+#pragma unroll
+                    for (int r = 0; r < IT; ++r)
+                        if (br[r] != kNone)
+                            or_field(&wd[br[r] & kBktMask], ix.fmt, br[r] >> (kMaxLocalBits + 1),
+                                     qt[r], high);
+                } else if constexpr (!ANY) {  // from the sorted bin
+                    for (uint32_t p = threadIdx.x; p < L; p += kLocalThreads) {
+                        uint32_t q;
+                        const uint32_t v = bucket_of(skeys[p], p, q);
+                        or_field(&wd[v], ix.fmt, p - cnt[v], q, high);
+                    }
+                }
+            },
+            words, skeys, out, v0, nb, cnt, offsets, ix, lr, med);
+    } else {
         for (uint32_t v = threadIdx.x; v < nb; v += kLocalThreads) {
-            const uint32_t lo = cnt[v], hi = (v + 1 < NB) ? cnt[v + 1] : L;
+            const uint32_t lo = cnt[v], hi = cnt[v + 1];
             offsets[v0 + v] = out + lo;
-            if (ix.head) note_bucket<Key>(ix, lr, med, v0, v, out, lo, hi, skeys + lo);
+            if (W && !list_bucket<Key>(lr, med, v0, v, lo, hi))
+                put_short<Key>(ix, v0 + v, out + lo, out + hi, skeys + lo);
         }
     }
     for (uint32_t p = threadIdx.x; p < L; p += kLocalThreads) {
         ekeys[out + p] = skeys[p];
         ids[out + p] = sids[p];
     }
-    if (ix.head) bin_long_runs<Key>(ix, lr, med, skeys, sids, out, v0 >> k, v0);
+    if constexpr (W != 0) bin_long_runs<Key>(ix, lr, med, skeys, sids, out, v0 >> k, v0);
 }
 
 // The usual bin: buckets [v0, v0 + nb) of the table's hash function.
-template <typename Key>
+template <typename Key, bool ANY, int W>
 __device__ __forceinline__ void light_bin_body(const Key* __restrict__ src_keys,
                                                const uint32_t* __restrict__ src_ids,
                                                uint32_t id_base, uint32_t L, uint32_t out,
@@ -763,11 +833,19 @@ __device__ __forceinline__ void light_bin_body(const Key* __restrict__ src_keys,
                                                uint32_t* __restrict__ offsets,
                                                const IndexOut& ix,
                                                uint32_t* __restrict__ ids, Key* __restrict__ ekeys,
-                                               unsigned char* smem, bool any_order = false) {
-    light_bin_body_by<Key>(
+                                               unsigned char* smem) {
+    light_bin_body_by<Key, ANY, W>(
         src_keys, src_ids, id_base, L, out, v0, k, nb,
-        [&](Key key, uint32_t) { return KeyTraits<Key>::bucket(key, hp) - v0; }, offsets, ix, ids,
-        ekeys, smem, any_order);
+        [&](Key key, uint32_t, uint32_t& q) {
+            if constexpr (sizeof(Key) == 4) {
+                uint32_t h;
+                q = KeyTraits<Key>::quotient(key, hp, h);
+                return h - v0;
+            } else {
+                return KeyTraits<Key>::bucket(key, hp) - v0;
+            }
+        },
+        offsets, ix, ids, ekeys, smem);
 }
 
 // Pointers into the heavy_smem layout.
@@ -965,7 +1043,7 @@ __device__ __forceinline__ void heavy_bin_body(const Key* __restrict__ src_keys,
             if (cur[v] - lo > kRunBucket)
                 ix.gen_list[gen_region(out, v0 >> k) + atomicAdd(nlisted, 1u)] = v0 + v;
             else
-                ix.head[v0 + v] = head_entry<Key>(lo, cur[v], ekeys + lo);
+                put_short<Key>(ix, v0 + v, lo, cur[v], ekeys + lo);
         }
         __syncthreads();
         if (threadIdx.x == 0) ix.gen_cnt[v0 >> k] = *nlisted;
