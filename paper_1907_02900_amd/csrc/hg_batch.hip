@@ -1055,7 +1055,7 @@ struct Server {
     static uint64_t table_bytes(uint64_t n, uint64_t V, int kb, bool index) {
         const uint64_t nn = n ? n : 1;
         return (V + 1) * 4 + nn * (4 + (uint64_t)kb / 8) +
-               (index ? V * 16 + nn * ((uint64_t)kb / 8 + 8) : 0);
+               (index ? V * head_fmt(n, V, kb).bytes + nn * ((uint64_t)kb / 8 + 8) : 0);
     }
 
     void free_table(STable& t, hipStream_t s) {

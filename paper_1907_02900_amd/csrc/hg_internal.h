@@ -128,7 +128,28 @@ template <typename Key>
 constexpr uint32_t light_cap() { return kLocalThreads * light_items<Key>(); }
 constexpr int kHeavyItems = 8;
 constexpr uint32_t kHeavyChunk = kLocalThreads * kHeavyItems;  // chunk of an oversize bin
-constexpr uint32_t kSliceKeys = 1u << 17;  // bins above this are split over workgroups
+// Bins above slice_keys(n) keys are split over workgroups, slice by slice.  A
+// bin below it is one workgroup's serial work, so slices shrink with n until a
+// build has about 2048 of them: with 2^17 keys at any n, the largest such bin
+// of 2^26 Zipf(1.2) keys ran 860 us alone.  (Builds of up to 2^17 keys split
+// nothing.)
+inline uint32_t slice_keys(uint64_t n) {
+    if (n <= (1u << 17)) return 1u << 17;
+    uint32_t k = 1u << 14;
+    while (k < (1u << 17) && (uint64_t)k * 2048 < n) k <<= 1;
+    return k;
+}
+// Most split bins of a build of n keys (n / slice_keys(n)), as a bound that
+// grows with n (a table's workspace serves every build up to its capacity);
+// their slices are at most twice as many.
+inline uint32_t split_cap(uint64_t n) {
+    const uint64_t a = n <= (1u << 17) ? 0 : n >> 14, b = n >> 17;
+    return (uint32_t)((a < 2048 ? a : 2048) > b ? (a < 2048 ? a : 2048) : b) + 1;
+}
+// Device counters of a build, zeroed by its first kernel: oversize bins, split
+// bins, their slices, long buckets of the chunked path, their chunks, whether
+// any bin listed a long bucket.
+enum : uint32_t { kCtrHeavy, kCtrSplit, kCtrSlices, kCtrLong, kCtrChunks, kCtrListed, kCtrWords };
 constexpr uint32_t kMaxLocalBits = 12;                          // buckets per bin <= 4096
 constexpr uint32_t kMaxDigitBits = 11;                       // partition fan-out <= 2048
 constexpr uint32_t kOneTierBits = 9;                         // single partition pass up to 512 bins
@@ -360,20 +381,31 @@ struct IndexOut {
     RunsDev runs{};
     uint32_t* gen_list = nullptr;
     uint32_t* gen_cnt = nullptr;  // [bins]
+    uint32_t* gen_any = nullptr;  // set when any bin lists a bucket
     uint32_t k = 0, bins = 0;
 };
 
-// The general pass over the long buckets the per-bin kernels listed (buckets
-// of many distinct keys, and every long bucket of the bins too large for
-// LDS).  Enqueued after the per-bin build; its work lists live on the device,
-// so nothing waits for the host.  ws: runs_ws_bytes(n, bins) bytes; rkeys /
-// rids: the build's reorganisation arrays (n entries), free by then and used
-// as scratch; ctr: two zeroed counters.
-size_t runs_ws_bytes(uint64_t n, uint64_t bins);
+// The rare path of a build, after its per-bin kernel: bins too large for LDS
+// and the long buckets whose key runs the per-bin kernels left (hg_runs.hip).
+// Its work lists live on the device, so nothing waits for the host.  ws:
+// runs_ws_bytes(n) bytes; rkeys / rids: the build's reorganised entries, free
+// afterwards; ctr: kCtrWords counters.
+struct RareArgs {
+    const uint32_t* bin_start;
+    const uint32_t* heavy_list;
+    const uint32_t *huge_list, *huge_s0, *slice_owner;
+    uint32_t *slice_hist, *range_sum;
+    uint32_t* ctr;
+    uint32_t huge_cap, slice_cap, slice;
+    uint32_t k, bins, V;
+    uint32_t any_order;
+};
+size_t runs_ws_bytes(uint64_t n);
+size_t range_sum_words(uint64_t slices);  // words of RareArgs::range_sum
 template <typename Key>
-hipError_t run_key_runs(const uint32_t* offsets, const uint32_t* ids, const Key* ekeys,
-                        uint64_t n, const uint32_t* bin_start, uint32_t bins, const IndexOut& ix,
-                        Key* rkeys, uint32_t* rids, uint32_t* ctr, void* ws, hipStream_t s);
+hipError_t run_rare(const RareArgs& a, uint32_t* offsets, uint32_t* ids, Key* ekeys, uint64_t n,
+                    typename KeyTraits<Key>::Params hp, const IndexOut& ix, Key* rkeys,
+                    uint32_t* rids, void* ws, hipStream_t s);
 
 // ix.head (may be null): V probe index entries (head_fmt(n, V, key width)), one
 // per bucket, and the key-run summary of long buckets (IndexOut).  stable: ids ascend inside

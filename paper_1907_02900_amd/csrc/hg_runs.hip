@@ -1,8 +1,13 @@
-// Key-run summaries of long buckets: exact probing under skew.
+// The rare path of a V2 build: bins too large for LDS, and the key-run
+// summaries of the long buckets that the per-bin kernel left.
 //
-// Probe-Standard (Sec. 3.4) scans a query's whole bucket.  When many entries
-// share a bucket -- heavy duplication, or Zipf keys where one key holds a
-// large share of the input -- every probe of that bucket pays its full
+// Oversize bins.  A bin of at most `slice` keys is one workgroup's work
+// (heavy_bin_body).  Larger ones (a hot key) are cut into slices: per-slice
+// bucket histograms, their scan over the slices, and a placement per slice.
+//
+// Key runs.  Probe-Standard (Sec. 3.4) scans a query's whole bucket.  When many
+// entries share a bucket -- heavy duplication, or Zipf keys where one key holds
+// a large share of the input -- every probe of that bucket pays its full
 // length, so a skewed join costs as much as the number of matching pairs.
 // For each bucket longer than kRunBucket the table therefore also keeps the
 // bucket's distinct keys in ascending order (its runs), each with the end of
@@ -12,13 +17,11 @@
 // those of a scan.  The arrays are parallel to the edge array (see RunsDev),
 // so every bucket's summary has a fixed place and nothing is sized on the
 // host: a build with the index never waits for the device.
-//
 // Most long buckets are built inside the per-bin kernel, from LDS
 // (bin_long_runs): a long bucket is usually one key repeated (duplicates) or
 // dominated by one key (skew), so the entries equal to the bucket's first key
 // (the lead key) form one run and the few others are sorted across a wave.
-// This file holds the general pass for the rest, which the per-bin kernels
-// list per bin:
+// The rest, which the per-bin kernels list per bin:
 //   * buckets of up to light_cap keys (one workgroup each, in LDS): the
 //     others are gathered, sorted (bitonic network in LDS) and cut into runs;
 //   * longer buckets (from bins too large for LDS), in chunks of kChunk
@@ -28,8 +31,11 @@
 //     lead ids to kperm, and one workgroup per bucket sorts the others (LDS,
 //     or a workgroup-wide radix sort through global memory when they exceed
 //     LDS) and writes their runs.
-// Every kernel takes its amount of work from device counters and strides
-// over it with a fixed grid.
+//
+// Uniform keys need none of it, but every build pays for the launches (2 to 4 us
+// each): one kernel for builds of up to 2^17 keys, which split no bin (their
+// rare workgroups see each long bucket through alone), eight for larger ones;
+// they were six and twelve.
 #include "hg_v2_device.h"
 
 namespace hg {
@@ -39,12 +45,11 @@ namespace {
 using namespace v2dev;
 
 constexpr int kRT = kLocalThreads;      // threads of the per-bucket kernels (512)
-constexpr int kCT = 256;                // threads of the per-chunk kernels
-constexpr int kCItems = 16;             // consecutive entries per thread of a chunk
-constexpr uint32_t kChunk = kCT * kCItems;  // 4096
-constexpr uint32_t kGenGrid = 2048;
-constexpr uint32_t kChunkGrid = 2048;
-constexpr uint32_t kBucketGrid = 512;
+constexpr int kCItems = 8;              // entries per thread of a chunk
+constexpr uint32_t kChunk = kRT * kCItems;  // 4096
+constexpr uint32_t kRareGrid = 512;     // two workgroups per CU (LDS)
+constexpr uint32_t kRangeBits = 8;      // buckets of one workgroup of the slice scan
+constexpr uint32_t kRanges = 1u << (kMaxLocalBits - kRangeBits);  // at most, per bin
 
 // Entries the LDS sort of a bucket's other keys holds: light_cap rounded up
 // to a power of two (8192 for 32-bit keys, 4096 for 64-bit keys).
@@ -174,8 +179,8 @@ __device__ void wg_radix_sort(Key* ka, uint32_t* pa, Key* kb, uint32_t* pb, uint
 // The lead key's ids are written by the caller.  Returns (via m.sh[0]) the
 // number of others below the lead key.  Whole workgroup; barriers.
 template <typename Key>
-__device__ void emit_runs(const Key* sk, const uint32_t* sp, uint32_t O, Key lead, uint32_t len,
-                          uint32_t st, uint32_t b, const uint32_t* __restrict__ ids,
+__device__ __forceinline__ void emit_runs(const Key* sk, const uint32_t* sp, uint32_t O, Key lead, uint32_t len,
+                          uint32_t st, uint32_t b, const uint32_t* ids,
                           const IndexOut& ix, const BucketLds<Key>& m) {
     Key* rkey = (Key*)ix.runs.run_key;
     uint32_t* rend = ix.runs.run_end;
@@ -260,178 +265,547 @@ G2Layout layout_g2(void* ws, uint64_t n) {
     return G2Layout{g, c.off + 256};
 }
 
-// The listed long buckets of every bin: first each wave finishes the buckets
-// whose entries other than the lead key fit its lanes (marking them done in
-// the list), then the workgroup sorts the other small ones in LDS; longer ones
-// are handed to the chunked path (ctr[0] buckets, ctr[1] chunks).
+// Everything the kernels read and write.
 template <typename Key>
-__global__ __launch_bounds__(kRT) void k_runs_general(
-    const uint32_t* __restrict__ offsets, const uint32_t* __restrict__ ids,
-    const Key* __restrict__ ekeys, const uint32_t* __restrict__ bin_start, uint32_t bins,
-    IndexOut ix, G2 g2, uint32_t* __restrict__ ctr) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const BucketLds<Key> m(smem);
-    for (uint32_t g = blockIdx.x; g < bins; g += gridDim.x) {
-        const uint32_t listed = ix.gen_cnt[g];
-        if (listed == 0) continue;  // uniform across the workgroup
-        uint32_t* list = ix.gen_list + gen_region(bin_start[g], g);
-        {
-            // a wave per bucket, its 64-entry buffers in the sort buffers
-            const uint32_t w = threadIdx.x / kWave, lane = lane_id();
-            Key* bk = m.sk + w * kWave;
-            uint16_t* bp = (uint16_t*)m.sp + w * kWave;
-            for (uint32_t t = w; t < listed; t += W_LOCAL) {
-                const uint32_t b = list[t];
-                const uint32_t st = offsets[b], len = offsets[b + 1] - st;
-                // (a bucket much longer than a wave rarely has its other
-                // keys fit one; it goes to the workgroup below directly)
-                if (len > 4u * kWave) continue;
-                if (wave_bucket_runs<Key>(ix, ekeys, ids, st, st + len, st, b, bk, bp) &&
-                    lane == 0)
-                    list[t] = ~0u;  // done
-            }
+struct Rare {
+    RareArgs a;
+    uint32_t* offsets;
+    uint32_t* ids;
+    Key* ekeys;
+    typename KeyTraits<Key>::Params hp;
+    IndexOut ix;
+    const Key* src_keys;  // the reorganised entries
+    const uint32_t* src_ids;
+    Key* skey;            // the same arrays as scratch, once all bins are placed
+    uint32_t* spos;
+    G2 g2;
+};
+
+// End of bucket b of bin g.  (While another workgroup may still be writing the
+// next bin's offsets, the bin's own end stands for them.)
+template <typename Key>
+__device__ __forceinline__ uint32_t bucket_end(const Rare<Key>& x, uint32_t g, uint32_t b) {
+    const bool last = ((b + 1) & ((1u << x.a.k) - 1u)) == 0 || b + 1 == x.a.V;
+    return last ? x.a.bin_start[g + 1] : x.offsets[b + 1];
+}
+
+// Slice `item` of a split bin: its bin and key range.
+struct SliceRef {
+    uint32_t b, begin, end;
+};
+
+__device__ __forceinline__ SliceRef slice_at(const RareArgs& a, uint32_t item) {
+    SliceRef r;
+    const uint32_t idx = a.slice_owner[item];
+    r.b = a.huge_list[idx];
+    const uint32_t bs = a.bin_start[r.b], be = a.bin_start[r.b + 1];
+    r.begin = bs + (item - a.huge_s0[idx]) * a.slice;
+    r.end = (be - r.begin > a.slice) ? r.begin + a.slice : be;
+    return r;
+}
+
+// Slices of split bin idx.
+__device__ __forceinline__ uint32_t slices_of(const RareArgs& a, uint32_t idx) {
+    const uint32_t b = a.huge_list[idx];
+    return (a.bin_start[b + 1] - a.bin_start[b] + a.slice - 1) / a.slice;
+}
+
+// An oversize bin, one workgroup.
+template <typename Key, bool ANY>
+__device__ __forceinline__ void heavy_bin(const Rare<Key>& x, uint32_t i, unsigned char* smem) {
+    const RareArgs& a = x.a;
+    const uint32_t g = a.heavy_list[i];
+    const uint32_t start = a.bin_start[g], end = a.bin_start[g + 1];
+    const uint32_t NB = 1u << a.k, v0 = g << a.k;
+    const uint32_t nb = (a.V - v0 < NB) ? a.V - v0 : NB;
+    heavy_bin_body<Key>(x.src_keys + start, x.src_ids + start, 0u, end - start, start, v0, a.k, nb,
+                        x.hp, x.offsets, x.ix, x.ids, x.ekeys, smem, ANY);
+}
+
+// Bucket histogram of a slice of a split bin: hist[item][0 .. 2^k).
+template <typename Key>
+__device__ __forceinline__ void slice_hist(const Rare<Key>& x, uint32_t item, unsigned char* smem) {
+    const RareArgs& a = x.a;
+    uint32_t* cnt = (uint32_t*)smem;
+    const uint32_t NB = 1u << a.k;
+    const SliceRef r = slice_at(a, item);
+    const uint32_t v0 = r.b << a.k;
+    for (uint32_t i = threadIdx.x; i < NB; i += kRT) cnt[i] = 0;
+    __syncthreads();
+    // a split bin holds a hot key: lanes sharing the first active lane's
+    // bucket add their count with one LDS atomic, the others one each
+    for (uint32_t i = r.begin + threadIdx.x; i < r.end; i += kRT) {
+        const uint32_t b = KeyTraits<Key>::bucket(x.src_keys[i], x.hp) - v0;
+        const uint32_t b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
+        const uint64_t same = ballot(b == b0);
+        if (b != b0) atomicAdd(&cnt[b], 1u);
+        else if (mbcnt(same) == 0) atomicAdd(&cnt[b0], (uint32_t)__popcll(same));
+    }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < NB; i += kRT)
+        a.slice_hist[(size_t)item * NB + i] = cnt[i];
+    // its sums over ranges of 2^kRangeBits buckets, a wave per range
+    const uint32_t lane = lane_id();
+    for (uint32_t q = threadIdx.x / kWave; q << kRangeBits < NB; q += W_LOCAL) {
+        uint32_t sum = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < (1u << kRangeBits) / kWave; ++j) {
+            const uint32_t v = (q << kRangeBits) + j * kWave + lane;
+            sum += v < NB ? cnt[v] : 0u;
         }
-        __syncthreads();
-        for (uint32_t t = 0; t < listed; ++t) {
-            const uint32_t b = list[t];
-            if (b == ~0u) continue;  // uniform: finished by a wave above
-            const uint32_t st = offsets[b], len = offsets[b + 1] - st;
-            const Key lead = ekeys[st];
-            if (len > small_cap<Key>()) {
-                if (threadIdx.x == 0) {
-                    const uint32_t nch = (len + kChunk - 1) / kChunk;
-                    const uint32_t i = atomicAdd(&ctr[0], 1u);
-                    const uint32_t c0 = atomicAdd(&ctr[1], nch);
-                    m.sh[2] = i;
-                    m.sh[3] = c0;
-                    if (i < g2.cap && c0 + nch <= g2.chunk_cap) {
-                        g2.list[i] = b;
-                        g2.c0[i] = c0;
-                    }
-                }
-                __syncthreads();
-                const uint32_t i = m.sh[2], c0 = m.sh[3];
-                const uint32_t nch = (len + kChunk - 1) / kChunk;
-                if (i < g2.cap && c0 + nch <= g2.chunk_cap)
-                    for (uint32_t j = threadIdx.x; j < nch; j += kRT) g2.owner[c0 + j] = i;
-                __syncthreads();
-                continue;
-            }
-            // gather the entries that differ from the lead key, in bucket order
-            uint32_t O = 0;
-            for (uint32_t c = 0; c < len; c += kRT) {
-                const uint32_t i = c + threadIdx.x;
-                const Key x = i < len ? ekeys[st + i] : lead;
-                const bool o = x != lead;
-                uint32_t all;
-                const uint32_t ex = block_excl_scan<kRT>(o ? 1u : 0u, m.tmp, &all);
-                if (o) {
-                    m.sk[O + ex] = x;
-                    m.sp[O + ex] = i;
-                }
-                O += all;
-            }
-            if (O == 0) {
-                if (threadIdx.x == 0) single_run<Key>(ix, b, st, len, lead);
-                __syncthreads();
-                continue;
-            }
-            uint32_t n2 = 1;
-            while (n2 < O) n2 <<= 1;
-            for (uint32_t i = O + threadIdx.x; i < n2; i += kRT) {
-                m.sk[i] = (Key)~(Key)0;
-                m.sp[i] = 0xffffffffu;
-            }
-            __syncthreads();
-            lds_bitonic<Key>(m.sk, m.sp, n2);
-            emit_runs<Key>(m.sk, m.sp, O, lead, len, st, b, ids, ix, m);
-            // the lead key's ids, in bucket order, after the smaller keys
-            const uint32_t nless = m.sh[0];
-            uint32_t done = 0;
-            for (uint32_t c = 0; c < len; c += kRT) {
-                const uint32_t i = c + threadIdx.x;
-                const bool isl = i < len && ekeys[st + i] == lead;
-                uint32_t all;
-                const uint32_t ex = block_excl_scan<kRT>(isl ? 1u : 0u, m.tmp, &all);
-                if (isl) ix.runs.kperm[st + nless + done + ex] = ids[st + i];
-                done += all;
-            }
-            __syncthreads();
-        }
+        sum = wave_sum(sum);
+        if (lane == 0) a.range_sum[(size_t)item * kRanges + q] = sum;
     }
 }
 
-// Chunk c of a long bucket: thread t holds entries [t*16, t*16 + 16) of the
-// chunk (consecutive, so thread order is bucket order).
+// Placement of a slice from its cursors.
+template <typename Key, bool ANY>
+__device__ __forceinline__ void place_slice(const Rare<Key>& x, uint32_t item,
+                                            unsigned char* smem) {
+    const RareArgs& a = x.a;
+    const uint32_t NB = 1u << a.k;
+    const HeavyLds<Key> m(smem, NB);
+    const SliceRef r = slice_at(a, item);
+    for (uint32_t i = threadIdx.x; i < NB; i += kRT)
+        m.cur[i] = a.slice_hist[(size_t)item * NB + i];
+    __syncthreads();
+    place_in_chunks<Key>(x.src_keys + r.begin, x.src_ids + r.begin, 0u, r.end - r.begin,
+                         a.bin_start[r.b], a.bin_start[r.b + 1], r.b << a.k, a.k, x.hp, x.ids,
+                         x.ekeys, smem, ANY);
+}
+
+// Probe index entries of a split bin's buckets (after their placement); the
+// long ones are listed.
+template <typename Key>
+__device__ __forceinline__ void split_index(const Rare<Key>& x, uint32_t idx,
+                                            unsigned char* smem) {
+    const RareArgs& a = x.a;
+    uint32_t* nlisted = (uint32_t*)smem;
+    const uint32_t NB = 1u << a.k;
+    const uint32_t b = a.huge_list[idx];
+    const uint32_t v0 = b << a.k, nb = (a.V - v0 < NB) ? a.V - v0 : NB;
+    const uint32_t bs = a.bin_start[b], be = a.bin_start[b + 1];
+    if (threadIdx.x == 0) *nlisted = 0;
+    __syncthreads();
+    for (uint32_t v = threadIdx.x; v < nb; v += kRT) {
+        const uint32_t lo = x.offsets[v0 + v];
+        const uint32_t hi = (v + 1 < nb) ? x.offsets[v0 + v + 1] : be;
+        if (hi - lo > kRunBucket)
+            x.ix.gen_list[gen_region(bs, b) + atomicAdd(nlisted, 1u)] = v0 + v;
+        else
+            put_short<Key>(x.ix, v0 + v, lo, hi, x.ekeys + lo);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) x.ix.gen_cnt[b] = *nlisted;
+    __syncthreads();
+}
+
+// Chunk c of a long bucket: wave w holds entries [w*512, w*512 + 512) of it,
+// lane l those at w*512 + j*64 + l, j < kCItems.
 struct ChunkRef {
-    uint32_t i, b, st, len, base, cl;
+    uint32_t i, b, st, base, cl;
 };
 
-template <typename Key>
-__device__ __forceinline__ ChunkRef chunk_at(uint32_t c, const G2& g2,
-                                             const uint32_t* __restrict__ offsets) {
+__device__ __forceinline__ ChunkRef chunk_at(uint32_t c, const G2& g2, const uint32_t* offsets) {
     ChunkRef r;
     r.i = g2.owner[c];
     r.b = g2.list[r.i];
     r.st = offsets[r.b];
-    r.len = offsets[r.b + 1] - r.st;
+    const uint32_t len = offsets[r.b + 1] - r.st;
     r.base = (c - g2.c0[r.i]) * kChunk;
-    r.cl = r.len - r.base < kChunk ? r.len - r.base : kChunk;
+    r.cl = len - r.base < kChunk ? len - r.base : kChunk;
     return r;
 }
 
-// Per chunk: entries that differ from the lead key, and of them those below it.
 template <typename Key>
-__global__ __launch_bounds__(kCT) void k_runs_chunk_count(const uint32_t* __restrict__ offsets,
-                                                          const Key* __restrict__ ekeys, G2 g2,
-                                                          const uint32_t* __restrict__ ctr) {
-    __shared__ uint32_t red[2 * (kCT / kWave)];
-    const uint32_t nch = ctr[1] < g2.chunk_cap ? ctr[1] : g2.chunk_cap;
-    for (uint32_t c = blockIdx.x; c < nch; c += gridDim.x) {
-        const ChunkRef r = chunk_at<Key>(c, g2, offsets);
-        const Key lead = ekeys[r.st];
-        uint32_t o = 0, l = 0;
-#pragma unroll 4
-        for (int j = 0; j < kCItems; ++j) {
-            const uint32_t e = threadIdx.x * kCItems + j;
-            if (e < r.cl) {
-                const Key x = ekeys[r.st + r.base + e];
-                o += x != lead;
-                l += x < lead;
-            }
+__device__ __forceinline__ void load_chunk(const ChunkRef& r, const Key* ekeys, Key lead,
+                                           Key (&k)[kCItems]) {
+    const uint32_t e0 = (threadIdx.x / kWave) * (kCItems * kWave) + lane_id();
+#pragma unroll
+    for (int j = 0; j < kCItems; ++j)
+        k[j] = e0 + j * kWave < r.cl ? ekeys[r.st + r.base + e0 + j * kWave] : lead;
+}
+
+// Entries of a chunk that differ from the lead key (o) and of them those below
+// it (l): the workgroup's sums, to every thread.  red: 2 * W_LOCAL words of LDS.
+// Barriers.
+template <typename Key>
+__device__ __forceinline__ void count_chunk(const Key (&k)[kCItems], Key lead, uint32_t* red,
+                                            uint32_t& o, uint32_t& l) {
+    o = l = 0;
+#pragma unroll
+    for (int j = 0; j < kCItems; ++j) {
+        o += k[j] != lead;
+        l += k[j] < lead;
+    }
+    o = wave_sum(o);
+    l = wave_sum(l);
+    __syncthreads();
+    if (lane_id() == 0) {
+        red[threadIdx.x / kWave] = o;
+        red[W_LOCAL + threadIdx.x / kWave] = l;
+    }
+    __syncthreads();
+    o = l = 0;
+    for (int q = 0; q < W_LOCAL; ++q) {
+        o += red[q];
+        l += red[W_LOCAL + q];
+    }
+}
+
+// Writes a chunk's others contiguously to the scratch arrays (key, position in
+// the bucket) from obase on, and the lead key's ids to kperm after the nless
+// smaller keys' ids.  red: W_LOCAL words of LDS.  Barriers.
+template <typename Key>
+__device__ __forceinline__ void scatter_chunk(const Rare<Key>& x, const ChunkRef& r,
+                                              const Key (&k)[kCItems], Key lead, uint32_t obase,
+                                              uint32_t nless, uint32_t* red) {
+    const uint32_t w = threadIdx.x / kWave;
+    const uint32_t e0 = w * (kCItems * kWave) + lane_id();
+    uint32_t mine = 0;
+#pragma unroll
+    for (int j = 0; j < kCItems; ++j) mine += (uint32_t)__popcll(ballot(k[j] != lead));
+    __syncthreads();
+    if (lane_id() == 0) red[w] = mine;
+    __syncthreads();
+    uint32_t o = obase;  // others before the wave's next round
+    for (uint32_t q = 0; q < w; ++q) o += red[q];
+    uint32_t l = r.base + w * (kCItems * kWave) - o;  // lead entries before it
+#pragma unroll
+    for (int j = 0; j < kCItems; ++j) {
+        const uint32_t e = e0 + j * kWave;
+        const uint64_t ob = ballot(k[j] != lead), lb = ballot(e < r.cl && k[j] == lead);
+        if (k[j] != lead) {
+            x.skey[r.st + o + mbcnt(ob)] = k[j];
+            x.spos[r.st + o + mbcnt(ob)] = r.base + e;
+        } else if (e < r.cl) {
+            x.ix.runs.kperm[r.st + nless + l + mbcnt(lb)] = x.ids[r.st + r.base + e];
         }
-        o = wave_sum(o);
-        l = wave_sum(l);
-        if (lane_id() == 0) {
-            red[threadIdx.x / kWave] = o;
-            red[kCT / kWave + threadIdx.x / kWave] = l;
+        o += (uint32_t)__popcll(ob);
+        l += (uint32_t)__popcll(lb);
+    }
+}
+
+// Sorts a long bucket's O > 0 others in the scratch arrays (LDS when they fit,
+// else a workgroup radix sort through global memory) and writes its runs.
+template <typename Key>
+__device__ __forceinline__ void sort_others(const Rare<Key>& x, uint32_t b, uint32_t st,
+                                            uint32_t len, uint32_t O, const BucketLds<Key>& m) {
+    const Key lead = x.ekeys[st];
+    if (O <= lds_sort_cap<Key>()) {
+        uint32_t n2 = 1;
+        while (n2 < O) n2 <<= 1;
+        for (uint32_t t = threadIdx.x; t < n2; t += kRT) {
+            m.sk[t] = t < O ? x.skey[st + t] : (Key)~(Key)0;
+            m.sp[t] = t < O ? x.spos[st + t] : 0xffffffffu;
         }
         __syncthreads();
+        lds_bitonic<Key>(m.sk, m.sp, n2);
+        emit_runs<Key>(m.sk, m.sp, O, lead, len, st, b, x.ids, x.ix, m);
+    } else {
+        // the run arrays of [st, st + O) serve as the second buffer; the
+        // sorted pairs end back in the scratch arrays
+        wg_radix_sort<Key>(x.skey + st, x.spos + st, (Key*)x.ix.runs.run_key + st,
+                           x.ix.runs.run_end + st, O, m);
+        emit_runs<Key>(x.skey + st, x.spos + st, O, lead, len, st, b, x.ids, x.ix, m);
+    }
+}
+
+// The runs of a bucket of any length by one workgroup (builds without split
+// bins: at most 2^17 entries).  The scratch arrays' places of the bucket are
+// its own bin's reorganised entries, placed by this workgroup before.
+template <typename Key>
+__device__ __forceinline__ void long_bucket(const Rare<Key>& x, uint32_t b, uint32_t st,
+                                            uint32_t len, const BucketLds<Key>& m) {
+    ChunkRef r{0, b, st, 0, 0};
+    const Key lead = x.ekeys[r.st];
+    Key k[kCItems];
+    uint32_t O = 0, nless = 0;
+    for (r.base = 0; r.base < len; r.base += kChunk) {
+        r.cl = len - r.base < kChunk ? len - r.base : kChunk;
+        load_chunk<Key>(r, x.ekeys, lead, k);
+        uint32_t o, l;
+        count_chunk<Key>(k, lead, m.tmp, o, l);
+        O += o;
+        nless += l;
+    }
+    if (O == 0) {
+        if (threadIdx.x == 0) single_run<Key>(x.ix, b, r.st, len, lead);
+        __syncthreads();
+        return;
+    }
+    uint32_t before = 0;
+    for (r.base = 0; r.base < len; r.base += kChunk) {
+        r.cl = len - r.base < kChunk ? len - r.base : kChunk;
+        load_chunk<Key>(r, x.ekeys, lead, k);
+        uint32_t o, l;
+        count_chunk<Key>(k, lead, m.tmp, o, l);
+        scatter_chunk<Key>(x, r, k, lead, before, nless, m.tmp);
+        before += o;
+    }
+    __syncthreads();
+    sort_others<Key>(x, b, st, len, O, m);
+    __syncthreads();
+}
+
+// The listed long buckets of one bin: first each wave finishes the buckets
+// whose entries other than the lead key fit its lanes (marking them done in
+// the list), then the workgroup sorts the other small ones in LDS; longer ones
+// are handed to the chunked path (ctr[kCtrLong] buckets, ctr[kCtrChunks] chunks)
+// or, SOLO, seen through by this workgroup.
+template <typename Key, bool SOLO>
+__device__ __forceinline__ void listed_of_bin(const Rare<Key>& x, uint32_t g, uint32_t listed,
+                                              const BucketLds<Key>& m) {
+    const IndexOut& ix = x.ix;
+    const uint32_t* offsets = x.offsets;
+    const uint32_t* ids = x.ids;
+    const Key* ekeys = x.ekeys;
+    uint32_t* ctr = x.a.ctr;
+    const G2& g2 = x.g2;
+    uint32_t* list = ix.gen_list + gen_region(x.a.bin_start[g], g);
+    {
+        // a wave per bucket, its 64-entry buffers in the sort buffers
+        const uint32_t w = threadIdx.x / kWave, lane = lane_id();
+        Key* bk = m.sk + w * kWave;
+        uint16_t* bp = (uint16_t*)m.sp + w * kWave;
+        for (uint32_t t = w; t < listed; t += W_LOCAL) {
+            const uint32_t b = list[t];
+            const uint32_t st = offsets[b], len = bucket_end(x, g, b) - st;
+            // (a bucket much longer than a wave rarely has its other
+            // keys fit one; it goes to the workgroup below directly)
+            if (len > 4u * kWave) continue;
+            if (wave_bucket_runs<Key>(ix, ekeys, ids, st, st + len, st, b, bk, bp) && lane == 0)
+                list[t] = ~0u;  // done
+        }
+    }
+    __syncthreads();
+    for (uint32_t t = 0; t < listed; ++t) {
+        const uint32_t b = list[t];
+        if (b == ~0u) continue;  // uniform: finished by a wave above
+        const uint32_t st = offsets[b], len = bucket_end(x, g, b) - st;
+        const Key lead = ekeys[st];
+        if (SOLO && len > small_cap<Key>()) {
+            long_bucket<Key>(x, b, st, len, m);
+            continue;
+        }
+        if (len > small_cap<Key>()) {
+            const uint32_t nch = (len + kChunk - 1) / kChunk;
+            if (threadIdx.x == 0) {
+                const uint32_t i = atomicAdd(&ctr[kCtrLong], 1u);
+                const uint32_t c0 = atomicAdd(&ctr[kCtrChunks], nch);
+                m.sh[2] = i;
+                m.sh[3] = c0;
+                if (i < g2.cap && c0 + nch <= g2.chunk_cap) {
+                    g2.list[i] = b;
+                    g2.c0[i] = c0;
+                }
+            }
+            __syncthreads();
+            const uint32_t i = m.sh[2], c0 = m.sh[3];
+            if (i < g2.cap && c0 + nch <= g2.chunk_cap)
+                for (uint32_t j = threadIdx.x; j < nch; j += kRT) g2.owner[c0 + j] = i;
+            __syncthreads();
+            continue;
+        }
+        // gather the entries that differ from the lead key, in bucket order
+        uint32_t O = 0;
+        for (uint32_t c = 0; c < len; c += kRT) {
+            const uint32_t i = c + threadIdx.x;
+            const Key k = i < len ? ekeys[st + i] : lead;
+            const bool o = k != lead;
+            uint32_t all;
+            const uint32_t ex = block_excl_scan<kRT>(o ? 1u : 0u, m.tmp, &all);
+            if (o) {
+                m.sk[O + ex] = k;
+                m.sp[O + ex] = i;
+            }
+            O += all;
+        }
+        if (O == 0) {
+            if (threadIdx.x == 0) single_run<Key>(ix, b, st, len, lead);
+            __syncthreads();
+            continue;
+        }
+        uint32_t n2 = 1;
+        while (n2 < O) n2 <<= 1;
+        for (uint32_t i = O + threadIdx.x; i < n2; i += kRT) {
+            m.sk[i] = (Key)~(Key)0;
+            m.sp[i] = 0xffffffffu;
+        }
+        __syncthreads();
+        lds_bitonic<Key>(m.sk, m.sp, n2);
+        emit_runs<Key>(m.sk, m.sp, O, lead, len, st, b, ids, ix, m);
+        // the lead key's ids, in bucket order, after the smaller keys
+        const uint32_t nless = m.sh[0];
+        uint32_t done = 0;
+        for (uint32_t c = 0; c < len; c += kRT) {
+            const uint32_t i = c + threadIdx.x;
+            const bool isl = i < len && ekeys[st + i] == lead;
+            uint32_t all;
+            const uint32_t ex = block_excl_scan<kRT>(isl ? 1u : 0u, m.tmp, &all);
+            if (isl) ix.runs.kperm[st + nless + done + ex] = ids[st + i];
+            done += all;
+        }
+        __syncthreads();
+    }
+}
+
+// First kernel of the rare path: every oversize bin with its long buckets, the
+// long buckets that the bins in LDS listed, and the histograms of the split
+// bins' slices; nothing here depends on another workgroup.  SOLO: a build
+// without split bins, whose rare path this is.
+template <typename Key, bool SOLO, bool ANY>
+__global__ __launch_bounds__(kRT) void k_rare_bins(Rare<Key> x) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const RareArgs& a = x.a;
+    const uint32_t nheavy = a.ctr[kCtrHeavy];
+    const uint32_t nsl = SOLO ? 0u : a.ctr[kCtrSlices] < a.slice_cap ? a.ctr[kCtrSlices] : a.slice_cap;
+    const BucketLds<Key> m(smem);
+    for (uint32_t i = blockIdx.x; i < nheavy + nsl; i += gridDim.x) {
+        if (i < nheavy) heavy_bin<Key, ANY>(x, i, smem);
+        else slice_hist<Key>(x, i - nheavy, smem);
+        __syncthreads();
+    }
+    if (!x.ix.head) return;
+    // the long buckets of this workgroup's oversize bins, and of the bins held
+    // in LDS (their flag may also come from an oversize bin of this launch:
+    // then they are looked through for nothing)
+    const uint32_t nlight = a.ctr[kCtrListed] ? a.bins : 0u;
+    for (uint32_t i = blockIdx.x; i < nheavy + nlight; i += gridDim.x) {
+        const uint32_t g = i < nheavy ? a.heavy_list[i] : i - nheavy;
+        if (i >= nheavy && a.bin_start[g + 1] - a.bin_start[g] > light_cap<Key>()) continue;
+        const uint32_t listed = x.ix.gen_cnt[g];
+        if (listed) listed_of_bin<Key, SOLO>(x, g, listed, m);
+        __syncthreads();
+    }
+}
+
+// The scan over the split bins' slice histograms: a workgroup takes 256 buckets
+// of a bin, four groups of slices side by side.  Buckets start after the bin's
+// lower ranges, whose sums per slice the histogram pass left; every count turns
+// into the position of its slice's first entry of the bucket.
+constexpr int kScanThreads = 1024;
+
+__global__ __launch_bounds__(kScanThreads) void k_slice_scan(RareArgs a, uint32_t* offsets) {
+    constexpr uint32_t B = 1u << kRangeBits, G = kScanThreads / B;
+    __shared__ uint32_t tmp[kScanThreads / kWave + 1];
+    __shared__ uint32_t part[G][B];
+    __shared__ uint32_t start[B];
+    const uint32_t NB = 1u << a.k;
+    const uint32_t ranges = a.k > kRangeBits ? NB >> kRangeBits : 1u;
+    const uint32_t nh = a.ctr[kCtrSplit] < a.huge_cap ? a.ctr[kCtrSplit] : a.huge_cap;
+    const uint32_t t = threadIdx.x & (B - 1), grp = threadIdx.x / B;
+    for (uint32_t w = blockIdx.x; w < nh * ranges; w += gridDim.x) {
+        const uint32_t idx = w / ranges, q = w % ranges;
+        const uint32_t b = a.huge_list[idx], s0 = a.huge_s0[idx], ns = slices_of(a, idx);
+        const uint32_t v0 = b << a.k, nb = (a.V - v0 < NB) ? a.V - v0 : NB;
+        const uint32_t v = (q << kRangeBits) + t;
+        uint32_t low = 0;  // entries of the bin in lower ranges
+        for (uint32_t i = threadIdx.x; i < ns * q; i += kScanThreads)
+            low += a.range_sum[(size_t)(s0 + i / q) * kRanges + i % q];
+        uint32_t below;
+        (void)block_excl_scan<kScanThreads>(low, tmp, &below);
+        const uint32_t len = (ns + G - 1) / G;
+        const uint32_t sa = grp * len < ns ? grp * len : ns;
+        const uint32_t sb = ns - sa > len ? sa + len : ns;
+        uint32_t* h = a.slice_hist + (size_t)s0 * NB + v;
+        uint32_t acc = 0;
+        if (v < NB)
+            for (uint32_t s = sa; s < sb; s += 8) {
+                uint32_t c[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) c[u] = s + u < sb ? h[(size_t)(s + u) * NB] : 0u;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) acc += c[u];
+            }
+        part[grp][t] = acc;
+        __syncthreads();
+        uint32_t tot = 0;
+        if (grp == 0)
+            for (uint32_t g = 0; g < G; ++g) tot += part[g][t];
+        uint32_t all;
+        const uint32_t ex = a.bin_start[b] + below + block_excl_scan<kScanThreads>(tot, tmp, &all);
+        if (grp == 0) {
+            start[t] = ex;
+            if (v < nb) offsets[v0 + v] = ex;
+        }
+        __syncthreads();
+        uint32_t r = start[t];
+        for (uint32_t g = 0; g < grp; ++g) r += part[g][t];
+        if (v < NB)
+            for (uint32_t s = sa; s < sb; s += 8) {
+                uint32_t c[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) c[u] = s + u < sb ? h[(size_t)(s + u) * NB] : 0u;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    if (s + u < sb) h[(size_t)(s + u) * NB] = r;
+                    r += c[u];
+                }
+            }
+        __syncthreads();
+    }
+}
+
+// Places every slice of every split bin: key and id read once, one LDS counter
+// atomic each and two scattered writes, bound by the counters and the writes.
+// The order is a template argument: with both orders in one kernel it took 129
+// VGPRs, one past what two workgroups per CU leave, and 781 us at 2^26 Zipf(1.2)
+// keys, now 472.
+template <typename Key, bool ANY>
+__global__ __launch_bounds__(kRT) void k_slice_place(Rare<Key> x) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const RareArgs& a = x.a;
+    const uint32_t nsl = a.ctr[kCtrSlices] < a.slice_cap ? a.ctr[kCtrSlices] : a.slice_cap;
+    for (uint32_t i = blockIdx.x; i < nsl; i += gridDim.x) {
+        place_slice<Key, ANY>(x, i, smem);
+        __syncthreads();
+    }
+}
+
+// Probe index entries and long buckets of the split bins.
+template <typename Key>
+__global__ __launch_bounds__(kRT) void k_split_index(Rare<Key> x) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const RareArgs& a = x.a;
+    const uint32_t nh = a.ctr[kCtrSplit] < a.huge_cap ? a.ctr[kCtrSplit] : a.huge_cap;
+    const BucketLds<Key> m(smem);
+    for (uint32_t i = blockIdx.x; i < nh; i += gridDim.x) {
+        split_index<Key>(x, i, smem);
+        const uint32_t g = a.huge_list[i], listed = x.ix.gen_cnt[g];
+        if (listed) listed_of_bin<Key, false>(x, g, listed, m);
+        __syncthreads();
+    }
+}
+
+template <typename Key>
+__global__ __launch_bounds__(kRT) void k_runs_chunk_count(Rare<Key> x) {
+    __shared__ uint32_t red[2 * W_LOCAL];
+    const uint32_t c1 = x.a.ctr[kCtrChunks], nc = c1 < x.g2.chunk_cap ? c1 : x.g2.chunk_cap;
+    for (uint32_t c = blockIdx.x; c < nc; c += gridDim.x) {
+        const ChunkRef r = chunk_at(c, x.g2, x.offsets);
+        const Key lead = x.ekeys[r.st];
+        Key k[kCItems];
+        load_chunk<Key>(r, x.ekeys, lead, k);
+        uint32_t o, l;
+        count_chunk<Key>(k, lead, red, o, l);
         if (threadIdx.x == 0) {
-            uint32_t so = 0, sl = 0;
-            for (int q = 0; q < kCT / kWave; ++q) {
-                so += red[q];
-                sl += red[kCT / kWave + q];
-            }
-            g2.oth[c] = so;
-            g2.less[c] = sl;
+            x.g2.oth[c] = o;
+            x.g2.less[c] = l;
         }
-        __syncthreads();
     }
 }
 
 // Per long bucket: exclusive prefixes of its chunks' counts (in place), the
 // totals, and a bucket of one key finished outright.
 template <typename Key>
-__global__ __launch_bounds__(kRT) void k_runs_chunk_scan(const uint32_t* __restrict__ offsets,
-                                                         const Key* __restrict__ ekeys,
-                                                         IndexOut ix, G2 g2,
-                                                         const uint32_t* __restrict__ ctr) {
-    __shared__ uint32_t tmp[kRT / kWave + 1];
-    const uint32_t nb2 = ctr[0] < g2.cap ? ctr[0] : g2.cap;
-    for (uint32_t i = blockIdx.x; i < nb2; i += gridDim.x) {
+__global__ __launch_bounds__(kRT) void k_runs_chunk_scan(Rare<Key> x) {
+    __shared__ uint32_t tmp[W_LOCAL + 1];
+    const G2& g2 = x.g2;
+    const uint32_t c1 = x.a.ctr[kCtrLong], nl = c1 < g2.cap ? c1 : g2.cap;
+    for (uint32_t i = blockIdx.x; i < nl; i += gridDim.x) {
         const uint32_t b = g2.list[i], c0 = g2.c0[i];
-        const uint32_t st = offsets[b], len = offsets[b + 1] - st;
+        const uint32_t st = x.offsets[b], len = x.offsets[b + 1] - st;
         const uint32_t nch = (len + kChunk - 1) / kChunk;
         uint32_t co = 0, cl = 0;
         for (uint32_t t0 = 0; t0 < nch; t0 += kRT) {
@@ -451,149 +825,118 @@ __global__ __launch_bounds__(kRT) void k_runs_chunk_scan(const uint32_t* __restr
         if (threadIdx.x == 0) {
             g2.info[2 * i] = co;
             g2.info[2 * i + 1] = cl;
-            if (co == 0) single_run<Key>(ix, b, st, len, ekeys[st]);
+            if (co == 0) single_run<Key>(x.ix, b, st, len, x.ekeys[st]);
         }
     }
 }
 
-// Per chunk (buckets with other keys): the others go contiguously to the
-// scratch arrays (key, position in the bucket), the lead key's ids to kperm
-// after the smaller keys' groups.
 template <typename Key>
-__global__ __launch_bounds__(kCT) void k_runs_chunk_scatter(
-    const uint32_t* __restrict__ offsets, const uint32_t* __restrict__ ids,
-    const Key* __restrict__ ekeys, IndexOut ix, G2 g2, const uint32_t* __restrict__ ctr,
-    Key* __restrict__ skey, uint32_t* __restrict__ spos) {
-    __shared__ uint32_t tmp[kCT / kWave + 1];
-    const uint32_t nch = ctr[1] < g2.chunk_cap ? ctr[1] : g2.chunk_cap;
-    for (uint32_t c = blockIdx.x; c < nch; c += gridDim.x) {
-        const ChunkRef r = chunk_at<Key>(c, g2, offsets);
-        const uint32_t O = g2.info[2 * r.i], nless = g2.info[2 * r.i + 1];
-        if (O == 0) continue;  // uniform: a single run, no kperm
-        const Key lead = ekeys[r.st];
-        const uint32_t obase = g2.oth[c], lbase = r.base - obase;
-        Key x[kCItems];
-        uint32_t mine = 0;
-#pragma unroll
-        for (int j = 0; j < kCItems; ++j) {
-            const uint32_t e = threadIdx.x * kCItems + j;
-            x[j] = e < r.cl ? ekeys[r.st + r.base + e] : lead;
-            mine += x[j] != lead;
-        }
-        uint32_t all;
-        uint32_t o = obase + block_excl_scan<kCT>(mine, tmp, &all);
-        uint32_t l = lbase + threadIdx.x * kCItems - (o - obase);
-#pragma unroll
-        for (int j = 0; j < kCItems; ++j) {
-            // a predicate rather than a break, so that the loop unrolls and
-            // x[] stays in registers
-            const uint32_t e = threadIdx.x * kCItems + j;
-            if (e < r.cl) {
-                if (x[j] != lead) {
-                    skey[r.st + o] = x[j];
-                    spos[r.st + o] = r.base + e;
-                    ++o;
-                } else {
-                    ix.runs.kperm[r.st + nless + l] = ids[r.st + r.base + e];
-                    ++l;
-                }
-            }
-        }
+__global__ __launch_bounds__(kRT) void k_runs_chunk_scatter(Rare<Key> x) {
+    __shared__ uint32_t red[W_LOCAL];
+    const G2& g2 = x.g2;
+    const uint32_t c1 = x.a.ctr[kCtrChunks], nc = c1 < g2.chunk_cap ? c1 : g2.chunk_cap;
+    for (uint32_t c = blockIdx.x; c < nc; c += gridDim.x) {
+        const ChunkRef r = chunk_at(c, g2, x.offsets);
+        if (g2.info[2 * r.i] == 0) continue;  // uniform: a single run, no kperm
+        const Key lead = x.ekeys[r.st];
+        Key k[kCItems];
+        load_chunk<Key>(r, x.ekeys, lead, k);
+        scatter_chunk<Key>(x, r, k, lead, g2.oth[c], g2.info[2 * r.i + 1], red);
     }
 }
 
-// Per long bucket with other keys: sort the others (LDS when they fit, else a
-// workgroup radix sort through global memory) and write their runs.
 template <typename Key>
-__global__ __launch_bounds__(kRT) void k_runs_chunk_sort(
-    const uint32_t* __restrict__ offsets, const uint32_t* __restrict__ ids,
-    const Key* __restrict__ ekeys, IndexOut ix, G2 g2, const uint32_t* __restrict__ ctr,
-    Key* __restrict__ skey, uint32_t* __restrict__ spos) {
+__global__ __launch_bounds__(kRT) void k_runs_chunk_sort(Rare<Key> x) {
     extern __shared__ __align__(16) unsigned char smem[];
+    const G2& g2 = x.g2;
+    const uint32_t c1 = x.a.ctr[kCtrLong], nl = c1 < g2.cap ? c1 : g2.cap;
     const BucketLds<Key> m(smem);
-    const uint32_t nb2 = ctr[0] < g2.cap ? ctr[0] : g2.cap;
-    for (uint32_t i = blockIdx.x; i < nb2; i += gridDim.x) {
-        const uint32_t O = g2.info[2 * i];
-        if (O == 0) continue;
-        const uint32_t b = g2.list[i];
-        const uint32_t st = offsets[b], len = offsets[b + 1] - st;
-        const Key lead = ekeys[st];
-        if (O <= lds_sort_cap<Key>()) {
-            uint32_t n2 = 1;
-            while (n2 < O) n2 <<= 1;
-            for (uint32_t t = threadIdx.x; t < n2; t += kRT) {
-                m.sk[t] = t < O ? skey[st + t] : (Key)~(Key)0;
-                m.sp[t] = t < O ? spos[st + t] : 0xffffffffu;
-            }
-            __syncthreads();
-            lds_bitonic<Key>(m.sk, m.sp, n2);
-            emit_runs<Key>(m.sk, m.sp, O, lead, len, st, b, ids, ix, m);
-        } else {
-            // the run arrays of [st, st + O) serve as the second buffer; the
-            // sorted pairs end back in the scratch arrays
-            wg_radix_sort<Key>(skey + st, spos + st, (Key*)ix.runs.run_key + st,
-                               ix.runs.run_end + st, O, m);
-            emit_runs<Key>(skey + st, spos + st, O, lead, len, st, b, ids, ix, m);
-        }
+    for (uint32_t i = blockIdx.x; i < nl; i += gridDim.x) {
+        const uint32_t b = g2.list[i], O = g2.info[2 * i];
+        const uint32_t st = x.offsets[b], len = x.offsets[b + 1] - st;
+        if (O) sort_others<Key>(x, b, st, len, O, m);
+        __syncthreads();
     }
 }
 
 template <typename Key>
-hipError_t set_runs_smem() {
+size_t rare_smem(uint32_t k) {
+    const size_t h = heavy_smem<Key>(k), b = BucketLds<Key>::bytes();
+    return h > b ? h : b;
+}
+
+template <typename Key>
+hipError_t set_rare_smem() {
     static std::atomic<uint64_t> done{0};
     return once_per_device(done, [] {
-        const int lim = 160 * 1024;
-        HG_TRY(hipFuncSetAttribute((const void*)k_runs_general<Key>,
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, lim));
-        HG_TRY(hipFuncSetAttribute((const void*)k_runs_chunk_sort<Key>,
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, lim));
-        return hipSuccess;
+        const int lim = (int)rare_smem<Key>(kMaxLocalBits);
+        const hipFuncAttribute at = hipFuncAttributeMaxDynamicSharedMemorySize;
+        HG_TRY(hipFuncSetAttribute((const void*)k_rare_bins<Key, true, true>, at, lim));
+        HG_TRY(hipFuncSetAttribute((const void*)k_rare_bins<Key, true, false>, at, lim));
+        HG_TRY(hipFuncSetAttribute((const void*)k_rare_bins<Key, false, true>, at, lim));
+        HG_TRY(hipFuncSetAttribute((const void*)k_rare_bins<Key, false, false>, at, lim));
+        HG_TRY(hipFuncSetAttribute((const void*)k_slice_place<Key, true>, at, lim));
+        HG_TRY(hipFuncSetAttribute((const void*)k_slice_place<Key, false>, at, lim));
+        HG_TRY(hipFuncSetAttribute((const void*)k_split_index<Key>, at, lim));
+        return hipFuncSetAttribute((const void*)k_runs_chunk_sort<Key>, at, lim);
     });
 }
 
 }  // namespace
 
-size_t runs_ws_bytes(uint64_t n, uint64_t bins) {
-    (void)bins;
-    return layout_g2(nullptr, n).bytes;
-}
+size_t runs_ws_bytes(uint64_t n) { return layout_g2(nullptr, n).bytes; }
+size_t range_sum_words(uint64_t slices) { return slices * kRanges; }
 
 template <typename Key>
-hipError_t run_key_runs(const uint32_t* offsets, const uint32_t* ids, const Key* ekeys,
-                        uint64_t n, const uint32_t* bin_start, uint32_t bins, const IndexOut& ix,
-                        Key* rkeys, uint32_t* rids, uint32_t* ctr, void* ws, hipStream_t s) {
-    if (n == 0 || bins == 0) return hipSuccess;
-    HG_TRY(set_runs_smem<Key>());
-    const G2 g2 = layout_g2(ws, n).g;
-    const size_t lds = BucketLds<Key>::bytes();
-    HG_PROF("runs_build", s);
-    const uint32_t gg = bins < kGenGrid ? bins : kGenGrid;
-    hipLaunchKernelGGL(k_runs_general<Key>, dim3(gg), dim3(kRT), lds, s, offsets, ids, ekeys,
-                       bin_start, bins, ix, g2, ctr);
+hipError_t run_rare(const RareArgs& a, uint32_t* offsets, uint32_t* ids, Key* ekeys, uint64_t n,
+                    typename KeyTraits<Key>::Params hp, const IndexOut& ix, Key* rkeys,
+                    uint32_t* rids, void* ws, hipStream_t s) {
+    HG_TRY(set_rare_smem<Key>());
+    const Rare<Key> x{a, offsets, ids, ekeys, hp, ix, rkeys, rids, rkeys, rids,
+                      layout_g2(ws, n).g};
+    const size_t lds = rare_smem<Key>(a.k), blds = BucketLds<Key>::bytes();
+    const bool solo = n <= a.slice;  // no bin is split
+    const dim3 gb(a.bins < kRareGrid ? a.bins : kRareGrid), th(kRT);
+    {
+        HG_PROF("v2_rare_bins", s);
+        if (solo) {
+            const auto f = a.any_order ? k_rare_bins<Key, true, true> : k_rare_bins<Key, true, false>;
+            hipLaunchKernelGGL(f, gb, th, lds, s, x);
+            return hipGetLastError();
+        }
+        // (slices may outnumber the bins)
+        const auto f = a.any_order ? k_rare_bins<Key, false, true> : k_rare_bins<Key, false, false>;
+        hipLaunchKernelGGL(f, dim3(kRareGrid), th, lds, s, x);
+    }
     HG_TRY(hipGetLastError());
-    // the chunked path: grids sized for the most work there can be, strided
-    // over what the counters hold
-    const uint32_t cg = (uint32_t)(g2.chunk_cap < kChunkGrid ? g2.chunk_cap : kChunkGrid);
-    const uint32_t bg = g2.cap < kBucketGrid ? g2.cap : kBucketGrid;
-    hipLaunchKernelGGL(k_runs_chunk_count<Key>, dim3(cg), dim3(kCT), 0, s, offsets, ekeys, g2,
-                       (const uint32_t*)ctr);
+    HG_PROF("v2_split_bins", s);
+    hipLaunchKernelGGL(k_slice_scan, dim3(256), dim3(kScanThreads), 0, s, a, offsets);
     HG_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_runs_chunk_scan<Key>, dim3(bg), dim3(kRT), 0, s, offsets, ekeys, ix, g2,
-                       (const uint32_t*)ctr);
+    const auto place = a.any_order ? k_slice_place<Key, true> : k_slice_place<Key, false>;
+    hipLaunchKernelGGL(place, dim3(kRareGrid), th, heavy_smem<Key>(a.k), s, x);
     HG_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_runs_chunk_scatter<Key>, dim3(cg), dim3(kCT), 0, s, offsets, ids, ekeys,
-                       ix, g2, (const uint32_t*)ctr, rkeys, rids);
+    if (!ix.head) return hipSuccess;
+    hipLaunchKernelGGL(k_split_index<Key>, dim3(256), th, blds, s, x);
     HG_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_runs_chunk_sort<Key>, dim3(bg), dim3(kRT), lds, s, offsets, ids, ekeys, ix,
-                       g2, (const uint32_t*)ctr, rkeys, rids);
+    // long buckets in chunks: grids sized for the most work there can be,
+    // strided over what the counters hold
+    const dim3 cg(x.g2.chunk_cap < 1024 ? x.g2.chunk_cap : 1024);
+    const dim3 bg(x.g2.cap < kRareGrid ? x.g2.cap : kRareGrid);
+    hipLaunchKernelGGL(k_runs_chunk_count<Key>, cg, th, 0, s, x);
+    HG_TRY(hipGetLastError());
+    hipLaunchKernelGGL(k_runs_chunk_scan<Key>, bg, th, 0, s, x);
+    HG_TRY(hipGetLastError());
+    hipLaunchKernelGGL(k_runs_chunk_scatter<Key>, cg, th, 0, s, x);
+    HG_TRY(hipGetLastError());
+    hipLaunchKernelGGL(k_runs_chunk_sort<Key>, bg, th, blds, s, x);
     return hipGetLastError();
 }
 
-template hipError_t run_key_runs<uint32_t>(const uint32_t*, const uint32_t*, const uint32_t*,
-                                           uint64_t, const uint32_t*, uint32_t, const IndexOut&,
-                                           uint32_t*, uint32_t*, uint32_t*, void*, hipStream_t);
-template hipError_t run_key_runs<uint64_t>(const uint32_t*, const uint32_t*, const uint64_t*,
-                                           uint64_t, const uint32_t*, uint32_t, const IndexOut&,
-                                           uint64_t*, uint32_t*, uint32_t*, void*, hipStream_t);
+template hipError_t run_rare<uint32_t>(const RareArgs&, uint32_t*, uint32_t*, uint32_t*, uint64_t,
+                                       HashParams, const IndexOut&, uint32_t*, uint32_t*, void*,
+                                       hipStream_t);
+template hipError_t run_rare<uint64_t>(const RareArgs&, uint32_t*, uint32_t*, uint64_t*, uint64_t,
+                                       HashParams64, const IndexOut&, uint64_t*, uint32_t*, void*,
+                                       hipStream_t);
 
 }  // namespace hg

@@ -13,10 +13,10 @@
 //     and a partition kernel that ranks a tile's keys by digit with wave64
 //     ballots and writes digit-contiguous runs;
 //   * one workgroup per final bin counts, scans and stably places the bin's
-//     keys in LDS (two LSD ranking passes over the local bucket index) and
+//     keys in LDS and
 //     writes the bin's edge segment and offsets with coalesced stores.  Bins
 //     larger than LDS (heavy skew only) are listed on the device and handled
-//     by a second kernel in chunks with running per-bucket cursors.
+//     by the rare path's kernel (hg_runs.hip).
 // Every pass keeps input order among equal digits, so ids come out ascending
 // inside each bucket: the result is the stable layout, entry for entry.
 //
@@ -492,12 +492,10 @@ size_t partition_smem(uint32_t bits) {
 
 // -------------------------------------------------------- segment setup ---
 
-// Tier-1 segment: the whole input; also clears the build's device counters
-// (oversize bins, split bins, their slices, and the general key-run pass's
-// two work counters).
+// Tier-1 segment: the whole input; also clears the build's device counters.
 __global__ void k_segs_single(Segs g, uint32_t n, uint32_t ntiles, uint32_t nchunks,
                               uint32_t* ctr) {
-    if (threadIdx.x < 5) ctr[threadIdx.x] = 0;
+    if (threadIdx.x < kCtrWords) ctr[threadIdx.x] = 0;
     if (threadIdx.x == 0) {
         g.seg_start[0] = 0;
         g.seg_start[1] = n;
@@ -552,17 +550,16 @@ __global__ __launch_bounds__(1024) void k_segs_from_bases(const uint32_t* __rest
 // Start of every final bin (bin = segment * 2^bits + digit) in the
 // partitioned array, bin_start[bins] = n, offsets[V] = n, and the list of
 // bins too large for the LDS kernel.
-// Bins above kSliceKeys keys are split into slices of kSliceKeys for several
+// Bins above `slice` keys are split into slices of that many for several
 // workgroups: they are listed in huge_list with their first slice in huge_s0,
-// and slice_owner maps every slice back to its entry.  ctr: oversize bins,
-// split bins, slices.
+// and slice_owner maps every slice back to its entry.
 __global__ void k_bin_starts(const uint32_t* __restrict__ base, Segs g, uint32_t bits,
                              uint32_t light_keys,
                              uint32_t bins, uint32_t n, uint32_t V, uint32_t* __restrict__ bin_start,
                              uint32_t* __restrict__ offsets, uint32_t* __restrict__ heavy_list,
                              uint32_t* __restrict__ ctr, uint32_t* __restrict__ huge_list,
                              uint32_t* __restrict__ huge_s0, uint32_t* __restrict__ slice_owner,
-                             uint32_t huge_cap, uint32_t slice_cap) {
+                             uint32_t huge_cap, uint32_t slice_cap, uint32_t slice) {
     const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
     uint32_t st = 0, nx = 0;
     bool have = false;
@@ -584,205 +581,21 @@ __global__ void k_bin_starts(const uint32_t* __restrict__ base, Segs g, uint32_t
     }
     if (have) {
         const uint32_t L = nx - st;
-        if (L <= kSliceKeys) {
-            const uint32_t slot = atomicAdd(&ctr[0], 1u);
+        if (L <= slice) {
+            const uint32_t slot = atomicAdd(&ctr[kCtrHeavy], 1u);
             heavy_list[slot] = b;
         } else {
-            // capacities hold: a split bin has > kSliceKeys keys, so there are
-            // at most n / kSliceKeys of them and fewer than 2n / kSliceKeys slices
-            const uint32_t ns = (L + kSliceKeys - 1) / kSliceKeys;
-            const uint32_t idx = atomicAdd(&ctr[1], 1u);
-            const uint32_t s0 = atomicAdd(&ctr[2], ns);
+            // capacities hold: a split bin has > slice keys, so there are at
+            // most n / slice of them and fewer than 2n / slice slices
+            const uint32_t ns = (L + slice - 1) / slice;
+            const uint32_t idx = atomicAdd(&ctr[kCtrSplit], 1u);
+            const uint32_t s0 = atomicAdd(&ctr[kCtrSlices], ns);
             if (idx < huge_cap && s0 + ns <= slice_cap) {
                 huge_list[idx] = b;
                 huge_s0[idx] = s0;
                 for (uint32_t j = 0; j < ns; ++j) slice_owner[s0 + j] = idx;
             }
         }
-    }
-}
-
-// Slice `item` of a split bin: its bin and key range.
-struct SliceRef {
-    uint32_t idx, b, begin, end;
-};
-
-__device__ __forceinline__ SliceRef slice_at(uint32_t item, const uint32_t* __restrict__ bin_start,
-                                             const uint32_t* __restrict__ huge_list,
-                                             const uint32_t* __restrict__ huge_s0,
-                                             const uint32_t* __restrict__ slice_owner) {
-    SliceRef r;
-    r.idx = slice_owner[item];
-    r.b = huge_list[r.idx];
-    const uint32_t j = item - huge_s0[r.idx];
-    const uint32_t bs = bin_start[r.b], be = bin_start[r.b + 1];
-    r.begin = bs + j * kSliceKeys;
-    r.end = (be - r.begin > kSliceKeys) ? r.begin + kSliceKeys : be;
-    return r;
-}
-
-// Per-slice bucket histograms of the split bins: hist[item][0 .. 2^k).
-template <typename Key>
-__global__ __launch_bounds__(kLocalThreads) void k_huge_hist(
-    const Key* __restrict__ src_keys, const uint32_t* __restrict__ bin_start,
-    const uint32_t* __restrict__ huge_list, const uint32_t* __restrict__ huge_s0,
-    const uint32_t* __restrict__ slice_owner, const uint32_t* __restrict__ ctr,
-    typename KeyTraits<Key>::Params hp, uint32_t k, uint32_t* __restrict__ hist) {
-    extern __shared__ uint32_t cnt[];
-    const uint32_t NB = 1u << k, nsl = ctr[2];
-    for (uint32_t item = blockIdx.x; item < nsl; item += gridDim.x) {
-        const SliceRef r = slice_at(item, bin_start, huge_list, huge_s0, slice_owner);
-        const uint32_t v0 = r.b << k;
-        for (uint32_t i = threadIdx.x; i < NB; i += kLocalThreads) cnt[i] = 0;
-        __syncthreads();
-        // a split bin holds a hot key: lanes sharing the first active lane's
-        // bucket add their count with one LDS atomic, the others one each
-        for (uint32_t i = r.begin + threadIdx.x; i < r.end; i += kLocalThreads) {
-            const uint32_t b = KeyTraits<Key>::bucket(src_keys[i], hp) - v0;
-            const uint32_t b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
-            const uint64_t same = ballot(b == b0);
-            if (b != b0) atomicAdd(&cnt[b], 1u);
-            else if (mbcnt(same) == 0) atomicAdd(&cnt[b0], (uint32_t)__popcll(same));
-        }
-        __syncthreads();
-        for (uint32_t i = threadIdx.x; i < NB; i += kLocalThreads)
-            hist[(size_t)item * NB + i] = cnt[i];
-        __syncthreads();
-    }
-}
-
-// The scan over the split bins' slice histograms, in three steps so that a
-// bin of many slices is spread over many threads: per (bin, bucket) the total
-// over the bin's slices; per bin the bucket starts (written to offsets, and
-// kept in place of the totals); per (bin, bucket) the position of every
-// slice's first entry of the bucket, in place of its count.
-
-// Slices of split bin idx: [s0, s0 + ns).
-__device__ __forceinline__ uint32_t huge_slices(const uint32_t* __restrict__ bin_start,
-                                                const uint32_t* __restrict__ huge_list,
-                                                uint32_t idx) {
-    const uint32_t b = huge_list[idx];
-    return (bin_start[b + 1] - bin_start[b] + kSliceKeys - 1) / kSliceKeys;
-}
-
-__global__ __launch_bounds__(256) void k_huge_tot(
-    const uint32_t* __restrict__ bin_start, const uint32_t* __restrict__ huge_list,
-    const uint32_t* __restrict__ huge_s0, const uint32_t* __restrict__ ctr, uint32_t k,
-    uint32_t huge_cap, const uint32_t* __restrict__ hist, uint32_t* __restrict__ tot) {
-    const uint32_t NB = 1u << k, nh = ctr[1] < huge_cap ? ctr[1] : huge_cap;
-    const uint64_t all = (uint64_t)nh << k, st = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t x = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; x < all; x += st) {
-        const uint32_t idx = (uint32_t)(x >> k), v = (uint32_t)x & (NB - 1);
-        const uint32_t s0 = huge_s0[idx], ns = huge_slices(bin_start, huge_list, idx);
-        const uint32_t* h = hist + (size_t)s0 * NB + v;
-        uint32_t acc = 0;
-#pragma unroll 4
-        for (uint32_t sl = 0; sl < ns; ++sl) acc += h[(size_t)sl * NB];
-        tot[x] = acc;
-    }
-}
-
-__global__ __launch_bounds__(kLocalThreads) void k_huge_starts(
-    const uint32_t* __restrict__ bin_start, const uint32_t* __restrict__ huge_list,
-    const uint32_t* __restrict__ ctr, uint32_t k, uint32_t V, uint32_t huge_cap,
-    uint32_t* __restrict__ tot, uint32_t* __restrict__ offsets) {
-    __shared__ uint32_t tmp[kLocalThreads / kWave + 1];
-    const uint32_t NB = 1u << k, nh = ctr[1] < huge_cap ? ctr[1] : huge_cap;
-    const uint32_t per = NB >= (uint32_t)kLocalThreads ? NB / kLocalThreads : 1u;  // <= 16
-    const uint32_t i0 = threadIdx.x * per;
-    for (uint32_t idx = blockIdx.x; idx < nh; idx += gridDim.x) {
-        const uint32_t b = huge_list[idx];
-        const uint32_t v0 = b << k, nb = (V - v0 < NB) ? V - v0 : NB;
-        uint32_t* t = tot + ((size_t)idx << k);
-        uint32_t c[16];
-        uint32_t mine = 0;
-        for (uint32_t j = 0; j < per; ++j) {
-            c[j] = i0 + j < NB ? t[i0 + j] : 0u;
-            mine += c[j];
-        }
-        uint32_t all;
-        uint32_t run = bin_start[b] + block_excl_scan<kLocalThreads>(mine, tmp, &all);
-        for (uint32_t j = 0; j < per; ++j) {
-            const uint32_t v = i0 + j;
-            if (v < NB) {
-                if (v < nb) offsets[v0 + v] = run;
-                t[v] = run;
-            }
-            run += c[j];
-        }
-        __syncthreads();
-    }
-}
-
-__global__ __launch_bounds__(256) void k_huge_down(
-    const uint32_t* __restrict__ bin_start, const uint32_t* __restrict__ huge_list,
-    const uint32_t* __restrict__ huge_s0, const uint32_t* __restrict__ ctr, uint32_t k,
-    uint32_t huge_cap, const uint32_t* __restrict__ tot, uint32_t* __restrict__ hist) {
-    const uint32_t NB = 1u << k, nh = ctr[1] < huge_cap ? ctr[1] : huge_cap;
-    const uint64_t all = (uint64_t)nh << k, st = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t x = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; x < all; x += st) {
-        const uint32_t idx = (uint32_t)(x >> k), v = (uint32_t)x & (NB - 1);
-        const uint32_t s0 = huge_s0[idx], ns = huge_slices(bin_start, huge_list, idx);
-        uint32_t* h = hist + (size_t)s0 * NB + v;
-        uint32_t r = tot[x];
-        for (uint32_t sl = 0; sl < ns; ++sl) {
-            const uint32_t c = h[(size_t)sl * NB];
-            h[(size_t)sl * NB] = r;
-            r += c;
-        }
-    }
-}
-
-// Stable placement of every slice of the split bins, from its cursors.
-template <typename Key>
-__global__ __launch_bounds__(kLocalThreads) void k_huge_place(
-    const Key* __restrict__ src_keys, const uint32_t* __restrict__ src_ids,
-    const uint32_t* __restrict__ bin_start, const uint32_t* __restrict__ huge_list,
-    const uint32_t* __restrict__ huge_s0, const uint32_t* __restrict__ slice_owner,
-    const uint32_t* __restrict__ ctr, typename KeyTraits<Key>::Params hp, uint32_t k,
-    const uint32_t* __restrict__ hist, uint32_t* __restrict__ ids, Key* __restrict__ ekeys,
-    bool any_order) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const uint32_t NB = 1u << k, nsl = ctr[2];
-    const HeavyLds<Key> m(smem, NB);
-    for (uint32_t item = blockIdx.x; item < nsl; item += gridDim.x) {
-        const SliceRef r = slice_at(item, bin_start, huge_list, huge_s0, slice_owner);
-        for (uint32_t i = threadIdx.x; i < NB; i += kLocalThreads)
-            m.cur[i] = hist[(size_t)item * NB + i];
-        __syncthreads();
-        place_in_chunks<Key>(src_keys + r.begin, src_ids + r.begin, 0u, r.end - r.begin,
-                             bin_start[r.b], bin_start[r.b + 1], r.b << k, k, hp, ids, ekeys,
-                             smem, any_order);
-        __syncthreads();
-    }
-}
-
-// Probe index entries of the split bins' buckets (after their placement);
-// their long buckets are listed for the general pass of the key runs.
-template <typename Key>
-__global__ __launch_bounds__(kLocalThreads) void k_huge_index(
-    const uint32_t* __restrict__ bin_start, const uint32_t* __restrict__ huge_list,
-    const uint32_t* __restrict__ ctr, uint32_t k, uint32_t V,
-    const uint32_t* __restrict__ offsets, const Key* __restrict__ ekeys, IndexOut ix) {
-    __shared__ uint32_t nlisted;
-    const uint32_t NB = 1u << k, nh = ctr[1];
-    for (uint32_t idx = blockIdx.x; idx < nh; idx += gridDim.x) {
-        const uint32_t b = huge_list[idx];
-        const uint32_t v0 = b << k, nb = (V - v0 < NB) ? V - v0 : NB;
-        const uint32_t bs = bin_start[b], be = bin_start[b + 1];
-        if (threadIdx.x == 0) nlisted = 0;
-        __syncthreads();
-        for (uint32_t v = threadIdx.x; v < nb; v += kLocalThreads) {
-            const uint32_t lo = offsets[v0 + v];
-            const uint32_t hi = (v + 1 < nb) ? offsets[v0 + v + 1] : be;
-            if (hi - lo > kRunBucket)
-                ix.gen_list[gen_region(bs, b) + atomicAdd(&nlisted, 1u)] = v0 + v;
-            else
-                put_short<Key>(ix, v0 + v, lo, hi, ekeys + lo);
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) ix.gen_cnt[b] = nlisted;
-        __syncthreads();
     }
 }
 
@@ -801,7 +614,7 @@ __global__ __launch_bounds__(kLocalThreads, 4) void k_local_light(
     const uint32_t g = blockIdx.x;
     const uint32_t start = bin_start[g], end = bin_start[g + 1];
     const uint32_t L = end - start;
-    if (L > light_cap<Key>()) return;  // oversize bins go to k_local_heavy
+    if (L > light_cap<Key>()) return;  // oversize bins are left to the rare path
     const uint32_t NB = 1u << k, v0 = g << k, V = hp.range;
     const uint32_t nb = (V - v0 < NB) ? V - v0 : NB;
     light_bin_body<Key, ANY, W>(src_keys + start, src_ids + start, 0u, L, start, v0, k, nb, hp,
@@ -819,28 +632,6 @@ void with_layout(bool any_order, const IndexOut& ix, F&& f) {
     };
     if (any_order) by_width(std::true_type{});
     else by_width(std::false_type{});
-}
-
-// Oversize bins (from the device list), one workgroup per bin.
-template <typename Key>
-__global__ __launch_bounds__(kLocalThreads) void k_local_heavy(
-    const Key* __restrict__ src_keys, const uint32_t* __restrict__ src_ids,
-    const uint32_t* __restrict__ bin_start, const uint32_t* __restrict__ heavy_list,
-    const uint32_t* __restrict__ heavy_count, typename KeyTraits<Key>::Params hp, uint32_t k,
-    uint32_t* __restrict__ offsets, IndexOut ix, uint32_t* __restrict__ ids,
-    Key* __restrict__ ekeys, bool any_order) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const uint32_t NB = 1u << k, V = hp.range;
-    const uint32_t nheavy = *heavy_count;
-    for (uint32_t i = blockIdx.x; i < nheavy; i += gridDim.x) {
-        const uint32_t g = heavy_list[i];
-        const uint32_t start = bin_start[g], end = bin_start[g + 1];
-        const uint32_t v0 = g << k;
-        const uint32_t nb = (V - v0 < NB) ? V - v0 : NB;
-        heavy_bin_body<Key>(src_keys + start, src_ids + start, 0u, end - start, start, v0, k, nb,
-                            hp, offsets, ix, ids, ekeys, smem, any_order);
-        __syncthreads();
-    }
 }
 
 // Final step of the scatter by a permutation: bin g holds the entries whose
@@ -930,8 +721,8 @@ struct V2Ws {
     void* rkeys;
     uint32_t* rids;
     uint32_t *m1, *c1, *m2, *c2, *bin_start, *heavy_list;
-    uint32_t* ctr;  // [5]: oversize bins, split bins, slices of split bins, key-run work
-    uint32_t *huge_list, *huge_s0, *slice_owner, *slice_hist, *huge_tot;
+    uint32_t* ctr;  // [kCtrWords]
+    uint32_t *huge_list, *huge_s0, *slice_owner, *slice_hist, *range_sum;
     uint32_t huge_cap, slice_cap;
     uint32_t *gen_list, *gen_cnt;  // long buckets left to the general key-run pass
     void* runs_ws;
@@ -963,17 +754,17 @@ size_t layout_v2(void* ws, const V2Plan& p, size_t key_size, V2Ws* out) {
     }
     w.bin_start = c.take<uint32_t>((size_t)p.bins + 1);
     w.heavy_list = c.take<uint32_t>((size_t)p.bins);
-    w.ctr = c.take<uint32_t>(5);
-    w.huge_cap = (uint32_t)(p.n / kSliceKeys + 1);
+    w.ctr = c.take<uint32_t>(kCtrWords);
+    w.huge_cap = split_cap(p.n);
     w.slice_cap = 2 * w.huge_cap;
     w.huge_list = c.take<uint32_t>(w.huge_cap);
     w.huge_s0 = c.take<uint32_t>(w.huge_cap);
     w.slice_owner = c.take<uint32_t>(w.slice_cap);
     w.slice_hist = c.take<uint32_t>((size_t)w.slice_cap << p.k);
-    w.huge_tot = c.take<uint32_t>((size_t)w.huge_cap << p.k);
+    w.range_sum = c.take<uint32_t>(range_sum_words(w.slice_cap));
     w.gen_list = c.take<uint32_t>(gen_list_cap(p.n, p.bins));
     w.gen_cnt = c.take<uint32_t>((size_t)p.bins + 1);
-    w.runs_ws = c.take<char>(runs_ws_bytes(p.n, p.bins));
+    w.runs_ws = c.take<char>(runs_ws_bytes(p.n));
     if (out) *out = w;
     return c.off + 256;
 }
@@ -1101,10 +892,6 @@ hipError_t set_smem_limits() {
             });
         }
         HG_TRY(le);
-        HG_TRY(hipFuncSetAttribute((const void*)k_local_heavy<Key>,
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, lim));
-        HG_TRY(hipFuncSetAttribute((const void*)k_huge_place<Key>,
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, lim));
         HG_TRY(hipFuncSetAttribute((const void*)k_ungroup_by_pos,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, lim));
         return hipSuccess;
@@ -1145,6 +932,7 @@ hipError_t run_build_v2(const Key* keys, uint64_t n, uint64_t V, uint64_t seed, 
     layout_v2(ws, p, sizeof(Key), &w);
     ix.gen_list = w.gen_list;
     ix.gen_cnt = w.gen_cnt;
+    ix.gen_any = w.ctr + kCtrListed;
     auto hp = KeyTraits<Key>::make(V, seed);
     Key* rkeys = (Key*)w.rkeys;
     {
@@ -1184,7 +972,7 @@ hipError_t run_build_v2(const Key* keys, uint64_t n, uint64_t V, uint64_t seed, 
                            s, bin_mat, bin_segs, bin_bits, light_cap<Key>(), p.bins, (uint32_t)n,
                            (uint32_t)V,
                            w.bin_start, offsets, w.heavy_list, w.ctr, w.huge_list, w.huge_s0,
-                           w.slice_owner, w.huge_cap, w.slice_cap);
+                           w.slice_owner, w.huge_cap, w.slice_cap, slice_keys(n));
     }
     HG_TRY(hipGetLastError());
     {
@@ -1198,57 +986,10 @@ hipError_t run_build_v2(const Key* keys, uint64_t n, uint64_t V, uint64_t seed, 
         });
     }
     HG_TRY(hipGetLastError());
-    {
-        HG_PROF("v2_local_heavy", s);
-        const uint32_t hg_grid = p.bins < 512 ? p.bins : 512;
-        hipLaunchKernelGGL(k_local_heavy<Key>, dim3(hg_grid), dim3(kLocalThreads),
-                           heavy_smem<Key>(p.k), s, (const Key*)rkeys, (const uint32_t*)w.rids,
-                           (const uint32_t*)w.bin_start, (const uint32_t*)w.heavy_list,
-                           (const uint32_t*)w.ctr, hp, p.k, offsets, ix, ids, ekeys, !stable);
-    }
-    HG_TRY(hipGetLastError());
-    if (n > kSliceKeys) {
-        // bins above kSliceKeys keys (skew): per-slice counts, per-bin scan,
-        // per-slice placement; the grids drain device-side work lists
-        HG_PROF("v2_split_bins", s);
-        const uint32_t* bs = w.bin_start;
-        hipLaunchKernelGGL(k_huge_hist<Key>, dim3(1024), dim3(kLocalThreads),
-                           (size_t)4 << p.k, s, (const Key*)rkeys, bs,
-                           (const uint32_t*)w.huge_list, (const uint32_t*)w.huge_s0,
-                           (const uint32_t*)w.slice_owner, (const uint32_t*)w.ctr, hp, p.k,
-                           w.slice_hist);
-        HG_TRY(hipGetLastError());
-        hipLaunchKernelGGL(k_huge_tot, dim3(1024), dim3(256), 0, s, bs,
-                           (const uint32_t*)w.huge_list, (const uint32_t*)w.huge_s0,
-                           (const uint32_t*)w.ctr, p.k, w.huge_cap,
-                           (const uint32_t*)w.slice_hist, w.huge_tot);
-        HG_TRY(hipGetLastError());
-        hipLaunchKernelGGL(k_huge_starts, dim3(256), dim3(kLocalThreads), 0, s, bs,
-                           (const uint32_t*)w.huge_list, (const uint32_t*)w.ctr, p.k,
-                           (uint32_t)V, w.huge_cap, w.huge_tot, offsets);
-        HG_TRY(hipGetLastError());
-        hipLaunchKernelGGL(k_huge_down, dim3(1024), dim3(256), 0, s, bs,
-                           (const uint32_t*)w.huge_list, (const uint32_t*)w.huge_s0,
-                           (const uint32_t*)w.ctr, p.k, w.huge_cap,
-                           (const uint32_t*)w.huge_tot, w.slice_hist);
-        HG_TRY(hipGetLastError());
-        hipLaunchKernelGGL(k_huge_place<Key>, dim3(1024), dim3(kLocalThreads),
-                           heavy_smem<Key>(p.k), s, (const Key*)rkeys, (const uint32_t*)w.rids,
-                           bs, (const uint32_t*)w.huge_list, (const uint32_t*)w.huge_s0,
-                           (const uint32_t*)w.slice_owner, (const uint32_t*)w.ctr, hp, p.k,
-                           (const uint32_t*)w.slice_hist, ids, ekeys, !stable);
-        HG_TRY(hipGetLastError());
-        if (ix.head) {
-            hipLaunchKernelGGL(k_huge_index<Key>, dim3(256), dim3(kLocalThreads), 0, s, bs,
-                               (const uint32_t*)w.huge_list, (const uint32_t*)w.ctr, p.k,
-                               (uint32_t)V, (const uint32_t*)offsets, (const Key*)ekeys, ix);
-            HG_TRY(hipGetLastError());
-        }
-    }
-    if (ix.head)
-        HG_TRY(run_key_runs<Key>(offsets, ids, ekeys, n, w.bin_start, p.bins, ix, rkeys, w.rids,
-                                 w.ctr + 3, w.runs_ws, s));
-    return hipSuccess;
+    const RareArgs a{w.bin_start, w.heavy_list, w.huge_list, w.huge_s0, w.slice_owner,
+                     w.slice_hist, w.range_sum, w.ctr, w.huge_cap, w.slice_cap, slice_keys(n),
+                     p.k, p.bins, (uint32_t)V, stable ? 0u : 1u};
+    return run_rare<Key>(a, offsets, ids, ekeys, n, hp, ix, rkeys, w.rids, w.runs_ws, s);
 }
 
 // ------------------------------------------------ scatter by a permutation --
@@ -1370,7 +1111,7 @@ size_t layout_group(void* ws, const GroupPlan& p, uint64_t m, size_t key_size, G
     w.gc = c.take<uint32_t>(m);
     w.mat = c.take<uint32_t>((size_t)p.ntiles * D);
     w.csum = c.take<uint32_t>((size_t)p.nchunks * D);
-    w.ctr = c.take<uint32_t>(5);
+    w.ctr = c.take<uint32_t>(kCtrWords);
     w.seg.seg_start = c.take<uint32_t>(2);
     w.seg.tile_prefix = c.take<uint32_t>(2);
     w.seg.chunk_prefix = c.take<uint32_t>(2);

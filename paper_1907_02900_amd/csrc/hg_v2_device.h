@@ -588,7 +588,10 @@ __device__ __forceinline__ void bin_long_runs(const IndexOut& ix, const LongLds<
             ix.gen_list[gen_region(out, g) + atomicAdd(&lr.cnt[1], 1u)] = b;
     }
     __syncthreads();
-    if (threadIdx.x == 0) ix.gen_cnt[g] = lr.cnt[1];
+    if (threadIdx.x == 0) {
+        ix.gen_cnt[g] = lr.cnt[1];
+        if (lr.cnt[1]) *ix.gen_any = 1u;
+    }
 }
 
 // Index entries of a bin's buckets (32-bit keys).  Entry words are put together
@@ -1046,7 +1049,10 @@ __device__ __forceinline__ void heavy_bin_body(const Key* __restrict__ src_keys,
                 put_short<Key>(ix, v0 + v, lo, cur[v], ekeys + lo);
         }
         __syncthreads();
-        if (threadIdx.x == 0) ix.gen_cnt[v0 >> k] = *nlisted;
+        if (threadIdx.x == 0) {
+            ix.gen_cnt[v0 >> k] = *nlisted;
+            if (*nlisted) *ix.gen_any = 1u;
+        }
     }
 }
 

@@ -41,7 +41,8 @@ RANGES = [
     ("k_tile_hist<unsigned int, false, true", "probe_group_hist"),
     ("k_ungroup_by_pos", "probe_ungroup"),
     ("k_local_light", "v2_local_build"),
-    ("k_local_heavy", "v2_local_heavy"),
+    ("k_rare_bins", "v2_rare_bins"),
+    ("k_build_one", "v2_build_one"),
     ("k_tile_partition<unsigned int, false", "v2_partition_t1"),
     ("k_tile_partition<unsigned int, true", "v2_partition_t2"),
     ("k_tile_hist", "v2_tile_hist"),
