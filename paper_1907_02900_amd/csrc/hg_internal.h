@@ -400,6 +400,14 @@ struct RareArgs {
     uint32_t k, bins, V;
     uint32_t any_order;
 };
+// A table of one bin that fits in LDS (n <= light_cap, V <= 2^k <= 2^12): the
+// whole build in one workgroup.  ANY, W: layout and index entry bytes.
+// bin_start: 2 words of workspace.
+template <typename Key, bool ANY, int W>
+hipError_t run_build_one(const Key* keys, uint64_t n, uint32_t k, uint32_t V, uint32_t* offsets,
+                         uint32_t* ids, Key* ekeys, typename KeyTraits<Key>::Params hp,
+                         const IndexOut& ix, uint32_t* bin_start, Key* rkeys, uint32_t* rids,
+                         void* ws, hipStream_t s);
 size_t runs_ws_bytes(uint64_t n);
 size_t range_sum_words(uint64_t slices);  // words of RareArgs::range_sum
 template <typename Key>

@@ -859,6 +859,27 @@ __global__ __launch_bounds__(kRT) void k_runs_chunk_sort(Rare<Key> x) {
     }
 }
 
+// A table that is one bin held in LDS, from the caller's keys: the per-bin build
+// and its long buckets.  (A build of 1500 keys as partition, scan and per-bin
+// kernels took 12 launches and 47 us, of which the kernels ran 36.)
+template <typename Key, bool ANY, int W>
+__global__ __launch_bounds__(kRT) void k_build_one(Rare<Key> x, const Key* __restrict__ keys,
+                                                   uint32_t n, uint32_t* bin_start) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    if (threadIdx.x == 0) {
+        bin_start[0] = 0;
+        bin_start[1] = n;
+        x.offsets[x.a.V] = n;
+    }
+    light_bin_body<Key, ANY, W>(keys, nullptr, 0u, n, 0u, 0u, x.a.k, x.a.V, x.hp, x.offsets, x.ix,
+                                x.ids, x.ekeys, smem);
+    if constexpr (W != 0) {
+        __syncthreads();
+        const uint32_t listed = x.ix.gen_cnt[0];
+        if (listed) listed_of_bin<Key, true>(x, 0u, listed, BucketLds<Key>(smem));
+    }
+}
+
 template <typename Key>
 size_t rare_smem(uint32_t k) {
     const size_t h = heavy_smem<Key>(k), b = BucketLds<Key>::bytes();
@@ -931,6 +952,50 @@ hipError_t run_rare(const RareArgs& a, uint32_t* offsets, uint32_t* ids, Key* ek
     hipLaunchKernelGGL(k_runs_chunk_sort<Key>, bg, th, blds, s, x);
     return hipGetLastError();
 }
+
+template <typename Key, bool ANY, int W>
+hipError_t run_build_one(const Key* keys, uint64_t n, uint32_t k, uint32_t V, uint32_t* offsets,
+                         uint32_t* ids, Key* ekeys, typename KeyTraits<Key>::Params hp,
+                         const IndexOut& ix, uint32_t* bin_start, Key* rkeys, uint32_t* rids,
+                         void* ws, hipStream_t s) {
+    static std::atomic<uint64_t> done{0};
+    auto smem = [](uint32_t kk) {
+        const size_t l = W ? light_smem_index<Key>(kk) : light_smem<Key>(kk);
+        return W && BucketLds<Key>::bytes() > l ? BucketLds<Key>::bytes() : l;
+    };
+    HG_TRY(once_per_device(done, [&] {
+        return hipFuncSetAttribute((const void*)k_build_one<Key, ANY, W>,
+                                   hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   (int)smem(kMaxLocalBits));
+    }));
+    RareArgs a{};
+    a.bin_start = bin_start;
+    a.k = k;
+    a.bins = 1;
+    a.V = V;
+    const Rare<Key> x{a, offsets, ids, ekeys, hp, ix, rkeys, rids, rkeys, rids,
+                      layout_g2(ws, n).g};
+    HG_PROF("v2_build_one", s);
+    hipLaunchKernelGGL((k_build_one<Key, ANY, W>), dim3(1), dim3(kRT), smem(k), s, x, keys,
+                       (uint32_t)n, bin_start);
+    return hipGetLastError();
+}
+
+#define HG_ONE_INST(Key, ANY, W)                                                               \
+    template hipError_t run_build_one<Key, ANY, W>(                                            \
+        const Key*, uint64_t, uint32_t, uint32_t, uint32_t*, uint32_t*, Key*,                  \
+        KeyTraits<Key>::Params, const IndexOut&, uint32_t*, Key*, uint32_t*, void*, hipStream_t);
+HG_ONE_INST(uint32_t, false, 0)
+HG_ONE_INST(uint32_t, false, 4)
+HG_ONE_INST(uint32_t, false, 8)
+HG_ONE_INST(uint32_t, true, 0)
+HG_ONE_INST(uint32_t, true, 4)
+HG_ONE_INST(uint32_t, true, 8)
+HG_ONE_INST(uint64_t, false, 0)
+HG_ONE_INST(uint64_t, false, 16)
+HG_ONE_INST(uint64_t, true, 0)
+HG_ONE_INST(uint64_t, true, 16)
+#undef HG_ONE_INST
 
 template hipError_t run_rare<uint32_t>(const RareArgs&, uint32_t*, uint32_t*, uint32_t*, uint64_t,
                                        HashParams, const IndexOut&, uint32_t*, uint32_t*, void*,

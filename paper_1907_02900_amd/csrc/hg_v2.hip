@@ -35,13 +35,29 @@ using namespace v2dev;
 
 // Segments of the source array, each cut into tiles of kPartTile entries, and
 // the tiles grouped into chunks of `ch` consecutive tiles for the column scan.
+// One segment known to the host (seg_start null): n entries, ntiles, nchunks.
 struct Segs {
     uint32_t* seg_start;     // [S+1]
     uint32_t* tile_prefix;   // [S+1]
     uint32_t* chunk_prefix;  // [S+1]
     uint32_t S;
     uint32_t ch;
+    uint32_t n, ntiles, nchunks;
+
+    __device__ __forceinline__ uint32_t start(uint32_t s) const {
+        return seg_start ? seg_start[s] : (s ? n : 0u);
+    }
+    __device__ __forceinline__ uint32_t tile0(uint32_t s) const {
+        return seg_start ? tile_prefix[s] : (s ? ntiles : 0u);
+    }
+    __device__ __forceinline__ uint32_t chunk0(uint32_t s) const {
+        return seg_start ? chunk_prefix[s] : (s ? nchunks : 0u);
+    }
 };
+
+Segs one_segment(uint64_t n, uint32_t ntiles, uint32_t nchunks, uint32_t ch) {
+    return Segs{nullptr, nullptr, nullptr, 1, ch, (uint32_t)n, ntiles, nchunks};
+}
 
 // largest s in [0, S) with pre[s] <= x (pre non-decreasing, pre[0] = 0)
 __device__ __forceinline__ uint32_t find_seg(const uint32_t* __restrict__ pre, uint32_t S,
@@ -57,10 +73,10 @@ __device__ __forceinline__ uint32_t find_seg(const uint32_t* __restrict__ pre, u
 
 __device__ __forceinline__ bool locate_tile(const Segs& g, uint32_t t, uint32_t& seg,
                                             uint32_t& begin, uint32_t& end) {
-    if (t >= g.tile_prefix[g.S]) return false;
-    seg = find_seg(g.tile_prefix, g.S, t);
-    begin = g.seg_start[seg] + (t - g.tile_prefix[seg]) * kPartTile;
-    const uint32_t se = g.seg_start[seg + 1];
+    if (t >= g.tile0(g.S)) return false;
+    seg = g.S > 1 ? find_seg(g.tile_prefix, g.S, t) : 0u;
+    begin = g.start(seg) + (t - g.tile0(seg)) * kPartTile;
+    const uint32_t se = g.start(seg + 1);
     end = (se - begin > kPartTile) ? begin + kPartTile : se;
     return true;
 }
@@ -115,10 +131,10 @@ __global__ __launch_bounds__(kPartThreads) void k_tile_hist(const Key* __restric
 
 __device__ __forceinline__ bool locate_chunk(const Segs& g, uint32_t c, uint32_t& seg,
                                              uint32_t& t0, uint32_t& t1) {
-    if (c >= g.chunk_prefix[g.S]) return false;
-    seg = find_seg(g.chunk_prefix, g.S, c);
-    t0 = g.tile_prefix[seg] + (c - g.chunk_prefix[seg]) * g.ch;
-    const uint32_t te = g.tile_prefix[seg + 1];
+    if (c >= g.chunk0(g.S)) return false;
+    seg = g.S > 1 ? find_seg(g.chunk_prefix, g.S, c) : 0u;
+    t0 = g.tile0(seg) + (c - g.chunk0(seg)) * g.ch;
+    const uint32_t te = g.tile0(seg + 1);
     t1 = (te - t0 > g.ch) ? t0 + g.ch : te;
     return true;
 }
@@ -147,16 +163,40 @@ __global__ __launch_bounds__(256) void k_colscan_reduce(const uint32_t* __restri
 // rows of 256 digits at 2^28 keys), so up to 16 row groups walk the chunks side
 // by side with eight loads in flight each: 78 -> 12 us at 2^28, 25 -> 6 us at
 // 300 007 keys, against one thread per digit walking all rows.
+// It knows where every digit of its segment starts, so the starts that the next
+// kernels need come from here as well, not from launches of their own.
 constexpr int kSegThreads = 1024;
 
+// What a segment scan derives from its digits' starts (all null: nothing).
+struct SegsOut {
+    uint32_t* zero = nullptr;  // [kCtrWords], cleared (one segment)
+    Segs next{};               // the segments of the second pass, one per digit (seg_start set)
+    // final bins (bin = segment * digits + digit): their starts, and the lists
+    // of those too large for the LDS kernel
+    uint32_t* bin_start = nullptr;  // [bins + 1]
+    uint32_t bins = 0, n = 0, V = 0, light_keys = 0, slice = 0;
+    uint32_t* offsets = nullptr;    // offsets[V] = n
+    uint32_t *heavy_list = nullptr, *ctr = nullptr;
+    uint32_t *huge_list = nullptr, *huge_s0 = nullptr, *slice_owner = nullptr;
+    uint32_t huge_cap = 0, slice_cap = 0;
+};
+
+__device__ void next_segments(const Segs& g, const uint32_t* dbase, uint32_t n, uint32_t* tmp);
+__device__ void note_bin(const SegsOut& o, uint32_t b, uint32_t st, uint32_t nx);
+
 __global__ __launch_bounds__(kSegThreads) void k_colscan_seg(Segs g, uint32_t D,
-                                                             uint32_t* __restrict__ csum) {
+                                                             uint32_t* __restrict__ csum,
+                                                             SegsOut out) {
     __shared__ uint32_t tmp[kSegThreads / kWave + 1];
     __shared__ uint32_t part[2 * kSegThreads];   // [row group][digit] sums
     __shared__ uint32_t dbase[1u << kMaxDigitBits];
     const uint32_t s = blockIdx.x;
-    const uint32_t c0 = g.chunk_prefix[s], c1 = g.chunk_prefix[s + 1];
-    if (c0 == c1) return;
+    const uint32_t c0 = g.chunk0(s), c1 = g.chunk0(s + 1);
+    if (out.zero && threadIdx.x < kCtrWords) {
+        out.zero[threadIdx.x] = 0;
+        __threadfence();  // before the atomics below
+    }
+    if (c0 == c1 && !out.bin_start) return;
     static_assert((1u << kMaxDigitBits) <= 2 * kSegThreads, "at most two digits per thread");
     const uint32_t per = D > (uint32_t)kSegThreads ? 2u : 1u;
     uint32_t G = (uint32_t)kSegThreads / D;  // row groups (D is a power of two)
@@ -183,12 +223,16 @@ __global__ __launch_bounds__(kSegThreads) void k_colscan_seg(Segs g, uint32_t D,
         for (uint32_t j = 0; j < per; ++j)
             for (uint32_t x = 0; x < G; ++x) tot[j] += part[x * D + d0 + j];
     uint32_t all;
-    const uint32_t ex = g.seg_start[s] + block_excl_scan<kSegThreads>(tot[0] + tot[1], tmp, &all);
+    const uint32_t ex = g.start(s) + block_excl_scan<kSegThreads>(tot[0] + tot[1], tmp, &all);
     if (grp == 0) {
         dbase[d0] = ex;
         if (per == 2) dbase[d0 + 1] = ex + tot[0];
     }
     __syncthreads();
+    if (out.bin_start)
+        for (uint32_t d = threadIdx.x; d < D; d += kSegThreads)
+            note_bin(out, s * D + d, dbase[d], d + 1 < D ? dbase[d + 1] : g.start(s + 1));
+    if (out.next.seg_start) next_segments(out.next, dbase, g.start(1), tmp);
     for (uint32_t j = 0; j < per; ++j) {
         if (ra >= rb) break;
         uint32_t r = dbase[d0 + j];
@@ -310,7 +354,7 @@ __global__ __launch_bounds__(kPartThreads) void k_tile_partition(
     __syncthreads();
     // every output lies inside this segment's range; the guard keeps a
     // corrupted base from turning into a stray store
-    const uint32_t seg_lo = g.seg_start[seg], seg_len = g.seg_start[seg + 1] - seg_lo;
+    const uint32_t seg_lo = g.start(seg), seg_len = g.start(seg + 1) - seg_lo;
     for (uint32_t p = threadIdx.x; p < cnt; p += kPartThreads) {
         const uint32_t o = tbase[sdig[p]] + p;
         if (o - seg_lo < seg_len) {
@@ -490,36 +534,20 @@ size_t partition_smem(uint32_t bits) {
            64;
 }
 
-// -------------------------------------------------------- segment setup ---
+// ------------------------------------------------- from digits' starts ---
 
-// Tier-1 segment: the whole input; also clears the build's device counters.
-__global__ void k_segs_single(Segs g, uint32_t n, uint32_t ntiles, uint32_t nchunks,
-                              uint32_t* ctr) {
-    if (threadIdx.x < kCtrWords) ctr[threadIdx.x] = 0;
-    if (threadIdx.x == 0) {
-        g.seg_start[0] = 0;
-        g.seg_start[1] = n;
-        g.tile_prefix[0] = 0;
-        g.tile_prefix[1] = ntiles;
-        g.chunk_prefix[0] = 0;
-        g.chunk_prefix[1] = nchunks;
-    }
-}
-
-// Tier-2 segments: one per tier-1 digit, from row 0 of the scanned tier-1
-// matrix (the start of every digit's range).  One workgroup; S <= 2048.
-__global__ __launch_bounds__(1024) void k_segs_from_bases(const uint32_t* __restrict__ base1,
-                                                          uint32_t ntiles1, uint32_t n, Segs g) {
-    __shared__ uint32_t tmp[1024 / kWave + 1];
+// Tier-2 segments, one per tier-1 digit, from the digits' starts (in LDS).
+// One workgroup; S <= 2048.
+__device__ void next_segments(const Segs& g, const uint32_t* dbase, uint32_t n, uint32_t* tmp) {
     const uint32_t S = g.S;
-    const uint32_t per = (S + 1023) / 1024;  // <= 2
+    const uint32_t per = (S + kSegThreads - 1) / kSegThreads;  // <= 2
     uint32_t nt[2] = {0, 0}, nc[2] = {0, 0}, st[2] = {0, 0};
     uint32_t mt = 0, mc = 0;
     for (uint32_t j = 0; j < per; ++j) {
         const uint32_t a = threadIdx.x * per + j;
         if (a < S) {
-            const uint32_t s0 = ntiles1 ? base1[a] : 0u;
-            const uint32_t s1 = (a + 1 < S) ? (ntiles1 ? base1[a + 1] : 0u) : n;
+            const uint32_t s0 = dbase[a];
+            const uint32_t s1 = a + 1 < S ? dbase[a + 1] : n;
             st[j] = s0;
             nt[j] = (s1 - s0 + kPartTile - 1) / kPartTile;
             nc[j] = (nt[j] + g.ch - 1) / g.ch;
@@ -528,8 +556,8 @@ __global__ __launch_bounds__(1024) void k_segs_from_bases(const uint32_t* __rest
         }
     }
     uint32_t tt, tc;
-    uint32_t rt = block_excl_scan<1024>(mt, tmp, &tt);
-    uint32_t rc = block_excl_scan<1024>(mc, tmp, &tc);
+    uint32_t rt = block_excl_scan<kSegThreads>(mt, tmp, &tt);
+    uint32_t rc = block_excl_scan<kSegThreads>(mc, tmp, &tc);
     for (uint32_t j = 0; j < per; ++j) {
         const uint32_t a = threadIdx.x * per + j;
         if (a < S) {
@@ -547,55 +575,33 @@ __global__ __launch_bounds__(1024) void k_segs_from_bases(const uint32_t* __rest
     }
 }
 
-// Start of every final bin (bin = segment * 2^bits + digit) in the
-// partitioned array, bin_start[bins] = n, offsets[V] = n, and the list of
-// bins too large for the LDS kernel.
+// Final bin b = [st, nx) of the partitioned array (b past the last bin: empty):
+// its start, and its place in a list when it is too large for the LDS kernel.
 // Bins above `slice` keys are split into slices of that many for several
 // workgroups: they are listed in huge_list with their first slice in huge_s0,
 // and slice_owner maps every slice back to its entry.
-__global__ void k_bin_starts(const uint32_t* __restrict__ base, Segs g, uint32_t bits,
-                             uint32_t light_keys,
-                             uint32_t bins, uint32_t n, uint32_t V, uint32_t* __restrict__ bin_start,
-                             uint32_t* __restrict__ offsets, uint32_t* __restrict__ heavy_list,
-                             uint32_t* __restrict__ ctr, uint32_t* __restrict__ huge_list,
-                             uint32_t* __restrict__ huge_s0, uint32_t* __restrict__ slice_owner,
-                             uint32_t huge_cap, uint32_t slice_cap, uint32_t slice) {
-    const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
-    uint32_t st = 0, nx = 0;
-    bool have = false;
-    if (b <= bins) {
-        const uint32_t D = 1u << bits;
-        auto start_of = [&](uint32_t x) -> uint32_t {
-            if (x >= bins) return n;
-            const uint32_t s = x >> bits, d = x & (D - 1);
-            const uint32_t t0 = g.tile_prefix[s];
-            return (g.tile_prefix[s + 1] > t0) ? base[(size_t)t0 * D + d] : g.seg_start[s];
-        };
-        st = start_of(b);
-        bin_start[b] = st;
-        if (b == bins) offsets[V] = n;
-        if (b < bins) {
-            nx = start_of(b + 1);
-            have = nx - st > light_keys;
-        }
+__device__ void note_bin(const SegsOut& o, uint32_t b, uint32_t st, uint32_t nx) {
+    if (b >= o.bins) return;
+    o.bin_start[b] = st;
+    if (b + 1 == o.bins) {
+        o.bin_start[o.bins] = o.n;
+        o.offsets[o.V] = o.n;
     }
-    if (have) {
-        const uint32_t L = nx - st;
-        if (L <= slice) {
-            const uint32_t slot = atomicAdd(&ctr[kCtrHeavy], 1u);
-            heavy_list[slot] = b;
-        } else {
-            // capacities hold: a split bin has > slice keys, so there are at
-            // most n / slice of them and fewer than 2n / slice slices
-            const uint32_t ns = (L + slice - 1) / slice;
-            const uint32_t idx = atomicAdd(&ctr[kCtrSplit], 1u);
-            const uint32_t s0 = atomicAdd(&ctr[kCtrSlices], ns);
-            if (idx < huge_cap && s0 + ns <= slice_cap) {
-                huge_list[idx] = b;
-                huge_s0[idx] = s0;
-                for (uint32_t j = 0; j < ns; ++j) slice_owner[s0 + j] = idx;
-            }
-        }
+    const uint32_t L = nx - st;
+    if (L <= o.light_keys) return;
+    if (L <= o.slice) {
+        o.heavy_list[atomicAdd(&o.ctr[kCtrHeavy], 1u)] = b;
+        return;
+    }
+    // capacities hold: a split bin has > slice keys, so there are at most
+    // n / slice of them and fewer than 2n / slice slices
+    const uint32_t ns = (L + o.slice - 1) / o.slice;
+    const uint32_t idx = atomicAdd(&o.ctr[kCtrSplit], 1u);
+    const uint32_t s0 = atomicAdd(&o.ctr[kCtrSlices], ns);
+    if (idx < o.huge_cap && s0 + ns <= o.slice_cap) {
+        o.huge_list[idx] = b;
+        o.huge_s0[idx] = s0;
+        for (uint32_t j = 0; j < ns; ++j) o.slice_owner[s0 + j] = idx;
     }
 }
 
@@ -738,11 +744,7 @@ size_t layout_v2(void* ws, const V2Plan& p, size_t key_size, V2Ws* out) {
     const uint32_t D1 = 1u << p.b1, D2 = 1u << p.b2;
     w.m1 = c.take<uint32_t>((size_t)p.ntiles1 * D1);
     w.c1 = c.take<uint32_t>((size_t)p.nchunks1 * D1);
-    w.s1.seg_start = c.take<uint32_t>(2);
-    w.s1.tile_prefix = c.take<uint32_t>(2);
-    w.s1.chunk_prefix = c.take<uint32_t>(2);
-    w.s1.S = 1;
-    w.s1.ch = p.ch1;
+    w.s1 = one_segment(p.n, p.ntiles1, p.nchunks1, p.ch1);
     if (p.tiers == 2) {
         w.m2 = c.take<uint32_t>((size_t)p.ntiles2_ub * D2);
         w.c2 = c.take<uint32_t>((size_t)p.nchunks2_ub * D2);
@@ -771,10 +773,10 @@ size_t layout_v2(void* ws, const V2Plan& p, size_t key_size, V2Ws* out) {
 
 // for_probe: profiled under the grouped probe's names
 hipError_t colscan(uint32_t* mat, const Segs& g, uint32_t D, uint32_t* csum, uint32_t nchunks_ub,
-                   hipStream_t s, bool for_probe) {
+                   hipStream_t s, bool for_probe, const SegsOut& out) {
     if (g.ch == 1) {  // chunks of one tile: the matrix is its own chunk sums
         HG_PROF(for_probe ? "probe_group_scan_seg" : "v2_colscan_seg", s);
-        hipLaunchKernelGGL(k_colscan_seg, dim3(g.S), dim3(kSegThreads), 0, s, g, D, mat);
+        hipLaunchKernelGGL(k_colscan_seg, dim3(g.S), dim3(kSegThreads), 0, s, g, D, mat, out);
         return hipGetLastError();
     }
     {
@@ -785,7 +787,7 @@ hipError_t colscan(uint32_t* mat, const Segs& g, uint32_t D, uint32_t* csum, uin
     HG_TRY(hipGetLastError());
     {
         HG_PROF(for_probe ? "probe_group_scan_seg" : "v2_colscan_seg", s);
-        hipLaunchKernelGGL(k_colscan_seg, dim3(g.S), dim3(kSegThreads), 0, s, g, D, csum);
+        hipLaunchKernelGGL(k_colscan_seg, dim3(g.S), dim3(kSegThreads), 0, s, g, D, csum, out);
     }
     HG_TRY(hipGetLastError());
     {
@@ -815,7 +817,7 @@ hipError_t partition_pass(const Key* src_keys, const uint32_t* src_ids, Key* dst
                           uint32_t* dst_ids, const Segs& g, typename KeyTraits<Key>::Params hp,
                           uint32_t shift, uint32_t bits, uint32_t* mat, uint32_t* csum,
                           uint32_t tiles_ub, uint32_t nchunks_ub, int tier, bool stable,
-                          hipStream_t s, bool id_digit = false) {
+                          hipStream_t s, bool id_digit = false, const SegsOut& out = SegsOut{}) {
     const uint32_t D = 1u << bits;
     const uint32_t grid = (uint32_t)(8 * ceil_div(tiles_ub, 8));
     if (id_digit && (sizeof(Key) != 4 || !src_ids || stable)) return hipErrorInvalidValue;
@@ -833,7 +835,7 @@ hipError_t partition_pass(const Key* src_keys, const uint32_t* src_ids, Key* dst
                                src_keys, g, hp, shift, bits, mat, tiles_ub, nullptr);
     }
     HG_TRY(hipGetLastError());
-    HG_TRY(colscan(mat, g, D, csum, nchunks_ub, s, tier == 3));
+    HG_TRY(colscan(mat, g, D, csum, nchunks_ub, s, tier == 3, out));
     const size_t smem = partition_smem<Key>(bits);
     {
         HG_PROF(tier == 1 ? "v2_partition_t1" : tier == 2 ? "v2_partition_t2" : "probe_group", s);
@@ -935,46 +937,47 @@ hipError_t run_build_v2(const Key* keys, uint64_t n, uint64_t V, uint64_t seed, 
     ix.gen_any = w.ctr + kCtrListed;
     auto hp = KeyTraits<Key>::make(V, seed);
     Key* rkeys = (Key*)w.rkeys;
-    {
-        HG_PROF("v2_segs", s);
-        hipLaunchKernelGGL(k_segs_single, dim3(1), dim3(64), 0, s, w.s1, (uint32_t)n, p.ntiles1,
-                           p.nchunks1, w.ctr);
+    hipError_t e = hipSuccess;
+    if (p.bins == 1 && n <= light_cap<Key>()) {
+        // the whole table is one bin: one workgroup builds it from the input
+        with_layout<Key>(!stable, ix, [&](auto any, auto width) {
+            e = run_build_one<Key, decltype(any)::value, decltype(width)::value>(
+                keys, n, p.k, (uint32_t)V, offsets, ids, ekeys, hp, ix, w.bin_start, rkeys, w.rids,
+                w.runs_ws, s);
+        });
+        return e;
     }
-    HG_TRY(hipGetLastError());
-    const uint32_t* bin_mat;
-    Segs bin_segs;
-    uint32_t bin_bits;
+    // the last pass's scan also leaves the final bins' starts and the lists of
+    // the oversize ones, the first of two passes the second's segments
+    SegsOut bins;
+    bins.bin_start = w.bin_start;
+    bins.bins = p.bins;
+    bins.n = (uint32_t)n;
+    bins.V = (uint32_t)V;
+    bins.light_keys = light_cap<Key>();
+    bins.slice = slice_keys(n);
+    bins.offsets = offsets;
+    bins.heavy_list = w.heavy_list;
+    bins.ctr = w.ctr;
+    bins.huge_list = w.huge_list;
+    bins.huge_s0 = w.huge_s0;
+    bins.slice_owner = w.slice_owner;
+    bins.huge_cap = w.huge_cap;
+    bins.slice_cap = w.slice_cap;
     if (p.tiers == 1) {
+        bins.zero = w.ctr;
         HG_TRY(partition_pass<Key>(keys, nullptr, rkeys, w.rids, w.s1, hp, p.k, p.b1, w.m1, w.c1,
-                                   p.ntiles1, p.nchunks1, 1, stable, s));
-        bin_mat = w.m1;
-        bin_segs = w.s1;
-        bin_bits = p.b1;
+                                   p.ntiles1, p.nchunks1, 1, stable, s, false, bins));
     } else {
         // tier 1 into the table's own arrays, tier 2 into the workspace
+        SegsOut first;
+        first.zero = w.ctr;
+        first.next = w.s2;
         HG_TRY(partition_pass<Key>(keys, nullptr, ekeys, ids, w.s1, hp, p.k + p.b2, p.b1, w.m1,
-                                   w.c1, p.ntiles1, p.nchunks1, 1, stable, s));
-        {
-            HG_PROF("v2_segs", s);
-            hipLaunchKernelGGL(k_segs_from_bases, dim3(1), dim3(1024), 0, s,
-                               (const uint32_t*)w.m1, p.ntiles1, (uint32_t)n, w.s2);
-        }
-        HG_TRY(hipGetLastError());
+                                   w.c1, p.ntiles1, p.nchunks1, 1, stable, s, false, first));
         HG_TRY(partition_pass<Key>(ekeys, ids, rkeys, w.rids, w.s2, hp, p.k, p.b2, w.m2, w.c2,
-                                   p.ntiles2_ub, p.nchunks2_ub, 2, stable, s));
-        bin_mat = w.m2;
-        bin_segs = w.s2;
-        bin_bits = p.b2;
+                                   p.ntiles2_ub, p.nchunks2_ub, 2, stable, s, false, bins));
     }
-    {
-        HG_PROF("v2_bin_starts", s);
-        hipLaunchKernelGGL(k_bin_starts, dim3((uint32_t)ceil_div(p.bins + 1, 256)), dim3(256), 0,
-                           s, bin_mat, bin_segs, bin_bits, light_cap<Key>(), p.bins, (uint32_t)n,
-                           (uint32_t)V,
-                           w.bin_start, offsets, w.heavy_list, w.ctr, w.huge_list, w.huge_s0,
-                           w.slice_owner, w.huge_cap, w.slice_cap, slice_keys(n));
-    }
-    HG_TRY(hipGetLastError());
     {
         HG_PROF("v2_local_build", s);
         with_layout<Key>(!stable, ix, [&](auto any, auto width) {
@@ -1043,18 +1046,14 @@ hipError_t scatter_perm(const uint32_t* ids, const uint32_t* vals, uint64_t n, u
     perm_layout(ws, p, &w, &xv, &xi);
     const auto hp = KeyTraits<uint32_t>::make(1, 0);  // unused: digits come from the ids
     uint32_t* rv = (uint32_t*)w.rkeys;
-    hipLaunchKernelGGL(k_segs_single, dim3(1), dim3(64), 0, s, w.s1, (uint32_t)n, p.ntiles1,
-                       p.nchunks1, w.ctr);
-    HG_TRY(hipGetLastError());
     if (p.tiers == 1) {
         HG_TRY(partition_pass<uint32_t>(vals, ids, rv, w.rids, w.s1, hp, p.k, p.b1, w.m1, w.c1,
                                         p.ntiles1, p.nchunks1, 1, false, s, true));
     } else {
+        SegsOut first;
+        first.next = w.s2;
         HG_TRY(partition_pass<uint32_t>(vals, ids, xv, xi, w.s1, hp, p.k + p.b2, p.b1, w.m1,
-                                        w.c1, p.ntiles1, p.nchunks1, 1, false, s, true));
-        hipLaunchKernelGGL(k_segs_from_bases, dim3(1), dim3(1024), 0, s, (const uint32_t*)w.m1,
-                           p.ntiles1, (uint32_t)n, w.s2);
-        HG_TRY(hipGetLastError());
+                                        w.c1, p.ntiles1, p.nchunks1, 1, false, s, true, first));
         HG_TRY(partition_pass<uint32_t>(xv, xi, rv, w.rids, w.s2, hp, p.k, p.b2, w.m2, w.c2,
                                         p.ntiles2_ub, p.nchunks2_ub, 2, false, s, true));
     }
@@ -1137,13 +1136,13 @@ hipError_t run_probe_grouped(const TableDev& t, const Key* queries, uint64_t m, 
     layout_group(ws, p, m, sizeof(Key), &w);
     const auto hp = KeyTraits<Key>::make(t.V, t.seed);
     const uint32_t* gate = decide ? w.ctr : nullptr;  // ctr[0]: 1 grouped, 0 input order
-    if (decide)
+    if (decide) {
         hipLaunchKernelGGL(k_group_sample<Key>, dim3(1), dim3(1024), 0, s, queries, m, hp,
                            p.shift, p.bits, w.seg, p.ntiles, p.nchunks, w.ctr);
-    else
-        hipLaunchKernelGGL(k_segs_single, dim3(1), dim3(64), 0, s, w.seg, (uint32_t)m, p.ntiles,
-                           p.nchunks, w.ctr);
-    HG_TRY(hipGetLastError());
+        HG_TRY(hipGetLastError());
+    } else {
+        w.seg = one_segment(m, p.ntiles, p.nchunks, p.ch);
+    }
     Key* gq = (Key*)w.gq;
     // positions only when the counts go back to input order
     HG_TRY(partition_pass<Key>(queries, nullptr, gq, counts ? w.gpos : nullptr, w.seg, hp,
