@@ -106,21 +106,22 @@ def kernel_bytes(name, n, m, V, kb, sum_len, plan):
 
       probe_group_hist  reads the queries, writes their tile histograms;
       probe_group       reads the queries and the tile bases, writes the
-                        queries and their input positions in grouped order;
-      probe_ungroup     reads positions and counts in grouped order and two
-                        rows of bases per four tiles, writes the counts.
+                        queries and their 16-bit input places in grouped order;
+      probe_ungroup     reads places and 8-bit counts in grouped order and two
+                        rows of bases per 16384 queries, writes the counts.
 
     The per-bucket probe index is this design's addition and is not counted
     here (index_bytes gives the bytes with it)."""
-    gm = group_matrix_bytes(m, V)
+    tile = 8192 if kb == 4 else 4096
+    gm = group_matrix_bytes(m, V, tile)
     if name == "probe_count":
         return m * kb + 8 * m + kb * sum_len + 4 * m
     if name == "probe_group_hist":
         return m * kb + gm
     if name == "probe_group":
-        return m * kb + gm + m * kb + 4 * m
+        return m * kb + gm + m * kb + 2 * m
     if name == "probe_ungroup":
-        return 4 * m + 4 * m + 4 * m + gm // 2
+        return 2 * m + m + 4 * m + 2 * gm * tile // 16384
     if name == "v2_local_build":
         return 2 * n * (kb + 4) + (V + 1) * 4
     if name == "v2_partition_t1":
@@ -134,12 +135,12 @@ def kernel_bytes(name, n, m, V, kb, sum_len, plan):
     return None
 
 
-def group_matrix_bytes(m, V):
-    """Tile x range matrix of the probe's query grouping: 4096 queries per
-    tile, 2^min(9, ceil(log2 V)) ranges (at least 2), 4 bytes each."""
+def group_matrix_bytes(m, V, tile=4096):
+    """Tile x range matrix of the probe's query grouping: one row per tile of
+    queries, 2^min(9, ceil(log2 V)) ranges (at least 2), 4 bytes each."""
     kv = max(int(V - 1).bit_length(), 0)
     bits = 9 if kv >= 9 else max(kv, 1)
-    return -(-m // 4096) * (1 << bits) * 4
+    return -(-m // tile) * (1 << bits) * 4
 
 
 def entry_format(n, V, kb):
@@ -167,12 +168,17 @@ def index_bytes(name, n, m, V, kb, sum_tail):
     return None
 
 
-def v2_plan_bytes(hg, n, V, kb=4):
+def v2_plan_bytes(hg, n, V, kb=4, any_order=False):
     """Tile x digit matrix bytes of each partition pass, from the library's
-    own plan (hg_build_plan)."""
+    own plan (hg_build_plan, whose tiles are those of the stable order;
+    32-bit keys in any order take tiles of 8192)."""
     p = hg.build_plan(n, V, 8 * kb)
-    m1 = p["tiles"][0] * (1 << p["digit_bits"][0]) * 4
-    m2 = p["tiles"][1] * (1 << p["digit_bits"][1]) * 4 if p["passes"] == 2 else 0
+    tiles = list(p["tiles"])
+    if any_order and kb == 4:
+        rows = -(-n // 8192)
+        tiles = [rows, rows + (1 << p["digit_bits"][0]) if tiles[1] else 0]
+    m1 = tiles[0] * (1 << p["digit_bits"][0]) * 4
+    m2 = tiles[1] * (1 << p["digit_bits"][1]) * 4 if p["passes"] == 2 else 0
     return {"m1_bytes": m1, "m2_bytes": m2, "plan": p}
 
 
@@ -581,7 +587,7 @@ def main():
     n_tail = int(reads.sum().item())  # queries that also read the edge array
     del h, offl, off, blen, ek, eku, qu, first, reads, sel
 
-    plan = v2_plan_bytes(hg, n, V, kb)
+    plan = v2_plan_bytes(hg, n, V, kb, any_order=not args.stable)
     kernels = {}
     for name, (launches, tot_ms) in prof.items():
         per = launches / args.steps

@@ -204,7 +204,7 @@ typedef struct hg_plan_info {
     uint32_t passes;          /* partition passes before the per-bin build     */
     uint32_t digit_bits[2];   /* digit width of each pass (0 if unused)        */
     uint32_t tiles[2];        /* partition tiles of each pass (second: bound)  */
-    uint32_t tile_keys;       /* keys per partition tile                       */
+    uint32_t tile_keys;       /* keys per partition tile (stable order)        */
     uint64_t workspace_bytes; /* device workspace of the build                 */
 } hg_plan_info;
 
@@ -322,7 +322,7 @@ hg_status hg_probe(const hg_table *t, const void *d_queries, uint64_t m, uint32_
  *   HG_PROBE_GROUPED: the queries are first partitioned into up to 512
  *     ranges of buckets (with their input positions), probed range by range
  *     with each XCD reading one window of the index at a time, and the
- *     counts are put back in input order.  Needs m * (key_bits / 8 + 8) bytes
+ *     counts are put back in input order.  Needs m * (key_bits / 8 + 7) bytes
  *     of workspace plus 2 KiB per 4096 queries (from the allocator,
  *     hg_set_allocator).
  *   HG_PROBE_GROUPED_UNLESS_SKEWED: the queries' histogram over the ranges

@@ -391,7 +391,7 @@ hg_status hg_build_plan(uint64_t n, uint64_t hash_range, int key_bits, uint32_t 
     if (!out || !valid_kb(key_bits) || !valid_range(hash_range) || n > kU32Max ||
         (bins && bins > hash_range))
         return HG_ERR_INVALID_ARG;
-    const V2Plan p = plan_v2(n, hash_range, key_bits, bins);
+    const V2Plan p = plan_v2(n, hash_range, key_bits, bins, false);
     *out = hg_plan_info{};
     out->bucket_bits = p.k;
     out->bins = p.bins;
@@ -400,7 +400,7 @@ hg_status hg_build_plan(uint64_t n, uint64_t hash_range, int key_bits, uint32_t 
     out->digit_bits[1] = p.tiers == 2 ? p.b2 : 0u;
     out->tiles[0] = p.ntiles1;
     out->tiles[1] = p.tiers == 2 ? p.ntiles2_ub : 0u;
-    out->tile_keys = kPartTile;
+    out->tile_keys = p.tile;
     out->workspace_bytes = build_ws_bytes(HG_VARIANT_V2, n, hash_range, key_bits, bins);
     return HG_OK;
 }

@@ -114,9 +114,15 @@ struct Carver {
 };
 
 // ---- partition geometry shared by the V2 kernels --------------------------
-constexpr int kPartThreads = 256;
-constexpr int kPartItems = 16;
-constexpr uint32_t kPartTile = kPartThreads * kPartItems;  // entries per tile
+// Entries per partition tile.  Long runs per digit save partial lines beyond the
+// L2 and large tiles cost LDS, that is waves in flight: 8192 32-bit keys where
+// any order needs one set of counters (2^28 keys, first pass: 688 us, in tiles of
+// 4096 1150); 4096 64-bit keys, or 32-bit keys ranked stably with counters per
+// wave (2^26 keys, first pass: 216 us, in tiles of 8192 255 to 342).
+constexpr uint32_t part_tile(size_t key_size, bool any_order) {
+    return key_size == 4 && any_order ? 8192u : 4096u;
+}
+constexpr int kPartThreads = 256;  // of the batched partition
 constexpr int kLocalThreads = 512;
 // Keys per thread a bin held in LDS may have, and the bin's capacity: 9 for
 // 32-bit keys (4608 keys, bins planned at about 4096); 6 for 64-bit keys
@@ -163,11 +169,12 @@ struct V2Plan {
     uint32_t tiers = 1;    // partition passes (1 or 2)
     uint32_t b1 = 0, b2 = 0;
     uint64_t n = 0, V = 0;
+    uint32_t tile = 0;     // entries per partition tile
     uint32_t ntiles1 = 0, nchunks1 = 0, ch1 = 1;
     uint32_t ntiles2_ub = 0, nchunks2_ub = 0, ch2 = 1;
 };
 
-V2Plan plan_v2(uint64_t n, uint64_t V, int key_bits, uint32_t bins_hint);
+V2Plan plan_v2(uint64_t n, uint64_t V, int key_bits, uint32_t bins_hint, bool any_order);
 
 // Workspace bytes needed by a build.
 size_t build_ws_bytes(int variant, uint64_t n, uint64_t V, int key_bits, uint32_t bins_hint);
@@ -462,13 +469,15 @@ size_t probe_ws_bytes(uint64_t m);
 // what the pairs pass needs instead of that entry.
 // xcd_order: query tiles are dealt out per XCD (xcd_tile), for queries that
 // are grouped by bucket range.  gate (device, may be null): when *gate == 0
-// the launch probes q_in into counts_in in input order instead.
+// the launch probes q_in into counts_in in input order instead.  bytes (may be
+// null): the counts as bytes, with counts written only from 255 on (bytes 255);
+// not for queries in input order.
 template <typename Key>
 hipError_t run_probe_counts(const TableDev& t, const Key* queries, uint64_t m, uint32_t* counts,
                             unsigned long long* d_total, hipStream_t s,
                             uint16_t* held = nullptr, bool xcd_order = false,
                             const uint32_t* gate = nullptr, const Key* q_in = nullptr,
-                            uint32_t* counts_in = nullptr);
+                            uint32_t* counts_in = nullptr, uint8_t* bytes = nullptr);
 
 // The same counts (and total) with the queries first grouped by bucket range
 // and the counts put back in input order; ws holds

@@ -235,6 +235,7 @@ __device__ __forceinline__ uint32_t count_unsettled(const View<Key>& t,
 // of the index per XCD at a time).  gate (may be null): when *gate == 0 the
 // launch probes q_in into counts_in instead, block b taking tile b (the
 // grouped probe decides on the device whether its queries were grouped).
+// bytes (may be null): counts go there as bytes, and to counts only from 255 on.
 // held (32-bit keys): per query 0x8000 | the mask of the bucket's keys equal
 // to it when it has matches and its entry holds the bucket whole, else 0.
 template <typename Key, int W>
@@ -242,12 +243,13 @@ __global__ __launch_bounds__(kProbeThreads) void k_probe_count(
     const Key* __restrict__ q, uint64_t m, View<Key> t, uint32_t* __restrict__ counts,
     unsigned long long* __restrict__ total, uint16_t* __restrict__ held, uint32_t xcd_tiles,
     const uint32_t* __restrict__ gate, const Key* __restrict__ q_in,
-    uint32_t* __restrict__ counts_in) {
+    uint32_t* __restrict__ counts_in, uint8_t* __restrict__ bytes) {
     __shared__ uint64_t red[kProbeThreads / kWave + 1];
     uint32_t tile = xcd_tiles ? xcd_tile(blockIdx.x, xcd_tiles) : blockIdx.x;
     if (gate && *gate == 0u) {
         q = q_in;
         counts = counts_in;
+        bytes = nullptr;
         tile = blockIdx.x;
     }
     const uint64_t base = (uint64_t)tile * (kProbeThreads * kProbeItems) + threadIdx.x;
@@ -278,7 +280,10 @@ __global__ __launch_bounds__(kProbeThreads) void k_probe_count(
             if (c == kUnsettled)  // (not for j >= m: their entry is empty)
                 c = count_unsettled<Key, W>(t, e[r], qq[r], KeyTraits<Key>::bucket(qq[r], t.hp));
         }
-        if (j < m && counts) counts[j] = c;
+        if (j < m && counts) {
+            if (bytes) bytes[j] = (uint8_t)(c < 255u ? c : 255u);
+            if (!bytes || c >= 255u) counts[j] = c;
+        }
         if constexpr (W == 4 || W == 8) {
             if (held && j < m) {
                 const uint32_t code = (uint32_t)e[r] & 15u;
@@ -536,7 +541,7 @@ template <typename Key>
 hipError_t run_probe_counts(const TableDev& t, const Key* queries, uint64_t m, uint32_t* counts,
                             unsigned long long* d_total, hipStream_t s, uint16_t* held,
                             bool xcd_order, const uint32_t* gate, const Key* q_in,
-                            uint32_t* counts_in) {
+                            uint32_t* counts_in, uint8_t* bytes) {
     if (m == 0) return d_total ? fill_u32((uint32_t*)d_total, 2, 0u, s) : hipSuccess;
     const uint32_t tiles = grid_for(m, kProbeThreads * kProbeItems);
     const uint32_t xt = xcd_order ? tiles : 0u;
@@ -546,7 +551,7 @@ hipError_t run_probe_counts(const TableDev& t, const Key* queries, uint64_t m, u
         with_entry<Key>(t, [&](auto w) {
             hipLaunchKernelGGL((k_probe_count<Key, decltype(w)::value>), grid,
                                dim3(kProbeThreads), 0, s, queries, m, view_of<Key>(t), counts,
-                               d_total, held, xt, gate, q_in, counts_in);
+                               d_total, held, xt, gate, q_in, counts_in, bytes);
         });
     }
     HG_TRY(hipGetLastError());
@@ -608,7 +613,7 @@ hipError_t run_intersect_pairs(const TableDev& a, const TableDev& b, const uint6
 #define HG_PINST(Key)                                                                           \
     template hipError_t run_probe_counts<Key>(const TableDev&, const Key*, uint64_t, uint32_t*, \
                                               unsigned long long*, hipStream_t, uint16_t*, bool, \
-                                              const uint32_t*, const Key*, uint32_t*);           \
+                                              const uint32_t*, const Key*, uint32_t*, uint8_t*); \
     template hipError_t run_probe_pairs<Key>(const TableDev&, const Key*, uint64_t,             \
                                              const uint64_t*, uint32_t*, uint32_t*,             \
                                              hipStream_t, const uint16_t*);                     \

@@ -33,7 +33,7 @@ namespace {
 
 using namespace v2dev;
 
-// Segments of the source array, each cut into tiles of kPartTile entries, and
+// Segments of the source array, each cut into tiles of `tile` entries, and
 // the tiles grouped into chunks of `ch` consecutive tiles for the column scan.
 // One segment known to the host (seg_start null): n entries, ntiles, nchunks.
 struct Segs {
@@ -42,7 +42,7 @@ struct Segs {
     uint32_t* chunk_prefix;  // [S+1]
     uint32_t S;
     uint32_t ch;
-    uint32_t n, ntiles, nchunks;
+    uint32_t n, ntiles, nchunks, tile;
 
     __device__ __forceinline__ uint32_t start(uint32_t s) const {
         return seg_start ? seg_start[s] : (s ? n : 0u);
@@ -55,8 +55,8 @@ struct Segs {
     }
 };
 
-Segs one_segment(uint64_t n, uint32_t ntiles, uint32_t nchunks, uint32_t ch) {
-    return Segs{nullptr, nullptr, nullptr, 1, ch, (uint32_t)n, ntiles, nchunks};
+Segs one_segment(uint64_t n, uint32_t ntiles, uint32_t nchunks, uint32_t ch, uint32_t tile) {
+    return Segs{nullptr, nullptr, nullptr, 1, ch, (uint32_t)n, ntiles, nchunks, tile};
 }
 
 // largest s in [0, S) with pre[s] <= x (pre non-decreasing, pre[0] = 0)
@@ -75,9 +75,9 @@ __device__ __forceinline__ bool locate_tile(const Segs& g, uint32_t t, uint32_t&
                                             uint32_t& begin, uint32_t& end) {
     if (t >= g.tile0(g.S)) return false;
     seg = g.S > 1 ? find_seg(g.tile_prefix, g.S, t) : 0u;
-    begin = g.start(seg) + (t - g.tile0(seg)) * kPartTile;
+    begin = g.start(seg) + (t - g.tile0(seg)) * g.tile;
     const uint32_t se = g.start(seg + 1);
-    end = (se - begin > kPartTile) ? begin + kPartTile : se;
+    end = (se - begin > g.tile) ? begin + g.tile : se;
     return true;
 }
 
@@ -90,24 +90,24 @@ __device__ __forceinline__ bool locate_tile(const Segs& g, uint32_t t, uint32_t&
 // instead of the bucket of its key (the scatter by a permutation below).
 // QUERIES: the same code, instantiated apart for grouping a probe's queries
 // so that kernel traces tell it from the build's passes (also below).
-template <typename Key, bool ID_DIGIT = false, bool QUERIES = false>
-__global__ __launch_bounds__(kPartThreads) void k_tile_hist(const Key* __restrict__ keys, Segs g,
-                                                            typename KeyTraits<Key>::Params hp,
-                                                            uint32_t shift, uint32_t bits,
-                                                            uint32_t* __restrict__ mat,
-                                                            uint32_t tiles_ub,
-                                                            const uint32_t* __restrict__ ids = nullptr) {
+constexpr int kHistThreads = 512;
+
+template <typename Key, bool ID_DIGIT, bool QUERIES, uint32_t TILE>
+__global__ __launch_bounds__(kHistThreads) void k_tile_hist(
+    const Key* __restrict__ keys, Segs g, typename KeyTraits<Key>::Params hp, uint32_t shift,
+    uint32_t bits, uint32_t* __restrict__ mat, uint32_t tiles_ub,
+    const uint32_t* __restrict__ ids = nullptr) {
     extern __shared__ uint32_t cnt[];
     const uint32_t D = 1u << bits;
     const uint32_t t = xcd_tile(blockIdx.x, tiles_ub);
     uint32_t seg, begin, end;
     if (!locate_tile(g, t, seg, begin, end)) return;
-    for (uint32_t d = threadIdx.x; d < D; d += kPartThreads) cnt[d] = 0;
-    constexpr int IT = kPartItems;
+    for (uint32_t d = threadIdx.x; d < D; d += kHistThreads) cnt[d] = 0;
+    constexpr int IT = TILE / kHistThreads;
     Key k[IT];
 #pragma unroll
     for (int r = 0; r < IT; ++r) {
-        const uint32_t i = begin + r * kPartThreads + threadIdx.x;
+        const uint32_t i = begin + r * kHistThreads + threadIdx.x;
         if (ID_DIGIT) k[r] = (i < end) ? (Key)ids[i] : (Key)0;
         else k[r] = (i < end) ? keys[i] : (Key)0;
     }
@@ -115,13 +115,13 @@ __global__ __launch_bounds__(kPartThreads) void k_tile_hist(const Key* __restric
     const uint32_t mask = D - 1;
 #pragma unroll
     for (int r = 0; r < IT; ++r) {
-        const uint32_t i = begin + r * kPartThreads + threadIdx.x;
+        const uint32_t i = begin + r * kHistThreads + threadIdx.x;
         const uint32_t v = ID_DIGIT ? (uint32_t)k[r] : KeyTraits<Key>::bucket(k[r], hp);
         if (i < end) atomicAdd(&cnt[(v >> shift) & mask], 1u);
     }
     __syncthreads();
     uint32_t* row = mat + (size_t)t * D;
-    for (uint32_t d = threadIdx.x; d < D; d += kPartThreads) row[d] = cnt[d];
+    for (uint32_t d = threadIdx.x; d < D; d += kHistThreads) row[d] = cnt[d];
 }
 
 // ------------------------------------- segmented column scan of [tile][digit]
@@ -277,27 +277,73 @@ __global__ __launch_bounds__(256) void k_colscan_down(uint32_t* __restrict__ mat
 
 // ------------------------------------------------------------ partition ---
 
+// Consecutive queries that one workgroup of k_ungroup_by_pos puts back in order:
+// whole tiles, and a query's place among them fits 16 bits.
+constexpr uint32_t kUngroupSpan = 16384;
+
+// How a workgroup takes a tile: 8 items per thread, so that 64 VGPRs and the LDS
+// leave 24 to 32 waves a CU.  With 256 threads of 16 items (12 waves a CU) 2^27
+// 64-bit keys took 952 and 912 us a stable pass, now 723 and 709; 2^28 any-order
+// 32-bit keys in 8192-key tiles 856 us the first pass and 1061 the second, now
+// 640 and 1028.
+template <typename Key, bool STABLE>
+struct PartGeo {
+    static constexpr uint32_t kTile = part_tile(sizeof(Key), !STABLE);
+    static constexpr int kItems = 8;
+    static constexpr int kThreads = kTile / kItems;
+};
+
+// LDS of a partition tile, in this order: keys, ids (32 bits where the entries
+// carry ids, else their 16-bit place in the tile), digits of 64-bit keys (32-bit
+// keys are hashed again instead: their hash costs less than the LDS), the ranking
+// counters (per wave where it is stable), digit starts, output bases.  What a
+// tile takes sets how many share a CU: a 512-digit any-order tile of 8192 32-bit
+// keys 70 KB with ids and 54 without, two workgroups a CU either way.
+template <typename Key, bool HAS_IDS, bool STABLE>
+struct PartLds {
+    using Geo = PartGeo<Key, STABLE>;
+    static constexpr uint32_t kTile = Geo::kTile, kWaves = Geo::kThreads / kWave;
+    static constexpr bool kDigits = sizeof(Key) == 8;
+    using Id = typename std::conditional<HAS_IDS, uint32_t, uint16_t>::type;
+    Key* keys;
+    Id* ids;
+    uint16_t* dig;
+    uint32_t *wcnt, *dstart, *tbase, *tmp;
+    static constexpr size_t entry() { return sizeof(Key) + sizeof(Id) + (kDigits ? 2 : 0); }
+    static size_t bytes(uint32_t bits) {
+        const size_t D = (size_t)1 << bits;
+        return kTile * entry() + (STABLE ? kWaves : 1) * D * 4 + 2 * D * 4 + (kWaves + 1) * 4 + 64;
+    }
+    __device__ PartLds(unsigned char* p, uint32_t D) {
+        keys = (Key*)p;
+        ids = (Id*)(keys + kTile);
+        dig = (uint16_t*)(ids + kTile);
+        wcnt = (uint32_t*)(dig + (kDigits ? kTile : 0));
+        dstart = wcnt + (STABLE ? kWaves : 1) * D;
+        tbase = dstart + D;
+        tmp = tbase + D;
+    }
+};
+
 // Stable partition of one tile by a digit of the bucket index.  Writes every
 // entry to base(tile, digit) + its rank among the tile's entries of that
 // digit.
 // STABLE: entries of equal digit keep their order (rank_stable); otherwise
 // their order inside a run is unspecified (rank_any, no ballots).
+// QUERIES: instead of ids, dst_ids (may be null) receives 16-bit places in
+// the kUngroupSpan queries that k_ungroup_by_pos puts back together.
 template <typename Key, bool HAS_IDS, bool STABLE, bool ID_DIGIT = false, bool QUERIES = false>
-__global__ __launch_bounds__(kPartThreads) void k_tile_partition(
+__global__ __launch_bounds__((PartGeo<Key, STABLE>::kThreads)) void k_tile_partition(
     const Key* __restrict__ src_keys, const uint32_t* __restrict__ src_ids,
     Key* __restrict__ dst_keys, uint32_t* __restrict__ dst_ids, Segs g,
     typename KeyTraits<Key>::Params hp, uint32_t shift, uint32_t bits,
     const uint32_t* __restrict__ base, uint32_t tiles_ub) {
-    constexpr int IT = kPartItems;
+    using Geo = PartGeo<Key, STABLE>;
+    constexpr int IT = Geo::kItems, kThreads = Geo::kThreads;
+    using Lds = PartLds<Key, HAS_IDS, STABLE>;
     const uint32_t D = 1u << bits;
     extern __shared__ __align__(16) unsigned char smem[];
-    Key* skeys = (Key*)smem;
-    uint32_t* sids = (uint32_t*)(skeys + kPartTile);
-    uint16_t* sdig = (uint16_t*)(sids + kPartTile);
-    uint32_t* wcnt = (uint32_t*)(sdig + kPartTile);
-    uint32_t* dstart = wcnt + W_PART * D;
-    uint32_t* tbase = dstart + D;
-    uint32_t* tmp = tbase + D;
+    const Lds m(smem, D);
 
     const uint32_t t = xcd_tile(blockIdx.x, tiles_ub);
     uint32_t seg, begin, end;
@@ -312,22 +358,17 @@ __global__ __launch_bounds__(kPartThreads) void k_tile_partition(
 #pragma unroll
     for (int r = 0; r < IT; ++r) {
         const uint32_t e = wbase + r * kWave + lane;
-        if (e < cnt) {
-            k[r] = src_keys[begin + e];
-            id[r] = HAS_IDS ? src_ids[begin + e] : begin + e;
-        } else {
-            k[r] = 0;
-            id[r] = 0;
-        }
+        k[r] = e < cnt ? src_keys[begin + e] : (Key)0;
+        id[r] = HAS_IDS && e < cnt ? src_ids[begin + e] : 0u;
     }
     // the tile's digit bases, loaded now so that their latency overlaps the
     // ranking (D <= 2048: at most kRowPer per thread)
-    constexpr int kRowPer = (1 << kMaxDigitBits) / kPartThreads;
+    constexpr int kRowPer = (1 << kMaxDigitBits) / kThreads;
     const uint32_t* row = base + (size_t)t * D;
     uint32_t rowv[kRowPer];
 #pragma unroll
     for (int j = 0; j < kRowPer; ++j) {
-        const uint32_t d = threadIdx.x + j * kPartThreads;
+        const uint32_t d = threadIdx.x + j * kThreads;
         rowv[j] = d < D ? row[d] : 0u;
     }
 #pragma unroll
@@ -336,132 +377,139 @@ __global__ __launch_bounds__(kPartThreads) void k_tile_partition(
         const uint32_t v = ID_DIGIT ? id[r] : KeyTraits<Key>::bucket(k[r], hp);
         dig[r] = (e < cnt) ? ((v >> shift) & mask) : D;
     }
-    if (STABLE) rank_stable<kPartThreads, IT>(dig, bits, wcnt, dstart, tmp, pos);
-    else rank_any<kPartThreads, IT>(dig, bits, wcnt, dstart, tmp, pos);
+    if (STABLE) rank_stable<kThreads, IT>(dig, bits, m.wcnt, m.dstart, m.tmp, pos);
+    else rank_any<kThreads, IT>(dig, bits, m.wcnt, m.dstart, m.tmp, pos);
 #pragma unroll
     for (int j = 0; j < kRowPer; ++j) {
-        const uint32_t d = threadIdx.x + j * kPartThreads;
-        if (d < D) tbase[d] = rowv[j] - dstart[d];
+        const uint32_t d = threadIdx.x + j * kThreads;
+        if (d < D) m.tbase[d] = rowv[j] - m.dstart[d];
     }
 #pragma unroll
     for (int r = 0; r < IT; ++r) {
         if (dig[r] < D) {
-            skeys[pos[r]] = k[r];
-            sids[pos[r]] = id[r];
-            sdig[pos[r]] = (uint16_t)dig[r];
+            m.keys[pos[r]] = k[r];
+            m.ids[pos[r]] = HAS_IDS ? (typename Lds::Id)id[r]
+                                    : (typename Lds::Id)(wbase + r * kWave + lane);
+            if (Lds::kDigits) m.dig[pos[r]] = (uint16_t)dig[r];
         }
     }
     __syncthreads();
     // every output lies inside this segment's range; the guard keeps a
     // corrupted base from turning into a stray store
     const uint32_t seg_lo = g.start(seg), seg_len = g.start(seg + 1) - seg_lo;
-    for (uint32_t p = threadIdx.x; p < cnt; p += kPartThreads) {
-        const uint32_t o = tbase[sdig[p]] + p;
+    uint16_t* dst_place = (uint16_t*)dst_ids;
+    const uint32_t place0 = QUERIES ? (t % (kUngroupSpan / Geo::kTile)) * Geo::kTile : 0u;
+    for (uint32_t p = threadIdx.x; p < cnt; p += kThreads) {
+        const Key key = m.keys[p];
+        const uint32_t x = m.ids[p];
+        const uint32_t d = Lds::kDigits ? m.dig[p]
+                                        : ((ID_DIGIT ? x : KeyTraits<Key>::bucket(key, hp)) >> shift) & mask;
+        const uint32_t o = m.tbase[d] + p;
         if (o - seg_lo < seg_len) {
-            dst_keys[o] = skeys[p];
-            if (HAS_IDS || dst_ids) dst_ids[o] = sids[p];  // positions may be dropped
+            dst_keys[o] = key;
+            if (QUERIES) {
+                if (dst_ids) dst_place[o] = (uint16_t)(place0 + x);
+            } else {
+                dst_ids[o] = HAS_IDS ? x : begin + x;
+            }
         }
     }
 }
 
 // ------------------------------------------------------ grouped probing ---
 
-// Puts values computed in grouped order back in input order.  Entry e of
-// partition tile t was written (HAS_IDS = false, so its id is its input
-// position) to base(t, d) + its rank inside the tile's run of digit d, with
-// its position in gpos.  The runs of kUngroupTiles consecutive tiles are
-// adjacent in grouped order, so one workgroup takes such a group of tiles:
-// its run of digit d is [base(t0, d), next(t1, d)), next being base(t1, d),
-// or past the last tile the start of digit d + 1 (m after the last digit),
-// long enough that every read uses whole lines.  Each thread takes entries
-// of the group's runs in order (a binary search over the runs' starts gives
-// the digit: skew only lengthens runs), loads position and value, places the
-// value in LDS by its position, and the group's values are then written in
-// input order.  One segment (S = 1).
+// Puts counts found in grouped order back in input order.  Entry e of
+// partition tile t was written to base(t, d) + its rank inside the tile's run
+// of digit d, with its place among kUngroupSpan queries in `place`.  The runs of
+// consecutive tiles are adjacent in grouped order, so one workgroup takes the
+// tiles [t0, t1) of kUngroupSpan queries: its run of digit d is
+// [base(t0, d), next(t1, d)), next being base(t1, d), or past the last tile the
+// start of digit d + 1 (m after the last digit).  A wave takes the runs of up to
+// 64 consecutive digits, one lane finds each run's start and length, and each
+// run's first 64 entries are one load of places and one of counts, eight runs in
+// flight; what is longer (32 entries are usual, skew lengthens runs) is listed and
+// taken by the whole workgroup.  Counts go to LDS by place and from there in
+// input order; they come as bytes, and 255 stands for the 32-bit one in `wide`,
+// which the thread that meets it writes itself.  One segment (S = 1).
+// Bound by HBM and by latency: 3 bytes read and 4 written per query.  2^28
+// queries: 943 us with 32-bit positions and counts and a binary search over the
+// runs' starts per entry, 725 with these bytes and a walk along the starts, 503
+// by runs.
 constexpr uint32_t kUngroupThreads = 1024;
-constexpr uint32_t kUngroupTiles = 4;
-constexpr uint32_t kUngroupSpan = kUngroupTiles * kPartTile;  // entries per workgroup
+constexpr uint32_t kUngroupLong = kUngroupSpan / (kWave + 1);  // runs above 64 entries, at most
+static_assert((1u << 9) <= kUngroupThreads, "a wave's digits fit its lanes");
 
-__global__ __launch_bounds__(kUngroupThreads) void k_ungroup_by_pos(
-    uint64_t m, uint32_t ntiles, uint32_t bits, const uint32_t* __restrict__ base,
-    uint32_t groups, const uint32_t* __restrict__ gpos, const uint32_t* __restrict__ src,
-    uint32_t* __restrict__ dst, const uint32_t* __restrict__ gate) {
+__global__ __launch_bounds__(kUngroupThreads, 8) void k_ungroup_by_pos(
+    uint64_t m, uint32_t ntiles, uint32_t tile, uint32_t bits, const uint32_t* __restrict__ base,
+    uint32_t groups, const uint16_t* __restrict__ place, const uint8_t* __restrict__ src,
+    const uint32_t* __restrict__ wide, uint32_t* __restrict__ dst,
+    const uint32_t* __restrict__ gate) {
     if (gate && *gate != 1u) return;  // the probe kept input order
-    extern __shared__ __align__(16) uint32_t ush[];
-    uint32_t* sval = ush;                          // [kUngroupSpan]
-    uint32_t* rstart = sval + kUngroupSpan;        // [D + 1] run starts inside the group
-    uint32_t* rbase = rstart + (1u << bits) + 1;   // [D] grouped start - run start
-    uint32_t* tmp = rbase + (1u << bits);          // [kUngroupThreads / 64 + 1]
+    __shared__ uint32_t sval32[kUngroupSpan / 4];
+    __shared__ uint32_t lstart[kUngroupLong], llen[kUngroupLong];
+    __shared__ uint32_t nlong;
+    uint8_t* sval = (uint8_t*)sval32;
     const uint32_t D = 1u << bits;
     const uint32_t gi = xcd_tile(blockIdx.x, groups);
     if (gi >= groups) return;
-    const uint32_t t0 = gi * kUngroupTiles;
-    const uint32_t t1 = t0 + kUngroupTiles < ntiles ? t0 + kUngroupTiles : ntiles;
-    const uint64_t begin = (uint64_t)t0 * kPartTile;
-    const uint64_t end64 = (uint64_t)t1 * kPartTile;
+    if (threadIdx.x == 0) nlong = 0;
+    __syncthreads();
+    const uint32_t tiles = kUngroupSpan / tile;
+    const uint32_t t0 = gi * tiles;
+    const uint32_t t1 = t0 + tiles < ntiles ? t0 + tiles : ntiles;
+    const uint64_t begin = (uint64_t)t0 * tile;
+    const uint64_t end64 = (uint64_t)t1 * tile;
     const uint32_t cnt = (uint32_t)((end64 < m ? end64 : m) - begin);
-    constexpr uint32_t kPer = (1u << kMaxDigitBits) / kUngroupThreads;
-    const uint32_t per = (D + kUngroupThreads - 1) / kUngroupThreads;
-    const uint32_t d0 = threadIdx.x * per;
-    const uint32_t* row = base + (size_t)t0 * D;
-    const uint32_t* nrow = base + (size_t)t1 * D;
-    uint32_t b[kPer], c[kPer];
-    uint32_t mine = 0;
-#pragma unroll
-    for (uint32_t j = 0; j < kPer; ++j) {
-        const uint32_t d = d0 + j;
-        b[j] = c[j] = 0;
-        if (j < per && d < D) {
-            b[j] = row[d];
-            const uint32_t nx =
-                t1 < ntiles ? nrow[d] : (d + 1 < D ? base[d + 1] : (uint32_t)m);
-            c[j] = nx - b[j];
-        }
-        mine += c[j];
-    }
-    uint32_t all;
-    uint32_t run = block_excl_scan<kUngroupThreads>(mine, tmp, &all);
-#pragma unroll
-    for (uint32_t j = 0; j < kPer; ++j) {
-        const uint32_t d = d0 + j;
-        if (j < per && d < D) {
-            rstart[d] = run;
-            rbase[d] = b[j] - run;
-            run += c[j];
-        }
-    }
-    __syncthreads();
-    // all grouped positions of a thread first, then their loads, so that the
-    // loads overlap
-    constexpr int IT = kUngroupSpan / kUngroupThreads;
-    uint32_t o[IT];
-#pragma unroll
-    for (int r = 0; r < IT; ++r) {
-        const uint32_t p = r * kUngroupThreads + threadIdx.x;
-        o[r] = ~0u;
-        if (p < cnt) {
-            uint32_t lo = 0, hi = D;  // the last digit whose run starts at or before p
-            while (hi - lo > 1) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if (rstart[mid] <= p) lo = mid;
-                else hi = mid;
+    const uint32_t lane = lane_id();
+    constexpr uint32_t W = kUngroupThreads / kWave;
+    const uint32_t per = (D + W - 1) / W;  // digits per wave, at most 64
+    const uint32_t d = threadIdx.x / kWave * per + lane;
+    uint32_t b = 0, c = 0;
+    if (lane < per && d < D) {
+        b = base[(size_t)t0 * D + d];
+        const uint32_t nx = t1 < ntiles ? base[(size_t)t1 * D + d]
+                                        : (d + 1 < D ? base[d + 1] : (uint32_t)m);
+        c = nx - b;
+        if (c > kWave) {
+            const uint32_t i = atomicAdd(&nlong, 1u);
+            if (i < kUngroupLong) {
+                lstart[i] = b;
+                llen[i] = c;
             }
-            o[r] = rbase[lo] + p;
         }
     }
-    uint32_t gp[IT], v[IT];
+    // entry o of the grouped order, with its place and count loaded
+    auto put = [&](uint32_t o, uint32_t p, uint32_t v) {
+        if (p < cnt) {
+            sval[p] = (uint8_t)v;
+            if (v == 255u) dst[begin + p] = wide[o];
+        }
+    };
+    constexpr uint32_t U = 8;
+    for (uint32_t i0 = 0; i0 < per; i0 += U) {  // (lanes past the wave's digits hold c = 0)
+        uint32_t o[U], p[U], v[U];
 #pragma unroll
-    for (int r = 0; r < IT; ++r) {
-        gp[r] = o[r] < m ? gpos[o[r]] : 0u;
-        v[r] = o[r] < m ? src[o[r]] : 0u;
-    }
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t st = __builtin_amdgcn_readlane(b, i0 + u);
+            const uint32_t len = __builtin_amdgcn_readlane(c, i0 + u);
+            o[u] = st + lane;
+            const bool in = lane < len && o[u] < m;
+            p[u] = in ? place[o[u]] : ~0u;
+            v[u] = in ? src[o[u]] : 0u;
+        }
 #pragma unroll
-    for (int r = 0; r < IT; ++r) {
-        const uint64_t li = (uint64_t)gp[r] - begin;
-        if (o[r] < m && li < cnt) sval[li] = v[r];
+        for (uint32_t u = 0; u < U; ++u) put(o[u], p[u], v[u]);
     }
     __syncthreads();
-    for (uint32_t p = threadIdx.x; p < cnt; p += kUngroupThreads) dst[begin + p] = sval[p];
+    const uint32_t nl = nlong < kUngroupLong ? nlong : kUngroupLong;
+    for (uint32_t l = 0; l < nl; ++l)
+        for (uint32_t i = kWave + threadIdx.x; i < llen[l]; i += kUngroupThreads) {
+            const uint32_t o = lstart[l] + i;
+            if (o < m) put(o, place[o], src[o]);
+        }
+    __syncthreads();
+    for (uint32_t p = threadIdx.x; p < cnt; p += kUngroupThreads)
+        if (sval[p] != 255u) dst[begin + p] = sval[p];
 }
 
 // A range holding more than kGroupSkew times an even share of the sampled
@@ -523,17 +571,6 @@ __global__ __launch_bounds__(1024) void k_group_sample(const Key* __restrict__ q
     }
 }
 
-size_t ungroup_smem(uint32_t bits) {
-    return 4 * ((size_t)kUngroupSpan + 2 * ((size_t)1 << bits) + 1 + kUngroupThreads / 64 + 1);
-}
-
-template <typename Key>
-size_t partition_smem(uint32_t bits) {
-    const size_t D = 1u << bits;
-    return kPartTile * (sizeof(Key) + 4 + 2) + W_PART * D * 4 + 2 * D * 4 + (W_PART + 1) * 4 +
-           64;
-}
-
 // ------------------------------------------------- from digits' starts ---
 
 // Tier-2 segments, one per tier-1 digit, from the digits' starts (in LDS).
@@ -549,7 +586,7 @@ __device__ void next_segments(const Segs& g, const uint32_t* dbase, uint32_t n, 
             const uint32_t s0 = dbase[a];
             const uint32_t s1 = a + 1 < S ? dbase[a + 1] : n;
             st[j] = s0;
-            nt[j] = (s1 - s0 + kPartTile - 1) / kPartTile;
+            nt[j] = (s1 - s0 + g.tile - 1) / g.tile;
             nc[j] = (nt[j] + g.ch - 1) / g.ch;
             mt += nt[j];
             mc += nc[j];
@@ -676,8 +713,9 @@ V2Plan perm_plan(uint64_t n);
 
 // ------------------------------------------------------------------ plan --
 
-V2Plan plan_v2(uint64_t n, uint64_t V, int key_bits, uint32_t bins_hint) {
+V2Plan plan_v2(uint64_t n, uint64_t V, int key_bits, uint32_t bins_hint, bool any_order) {
     V2Plan p;
+    p.tile = part_tile(key_bits / 8, any_order);
     p.n = n;
     p.V = V;
     uint32_t k;
@@ -709,7 +747,7 @@ V2Plan plan_v2(uint64_t n, uint64_t V, int key_bits, uint32_t bins_hint) {
         p.b1 = bits / 2;
         p.b2 = bits - p.b1;
     }
-    p.ntiles1 = (uint32_t)ceil_div(n, kPartTile);
+    p.ntiles1 = (uint32_t)ceil_div(n, p.tile);
     p.ch1 = (uint32_t)pow2_ceil(ceil_div(p.ntiles1 ? p.ntiles1 : 1, 256));
     p.nchunks1 = (uint32_t)ceil_div(p.ntiles1, p.ch1);
     if (p.tiers == 2) {
@@ -744,7 +782,7 @@ size_t layout_v2(void* ws, const V2Plan& p, size_t key_size, V2Ws* out) {
     const uint32_t D1 = 1u << p.b1, D2 = 1u << p.b2;
     w.m1 = c.take<uint32_t>((size_t)p.ntiles1 * D1);
     w.c1 = c.take<uint32_t>((size_t)p.nchunks1 * D1);
-    w.s1 = one_segment(p.n, p.ntiles1, p.nchunks1, p.ch1);
+    w.s1 = one_segment(p.n, p.ntiles1, p.nchunks1, p.ch1, p.tile);
     if (p.tiers == 2) {
         w.m2 = c.take<uint32_t>((size_t)p.ntiles2_ub * D2);
         w.c2 = c.take<uint32_t>((size_t)p.nchunks2_ub * D2);
@@ -753,6 +791,7 @@ size_t layout_v2(void* ws, const V2Plan& p, size_t key_size, V2Ws* out) {
         w.s2.chunk_prefix = c.take<uint32_t>(D1 + 1);
         w.s2.S = D1;
         w.s2.ch = p.ch2;
+        w.s2.tile = p.tile;
     }
     w.bin_start = c.take<uint32_t>((size_t)p.bins + 1);
     w.heavy_list = c.take<uint32_t>((size_t)p.bins);
@@ -798,20 +837,31 @@ hipError_t colscan(uint32_t* mat, const Segs& g, uint32_t D, uint32_t* csum, uin
     return hipGetLastError();
 }
 
-template <typename Key, bool HAS_IDS, bool STABLE>
-void launch_partition(dim3 grid, size_t smem, hipStream_t s, const Key* src_keys,
-                      const uint32_t* src_ids, Key* dst_keys, uint32_t* dst_ids, const Segs& g,
+template <typename Key, bool ID_DIGIT, bool QUERIES, bool STABLE>
+void launch_hist(dim3 grid, hipStream_t s, const Key* keys, const uint32_t* ids, const Segs& g,
+                 typename KeyTraits<Key>::Params hp, uint32_t shift, uint32_t bits, uint32_t* mat,
+                 uint32_t tiles_ub) {
+    hipLaunchKernelGGL((k_tile_hist<Key, ID_DIGIT, QUERIES, PartGeo<Key, STABLE>::kTile>), grid,
+                       dim3(kHistThreads), 4u << bits, s, keys, g, hp, shift, bits, mat, tiles_ub,
+                       ids);
+}
+
+template <typename Key, bool HAS_IDS, bool STABLE, bool ID_DIGIT = false, bool QUERIES = false>
+void launch_partition(dim3 grid, hipStream_t s, const Key* src_keys, const uint32_t* src_ids,
+                      Key* dst_keys, uint32_t* dst_ids, const Segs& g,
                       typename KeyTraits<Key>::Params hp, uint32_t shift, uint32_t bits,
                       const uint32_t* mat, uint32_t tiles_ub) {
-    hipLaunchKernelGGL((k_tile_partition<Key, HAS_IDS, STABLE>), grid, dim3(kPartThreads), smem,
-                       s, src_keys, src_ids, dst_keys, dst_ids, g, hp, shift, bits, mat,
-                       tiles_ub);
+    hipLaunchKernelGGL((k_tile_partition<Key, HAS_IDS, STABLE, ID_DIGIT, QUERIES>), grid,
+                       dim3(PartGeo<Key, STABLE>::kThreads),
+                       (PartLds<Key, HAS_IDS, STABLE>::bytes(bits)), s,
+                       src_keys, src_ids, dst_keys, dst_ids, g, hp, shift, bits, mat, tiles_ub);
 }
 
 // One stable (or any-order) partition pass over the tiles of segments g.
 // id_digit (32-bit entries with ids only): the digit comes from the id.
 // tier: 1 or 2 for the build's passes, 3 for grouping the queries of a probe
-// (profiled under its own names); dst_ids may be null without src_ids.
+// (profiled under its own names), where dst_ids may be null and receives the
+// places that k_ungroup_by_pos reads.
 template <typename Key>
 hipError_t partition_pass(const Key* src_keys, const uint32_t* src_ids, Key* dst_keys,
                           uint32_t* dst_ids, const Segs& g, typename KeyTraits<Key>::Params hp,
@@ -821,45 +871,28 @@ hipError_t partition_pass(const Key* src_keys, const uint32_t* src_ids, Key* dst
     const uint32_t D = 1u << bits;
     const uint32_t grid = (uint32_t)(8 * ceil_div(tiles_ub, 8));
     if (id_digit && (sizeof(Key) != 4 || !src_ids || stable)) return hipErrorInvalidValue;
+    if (tier == 3 && (src_ids || stable)) return hipErrorInvalidValue;
     if (bits > kMaxDigitBits) return hipErrorInvalidValue;  // the kernels hold at most 2048 digits
     {
         HG_PROF(tier == 1 ? "v2_tile_hist_t1" : tier == 2 ? "v2_tile_hist_t2" : "probe_group_hist", s);
-        if (id_digit)
-            hipLaunchKernelGGL((k_tile_hist<Key, true>), dim3(grid), dim3(kPartThreads), D * 4, s,
-                               src_keys, g, hp, shift, bits, mat, tiles_ub, src_ids);
-        else if (tier == 3)
-            hipLaunchKernelGGL((k_tile_hist<Key, false, true>), dim3(grid), dim3(kPartThreads),
-                               D * 4, s, src_keys, g, hp, shift, bits, mat, tiles_ub, nullptr);
-        else
-            hipLaunchKernelGGL((k_tile_hist<Key, false>), dim3(grid), dim3(kPartThreads), D * 4, s,
-                               src_keys, g, hp, shift, bits, mat, tiles_ub, nullptr);
+        const auto launch = id_digit    ? launch_hist<Key, true, false, false>
+                            : tier == 3 ? launch_hist<Key, false, true, false>
+                            : stable    ? launch_hist<Key, false, false, true>
+                                        : launch_hist<Key, false, false, false>;
+        launch(dim3(grid), s, src_keys, src_ids, g, hp, shift, bits, mat, tiles_ub);
     }
     HG_TRY(hipGetLastError());
     HG_TRY(colscan(mat, g, D, csum, nchunks_ub, s, tier == 3, out));
-    const size_t smem = partition_smem<Key>(bits);
     {
         HG_PROF(tier == 1 ? "v2_partition_t1" : tier == 2 ? "v2_partition_t2" : "probe_group", s);
-        const dim3 gr(grid);
-        if (id_digit)
-            hipLaunchKernelGGL((k_tile_partition<Key, true, false, true>), gr, dim3(kPartThreads),
-                               smem, s, src_keys, src_ids, dst_keys, dst_ids, g, hp, shift, bits,
-                               (const uint32_t*)mat, tiles_ub);
-        else if (tier == 3 && !src_ids && !stable)
-            hipLaunchKernelGGL((k_tile_partition<Key, false, false, false, true>), gr,
-                               dim3(kPartThreads), smem, s, src_keys, src_ids, dst_keys, dst_ids,
-                               g, hp, shift, bits, (const uint32_t*)mat, tiles_ub);
-        else if (src_ids && stable)
-            launch_partition<Key, true, true>(gr, smem, s, src_keys, src_ids, dst_keys, dst_ids,
-                                              g, hp, shift, bits, mat, tiles_ub);
-        else if (src_ids)
-            launch_partition<Key, true, false>(gr, smem, s, src_keys, src_ids, dst_keys, dst_ids,
-                                               g, hp, shift, bits, mat, tiles_ub);
-        else if (stable)
-            launch_partition<Key, false, true>(gr, smem, s, src_keys, src_ids, dst_keys, dst_ids,
-                                               g, hp, shift, bits, mat, tiles_ub);
-        else
-            launch_partition<Key, false, false>(gr, smem, s, src_keys, src_ids, dst_keys,
-                                                dst_ids, g, hp, shift, bits, mat, tiles_ub);
+        const auto launch = id_digit        ? launch_partition<Key, true, false, true>
+                            : tier == 3     ? launch_partition<Key, false, false, false, true>
+                            : src_ids       ? (stable ? launch_partition<Key, true, true>
+                                                      : launch_partition<Key, true, false>)
+                            : stable        ? launch_partition<Key, false, true>
+                                            : launch_partition<Key, false, false>;
+        launch(dim3(grid), s, src_keys, src_ids, dst_keys, dst_ids, g, hp, shift, bits, mat,
+               tiles_ub);
     }
     return hipGetLastError();
 }
@@ -894,8 +927,6 @@ hipError_t set_smem_limits() {
             });
         }
         HG_TRY(le);
-        HG_TRY(hipFuncSetAttribute((const void*)k_ungroup_by_pos,
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, lim));
         return hipSuccess;
     });
 }
@@ -910,7 +941,10 @@ size_t build_ws_bytes(int variant, uint64_t n, uint64_t V, int key_bits, uint32_
         c.take<char>(scan_ws_bytes(V));
         return c.off + 256;
     }
-    return layout_v2(nullptr, plan_v2(n, V, key_bits, bins_hint), ks, nullptr);
+    // (a table's workspace serves builds of either order)
+    const size_t st = layout_v2(nullptr, plan_v2(n, V, key_bits, bins_hint, false), ks, nullptr);
+    const size_t any = layout_v2(nullptr, plan_v2(n, V, key_bits, bins_hint, true), ks, nullptr);
+    return st > any ? st : any;
 }
 
 template <typename Key>
@@ -925,7 +959,7 @@ hipError_t run_build_v2(const Key* keys, uint64_t n, uint64_t V, uint64_t seed, 
         if (ix.head) HG_TRY(fill_u32((uint32_t*)ix.head, ix.fmt.bytes / 4 * V, 0u, s));
         return fill_u32(offsets, V + 1, 0u, s);
     }
-    const V2Plan p = plan_v2(n, V, sizeof(Key) * 8, bins_hint);
+    const V2Plan p = plan_v2(n, V, sizeof(Key) * 8, bins_hint, !stable);
     ix.k = p.k;
     ix.bins = p.bins;
     ix.fmt = head_fmt(n, V, sizeof(Key) * 8);
@@ -1009,7 +1043,7 @@ namespace {
 
 V2Plan perm_plan(uint64_t n) {
     // the ids are the "buckets": V = n, bins of 2^12 ids
-    return plan_v2(n, n, 32, (uint32_t)ceil_div(n, 1ull << kMaxLocalBits));
+    return plan_v2(n, n, 32, (uint32_t)ceil_div(n, 1ull << kMaxLocalBits), true);
 }
 
 size_t perm_layout(void* ws, const V2Plan& p, V2Ws* w, uint32_t** xv, uint32_t** xi) {
@@ -1067,10 +1101,10 @@ hipError_t scatter_perm(const uint32_t* ids, const uint32_t* vals, uint64_t n, u
 
 // --------------------------------------------- grouped Probe-Standard ---
 // The queries are first partitioned into up to 2^kGroupBits ranges of
-// buckets with their input positions (one tile-histogram, column-scan and
+// buckets with their input places (one tile-histogram, column-scan and
 // partition pass, as in the build), probed in that order with the tiles
 // dealt out per XCD -- each XCD then reads one window of the index at a time
-// (8 MiB at 2^28 buckets), which its L2 holds, instead of random lines of
+// (2 MiB at 2^28 buckets of 4-byte entries), which its L2 holds, instead of random lines of
 // the whole index -- and the counts are put back in input order by
 // k_ungroup_by_pos.
 
@@ -1079,15 +1113,16 @@ namespace {
 constexpr uint32_t kGroupBits = 9;
 
 struct GroupPlan {
-    uint32_t bits, shift, ntiles, ch, nchunks;
+    uint32_t bits, shift, tile, ntiles, ch, nchunks;
 };
 
-GroupPlan group_plan(uint64_t m, uint64_t V) {
+GroupPlan group_plan(uint64_t m, uint64_t V, size_t key_size) {
     GroupPlan p;
+    p.tile = part_tile(key_size, true);
     const uint32_t kv = log2_ceil(V);
     p.bits = kv < kGroupBits ? (kv ? kv : 1u) : kGroupBits;  // at least two ranges
     p.shift = kv > p.bits ? kv - p.bits : 0u;
-    p.ntiles = (uint32_t)ceil_div(m, kPartTile);
+    p.ntiles = (uint32_t)ceil_div(m, p.tile);
     p.ch = (uint32_t)pow2_ceil(ceil_div(p.ntiles ? p.ntiles : 1, 256));
     p.nchunks = (uint32_t)ceil_div(p.ntiles, p.ch);
     return p;
@@ -1095,8 +1130,9 @@ GroupPlan group_plan(uint64_t m, uint64_t V) {
 
 struct GroupWs {
     void* gq;        // the queries in grouped order
-    uint32_t* gpos;  // their input positions
-    uint32_t* gc;    // their counts in grouped order
+    uint16_t* place; // their places among kUngroupSpan queries of the input
+    uint8_t* gc;     // their counts in grouped order; 255: see wide
+    uint32_t* wide;  // the counts from 255 on
     uint32_t *mat, *csum, *ctr;
     Segs seg;
 };
@@ -1106,8 +1142,9 @@ size_t layout_group(void* ws, const GroupPlan& p, uint64_t m, size_t key_size, G
     GroupWs w{};
     const uint32_t D = 1u << p.bits;
     w.gq = c.take<char>(m * key_size);
-    w.gpos = c.take<uint32_t>(m);
-    w.gc = c.take<uint32_t>(m);
+    w.place = c.take<uint16_t>(m);
+    w.gc = c.take<uint8_t>(m);
+    w.wide = c.take<uint32_t>(m);
     w.mat = c.take<uint32_t>((size_t)p.ntiles * D);
     w.csum = c.take<uint32_t>((size_t)p.nchunks * D);
     w.ctr = c.take<uint32_t>(kCtrWords);
@@ -1116,6 +1153,7 @@ size_t layout_group(void* ws, const GroupPlan& p, uint64_t m, size_t key_size, G
     w.seg.chunk_prefix = c.take<uint32_t>(2);
     w.seg.S = 1;
     w.seg.ch = p.ch;
+    w.seg.tile = p.tile;
     if (out) *out = w;
     return c.off + 256;
 }
@@ -1123,7 +1161,7 @@ size_t layout_group(void* ws, const GroupPlan& p, uint64_t m, size_t key_size, G
 }  // namespace
 
 size_t probe_grouped_ws_bytes(uint64_t m, uint64_t V, size_t key_size) {
-    return layout_group(nullptr, group_plan(m, V), m, key_size, nullptr);
+    return layout_group(nullptr, group_plan(m, V, key_size), m, key_size, nullptr);
 }
 
 template <typename Key>
@@ -1131,7 +1169,7 @@ hipError_t run_probe_grouped(const TableDev& t, const Key* queries, uint64_t m, 
                              unsigned long long* d_total, void* ws, hipStream_t s, bool decide) {
     if (m == 0) return run_probe_counts<Key>(t, queries, m, counts, d_total, s);
     HG_TRY(set_smem_limits<Key>());
-    const GroupPlan p = group_plan(m, t.V);
+    const GroupPlan p = group_plan(m, t.V, sizeof(Key));
     GroupWs w;
     layout_group(ws, p, m, sizeof(Key), &w);
     const auto hp = KeyTraits<Key>::make(t.V, t.seed);
@@ -1141,24 +1179,24 @@ hipError_t run_probe_grouped(const TableDev& t, const Key* queries, uint64_t m, 
                            p.shift, p.bits, w.seg, p.ntiles, p.nchunks, w.ctr);
         HG_TRY(hipGetLastError());
     } else {
-        w.seg = one_segment(m, p.ntiles, p.nchunks, p.ch);
+        w.seg = one_segment(m, p.ntiles, p.nchunks, p.ch, p.tile);
     }
     Key* gq = (Key*)w.gq;
-    // positions only when the counts go back to input order
-    HG_TRY(partition_pass<Key>(queries, nullptr, gq, counts ? w.gpos : nullptr, w.seg, hp,
+    // places only when the counts go back to input order
+    HG_TRY(partition_pass<Key>(queries, nullptr, gq, counts ? (uint32_t*)w.place : nullptr, w.seg, hp,
                                p.shift, p.bits, w.mat, w.csum, p.ntiles, p.nchunks, 3, false, s));
     // one probe launch: the grouped queries, or (gate 0) the queries in input
     // order straight into counts
-    HG_TRY(run_probe_counts<Key>(t, gq, m, counts ? w.gc : nullptr, d_total, s, nullptr, true,
-                                 gate, queries, counts));
+    HG_TRY(run_probe_counts<Key>(t, gq, m, counts ? w.wide : nullptr, d_total, s, nullptr, true,
+                                 gate, queries, counts, w.gc));
     if (!counts) return hipSuccess;
     {
         HG_PROF("probe_ungroup", s);
-        const uint32_t groups = (uint32_t)ceil_div(p.ntiles, kUngroupTiles);
+        const uint32_t groups = (uint32_t)ceil_div(p.ntiles, kUngroupSpan / p.tile);
         const uint32_t grid = (uint32_t)(8 * ceil_div(groups, 8));
-        hipLaunchKernelGGL(k_ungroup_by_pos, dim3(grid), dim3(kUngroupThreads),
-                           ungroup_smem(p.bits), s, m, p.ntiles, p.bits, (const uint32_t*)w.mat,
-                           groups, (const uint32_t*)w.gpos, (const uint32_t*)w.gc, counts, gate);
+        hipLaunchKernelGGL(k_ungroup_by_pos, dim3(grid), dim3(kUngroupThreads), 0, s, m, p.ntiles,
+                           p.tile, p.bits, (const uint32_t*)w.mat, groups, (const uint16_t*)w.place, (const uint8_t*)w.gc,
+                           (const uint32_t*)w.wide, counts, gate);
     }
     return hipGetLastError();
 }
