@@ -138,8 +138,12 @@ uint32_t hg_version(void);
  * caching allocator do this).  alloc_fn returns NULL when it cannot satisfy
  * the request (the call then fails with HG_ERR_OOM) and must return blocks
  * aligned to 256 bytes (a misaligned block is freed again and the call fails
- * with HG_ERR_INVALID_ARG).  Both functions NULL restore the default,
- * hipMallocAsync / hipFreeAsync; exactly one NULL is HG_ERR_INVALID_ARG.
+ * with HG_ERR_INVALID_ARG).  Both functions NULL restore the default, a
+ * stream-ordered pool of the library's own per device, which keeps at most
+ * 1/64 of the device's memory mapped while any table or collection lives and
+ * is emptied when the last one is freed or an allocation of the library runs
+ * out of memory (hipMallocAsync / hipFreeAsync without such objects and under
+ * stream capture); exactly one NULL is HG_ERR_INVALID_ARG.
  * The setting is process-wide and takes effect for calls that start after
  * it; a block already handed out is returned to the functions that gave it.
  * The memory that tables, collections, batch plans and servers keep

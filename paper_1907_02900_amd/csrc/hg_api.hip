@@ -3,6 +3,7 @@
 // Host-side validation, table objects, workspace handling and dispatch to the
 // kernels.  Nothing here computes on the CPU: every step of the path runs in
 // the HIP kernels of hg_build.hip, hg_scan.hip and hg_probe.hip.
+#include <atomic>
 #include <map>
 #include <mutex>
 #include <new>
@@ -19,12 +20,98 @@ std::mutex g_hook_mu;
 WsHook g_hook;  // guarded by g_hook_mu
 }  // namespace
 
+// ---- workspace pools -------------------------------------------------------
+
+namespace {
+constexpr int kPoolDevices = 64;
+std::mutex g_pool_mu;
+hipMemPool_t g_pool[kPoolDevices] = {};     // guarded by g_pool_mu; kept until the process ends
+bool g_pool_failed[kPoolDevices] = {};      // pools this device does not give
+std::atomic<int64_t> g_pool_users{0};
+
+hipMemPool_t pool_of(int dev) {
+    if (dev < 0 || dev >= kPoolDevices) return nullptr;
+    std::lock_guard<std::mutex> lock(g_pool_mu);
+    if (g_pool[dev] || g_pool_failed[dev]) return g_pool[dev];
+    hipMemPoolProps props{};
+    props.allocType = hipMemAllocationTypePinned;
+    props.location.type = hipMemLocationTypeDevice;
+    props.location.id = dev;
+    hipMemPool_t pool = nullptr;
+    size_t total = 0;
+    hipError_t e = hipDeviceTotalMem(&total, dev);
+    if (e == hipSuccess) e = hipMemPoolCreate(&pool, &props);
+    if (e == hipSuccess) {
+        uint64_t keep = total / 64;
+        e = hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep);
+        if (e != hipSuccess) (void)hipMemPoolDestroy(pool);
+    }
+    if (e == hipSuccess) {
+        g_pool[dev] = pool;
+    } else {
+        (void)hipGetLastError();
+        g_pool_failed[dev] = true;
+    }
+    return g_pool[dev];
+}
+
+void empty_pools() {
+    std::lock_guard<std::mutex> lock(g_pool_mu);
+    for (hipMemPool_t p : g_pool)
+        if (p && hipMemPoolTrimTo(p, 0) != hipSuccess) (void)hipGetLastError();
+}
+
+// f(): an allocation; once more with the pools emptied when memory is out
+template <typename F>
+hipError_t or_empty_pools(F&& f) {
+    hipError_t e = f();
+    if (e != hipErrorOutOfMemory) return e;
+    (void)hipGetLastError();
+    empty_pools();
+    return f();
+}
+
+// The pool for work on s; null: none.
+hipMemPool_t pool_for(hipStream_t s) {
+    if (g_pool_users.load(std::memory_order_relaxed) == 0) return nullptr;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    int dev = -1;
+    const bool named = s && s != hipStreamLegacy && s != hipStreamPerThread;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess ||
+        (named ? hipStreamGetDevice(s, &dev) : hipGetDevice(&dev)) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    return st == hipStreamCaptureStatusNone ? pool_of(dev) : nullptr;
+}
+}  // namespace
+
+hipError_t hg::ws_alloc(void** p, size_t bytes, hipStream_t s) {
+    const hipMemPool_t pool = pool_for(s);
+    if (!pool) return hipMallocAsync(p, bytes, s);
+    return or_empty_pools([&] { return hipMallocFromPoolAsync(p, bytes, pool, s); });
+}
+
+hipError_t hg::dev_malloc(void** p, size_t bytes) {
+    return or_empty_pools([&] { return hipMalloc(p, bytes); });
+}
+
+hipError_t hg::dev_malloc_async(void** p, size_t bytes, hipStream_t s) {
+    return or_empty_pools([&] { return hipMallocAsync(p, bytes, s); });
+}
+
+hg::PoolUser::PoolUser() { g_pool_users.fetch_add(1, std::memory_order_relaxed); }
+hg::PoolUser::~PoolUser() {
+    if (g_pool_users.fetch_sub(1, std::memory_order_relaxed) == 1) empty_pools();
+}
+
 WsHook hg::ws_hook() {
     std::lock_guard<std::mutex> lock(g_hook_mu);
     return g_hook;
 }
 
 struct hg_table {
+    PoolUser pool_user;
     int key_bits = 32;
     int variant = 0;
     uint64_t n = 0, V = 0, seed = 0;
@@ -94,10 +181,10 @@ hg_status ensure_index(hg_table* t) {
     const size_t nc = t->n_cap ? t->n_cap : 1;
     const size_t ks = key_size(t->key_bits);
     const size_t hb = t->V_cap * head_bytes_max(t->key_bits);
-    HG_CALL(hipMalloc(&t->head, hb));
-    HG_CALL(hipMalloc(&t->runs.run_key, nc * ks));
-    HG_CALL(hipMalloc((void**)&t->runs.run_end, nc * 4));
-    HG_CALL(hipMalloc((void**)&t->runs.kperm, nc * 4));
+    HG_CALL(dev_malloc((void**)&t->head, hb));
+    HG_CALL(dev_malloc((void**)&t->runs.run_key, nc * ks));
+    HG_CALL(dev_malloc((void**)&t->runs.run_end, nc * 4));
+    HG_CALL(dev_malloc((void**)&t->runs.kperm, nc * 4));
     t->bytes += hb + nc * (ks + 8);
     return HG_OK;
 }
@@ -163,15 +250,15 @@ hg_status alloc_table(uint64_t n_cap, uint64_t V_cap, int kb, bool with_ws, hg_t
     t->key_bits = kb;
     t->n_cap = n_cap;
     t->V_cap = V_cap;
-    hipError_t e = hipMalloc((void**)&t->offsets, (V_cap + 1) * sizeof(uint32_t));
-    if (e == hipSuccess) e = hipMalloc((void**)&t->ids, (n_cap ? n_cap : 1) * sizeof(uint32_t));
-    if (e == hipSuccess) e = hipMalloc(&t->keys, (n_cap ? n_cap : 1) * key_size(kb));
+    hipError_t e = dev_malloc((void**)&t->offsets, (V_cap + 1) * sizeof(uint32_t));
+    if (e == hipSuccess) e = dev_malloc((void**)&t->ids, (n_cap ? n_cap : 1) * sizeof(uint32_t));
+    if (e == hipSuccess) e = dev_malloc((void**)&t->keys, (n_cap ? n_cap : 1) * key_size(kb));
     t->bytes = (V_cap + 1) * 4 + (n_cap ? n_cap : 1) * (4 + key_size(kb));
     if (e == hipSuccess && with_ws) {
         size_t w1 = build_ws_bytes(1, n_cap, V_cap, kb, 0);
         size_t w2 = build_ws_bytes(2, n_cap, V_cap, kb, 0);
         t->ws_bytes = w1 > w2 ? w1 : w2;
-        e = hipMalloc(&t->ws, t->ws_bytes);
+        e = dev_malloc((void**)&t->ws, t->ws_bytes);
         t->bytes += t->ws_bytes;
     }
     if (e != hipSuccess) {
@@ -593,9 +680,9 @@ hg_status hg_table_erase(hg_table* t, const void* d_keys, uint64_t m, uint64_t* 
     if (!t->has_head) return HG_ERR_INVALID_ARG;  // needs a V2 table with the probe index
     if (device_ready() != HG_OK) return HG_ERR_DEVICE;
     if (!t->len) {
-        HG_CALL(hipMalloc((void**)&t->len, t->V_cap * 4));
-        HG_CALL(hipMalloc((void**)&t->dead, t->n_cap ? t->n_cap : 1));
-        HG_CALL(hipMalloc((void**)&t->touched, t->V_cap));
+        HG_CALL(dev_malloc((void**)&t->len, t->V_cap * 4));
+        HG_CALL(dev_malloc((void**)&t->dead, t->n_cap ? t->n_cap : 1));
+        HG_CALL(dev_malloc((void**)&t->touched, t->V_cap));
         t->bytes += t->V_cap * 5 + (t->n_cap ? t->n_cap : 1);
         HG_CALL(hipMemsetAsync(t->dead, 0, t->n_cap ? t->n_cap : 1, stream));
         HG_CALL(hipMemsetAsync(t->touched, 0, t->V_cap, stream));
@@ -630,6 +717,7 @@ hg_status hg_table_lengths(const hg_table* t, const uint32_t** d_lengths, uint64
 }
 
 struct hg_collection {
+    PoolUser pool_user;
     int key_bits = 32;
     uint64_t seed = 0;
     int32_t shift = 0;
@@ -656,8 +744,8 @@ void coll_release(hg_collection* c) {
 hg_status coll_build_into(hg_collection* c, const void* d_keys, const uint32_t* d_set_offsets,
                           hipStream_t stream) {
     const uint32_t S = c->S;
-    HG_CALL(hipMalloc((void**)&c->set_off, ((uint64_t)S + 1) * 4));
-    HG_CALL(hipMalloc((void**)&c->bb, ((uint64_t)S + 2) * 8));
+    HG_CALL(dev_malloc((void**)&c->set_off, ((uint64_t)S + 1) * 4));
+    HG_CALL(dev_malloc((void**)&c->bb, ((uint64_t)S + 2) * 8));
     HG_CALL(hipMemcpyAsync(c->set_off, d_set_offsets, ((uint64_t)S + 1) * 4,
                            hipMemcpyDeviceToDevice, stream));
     Workspace pws(stream);
@@ -669,9 +757,9 @@ hg_status coll_build_into(hg_collection* c, const void* d_keys, const uint32_t* 
     c->buckets = plan.buckets;
     c->heavy_keys = plan.big_keys;
     const size_t ks = key_size(c->key_bits);
-    HG_CALL(hipMalloc((void**)&c->offsets, (plan.buckets + 1) * 4));
-    HG_CALL(hipMalloc((void**)&c->ids, (plan.n ? plan.n : 1) * 4));
-    HG_CALL(hipMalloc(&c->keys, (plan.n ? plan.n : 1) * ks));
+    HG_CALL(dev_malloc((void**)&c->offsets, (plan.buckets + 1) * 4));
+    HG_CALL(dev_malloc((void**)&c->ids, (plan.n ? plan.n : 1) * 4));
+    HG_CALL(dev_malloc((void**)&c->keys, (plan.n ? plan.n : 1) * ks));
     c->bytes = ((uint64_t)S + 1) * 4 + ((uint64_t)S + 2) * 8 + (plan.buckets + 1) * 4 +
                plan.n * (4 + ks);
     Workspace bws(stream);
@@ -813,14 +901,17 @@ hg_status hg_probe_ordered(const hg_table* t, const void* d_queries, uint64_t m,
     const size_t kbytes = t->key_bits / 8;
     const size_t tot_bytes = h_total ? align_up(probe_total_slots(m) * 8, 256) : 0;
     Workspace ws(stream);
+    // (counts in input order need none)
     hipError_t ae =
-        ws.get(tot_bytes + (grouped ? probe_grouped_ws_bytes(m, t->V, kbytes) : 0) + 256);
+        h_total || grouped
+            ? ws.get(tot_bytes + (grouped ? probe_grouped_ws_bytes(m, t->V, kbytes) : 0) + 256)
+            : hipSuccess;
     if (ae == hipErrorOutOfMemory && grouped && order == HG_PROBE_AUTO) {
         // the grouping's workspace is out of reach: probe in input order
         (void)hipGetLastError();  // the failed allocation's error is not the probe's
         ws.p = nullptr;
         grouped = false;
-        ae = ws.get(tot_bytes + 256);
+        ae = h_total ? ws.get(tot_bytes + 256) : hipSuccess;
     }
     if (ae != hipSuccess) return from_hip(ae);
     unsigned long long* d_total = h_total ? (unsigned long long*)ws.p : nullptr;

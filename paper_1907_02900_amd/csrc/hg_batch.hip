@@ -532,7 +532,7 @@ struct BatchPlan : BatchPlanBase {
     // owned device memory, synchronous upload (graph plans)
     hipError_t upload() {
         void* base = nullptr;
-        HG_TRY(hipMalloc(&base, carve(nullptr)));
+        HG_TRY(dev_malloc((void**)&base, carve(nullptr)));
         carve(base);
         owns_block = true;
         std::vector<char> img(host_image_bytes());
@@ -1360,10 +1360,10 @@ struct Server {
         if (r0.kind == 0)
             for (size_t i = 0; i < gtab.size() && e == hipSuccess; ++i) {
                 STable& t = *gtab[i];
-                e = hipMallocAsync(&t.block, tbytes[i], s);
+                e = dev_malloc_async((void**)&t.block, tbytes[i], s);
                 if (e == hipSuccess) carve_table(t, t.block);
             }
-        if (e == hipSuccess && ws) e = hipMallocAsync(&L.transient, ws, s);
+        if (e == hipSuccess && ws) e = dev_malloc_async((void**)&L.transient, ws, s);
         for (size_t i = 0; i < waits.size() && e == hipSuccess; ++i)
             e = hipStreamWaitEvent(s, waits[i], 0);
         if (e == hipSuccess) {

@@ -57,13 +57,34 @@ struct ProfRange {
 #define HG_PROF(name, s) ::hg::ProfRange HG_PROF_CAT(hg_prof_, __LINE__)(name, s)
 
 // The allocator that temporary workspace comes from (hg_set_allocator); both
-// functions NULL means hipMallocAsync / hipFreeAsync.
+// functions NULL means ws_alloc / hipFreeAsync.
 struct WsHook {
     void* (*alloc)(size_t bytes, hipStream_t s, void* ctx) = nullptr;
     void (*free)(void* p, hipStream_t s, void* ctx) = nullptr;
     void* ctx = nullptr;
 };
 WsHook ws_hook();  // the hook installed now (hg_api.hip)
+
+// Temporary memory in stream order, given back with hipFreeAsync.  The device's
+// own pool unmaps what is free at every synchronisation and maps it anew at the
+// next call: for 2^27 64-bit queries 3 to 50 ms a call, against 3 ms of kernels.
+// While tables or collections live, blocks therefore come from a pool of the
+// library's that keeps up to 1/64 of the device's memory (4.5 GiB of 288; 2^28
+// grouped queries take 3.1), and that is emptied when the last of them is freed
+// and when an allocation of the library fails.  Under stream capture, and for a
+// stream whose device is unknown, plain hipMallocAsync.
+hipError_t ws_alloc(void** p, size_t bytes, hipStream_t s);
+// hipMalloc and hipMallocAsync that empty the pools and try again when memory is
+// out.
+hipError_t dev_malloc(void** p, size_t bytes);
+hipError_t dev_malloc_async(void** p, size_t bytes, hipStream_t s);
+// Held by every table and collection.
+struct PoolUser {
+    PoolUser();
+    ~PoolUser();
+    PoolUser(const PoolUser&) = delete;
+    PoolUser& operator=(const PoolUser&) = delete;
+};
 
 // Temporary device memory of one call, released at scope exit in stream
 // order: work already enqueued on s may still be using it.  The block goes
@@ -80,7 +101,7 @@ struct Workspace {
         if (p) return hipErrorInvalidValue;  // one block per object
         if (bytes == 0) bytes = 256;
         h = ws_hook();
-        if (!h.alloc) return hipMallocAsync(&p, bytes, s);
+        if (!h.alloc) return ws_alloc(&p, bytes, s);
         p = h.alloc(bytes, s, h.ctx);
         if (!p) return hipErrorOutOfMemory;
         if ((uintptr_t)p % 256) {  // the carvers and vector loads assume 256-byte blocks
