@@ -894,9 +894,15 @@ hg_status hg_probe_ordered(const hg_table* t, const void* d_queries, uint64_t m,
     if (device_ready() != HG_OK) return HG_ERR_DEVICE;
     TableDev d = dev_view(t);
     bool grouped = order == HG_PROBE_GROUPED || order == HG_PROBE_GROUPED_UNLESS_SKEWED;
-    if (order == HG_PROBE_AUTO)  // where grouping measured faster on MI355X
-        grouped = d.head != nullptr && m >= t->V / 2 &&
-                  t->V >= (d_counts ? (1ull << 27) : (1ull << 26));
+    // Where grouping measured faster, at loads 1 and 4 and both key widths: an
+    // index beyond the L2s (2^22 buckets) and enough queries for three passes
+    // over them to cost less than their random lines.  2^25 queries, input order
+    // against grouped: 702 : 537 us at 2^26 buckets (64-bit keys 1062 : 955), 689 :
+    // 503 at 2^25 (945 : 851), 806 : 666 at 2^23 with load 4; but 403 : 433 for 2^24
+    // queries at 2^25 buckets with load 4, and at 2^20 buckets input order wins.
+    if (order == HG_PROBE_AUTO)
+        grouped = d.head != nullptr && m >= (1ull << 25) && m >= t->V / 2 &&
+                  t->V >= (1ull << 22);
     grouped = grouped && m > 0;
     const size_t kbytes = t->key_bits / 8;
     const size_t tot_bytes = h_total ? align_up(probe_total_slots(m) * 8, 256) : 0;

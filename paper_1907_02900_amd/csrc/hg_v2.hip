@@ -517,13 +517,17 @@ __global__ __launch_bounds__(kUngroupThreads, 8) void k_ungroup_by_pos(
 constexpr uint32_t kGroupSkew = 8;
 
 // Whether grouping pays for these queries, from a sample: up to kGroupSample
-// queries spread evenly over the input are hashed into the ranges, and when
+// queries, 16 neighbours (a line of them, one page) at each of 1024 places spread
+// evenly over the input, are hashed into the ranges, and when
 // one range holds more than kGroupSkew times an even share of them the probe
 // keeps input order (skewed queries read few index lines, which stay cached
 // anyway).  Writes the one segment of the grouping passes -- with no tiles
 // at all for input order, so that every grouping kernel returns at once --
-// and gate[0] = 1 (grouped) or 0 (input order).  One workgroup.
+// and gate[0] = 1 (grouped) or 0 (input order).  One workgroup, bound by the
+// latency of its loads: 35 us at 2^28 queries with each sample on a page of its
+// own, now below 11.
 constexpr uint32_t kGroupSample = 1u << 14;  // 16 per thread, loaded together
+constexpr uint32_t kSampleRun = 16;
 
 template <typename Key>
 __global__ __launch_bounds__(1024) void k_group_sample(const Key* __restrict__ q, uint64_t m,
@@ -538,11 +542,12 @@ __global__ __launch_bounds__(1024) void k_group_sample(const Key* __restrict__ q
     __syncthreads();
     const uint32_t S = m < kGroupSample ? (uint32_t)m : kGroupSample;
     constexpr int IT = kGroupSample / 1024;
+    const uint64_t step = m > kGroupSample ? m / (kGroupSample / kSampleRun) : kSampleRun;
     Key k[IT];
 #pragma unroll
     for (int r = 0; r < IT; ++r) {
         const uint32_t i = r * 1024 + threadIdx.x;
-        k[r] = i < S ? q[(uint64_t)i * m / S] : (Key)0;
+        k[r] = i < S ? q[(uint64_t)(i / kSampleRun) * step + i % kSampleRun] : (Key)0;
     }
 #pragma unroll
     for (int r = 0; r < IT; ++r) {
