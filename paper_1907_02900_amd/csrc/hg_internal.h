@@ -70,7 +70,7 @@ WsHook ws_hook();  // the hook installed now (hg_api.hip)
 // next call: for 2^27 64-bit queries 3 to 50 ms a call, against 3 ms of kernels.
 // While tables or collections live, blocks therefore come from a pool of the
 // library's that keeps up to 1/64 of the device's memory (4.5 GiB of 288; 2^28
-// grouped queries take 3.1), and that is emptied when the last of them is freed
+// grouped queries take 2.8), and that is emptied when the last of them is freed
 // and when an allocation of the library fails.  Under stream capture, and for a
 // stream whose device is unknown, plain hipMallocAsync.
 hipError_t ws_alloc(void** p, size_t bytes, hipStream_t s);
@@ -137,7 +137,7 @@ struct Carver {
 // ---- partition geometry shared by the V2 kernels --------------------------
 // Entries per partition tile.  Long runs per digit save partial lines beyond the
 // L2 and large tiles cost LDS, that is waves in flight: 8192 32-bit keys where
-// any order needs one set of counters (2^28 keys, first pass: 688 us, in tiles of
+// any order needs one set of counters (2^28 keys, first pass: 639 us, in tiles of
 // 4096 1150); 4096 64-bit keys, or 32-bit keys ranked stably with counters per
 // wave (2^26 keys, first pass: 216 us, in tiles of 8192 255 to 342).
 constexpr uint32_t part_tile(size_t key_size, bool any_order) {
