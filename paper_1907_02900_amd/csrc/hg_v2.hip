@@ -90,6 +90,10 @@ __device__ __forceinline__ bool locate_tile(const Segs& g, uint32_t t, uint32_t&
 // instead of the bucket of its key (the scatter by a permutation below).
 // QUERIES: the same code, instantiated apart for grouping a probe's queries
 // so that kernel traces tell it from the build's passes (also below).
+// HBM-bound on uniform keys (2^28: 226 us, 4.8 TB/s read).  A hot digit would
+// serialise a wave's lanes on one counter, so each digit has four, side by side,
+// of which a lane takes lane % 4: 2^26 Zipf(1.2) keys 147 -> 65 us a pass, the
+// uniform ones unchanged.
 constexpr int kHistThreads = 512;
 
 template <typename Key, bool ID_DIGIT, bool QUERIES, uint32_t TILE>
@@ -97,12 +101,13 @@ __global__ __launch_bounds__(kHistThreads) void k_tile_hist(
     const Key* __restrict__ keys, Segs g, typename KeyTraits<Key>::Params hp, uint32_t shift,
     uint32_t bits, uint32_t* __restrict__ mat, uint32_t tiles_ub,
     const uint32_t* __restrict__ ids = nullptr) {
-    extern __shared__ uint32_t cnt[];
+    extern __shared__ __align__(16) uint32_t cnt[];
     const uint32_t D = 1u << bits;
     const uint32_t t = xcd_tile(blockIdx.x, tiles_ub);
     uint32_t seg, begin, end;
     if (!locate_tile(g, t, seg, begin, end)) return;
-    for (uint32_t d = threadIdx.x; d < D; d += kHistThreads) cnt[d] = 0;
+    for (uint32_t d = threadIdx.x; d < D; d += kHistThreads)
+        ((uint4*)cnt)[d] = make_uint4(0u, 0u, 0u, 0u);
     constexpr int IT = TILE / kHistThreads;
     Key k[IT];
 #pragma unroll
@@ -117,11 +122,14 @@ __global__ __launch_bounds__(kHistThreads) void k_tile_hist(
     for (int r = 0; r < IT; ++r) {
         const uint32_t i = begin + r * kHistThreads + threadIdx.x;
         const uint32_t v = ID_DIGIT ? (uint32_t)k[r] : KeyTraits<Key>::bucket(k[r], hp);
-        if (i < end) atomicAdd(&cnt[(v >> shift) & mask], 1u);
+        if (i < end) atomicAdd(&cnt[((v >> shift) & mask) * 4 + (threadIdx.x & 3u)], 1u);
     }
     __syncthreads();
     uint32_t* row = mat + (size_t)t * D;
-    for (uint32_t d = threadIdx.x; d < D; d += kHistThreads) row[d] = cnt[d];
+    for (uint32_t d = threadIdx.x; d < D; d += kHistThreads) {
+        const uint4 c = ((const uint4*)cnt)[d];
+        row[d] = c.x + c.y + c.z + c.w;
+    }
 }
 
 // ------------------------------------- segmented column scan of [tile][digit]
@@ -847,7 +855,7 @@ void launch_hist(dim3 grid, hipStream_t s, const Key* keys, const uint32_t* ids,
                  typename KeyTraits<Key>::Params hp, uint32_t shift, uint32_t bits, uint32_t* mat,
                  uint32_t tiles_ub) {
     hipLaunchKernelGGL((k_tile_hist<Key, ID_DIGIT, QUERIES, PartGeo<Key, STABLE>::kTile>), grid,
-                       dim3(kHistThreads), 4u << bits, s, keys, g, hp, shift, bits, mat, tiles_ub,
+                       dim3(kHistThreads), 16u << bits, s, keys, g, hp, shift, bits, mat, tiles_ub,
                        ids);
 }
 
