@@ -34,8 +34,8 @@
 //
 // Uniform keys need none of it, but every build pays for the launches (2 to 4 us
 // each): one kernel for builds of up to 2^17 keys, which split no bin (their
-// rare workgroups see each long bucket through alone), eight for larger ones;
-// they were six and twelve.
+// rare workgroups see each long bucket through alone), eight or, from 2^24 keys,
+// nine for larger ones; they were six and twelve.
 #include "hg_v2_device.h"
 
 namespace hg {
@@ -310,20 +310,25 @@ __device__ __forceinline__ uint32_t slices_of(const RareArgs& a, uint32_t idx) {
     return (a.bin_start[b + 1] - a.bin_start[b] + a.slice - 1) / a.slice;
 }
 
-// An oversize bin, one workgroup.
-template <typename Key, bool ANY>
+// What the first kernel of the rare path does: the oversize bins of a build
+// without split ones (whose only kernel it is), or also the split bins' slices, or
+// not (k_slice_hist).
+enum RareMode : int { kSolo, kBinsAndSlices, kBins };
+
+// An oversize bin, one workgroup.  U: loads in flight (count_hot_buckets).
+template <typename Key, bool ANY, int U>
 __device__ __forceinline__ void heavy_bin(const Rare<Key>& x, uint32_t i, unsigned char* smem) {
     const RareArgs& a = x.a;
     const uint32_t g = a.heavy_list[i];
     const uint32_t start = a.bin_start[g], end = a.bin_start[g + 1];
     const uint32_t NB = 1u << a.k, v0 = g << a.k;
     const uint32_t nb = (a.V - v0 < NB) ? a.V - v0 : NB;
-    heavy_bin_body<Key>(x.src_keys + start, x.src_ids + start, 0u, end - start, start, v0, a.k, nb,
-                        x.hp, x.offsets, x.ix, x.ids, x.ekeys, smem, ANY);
+    heavy_bin_body<Key, U>(x.src_keys + start, x.src_ids + start, 0u, end - start, start, v0, a.k,
+                           nb, x.hp, x.offsets, x.ix, x.ids, x.ekeys, smem, ANY);
 }
 
 // Bucket histogram of a slice of a split bin: hist[item][0 .. 2^k).
-template <typename Key>
+template <typename Key, int U>
 __device__ __forceinline__ void slice_hist(const Rare<Key>& x, uint32_t item, unsigned char* smem) {
     const RareArgs& a = x.a;
     uint32_t* cnt = (uint32_t*)smem;
@@ -332,15 +337,7 @@ __device__ __forceinline__ void slice_hist(const Rare<Key>& x, uint32_t item, un
     const uint32_t v0 = r.b << a.k;
     for (uint32_t i = threadIdx.x; i < NB; i += kRT) cnt[i] = 0;
     __syncthreads();
-    // a split bin holds a hot key: lanes sharing the first active lane's
-    // bucket add their count with one LDS atomic, the others one each
-    for (uint32_t i = r.begin + threadIdx.x; i < r.end; i += kRT) {
-        const uint32_t b = KeyTraits<Key>::bucket(x.src_keys[i], x.hp) - v0;
-        const uint32_t b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
-        const uint64_t same = ballot(b == b0);
-        if (b != b0) atomicAdd(&cnt[b], 1u);
-        else if (mbcnt(same) == 0) atomicAdd(&cnt[b0], (uint32_t)__popcll(same));
-    }
+    count_hot_buckets<Key, U>(x.src_keys + r.begin, r.end - r.begin, v0, x.hp, cnt);
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < NB; i += kRT)
         a.slice_hist[(size_t)item * NB + i] = cnt[i];
@@ -650,20 +647,26 @@ __device__ __forceinline__ void listed_of_bin(const Rare<Key>& x, uint32_t g, ui
     }
 }
 
-// First kernel of the rare path: every oversize bin with its long buckets, the
-// long buckets that the bins in LDS listed, and the histograms of the split
-// bins' slices; nothing here depends on another workgroup.  SOLO: a build
-// without split bins, whose rare path this is.
-template <typename Key, bool SOLO, bool ANY>
+// First kernel of the rare path: every oversize bin with its long buckets, and the
+// long buckets that the bins in LDS listed; nothing here depends on another
+// workgroup.
+// Bound by its longest oversize bin, one workgroup's chunks one after the other:
+// 295 us at 2^26 Zipf(1.2) keys (bins of up to 2^15).  Slices of half that length
+// took it to 202, but their histograms' scan and placement cost as much more.
+template <typename Key, int MODE, bool ANY>
 __global__ __launch_bounds__(kRT) void k_rare_bins(Rare<Key> x) {
     extern __shared__ __align__(16) unsigned char smem[];
     const RareArgs& a = x.a;
     const uint32_t nheavy = a.ctr[kCtrHeavy];
-    const uint32_t nsl = SOLO ? 0u : a.ctr[kCtrSlices] < a.slice_cap ? a.ctr[kCtrSlices] : a.slice_cap;
+    uint32_t nsl = 0;
+    if (MODE == kBinsAndSlices)
+        nsl = a.ctr[kCtrSlices] < a.slice_cap ? a.ctr[kCtrSlices] : a.slice_cap;
+    // (one load in flight keeps the kernel with the slices within 128 VGPRs)
+    constexpr int U = MODE == kBinsAndSlices ? 1 : 8;
     const BucketLds<Key> m(smem);
     for (uint32_t i = blockIdx.x; i < nheavy + nsl; i += gridDim.x) {
-        if (i < nheavy) heavy_bin<Key, ANY>(x, i, smem);
-        else slice_hist<Key>(x, i - nheavy, smem);
+        if (i < nheavy) heavy_bin<Key, ANY, U>(x, i, smem);
+        else slice_hist<Key, U>(x, i - nheavy, smem);
         __syncthreads();
     }
     if (!x.ix.head) return;
@@ -675,7 +678,7 @@ __global__ __launch_bounds__(kRT) void k_rare_bins(Rare<Key> x) {
         const uint32_t g = i < nheavy ? a.heavy_list[i] : i - nheavy;
         if (i >= nheavy && a.bin_start[g + 1] - a.bin_start[g] > light_cap<Key>()) continue;
         const uint32_t listed = x.ix.gen_cnt[g];
-        if (listed) listed_of_bin<Key, SOLO>(x, g, listed, m);
+        if (listed) listed_of_bin<Key, MODE == kSolo>(x, g, listed, m);
         __syncthreads();
     }
 }
@@ -685,6 +688,24 @@ __global__ __launch_bounds__(kRT) void k_rare_bins(Rare<Key> x) {
 // lower ranges, whose sums per slice the histogram pass left; every count turns
 // into the position of its slice's first entry of the bucket.
 constexpr int kScanThreads = 1024;
+
+// The histograms of the split bins' slices in a kernel of their own, so that four
+// workgroups share a CU: with the oversize bins, which take 128 VGPRs and 50 KB of
+// LDS, the two ran 449 us at 2^26 Zipf(1.2) keys, apart 295 and 71.  Builds below
+// kSliceHistMin keys keep them in one kernel: the launch costs a build of 2^18 keys
+// 1.6 us of 49.5, and 1024 slices leave no such tail.
+constexpr uint64_t kSliceHistMin = 1ull << 24;
+
+template <typename Key>
+__global__ __launch_bounds__(kRT) void k_slice_hist(Rare<Key> x) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const RareArgs& a = x.a;
+    const uint32_t nsl = a.ctr[kCtrSlices] < a.slice_cap ? a.ctr[kCtrSlices] : a.slice_cap;
+    for (uint32_t i = blockIdx.x; i < nsl; i += gridDim.x) {
+        slice_hist<Key, 8>(x, i, smem);
+        __syncthreads();
+    }
+}
 
 __global__ __launch_bounds__(kScanThreads) void k_slice_scan(RareArgs a, uint32_t* offsets) {
     constexpr uint32_t B = 1u << kRangeBits, G = kScanThreads / B;
@@ -892,10 +913,12 @@ hipError_t set_rare_smem() {
     return once_per_device(done, [] {
         const int lim = (int)rare_smem<Key>(kMaxLocalBits);
         const hipFuncAttribute at = hipFuncAttributeMaxDynamicSharedMemorySize;
-        HG_TRY(hipFuncSetAttribute((const void*)k_rare_bins<Key, true, true>, at, lim));
-        HG_TRY(hipFuncSetAttribute((const void*)k_rare_bins<Key, true, false>, at, lim));
-        HG_TRY(hipFuncSetAttribute((const void*)k_rare_bins<Key, false, true>, at, lim));
-        HG_TRY(hipFuncSetAttribute((const void*)k_rare_bins<Key, false, false>, at, lim));
+        HG_TRY(hipFuncSetAttribute((const void*)k_rare_bins<Key, kSolo, true>, at, lim));
+        HG_TRY(hipFuncSetAttribute((const void*)k_rare_bins<Key, kSolo, false>, at, lim));
+        HG_TRY(hipFuncSetAttribute((const void*)k_rare_bins<Key, kBins, true>, at, lim));
+        HG_TRY(hipFuncSetAttribute((const void*)k_rare_bins<Key, kBinsAndSlices, true>, at, lim));
+        HG_TRY(hipFuncSetAttribute((const void*)k_rare_bins<Key, kBins, false>, at, lim));
+        HG_TRY(hipFuncSetAttribute((const void*)k_rare_bins<Key, kBinsAndSlices, false>, at, lim));
         HG_TRY(hipFuncSetAttribute((const void*)k_slice_place<Key, true>, at, lim));
         HG_TRY(hipFuncSetAttribute((const void*)k_slice_place<Key, false>, at, lim));
         HG_TRY(hipFuncSetAttribute((const void*)k_split_index<Key>, at, lim));
@@ -921,16 +944,23 @@ hipError_t run_rare(const RareArgs& a, uint32_t* offsets, uint32_t* ids, Key* ek
     {
         HG_PROF("v2_rare_bins", s);
         if (solo) {
-            const auto f = a.any_order ? k_rare_bins<Key, true, true> : k_rare_bins<Key, true, false>;
+            const auto f =
+                a.any_order ? k_rare_bins<Key, kSolo, true> : k_rare_bins<Key, kSolo, false>;
             hipLaunchKernelGGL(f, gb, th, lds, s, x);
             return hipGetLastError();
         }
         // (slices may outnumber the bins)
-        const auto f = a.any_order ? k_rare_bins<Key, false, true> : k_rare_bins<Key, false, false>;
-        hipLaunchKernelGGL(f, dim3(kRareGrid), th, lds, s, x);
+        const auto both =
+            a.any_order ? k_rare_bins<Key, kBinsAndSlices, true> : k_rare_bins<Key, kBinsAndSlices, false>;
+        const auto alone = a.any_order ? k_rare_bins<Key, kBins, true> : k_rare_bins<Key, kBins, false>;
+        hipLaunchKernelGGL(n < kSliceHistMin ? both : alone, dim3(kRareGrid), th, lds, s, x);
     }
     HG_TRY(hipGetLastError());
     HG_PROF("v2_split_bins", s);
+    if (n >= kSliceHistMin) {
+        hipLaunchKernelGGL(k_slice_hist<Key>, dim3(1024), th, (size_t)4 << a.k, s, x);
+        HG_TRY(hipGetLastError());
+    }
     hipLaunchKernelGGL(k_slice_scan, dim3(256), dim3(kScanThreads), 0, s, a, offsets);
     HG_TRY(hipGetLastError());
     const auto place = a.any_order ? k_slice_place<Key, true> : k_slice_place<Key, false>;

@@ -1002,10 +1002,35 @@ __device__ __forceinline__ void place_in_chunks(const Key* __restrict__ src_keys
     }
 }
 
+// Adds the keys' buckets (from v0 on) to cnt, for keys among which one is hot:
+// lanes sharing the first active lane's bucket count with one LDS atomic, the
+// others one each.  U loads in flight per thread.  Whole workgroup; no barrier.
+template <typename Key, int U>
+__device__ __forceinline__ void count_hot_buckets(const Key* __restrict__ keys, uint32_t L,
+                                                  uint32_t v0,
+                                                  const typename KeyTraits<Key>::Params& hp,
+                                                  uint32_t* cnt) {
+    for (uint32_t i0 = threadIdx.x; i0 < L; i0 += U * kLocalThreads) {
+        Key k[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            k[u] = i0 + u * kLocalThreads < L ? keys[i0 + u * kLocalThreads] : (Key)0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (i0 + u * kLocalThreads >= L) continue;
+            const uint32_t b = KeyTraits<Key>::bucket(k[u], hp) - v0;
+            const uint32_t b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
+            const uint64_t same = ballot(b == b0);
+            if (b != b0) atomicAdd(&cnt[b], 1u);
+            else if (mbcnt(same) == 0) atomicAdd(&cnt[b0], (uint32_t)__popcll(same));
+        }
+    }
+}
+
 // The same for a bin of any size (arriving in id order) in one workgroup:
 // keys counted per bucket first, then placed with place_in_chunks, so
 // placement stays stable.
-template <typename Key>
+template <typename Key, int U = 8>
 __device__ __forceinline__ void heavy_bin_body(const Key* __restrict__ src_keys,
                                                const uint32_t* __restrict__ src_ids,
                                                uint32_t id_base, uint32_t L, uint32_t out,
@@ -1021,15 +1046,7 @@ __device__ __forceinline__ void heavy_bin_body(const Key* __restrict__ src_keys,
 
     for (uint32_t i = threadIdx.x; i < NB; i += kLocalThreads) cur[i] = 0;
     __syncthreads();
-    // lanes sharing the first active lane's bucket (a hot key) count with one
-    // LDS atomic, the others one each
-    for (uint32_t i = threadIdx.x; i < L; i += kLocalThreads) {
-        const uint32_t b = KeyTraits<Key>::bucket(src_keys[i], hp) - v0;
-        const uint32_t b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
-        const uint64_t same = ballot(b == b0);
-        if (b != b0) atomicAdd(&cur[b], 1u);
-        else if (mbcnt(same) == 0) atomicAdd(&cur[b0], (uint32_t)__popcll(same));
-    }
+    count_hot_buckets<Key, U>(src_keys, L, v0, hp, cur);
     __syncthreads();
     scan_counts(cur, NB, out, tmp);
     for (uint32_t i = threadIdx.x; i < nb; i += kLocalThreads) offsets[v0 + i] = cur[i];

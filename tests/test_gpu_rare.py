@@ -82,3 +82,24 @@ def test_neighbouring_oversize_bins(hg, kb, n, big):
     k = np.concatenate(parts)[:n]
     k = np.concatenate([k, workloads.uniform_keys(n - k.size, kb, 8)])
     check(hg, rng.permutation(k), V, kb)
+
+
+@pytest.mark.parametrize("n", [(1 << 24) - 1, 1 << 24])
+def test_split_bins_with_and_without_their_own_histogram_kernel(hg, n):
+    print("[case]", n, flush=True)
+    rng = np.random.default_rng(n)
+    k = workloads.uniform_keys(n, 32, 4)
+    k[rng.random(n) < 0.2] = 7  # one split bin of about 200 slices
+    k[rng.random(n) < 0.001] = 9  # and an oversize one
+    V = 1 << 24
+    off, ids, ek = oracle.build_table(k, V, SEED, 32)
+    t = hg.hg_build(hg.to_device(k), V, seed=SEED)
+    g_off, g_ids, g_ek = t.export()
+    torch.cuda.synchronize()
+    assert np.array_equal(hg.to_numpy(g_off, np.uint32), off)
+    assert np.array_equal(hg.to_numpy(g_ids, np.uint32), ids)
+    assert np.array_equal(hg.to_numpy(g_ek, np.uint32), ek)
+    c, tot = hg.hg_probe(t, hg.to_device(k[:50000]), counts=True, total=True)
+    exp, etot = oracle.probe_counts(k, k[:50000], 32)
+    assert np.array_equal(hg.to_numpy(c, np.uint32), exp) and tot == etot
+    t.free()
