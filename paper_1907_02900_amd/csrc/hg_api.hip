@@ -75,14 +75,18 @@ hipError_t or_empty_pools(F&& f) {
 hipMemPool_t pool_for(hipStream_t s) {
     if (g_pool_users.load(std::memory_order_relaxed) == 0) return nullptr;
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    int dev = -1;
-    const bool named = s && s != hipStreamLegacy && s != hipStreamPerThread;
-    if (hipStreamIsCapturing(s, &st) != hipSuccess ||
-        (named ? hipStreamGetDevice(s, &dev) : hipGetDevice(&dev)) != hipSuccess) {
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
         (void)hipGetLastError();
         return nullptr;
     }
-    return st == hipStreamCaptureStatusNone ? pool_of(dev) : nullptr;
+    if (st != hipStreamCaptureStatusNone) return nullptr;
+    int dev = -1;
+    const bool named = s && s != hipStreamLegacy && s != hipStreamPerThread;
+    if ((named ? hipStreamGetDevice(s, &dev) : hipGetDevice(&dev)) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    return pool_of(dev);
 }
 }  // namespace
 

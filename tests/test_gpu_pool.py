@@ -69,3 +69,28 @@ def test_the_pool_is_given_back(hg):
     torch.cuda.synchronize()
     # the table, its build's and the probe's workspace took about 700 MB
     assert torch.cuda.mem_get_info()[0] >= before - (64 << 20)
+
+
+def test_probes_under_capture(hg):
+    # captured without the pool: eager work between the replays uses it
+    k = workloads.duplicate_keys(50_000, 2.0, 32, seed=2)
+    q = workloads.probe_queries(k, 70_001, 0.5, seed=3)
+    exp, _ = oracle.probe_counts(k, q)
+    dq = hg.to_device(q)
+    t = hg.hg_build(hg.to_device(k), 40_000, seed=4)
+    for order in (hg.PROBE_INPUT_ORDER, hg.PROBE_GROUPED, hg.PROBE_GROUPED_UNLESS_SKEWED):
+        out = torch.zeros(q.size, device="cuda", dtype=torch.int32)
+        hg.hg_probe_ordered(t, dq, order, out=out)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            hg.hg_probe_ordered(t, dq, order, out=out)
+        for _ in range(4):
+            out.zero_()
+            g.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(hg.to_numpy(out, np.uint32), exp)
+            _, tot = hg.hg_probe_ordered(t, dq, hg.PROBE_GROUPED, total=True)
+            assert tot == exp.sum()
+        del g
+    t.free()
