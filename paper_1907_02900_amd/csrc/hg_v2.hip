@@ -205,57 +205,12 @@ __global__ __launch_bounds__(kSegThreads) void k_colscan_seg(Segs g, uint32_t D,
         __threadfence();  // before the atomics below
     }
     if (c0 == c1 && !out.bin_start) return;
-    static_assert((1u << kMaxDigitBits) <= 2 * kSegThreads, "at most two digits per thread");
-    const uint32_t per = D > (uint32_t)kSegThreads ? 2u : 1u;
-    uint32_t G = (uint32_t)kSegThreads / D;  // row groups (D is a power of two)
-    G = G > 16 ? 16 : (G ? G : 1);
-    const uint32_t d0 = per == 2 ? threadIdx.x * 2 : threadIdx.x & (D - 1);
-    const uint32_t grp = per == 2 ? 0u : threadIdx.x / D;
-    const uint32_t len = (c1 - c0 + G - 1) / G;
-    const uint32_t ra = grp < G && c0 + grp * len < c1 ? c0 + grp * len : c1;
-    const uint32_t rb = c1 - ra > len ? ra + len : c1;
-    for (uint32_t j = 0; j < per; ++j) {
-        uint32_t acc = 0;
-        for (uint32_t c = ra; c < rb; c += 8) {
-            uint32_t v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = c + u < rb ? csum[(size_t)(c + u) * D + d0 + j] : 0u;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) acc += v[u];
-        }
-        if (grp < G) part[grp * D + d0 + j] = acc;
-    }
-    __syncthreads();
-    uint32_t tot[2] = {0, 0};
-    if (grp == 0)
-        for (uint32_t j = 0; j < per; ++j)
-            for (uint32_t x = 0; x < G; ++x) tot[j] += part[x * D + d0 + j];
-    uint32_t all;
-    const uint32_t ex = g.start(s) + block_excl_scan<kSegThreads>(tot[0] + tot[1], tmp, &all);
-    if (grp == 0) {
-        dbase[d0] = ex;
-        if (per == 2) dbase[d0 + 1] = ex + tot[0];
-    }
-    __syncthreads();
-    if (out.bin_start)
-        for (uint32_t d = threadIdx.x; d < D; d += kSegThreads)
-            note_bin(out, s * D + d, dbase[d], d + 1 < D ? dbase[d + 1] : g.start(s + 1));
-    if (out.next.seg_start) next_segments(out.next, dbase, g.start(1), tmp);
-    for (uint32_t j = 0; j < per; ++j) {
-        if (ra >= rb) break;
-        uint32_t r = dbase[d0 + j];
-        for (uint32_t x = 0; x < grp; ++x) r += part[x * D + d0 + j];
-        for (uint32_t c = ra; c < rb; c += 8) {
-            uint32_t v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = c + u < rb ? csum[(size_t)(c + u) * D + d0 + j] : 0u;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                if (c + u < rb) csum[(size_t)(c + u) * D + d0 + j] = r;
-                r += v[u];
-            }
-        }
-    }
+    scan_columns<kSegThreads>(csum, c0, c1, D, g.start(s), part, dbase, tmp, [&] {
+        if (out.bin_start)
+            for (uint32_t d = threadIdx.x; d < D; d += kSegThreads)
+                note_bin(out, s * D + d, dbase[d], d + 1 < D ? dbase[d + 1] : g.start(s + 1));
+        if (out.next.seg_start) next_segments(out.next, dbase, g.start(1), tmp);
+    });
 }
 
 __global__ __launch_bounds__(256) void k_colscan_down(uint32_t* __restrict__ mat, Segs g, uint32_t D,

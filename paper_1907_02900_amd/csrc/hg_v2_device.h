@@ -120,6 +120,65 @@ __device__ __forceinline__ void rank_any(const uint32_t (&dig)[ITEMS], uint32_t 
     for (int r = 0; r < ITEMS; ++r) pos[r] += dstart[dig[r] & mask];
 }
 
+// Exclusive scan of a matrix of counts in (column, row) order, in place: rows [c0,
+// c1), D columns, starting at `start`; dbase[d] receives column d's start, and
+// with_starts() runs once they are there.  part: [2 * THREADS], dbase: [D], tmp:
+// [THREADS / 64 + 1], in LDS.  One workgroup against memory latency: up to 16 row
+// groups walk the rows side by side with eight loads in flight each.  Barriers.
+template <int THREADS, typename F>
+__device__ __forceinline__ void scan_columns(uint32_t* __restrict__ mat, uint32_t c0, uint32_t c1,
+                                             uint32_t D, uint32_t start, uint32_t* part,
+                                             uint32_t* dbase, uint32_t* tmp, F&& with_starts) {
+    static_assert((1u << kMaxDigitBits) <= 2 * THREADS, "at most two digits per thread");
+    const uint32_t per = D > (uint32_t)THREADS ? 2u : 1u;
+    uint32_t G = (uint32_t)THREADS / D;  // row groups (D is a power of two)
+    G = G > 16 ? 16 : (G ? G : 1);
+    const uint32_t d0 = per == 2 ? threadIdx.x * 2 : threadIdx.x & (D - 1);
+    const uint32_t grp = per == 2 ? 0u : threadIdx.x / D;
+    const uint32_t len = (c1 - c0 + G - 1) / G;
+    const uint32_t ra = grp < G && c0 + grp * len < c1 ? c0 + grp * len : c1;
+    const uint32_t rb = c1 - ra > len ? ra + len : c1;
+    for (uint32_t j = 0; j < per; ++j) {
+        uint32_t acc = 0;
+        for (uint32_t c = ra; c < rb; c += 8) {
+            uint32_t v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = c + u < rb ? mat[(size_t)(c + u) * D + d0 + j] : 0u;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) acc += v[u];
+        }
+        if (grp < G) part[grp * D + d0 + j] = acc;
+    }
+    __syncthreads();
+    uint32_t tot[2] = {0, 0};
+    if (grp == 0)
+        for (uint32_t j = 0; j < per; ++j)
+            for (uint32_t x = 0; x < G; ++x) tot[j] += part[x * D + d0 + j];
+    uint32_t all;
+    const uint32_t ex = start + block_excl_scan<THREADS>(tot[0] + tot[1], tmp, &all);
+    if (grp == 0) {
+        dbase[d0] = ex;
+        if (per == 2) dbase[d0 + 1] = ex + tot[0];
+    }
+    __syncthreads();
+    with_starts();
+    for (uint32_t j = 0; j < per; ++j) {
+        if (ra >= rb) break;
+        uint32_t r = dbase[d0 + j];
+        for (uint32_t x = 0; x < grp; ++x) r += part[x * D + d0 + j];
+        for (uint32_t c = ra; c < rb; c += 8) {
+            uint32_t v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = c + u < rb ? mat[(size_t)(c + u) * D + d0 + j] : 0u;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                if (c + u < rb) mat[(size_t)(c + u) * D + d0 + j] = r;
+                r += v[u];
+            }
+        }
+    }
+}
+
 // -------------------------------------------------- per-bin LDS build -----
 
 // Place one chunk of <= ITEMS*64*W entries held in registers: two stable LSD
