@@ -692,7 +692,7 @@ constexpr int kScanThreads = 1024;
 // The histograms of the split bins' slices in a kernel of their own, so that four
 // workgroups share a CU: with the oversize bins, which take 128 VGPRs and 50 KB of
 // LDS, the two ran 449 us at 2^26 Zipf(1.2) keys, apart 295 and 71.  Builds below
-// kSliceHistMin keys keep them in one kernel: the launch costs a build of 2^18 keys
+// kSliceHistMin keys keep them in one kernel: the launch costs a build of 300 007 keys
 // 1.6 us of 49.5, and 1024 slices leave no such tail.
 constexpr uint64_t kSliceHistMin = 1ull << 24;
 
