@@ -175,7 +175,9 @@ inline uint32_t split_cap(uint64_t n) {
 }
 // Device counters of a build, zeroed by its first kernel: oversize bins, split
 // bins, their slices, long buckets of the chunked path, their chunks, whether
-// any bin listed a long bucket.
+// a bin held in LDS listed a long bucket (written by the per-bin kernel only: the
+// rare path's first kernel reads it while its own workgroups run, and its waves
+// have to agree on it, since barriers follow).
 enum : uint32_t { kCtrHeavy, kCtrSplit, kCtrSlices, kCtrLong, kCtrChunks, kCtrListed, kCtrWords };
 constexpr uint32_t kMaxLocalBits = 12;                          // buckets per bin <= 4096
 constexpr uint32_t kMaxDigitBits = 11;                       // partition fan-out <= 2048
@@ -409,7 +411,7 @@ struct IndexOut {
     RunsDev runs{};
     uint32_t* gen_list = nullptr;
     uint32_t* gen_cnt = nullptr;  // [bins]
-    uint32_t* gen_any = nullptr;  // set when any bin lists a bucket
+    uint32_t* gen_any = nullptr;  // set when a bin held in LDS lists a bucket
     uint32_t k = 0, bins = 0;
 };
 

@@ -671,8 +671,8 @@ __global__ __launch_bounds__(kRT) void k_rare_bins(Rare<Key> x) {
     }
     if (!x.ix.head) return;
     // the long buckets of this workgroup's oversize bins, and of the bins held
-    // in LDS (their flag may also come from an oversize bin of this launch:
-    // then they are looked through for nothing)
+    // in LDS when one of them listed any (kCtrListed, which no workgroup of this
+    // launch writes)
     const uint32_t nlight = a.ctr[kCtrListed] ? a.bins : 0u;
     for (uint32_t i = blockIdx.x; i < nheavy + nlight; i += gridDim.x) {
         const uint32_t g = i < nheavy ? a.heavy_list[i] : i - nheavy;

@@ -1125,10 +1125,7 @@ __device__ __forceinline__ void heavy_bin_body(const Key* __restrict__ src_keys,
                 put_short<Key>(ix, v0 + v, lo, cur[v], ekeys + lo);
         }
         __syncthreads();
-        if (threadIdx.x == 0) {
-            ix.gen_cnt[v0 >> k] = *nlisted;
-            if (*nlisted) *ix.gen_any = 1u;
-        }
+        if (threadIdx.x == 0) ix.gen_cnt[v0 >> k] = *nlisted;
     }
 }
 
