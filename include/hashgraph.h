@@ -247,8 +247,8 @@ hg_status hg_build_tune(const void *d_keys, uint64_t n, int key_bits, uint64_t h
                         hg_build_opts *out, hg_tune_info *info);
 
 /* Allocate an empty table able to hold up to n_capacity keys and
- * range_capacity buckets, including the workspace a V2 build of that size
- * needs and the probe index with its key-run summary (hg_build_opts.no_index).
+ * range_capacity buckets, including the workspace that builds of up to those sizes
+ * need and the probe index with its key-run summary (hg_build_opts.no_index).
  * Later hg_table_build calls of up to those sizes (with the library's choice
  * of bins) allocate nothing and never wait for the device, so a rebuild and
  * the probes after it can be captured into a HIP graph. */

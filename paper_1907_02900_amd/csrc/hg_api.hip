@@ -259,9 +259,7 @@ hg_status alloc_table(uint64_t n_cap, uint64_t V_cap, int kb, bool with_ws, hg_t
     if (e == hipSuccess) e = dev_malloc((void**)&t->keys, (n_cap ? n_cap : 1) * key_size(kb));
     t->bytes = (V_cap + 1) * 4 + (n_cap ? n_cap : 1) * (4 + key_size(kb));
     if (e == hipSuccess && with_ws) {
-        size_t w1 = build_ws_bytes(1, n_cap, V_cap, kb, 0);
-        size_t w2 = build_ws_bytes(2, n_cap, V_cap, kb, 0);
-        t->ws_bytes = w1 > w2 ? w1 : w2;
+        t->ws_bytes = table_ws_bytes(n_cap, V_cap, kb);
         e = dev_malloc((void**)&t->ws, t->ws_bytes);
         t->bytes += t->ws_bytes;
     }

@@ -167,8 +167,7 @@ inline uint32_t slice_keys(uint64_t n) {
     return k;
 }
 // Most split bins of a build of n keys (n / slice_keys(n)), as a bound that
-// grows with n (a table's workspace serves every build up to its capacity);
-// their slices are at most twice as many.
+// grows with n (table_ws_bytes); their slices are at most twice as many.
 inline uint32_t split_cap(uint64_t n) {
     const uint64_t a = n <= (1u << 17) ? 0 : n >> 14, b = n >> 17;
     return (uint32_t)((a < 2048 ? a : 2048) > b ? (a < 2048 ? a : 2048) : b) + 1;
@@ -201,6 +200,11 @@ V2Plan plan_v2(uint64_t n, uint64_t V, int key_bits, uint32_t bins_hint, bool an
 
 // Workspace bytes needed by a build.
 size_t build_ws_bytes(int variant, uint64_t n, uint64_t V, int key_bits, uint32_t bins_hint);
+// The most that any build of up to n_cap keys and V_cap buckets needs (without a
+// bins hint).  That is not always the largest build's: fewer keys over the same
+// range take wider bins, whose slice histograms are longer, or one partition pass
+// of many digits instead of two of few.
+size_t table_ws_bytes(uint64_t n_cap, uint64_t V_cap, int key_bits);
 
 // Scan workspace for `n` inputs.
 size_t scan_ws_bytes(uint64_t n);

@@ -689,6 +689,38 @@ V2Plan perm_plan(uint64_t n);
 
 // ------------------------------------------------------------------ plan --
 
+namespace {
+
+// About 4096 keys per final bin for 32-bit keys (2^k * n / V ~ 4096), 2048 for
+// 64-bit keys, whose LDS bin then still leaves room for two workgroups per CU.
+uint64_t bin_keys(int key_bits) { return key_bits == 64 ? 2048 : 4096; }
+
+// The passes of a plan whose n, V, tile and k are set.
+void plan_passes(V2Plan& p) {
+    p.bins = (uint32_t)ceil_div(p.V, 1ull << p.k);
+    const uint32_t bits = log2_ceil(p.bins);
+    if (bits <= kOneTierBits) {
+        p.tiers = 1;
+        p.b1 = bits;
+        p.b2 = 0;
+    } else {
+        p.tiers = 2;
+        p.b1 = bits / 2;
+        p.b2 = bits - p.b1;
+    }
+    p.ntiles1 = (uint32_t)ceil_div(p.n, p.tile);
+    p.ch1 = (uint32_t)pow2_ceil(ceil_div(p.ntiles1 ? p.ntiles1 : 1, 256));
+    p.nchunks1 = (uint32_t)ceil_div(p.ntiles1, p.ch1);
+    if (p.tiers == 2) {
+        const uint32_t S = 1u << p.b1;
+        p.ntiles2_ub = p.ntiles1 + S;
+        p.ch2 = (uint32_t)pow2_ceil(ceil_div(p.ntiles1 ? p.ntiles1 : 1, (uint64_t)S * 4));
+        p.nchunks2_ub = (uint32_t)ceil_div(p.ntiles2_ub, p.ch2) + S;
+    }
+}
+
+}  // namespace
+
 V2Plan plan_v2(uint64_t n, uint64_t V, int key_bits, uint32_t bins_hint, bool any_order) {
     V2Plan p;
     p.tile = part_tile(key_bits / 8, any_order);
@@ -700,11 +732,7 @@ V2Plan plan_v2(uint64_t n, uint64_t V, int key_bits, uint32_t bins_hint, bool an
     } else if (n == 0) {
         k = kMaxLocalBits;
     } else {
-        // about 4096 keys per final bin for 32-bit keys (2^k * n / V ~ 4096),
-        // 2048 for 64-bit keys, whose LDS bin then still leaves room for two
-        // workgroups per CU
-        const double target = key_bits == 64 ? 2048.0 : 4096.0;
-        const double r = target * (double)V / (double)n;
+        const double r = (double)bin_keys(key_bits) * (double)V / (double)n;
         k = 0;
         while (k < kMaxLocalBits && (double)(1ull << (k + 1)) <= r) ++k;
     }
@@ -712,26 +740,7 @@ V2Plan plan_v2(uint64_t n, uint64_t V, int key_bits, uint32_t bins_hint, bool an
     const uint32_t kv = log2_ceil(V);
     if (k > kv) k = kv;
     p.k = k;
-    p.bins = (uint32_t)ceil_div(V, 1ull << k);
-    const uint32_t bits = log2_ceil(p.bins);
-    if (bits <= kOneTierBits) {
-        p.tiers = 1;
-        p.b1 = bits;
-        p.b2 = 0;
-    } else {
-        p.tiers = 2;
-        p.b1 = bits / 2;
-        p.b2 = bits - p.b1;
-    }
-    p.ntiles1 = (uint32_t)ceil_div(n, p.tile);
-    p.ch1 = (uint32_t)pow2_ceil(ceil_div(p.ntiles1 ? p.ntiles1 : 1, 256));
-    p.nchunks1 = (uint32_t)ceil_div(p.ntiles1, p.ch1);
-    if (p.tiers == 2) {
-        const uint32_t S = 1u << p.b1;
-        p.ntiles2_ub = p.ntiles1 + S;
-        p.ch2 = (uint32_t)pow2_ceil(ceil_div(p.ntiles1 ? p.ntiles1 : 1, (uint64_t)S * 4));
-        p.nchunks2_ub = (uint32_t)ceil_div(p.ntiles2_ub, p.ch2) + S;
-    }
+    plan_passes(p);
     return p;
 }
 
@@ -917,10 +926,45 @@ size_t build_ws_bytes(int variant, uint64_t n, uint64_t V, int key_bits, uint32_
         c.take<char>(scan_ws_bytes(V));
         return c.off + 256;
     }
-    // (a table's workspace serves builds of either order)
     const size_t st = layout_v2(nullptr, plan_v2(n, V, key_bits, bins_hint, false), ks, nullptr);
     const size_t any = layout_v2(nullptr, plan_v2(n, V, key_bits, bins_hint, true), ks, nullptr);
     return st > any ? st : any;
+}
+
+size_t table_ws_bytes(uint64_t n_cap, uint64_t V_cap, int key_bits) {
+    size_t most = build_ws_bytes(1, n_cap, V_cap, key_bits, 0);
+    const uint32_t kv_max = log2_ceil(V_cap);
+    for (uint32_t kv = 0; kv <= kv_max; ++kv) {
+        // the ranges with ceil(log2 V) = kv
+        const uint64_t lo = kv ? (1ull << (kv - 1)) + 1 : 1;
+        const uint64_t hi = (1ull << kv) < V_cap ? 1ull << kv : V_cap;
+        const uint32_t k_top = kv < kMaxLocalBits ? kv : kMaxLocalBits;
+        for (uint32_t k = 0; k <= k_top; ++k) {
+            // plan_v2 takes bins of 2^k buckets for bin_keys * V / 2^(k + 1) < n <=
+            // bin_keys * V / 2^k, the smallest k also for more keys and the largest
+            // for fewer; with them the layout grows with n
+            const uint64_t at = bin_keys(key_bits) * hi >> k;
+            const uint64_t n = k == 0 || at > n_cap ? n_cap : at;
+            if (k < k_top && n <= bin_keys(key_bits) * lo >> (k + 1)) continue;
+            for (bool any : {false, true}) {
+                V2Plan p;
+                p.tile = part_tile(key_bits / 8, any);
+                p.n = n;
+                p.V = hi;
+                p.k = k;
+                plan_passes(p);
+                // (the numbers of chunks, whose lengths are powers of two, do not
+                // grow with n: their bounds)
+                const uint32_t S = 1u << p.b1;
+                p.nchunks1 = p.ntiles1 < 256 ? p.ntiles1 : 256;
+                if (p.tiers == 2)
+                    p.nchunks2_ub = (p.ntiles2_ub < 5 * S ? p.ntiles2_ub : 5 * S) + S;
+                const size_t b = layout_v2(nullptr, p, key_bits / 8, nullptr);
+                most = b > most ? b : most;
+            }
+        }
+    }
+    return most;
 }
 
 template <typename Key>

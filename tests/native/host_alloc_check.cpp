@@ -1,0 +1,88 @@
+// Host paths of the library's memory handling, over fake_hip.h.  One check per
+// argument; exits non-zero at the first thing that is wrong.
+#include <stdio.h>
+#include <stdlib.h>
+
+#include <algorithm>
+#include <random>
+#include <string>
+#include <vector>
+
+#include "fake_hip.h"
+#include "hashgraph.h"
+
+using fake::st;
+
+static void* const kKeys = (void*)(uintptr_t)0x1000;
+
+#define CHECK(cond, ...)                              \
+    do {                                              \
+        if (!(cond)) {                                \
+            printf("%s:%d: %s: ", __FILE__, __LINE__, #cond); \
+            printf(__VA_ARGS__);                      \
+            printf("\n");                             \
+            exit(1);                                  \
+        }                                             \
+    } while (0)
+
+// Builds of any size up to a table's capacity allocate nothing.
+static void rebuilds_allocate_nothing() {
+    std::mt19937_64 rng(3);
+    std::vector<std::pair<uint64_t, uint64_t>> caps = {
+        {17616076, 1ull << 24}, {17616076, 1ull << 25}, {1ull << 28, 1ull << 28},
+        {1ull << 24, 1ull << 24}, {300007, 300007}, {(1 << 17) + 1, 1 << 17},
+        {(1 << 21) + 5000, 1 << 21}, {4608, 4096}, {1, 1}, {0, 7}, {1 << 20, 3},
+        {5000, 1ull << 28}, {1ull << 30, 1ull << 30}, {0xffffffffull, 0xffffffffull}};
+    for (int i = 0; i < 40; ++i) {
+        const uint64_t n = 1 + (rng() >> (36 + rng() % 24));
+        caps.push_back({n, std::max<uint64_t>(1, i % 2 ? n >> (rng() % 6) : n << (rng() % 4)) &
+                               0xffffffffull});
+        if (!caps.back().second) caps.back().second = 1;
+    }
+    for (int kb : {32, 64})
+        for (auto [nc, vc] : caps) {
+            hg_table* t = nullptr;
+            CHECK(hg_table_create(nc, vc, kb, &t) == HG_OK, "%llu %llu", (unsigned long long)nc,
+                  (unsigned long long)vc);
+            const long before = st.allocs;
+            std::vector<uint64_t> Vs = {vc, vc - 1, vc / 2, vc / 2 + 1, vc / 3, vc / 64, 1, 4096};
+            for (int b = 1; b < 32; ++b)
+                for (int d : {0, 1}) Vs.push_back((1ull << b) + d);
+            for (uint64_t V : Vs) {
+                if (V < 1 || V > vc) continue;
+                // where the bins' width and the number of passes step, and between
+                std::vector<uint64_t> ns = {nc, nc - 1, nc / 2, 0, 1, 1 << 17, (1 << 17) + 1,
+                                            nc - nc / 20};
+                for (int k = 0; k <= 13; ++k)
+                    for (int d = -1; d <= 1; ++d) ns.push_back((((kb == 64 ? 2048 : 4096) * V) >> k) + d);
+                for (int b = 14; b < 30; ++b) ns.push_back(1ull << b);
+                for (uint64_t n : ns) {
+                    if (n > nc) continue;
+                    for (int form = 0; form < 4; ++form) {
+                        hg_build_opts o{};
+                        o.any_order = form & 1;
+                        o.no_index = form >> 1;
+                        CHECK(hg_table_build(t, kKeys, n, V, 1, &o, nullptr) == HG_OK, "build");
+                        CHECK(st.allocs == before,
+                              "capacity %llu keys %llu buckets, %d bits: %llu keys, %llu buckets, "
+                              "any order %d", (unsigned long long)nc, (unsigned long long)vc, kb,
+                              (unsigned long long)n, (unsigned long long)V, form & 1);
+                    }
+                }
+            }
+            hg_build_opts o{};
+            o.variant = HG_VARIANT_V1;
+            CHECK(hg_table_build(t, kKeys, nc, vc, 1, &o, nullptr) == HG_OK, "V1");
+            CHECK(st.allocs == before, "V1");
+            hg_table_free(t);
+            CHECK(st.live.empty(), "left over");
+        }
+}
+
+int main(int argc, char** argv) {
+    const std::string what = argc > 1 ? argv[1] : "";
+    if (what == "rebuilds") rebuilds_allocate_nothing();
+    else return 2;
+    printf("OK\n");
+    return 0;
+}
