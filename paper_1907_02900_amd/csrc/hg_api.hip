@@ -177,6 +177,22 @@ hg_status read_u64(const uint64_t* d, uint64_t* h, hipStream_t s) {
         if (st__ != HG_OK) return st__;      \
     } while (0)
 
+// Up to four device blocks that a table gets together: all of them, or none when
+// one fails.
+struct NewBlocks {
+    void* got[4] = {};
+    int n = 0;
+    ~NewBlocks() {
+        while (n > 0) (void)hipFree(got[--n]);
+    }
+    hipError_t take(void** p, size_t bytes) {
+        HG_TRY(dev_malloc(p, bytes));
+        got[n++] = *p;
+        return hipSuccess;
+    }
+    void keep() { n = 0; }  // they are the table's now
+};
+
 // The probe index (up to 8 bytes per bucket of the range capacity, 64-bit keys
 // 16) and the key-run arrays of long buckets (sized for the worst case: every entry in a long
 // bucket), allocated once per table.
@@ -185,11 +201,36 @@ hg_status ensure_index(hg_table* t) {
     const size_t nc = t->n_cap ? t->n_cap : 1;
     const size_t ks = key_size(t->key_bits);
     const size_t hb = t->V_cap * head_bytes_max(t->key_bits);
-    HG_CALL(dev_malloc((void**)&t->head, hb));
-    HG_CALL(dev_malloc((void**)&t->runs.run_key, nc * ks));
-    HG_CALL(dev_malloc((void**)&t->runs.run_end, nc * 4));
-    HG_CALL(dev_malloc((void**)&t->runs.kperm, nc * 4));
+    NewBlocks blocks;
+    void* head;
+    RunsDev runs;
+    HG_CALL(blocks.take(&head, hb));
+    HG_CALL(blocks.take(&runs.run_key, nc * ks));
+    HG_CALL(blocks.take((void**)&runs.run_end, nc * 4));
+    HG_CALL(blocks.take((void**)&runs.kperm, nc * 4));
+    blocks.keep();
+    t->head = head;
+    t->runs = runs;
     t->bytes += hb + nc * (ks + 8);
+    return HG_OK;
+}
+
+// The length array and flags of a table that keys are erased from.
+hg_status ensure_lengths(hg_table* t, hipStream_t stream) {
+    if (t->len) return HG_OK;
+    const size_t nc = t->n_cap ? t->n_cap : 1;
+    NewBlocks blocks;
+    void *len, *dead, *touched;
+    HG_CALL(blocks.take(&len, t->V_cap * 4));
+    HG_CALL(blocks.take(&dead, nc));
+    HG_CALL(blocks.take(&touched, t->V_cap));
+    HG_CALL(hipMemsetAsync(dead, 0, nc, stream));
+    HG_CALL(hipMemsetAsync(touched, 0, t->V_cap, stream));
+    blocks.keep();
+    t->len = (uint32_t*)len;
+    t->dead = (uint8_t*)dead;
+    t->touched = (uint8_t*)touched;
+    t->bytes += t->V_cap * 5 + nc;
     return HG_OK;
 }
 
@@ -681,14 +722,7 @@ hg_status hg_table_erase(hg_table* t, const void* d_keys, uint64_t m, uint64_t* 
     if (!t || t->V == 0 || (m && !d_keys)) return HG_ERR_INVALID_ARG;
     if (!t->has_head) return HG_ERR_INVALID_ARG;  // needs a V2 table with the probe index
     if (device_ready() != HG_OK) return HG_ERR_DEVICE;
-    if (!t->len) {
-        HG_CALL(dev_malloc((void**)&t->len, t->V_cap * 4));
-        HG_CALL(dev_malloc((void**)&t->dead, t->n_cap ? t->n_cap : 1));
-        HG_CALL(dev_malloc((void**)&t->touched, t->V_cap));
-        t->bytes += t->V_cap * 5 + (t->n_cap ? t->n_cap : 1);
-        HG_CALL(hipMemsetAsync(t->dead, 0, t->n_cap ? t->n_cap : 1, stream));
-        HG_CALL(hipMemsetAsync(t->touched, 0, t->V_cap, stream));
-    }
+    HG_CALL_ST(ensure_lengths(t, stream));
     if (!t->has_len) {
         HG_CALL(init_lengths(t->offsets, t->V, t->len, stream));
         t->has_len = true;

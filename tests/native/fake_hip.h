@@ -24,7 +24,8 @@ struct State {
     size_t kept = 0;             // freed bytes that the pool still holds
     size_t capacity = ~(size_t)0;
     long allocs = 0;             // allocation calls that succeeded
-    long fail_in = -1;           // the call that many ahead fails (0: the next)
+    long fail_in = -1;           // the allocation call that many ahead fails (0: the next),
+    long fail_times = 2;         // and so do those after it: that many in all (a retry too)
     long memsets = 0, memset_fail_in = -1, launches = 0, trims = 0, pools = 0;
     bool capturing = false;
 };
@@ -33,7 +34,11 @@ inline State st;
 inline bool fails(long& in) { return in >= 0 && in-- == 0; }
 
 inline hipError_t alloc(void** p, size_t bytes, bool pooled) {
-    if (fails(st.fail_in)) return hipErrorOutOfMemory;
+    if (st.fail_in == 0 && st.fail_times > 0) {
+        --st.fail_times;
+        return hipErrorOutOfMemory;
+    }
+    if (st.fail_in > 0) --st.fail_in;
     const size_t reuse = pooled ? (bytes < st.kept ? bytes : st.kept) : 0;
     if (bytes - reuse > st.capacity || st.used + st.kept > st.capacity - (bytes - reuse))
         return hipErrorOutOfMemory;

@@ -79,9 +79,59 @@ static void rebuilds_allocate_nothing() {
         }
 }
 
+static uint64_t bytes_of(hg_table* t) {
+    hg_table_info i{};
+    CHECK(hg_table_view(t, &i) == HG_OK, "view");
+    return i.device_bytes;
+}
+
+// A call that runs out of memory half-way leaves the table as it was: the next one
+// allocates everything it needs.
+static void failed_allocations_leave_nothing_half_done() {
+    for (int kb : {32, 64}) {
+        hg_build_opts plain{};
+        plain.no_index = 1;
+        for (long at = 0; at < 4; ++at) {
+            hg_table* t = nullptr;
+            CHECK(hg_build(kKeys, 100000, kb, 1 << 16, 1, &plain, nullptr, &t) == HG_OK, "build");
+            CHECK(bytes_of(t) == st.used, "plain table");
+            const size_t before = st.used;
+            // (the build's workspace comes first)
+            st.fail_in = at + 1;
+            st.fail_times = 2;
+            CHECK(hg_table_build(t, kKeys, 90000, 1 << 16, 1, nullptr, nullptr) == HG_ERR_OOM,
+                  "index array %ld", at);
+            CHECK(st.used == before, "index array %ld: %zu bytes kept", at, st.used - before);
+            st.fail_in = -1;
+            CHECK(hg_table_build(t, kKeys, 90000, 1 << 16, 1, nullptr, nullptr) == HG_OK, "retry");
+            CHECK(bytes_of(t) == st.used && st.used > before, "index after array %ld failed", at);
+            hg_table_free(t);
+            CHECK(st.live.empty(), "left over");
+        }
+        for (int at = 0; at < 5; ++at) {  // three arrays, two fills
+            hg_table* t = nullptr;
+            CHECK(hg_build(kKeys, 100000, kb, 1 << 16, 1, nullptr, nullptr, &t) == HG_OK, "build");
+            const size_t before = st.used;
+            st.fail_times = 2;
+            if (at < 3) st.fail_in = at;
+            else st.memset_fail_in = at - 3;
+            CHECK(hg_table_erase(t, kKeys, 10, nullptr, nullptr) != HG_OK, "erase, failure %d", at);
+            CHECK(st.used == before, "failure %d: %zu bytes kept", at, st.used - before);
+            st.fail_in = st.memset_fail_in = -1;
+            st.memsets = 0;
+            CHECK(hg_table_erase(t, kKeys, 10, nullptr, nullptr) == HG_OK, "retry");
+            CHECK(bytes_of(t) == st.used && st.used > before && st.memsets == 2,
+                  "erase after failure %d", at);
+            hg_table_free(t);
+            CHECK(st.live.empty(), "left over");
+        }
+    }
+}
+
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "rebuilds") rebuilds_allocate_nothing();
+    else if (what == "failures") failed_allocations_leave_nothing_half_done();
     else return 2;
     printf("OK\n");
     return 0;

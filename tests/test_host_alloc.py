@@ -36,3 +36,7 @@ def check(tmp_path_factory):
 
 def test_rebuilds_within_the_capacity_allocate_nothing(check):
     check("rebuilds")
+
+
+def test_a_failed_allocation_leaves_nothing_half_done(check):
+    check("failures")
