@@ -48,6 +48,7 @@ constexpr int kRT = kLocalThreads;      // threads of the per-bucket kernels (51
 constexpr int kCItems = 8;              // entries per thread of a chunk
 constexpr uint32_t kChunk = kRT * kCItems;  // 4096
 constexpr uint32_t kRareGrid = 512;     // two workgroups per CU (LDS)
+constexpr uint32_t kListedGrid = 2048;
 constexpr uint32_t kRangeBits = 8;      // buckets of one workgroup of the slice scan
 constexpr uint32_t kRanges = 1u << (kMaxLocalBits - kRangeBits);  // at most, per bin
 
@@ -647,9 +648,9 @@ __device__ __forceinline__ void listed_of_bin(const Rare<Key>& x, uint32_t g, ui
     }
 }
 
-// First kernel of the rare path: every oversize bin with its long buckets, and the
-// long buckets that the bins in LDS listed; nothing here depends on another
-// workgroup.
+// First kernel of the rare path: every oversize bin and, as MODE says, the split
+// bins' slices or (SOLO) every bin's listed long buckets; nothing here depends on
+// another workgroup.
 // Bound by its longest oversize bin, one workgroup's chunks one after the other:
 // 295 us at 2^26 Zipf(1.2) keys (bins of up to 2^15).  Slices of half that length
 // took it to 202, but their histograms' scan and placement cost as much more.
@@ -663,22 +664,22 @@ __global__ __launch_bounds__(kRT) void k_rare_bins(Rare<Key> x) {
         nsl = a.ctr[kCtrSlices] < a.slice_cap ? a.ctr[kCtrSlices] : a.slice_cap;
     // (one load in flight keeps the kernel with the slices within 128 VGPRs)
     constexpr int U = MODE == kBinsAndSlices ? 1 : 8;
-    const BucketLds<Key> m(smem);
     for (uint32_t i = blockIdx.x; i < nheavy + nsl; i += gridDim.x) {
         if (i < nheavy) heavy_bin<Key, ANY, U>(x, i, smem);
         else slice_hist<Key, U>(x, i - nheavy, smem);
         __syncthreads();
     }
-    if (!x.ix.head) return;
+    if (MODE != kSolo || !x.ix.head) return;
     // the long buckets of this workgroup's oversize bins, and of the bins held
     // in LDS when one of them listed any (kCtrListed, which no workgroup of this
     // launch writes)
+    const BucketLds<Key> m(smem);
     const uint32_t nlight = a.ctr[kCtrListed] ? a.bins : 0u;
     for (uint32_t i = blockIdx.x; i < nheavy + nlight; i += gridDim.x) {
         const uint32_t g = i < nheavy ? a.heavy_list[i] : i - nheavy;
         if (i >= nheavy && a.bin_start[g + 1] - a.bin_start[g] > light_cap<Key>()) continue;
         const uint32_t listed = x.ix.gen_cnt[g];
-        if (listed) listed_of_bin<Key, MODE == kSolo>(x, g, listed, m);
+        if (listed) listed_of_bin<Key, true>(x, g, listed, m);
         __syncthreads();
     }
 }
@@ -784,16 +785,34 @@ __global__ __launch_bounds__(kRT) void k_slice_place(Rare<Key> x) {
     }
 }
 
-// Probe index entries and long buckets of the split bins.
+// Probe index entries of the split bins, and the listed long buckets of every bin:
+// split, oversize, and held in LDS.  Apart from k_rare_bins because the stable
+// placement takes 124 to 144 VGPRs there, one workgroup per CU for 64-bit keys, and a
+// long bucket's sort is a chain of LDS steps that lives on the second one: 2^24
+// 64-bit keys in 2^18 buckets, every bucket listed, stable: the build took 4841 us with
+// both in one kernel, now 2928.  The grid gives a build of up to 1024 bins a workgroup
+// per bin: with 512 workgroups of up to three bins each, 2^22 32-bit keys in 2^16
+// buckets, eight of a key, took 880 us, now 692.
 template <typename Key>
-__global__ __launch_bounds__(kRT) void k_split_index(Rare<Key> x) {
+__global__ __launch_bounds__(kRT) void k_listed_runs(Rare<Key> x) {
     extern __shared__ __align__(16) unsigned char smem[];
     const RareArgs& a = x.a;
     const uint32_t nh = a.ctr[kCtrSplit] < a.huge_cap ? a.ctr[kCtrSplit] : a.huge_cap;
+    const uint32_t nheavy = a.ctr[kCtrHeavy];
+    const uint32_t nlight = a.ctr[kCtrListed] ? a.bins : 0u;
     const BucketLds<Key> m(smem);
-    for (uint32_t i = blockIdx.x; i < nh; i += gridDim.x) {
-        split_index<Key>(x, i, smem);
-        const uint32_t g = a.huge_list[i], listed = x.ix.gen_cnt[g];
+    for (uint32_t i = blockIdx.x; i < nh + nheavy + nlight; i += gridDim.x) {
+        uint32_t g;
+        if (i < nh) {
+            g = a.huge_list[i];
+            split_index<Key>(x, i, smem);
+        } else if (i < nh + nheavy) {
+            g = a.heavy_list[i - nh];
+        } else {
+            g = i - nh - nheavy;
+            if (a.bin_start[g + 1] - a.bin_start[g] > light_cap<Key>()) continue;
+        }
+        const uint32_t listed = x.ix.gen_cnt[g];
         if (listed) listed_of_bin<Key, false>(x, g, listed, m);
         __syncthreads();
     }
@@ -921,7 +940,7 @@ hipError_t set_rare_smem() {
         HG_TRY(hipFuncSetAttribute((const void*)k_rare_bins<Key, kBinsAndSlices, false>, at, lim));
         HG_TRY(hipFuncSetAttribute((const void*)k_slice_place<Key, true>, at, lim));
         HG_TRY(hipFuncSetAttribute((const void*)k_slice_place<Key, false>, at, lim));
-        HG_TRY(hipFuncSetAttribute((const void*)k_split_index<Key>, at, lim));
+        HG_TRY(hipFuncSetAttribute((const void*)k_listed_runs<Key>, at, lim));
         return hipFuncSetAttribute((const void*)k_runs_chunk_sort<Key>, at, lim);
     });
 }
@@ -938,8 +957,9 @@ hipError_t run_rare(const RareArgs& a, uint32_t* offsets, uint32_t* ids, Key* ek
     HG_TRY(set_rare_smem<Key>());
     const Rare<Key> x{a, offsets, ids, ekeys, hp, ix, rkeys, rids, rkeys, rids,
                       layout_g2(ws, n).g};
-    const size_t lds = rare_smem<Key>(a.k), blds = BucketLds<Key>::bytes();
     const bool solo = n <= a.slice;  // no bin is split
+    const size_t blds = BucketLds<Key>::bytes();
+    const size_t lds = solo ? rare_smem<Key>(a.k) : heavy_smem<Key>(a.k);
     const dim3 gb(a.bins < kRareGrid ? a.bins : kRareGrid), th(kRT);
     {
         HG_PROF("v2_rare_bins", s);
@@ -967,7 +987,8 @@ hipError_t run_rare(const RareArgs& a, uint32_t* offsets, uint32_t* ids, Key* ek
     hipLaunchKernelGGL(place, dim3(kRareGrid), th, heavy_smem<Key>(a.k), s, x);
     HG_TRY(hipGetLastError());
     if (!ix.head) return hipSuccess;
-    hipLaunchKernelGGL(k_split_index<Key>, dim3(256), th, blds, s, x);
+    hipLaunchKernelGGL(k_listed_runs<Key>, dim3(a.bins < kListedGrid / 2 ? 2 * a.bins : kListedGrid),
+                       th, blds, s, x);
     HG_TRY(hipGetLastError());
     // long buckets in chunks: grids sized for the most work there can be,
     // strided over what the counters hold
