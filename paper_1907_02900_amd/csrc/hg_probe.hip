@@ -391,30 +391,6 @@ __global__ __launch_bounds__(kProbeThreads) void k_probe_pairs(
     }
 }
 
-// Alg. 3 over B's edges p: count the entries of A's bucket h(key_p) equal to
-// key_p.  A and B share hash parameters, so h is recomputed from B's key.  A's
-// buckets come in increasing order, so its index entries (W) are streamed:
-// they are smaller than its offsets and keys together.  (64-bit keys: 16 bytes
-// per bucket would cost more than the offsets; the index is read for long
-// buckets only.)
-template <typename Key, int W, int WE>
-__device__ __forceinline__ uint32_t count_in_a(const View<Key>& a,
-                                               const typename EntryOf<WE>::T& e, Key k,
-                                               uint32_t quot) {
-    if constexpr (W == 16) {
-        if (e.y - e.x > kRunBucket) {
-            const uint32_t h = KeyTraits<Key>::bucket(k, a.hp);
-            return count_long(a, long_ref<Key, 16>(a, h, ((const uint4*)a.head)[h]), k);
-        }
-    }
-    if constexpr (WE == 0) {
-        return count_in_bucket(a.keys, e.x, e.y, k);
-    } else {
-        const uint32_t c = count_settled<Key, WE>(a, e, k, quot);
-        return c != kUnsettled ? c : count_unsettled<Key, WE>(a, e, k, KeyTraits<Key>::bucket(k, a.hp));
-    }
-}
-
 // Whether slot p of B, holding key k, is stale (behind its bucket's live
 // entries after an erase): such slots get edge count 0 and no count by input.
 template <typename Key>
@@ -424,6 +400,15 @@ __device__ __forceinline__ bool stale(const View<Key>& b, uint64_t p, Key k) {
     return p - b.off[h] >= b.len[h];
 }
 
+// Alg. 3 over B's edges p: count the entries of A's bucket h(key_p) equal to
+// key_p.  A and B share hash parameters, so h is recomputed from B's key.
+//
+// With A's index (W = 4 or 8) or without one (W = 0).  A's buckets come in
+// increasing order, so its index entries are streamed: they are smaller than its
+// offsets and keys together.  A thread's counts are stored after the last of its
+// loads, since a load waits for the stores before it: 2^23 edges by 2^20 to 2^24
+// buckets without the index 27 to 66 us, now 25 to 63 (64-bit keys 34 to 79, now 31 to
+// 76).
 template <typename Key, int W>
 __global__ __launch_bounds__(kProbeThreads) void k_intersect_count(
     View<Key> a, View<Key> b, uint64_t nb, uint32_t* __restrict__ edge_counts,
@@ -432,9 +417,8 @@ __global__ __launch_bounds__(kProbeThreads) void k_intersect_count(
     uint64_t sum = 0;
     const uint64_t base = (uint64_t)blockIdx.x * (kProbeThreads * kProbeItems) + threadIdx.x;
     Key kk[kProbeItems];
-    uint32_t quot[kProbeItems];
-    constexpr int WE = W == 16 ? 0 : W;  // 64-bit keys read the offsets (see above)
-    typename EntryOf<WE>::T e[kProbeItems];
+    uint32_t quot[kProbeItems], c[kProbeItems];
+    typename EntryOf<W>::T e[kProbeItems];
 #pragma unroll
     for (int r = 0; r < kProbeItems; ++r) {
         const uint64_t p = base + (uint64_t)r * kProbeThreads;
@@ -444,25 +428,95 @@ __global__ __launch_bounds__(kProbeThreads) void k_intersect_count(
     for (int r = 0; r < kProbeItems; ++r) {
         const uint64_t p = base + (uint64_t)r * kProbeThreads;
         quot[r] = 0;
-        e[r] = typename EntryOf<WE>::T{};
-        if (p < nb) {
-            const uint32_t h = locate(a, kk[r], quot[r]);
-            e[r] = entry_at<Key, WE>(a, h);
-            if constexpr (W == 16)
-                if (a.len) e[r].y = e[r].x + a.len[h];
+        e[r] = typename EntryOf<W>::T{};
+        if (p < nb) e[r] = entry_at<Key, W>(a, locate(a, kk[r], quot[r]));
+    }
+    uint32_t gone = 0;  // stale slots of B, as bits
+#pragma unroll
+    for (int r = 0; r < kProbeItems; ++r) {
+        const uint64_t p = base + (uint64_t)r * kProbeThreads;
+        c[r] = 0;
+        if (p >= nb) continue;
+        if (stale(b, p, kk[r])) {
+            gone |= 1u << r;
+        } else if constexpr (W == 0) {
+            c[r] = count_in_bucket(a.keys, e[r].x, e[r].y, kk[r]);
+        } else {
+            c[r] = count_settled<Key, W>(a, e[r], kk[r], quot[r]);
+            if (c[r] == kUnsettled)
+                c[r] = count_unsettled<Key, W>(a, e[r], kk[r], KeyTraits<Key>::bucket(kk[r], a.hp));
+        }
+        sum += c[r];
+    }
+    if (edge_counts) {
+#pragma unroll
+        for (int r = 0; r < kProbeItems; ++r) {
+            const uint64_t p = base + (uint64_t)r * kProbeThreads;
+            if (p < nb) edge_counts[p] = c[r];
         }
     }
+    if (counts_by_input) {
+#pragma unroll
+        for (int r = 0; r < kProbeItems; ++r) {
+            const uint64_t p = base + (uint64_t)r * kProbeThreads;
+            if (p < nb && !(gone >> r & 1u)) counts_by_input[b.ids[p]] = c[r];
+        }
+    }
+    if (total) {
+        uint64_t all;
+        block_excl_scan64<kProbeThreads>(sum, red, &all);
+        if (threadIdx.x == 0) total[1 + blockIdx.x] = all;  // reduced by sum_u64
+    }
+}
+
+// Matches of k in A's bucket h, by its offsets: a scan, or A's key runs when the
+// bucket is long and has them.
+template <typename Key>
+__device__ __forceinline__ uint32_t count_by_offsets(const uint32_t* __restrict__ a_off,
+                                                     const uint32_t* __restrict__ a_len,
+                                                     const uint4* __restrict__ a_head,
+                                                     const Runs<Key>& runs,
+                                                     const Key* __restrict__ a_keys, uint32_t h,
+                                                     Key k) {
+    const uint32_t lo = a_off[h], hi = a_len ? lo + a_len[h] : a_off[h + 1];
+    if (hi - lo > kRunBucket) {
+        const uint4 e = a_head[h];
+        uint32_t gb, ge;
+        if (e.z != 0)
+            return run_group(LongRef{e.y, e.y + e.x, e.z}, runs, k, &gb, &ge) ? ge - gb : 0u;
+    }
+    return count_in_bucket(a_keys, lo, hi, k);
+}
+
+// With an index of 16-byte entries, which would cost more to stream than the two
+// offsets: they are read for long buckets only.  One edge after the other, each
+// loaded and counted before the next: as a batch like the above, with the branch for
+// long buckets in it, 2^23 64-bit edges by 2^20 to 2^24 buckets of load 0.25 to 4 took
+// 37 to 93 us, so 30 to 79.
+template <typename Key>
+__global__ __launch_bounds__(kProbeThreads) void k_intersect_scan(
+    const uint32_t* __restrict__ a_off, const uint32_t* __restrict__ a_len,
+    const uint4* __restrict__ a_head, Runs<Key> runs, const Key* __restrict__ a_keys,
+    const uint32_t* __restrict__ b_off, const uint32_t* __restrict__ b_len,
+    const Key* __restrict__ b_keys, const uint32_t* __restrict__ b_ids, uint64_t nb,
+    typename KeyTraits<Key>::Params hp, uint32_t* __restrict__ edge_counts,
+    uint32_t* __restrict__ counts_by_input, unsigned long long* __restrict__ total) {
+    __shared__ uint64_t red[kProbeThreads / kWave + 1];
+    uint64_t sum = 0;
+    const uint64_t base = (uint64_t)blockIdx.x * (kProbeThreads * kProbeItems) + threadIdx.x;
 #pragma unroll
     for (int r = 0; r < kProbeItems; ++r) {
         const uint64_t p = base + (uint64_t)r * kProbeThreads;
         if (p < nb) {
-            if (stale(b, p, kk[r])) {
+            const Key k = b_keys[p];
+            const uint32_t h = KeyTraits<Key>::bucket(k, hp);
+            if (b_len && p - b_off[h] >= b_len[h]) {
                 if (edge_counts) edge_counts[p] = 0;
                 continue;
             }
-            const uint32_t c = count_in_a<Key, W, WE>(a, e[r], kk[r], quot[r]);
+            const uint32_t c = count_by_offsets(a_off, a_len, a_head, runs, a_keys, h, k);
             if (edge_counts) edge_counts[p] = c;
-            if (counts_by_input) counts_by_input[b.ids[p]] = c;
+            if (counts_by_input) counts_by_input[b_ids[p]] = c;
             sum += c;
         }
     }
@@ -588,9 +642,17 @@ hipError_t run_intersect_counts(const TableDev& a, const TableDev& b, uint32_t* 
     {
         HG_PROF("intersect_count", s);
         with_entry<Key>(a, [&](auto w) {
-            hipLaunchKernelGGL((k_intersect_count<Key, decltype(w)::value>), dim3(grid),
-                               dim3(kProbeThreads), 0, s, view_of<Key>(a), view_of<Key>(b), b.n,
-                               edge_counts, counts_by_input, d_total);
+            constexpr int W = decltype(w)::value;
+            if constexpr (W != 16)
+                hipLaunchKernelGGL((k_intersect_count<Key, W>), dim3(grid), dim3(kProbeThreads), 0, s,
+                                   view_of<Key>(a), view_of<Key>(b), b.n, edge_counts,
+                                   counts_by_input, d_total);
+            else
+                hipLaunchKernelGGL(k_intersect_scan<Key>, dim3(grid), dim3(kProbeThreads), 0, s,
+                                   a.offsets, a.len, (const uint4*)a.head, view_of<Key>(a).runs,
+                                   (const Key*)a.keys, b.offsets, b.len, (const Key*)b.keys, b.ids,
+                                   b.n, KeyTraits<Key>::make(a.V, a.seed), edge_counts,
+                                   counts_by_input, d_total);
         });
     }
     HG_TRY(hipGetLastError());
