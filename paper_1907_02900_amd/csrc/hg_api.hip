@@ -193,14 +193,13 @@ struct NewBlocks {
     void keep() { n = 0; }  // they are the table's now
 };
 
-// The probe index (up to 8 bytes per bucket of the range capacity, 64-bit keys
-// 16) and the key-run arrays of long buckets (sized for the worst case: every entry in a long
-// bucket), allocated once per table.
+// The probe index and the key-run arrays of long buckets (sized for the worst case:
+// every entry in a long bucket), allocated once per table.
 hg_status ensure_index(hg_table* t) {
     if (t->head) return HG_OK;
     const size_t nc = t->n_cap ? t->n_cap : 1;
     const size_t ks = key_size(t->key_bits);
-    const size_t hb = t->V_cap * head_bytes_max(t->key_bits);
+    const size_t hb = index_bytes(t->n_cap, t->V_cap, t->key_bits);
     NewBlocks blocks;
     void* head;
     RunsDev runs;

@@ -1036,7 +1036,7 @@ struct Server {
     static uint64_t table_bytes(uint64_t n, uint64_t V, int kb, bool index) {
         const uint64_t nn = n ? n : 1;
         return (V + 1) * 4 + nn * (4 + (uint64_t)kb / 8) +
-               (index ? V * head_fmt(n, V, kb).bytes + nn * ((uint64_t)kb / 8 + 8) : 0);
+               (index ? V * index_fmt(n, V, kb).bytes + nn * ((uint64_t)kb / 8 + 8) : 0);
     }
 
     void free_table(STable& t, hipStream_t s) {
@@ -1052,7 +1052,7 @@ struct Server {
         t.ids = c.take<uint32_t>(nn);
         t.keys = c.take<char>(nn * ks);
         if (t.has_index) {
-            t.head = c.take<char>(t.V * head_fmt(t.n, t.V, t.key_bits).bytes);
+            t.head = c.take<char>(t.V * index_fmt(t.n, t.V, t.key_bits).bytes);
             t.runs.run_key = c.take<char>(nn * ks);
             t.runs.run_end = c.take<uint32_t>(nn);
             t.runs.kperm = c.take<uint32_t>(nn);
@@ -1364,7 +1364,7 @@ struct Server {
                 TableDev d{t.offsets, t.ids, t.keys, t.n, t.V, t.seed};
                 if (t.has_index) {
                     d.head = t.head;
-                    d.fmt = head_fmt(t.n, t.V, kb);
+                    d.fmt = index_fmt(t.n, t.V, kb);
                     d.runs = t.runs;
                 }
                 e = kb == 32 ? run_probe_counts<uint32_t>(d, (const uint32_t*)rq0.data, rq0.count,

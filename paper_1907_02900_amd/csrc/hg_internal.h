@@ -277,19 +277,19 @@ constexpr uint32_t kRunBucket = 32;
 //           more than the remaining bits hold)
 // Codes 14 and 15 find the bucket through the offsets when the entry does not
 // settle a query.
-// (The entries were 16 bytes, {len, key0, key1, key2}: at 2^28 buckets 4 GiB
-// of the build's writes, and windows of the grouped probe twice an XCD's L2.)
+// (With entries of 16 bytes, {len, key0, key1, key2}, the index of 2^28 buckets is 4
+// GiB of the build's writes, and windows of the grouped probe twice an XCD's L2.)
 // `one` has bit 0 of every field set, `low` all but the top bit of every
 // field and `high` the top bits: they compare all fields with a quotient at
 // once (held_matches).
 struct HeadFmt {
-    uint32_t bytes = 0;  // 4 or 8; 16: 64-bit keys
+    uint32_t bytes = 0;  // 4 or 8; 16: wide entries, of keys (index_fmt)
     uint32_t qb = 0, cap = 0, nf = 0;
     uint64_t one = 0, low = 0, high = 0;
 };
 constexpr uint32_t kCodeMedium = 14, kCodeLong = 15, kMaxHeld = 13;
 
-// Four bytes when they hold the buckets that matter: a query that hits sees
+// Quotient entries: four bytes when they hold the buckets that matter: a query that hits sees
 // a bucket of 1 + Poisson(n / V) keys, of which a capacity of 2 + 2n/V leaves
 // out at most 2% at loads 0.25 to 8; else eight.
 inline HeadFmt head_fmt(uint64_t n, uint64_t V, int key_bits) {
@@ -316,8 +316,51 @@ inline HeadFmt head_fmt(uint64_t n, uint64_t V, int key_bits) {
     return f;
 }
 
-// Bytes of index memory per bucket that any build of these keys may need.
-inline size_t head_bytes_max(int key_bits) { return key_bits == 64 ? 16 : 8; }
+// Wide entries, 16 bytes {len, y, z, w}, in which buckets longer than the entry holds
+// are found without the offsets:
+//   32-bit keys, len <= 3           y, z, w = the keys (unused: 0)
+//   32-bit keys, len <= kRunBucket  y = start, z = the first key, w = how many equal
+//                                   it (8 bits) and a 24-bit filter_bit filter of
+//                                   the other keys
+//   64-bit keys, len <= kRunBucket  y = start, z and w = the key of a bucket of one,
+//                                   or the filter of the keys of more (filter_bits64)
+//   longer                          y = start, z = key runs (0: none, after an
+//                                   erase), w = the key of a single run (32 bits)
+constexpr uint32_t kWideKeys = 3;
+
+// The entries of a table: wide ones for 64-bit keys, and for 32-bit keys where eight
+// bytes of quotients leave out too many of the buckets that a hit sees (1 + Poisson(n /
+// V) keys), whose offsets and edges then come after the entry.  A quotient takes 32
+// bits at V = 1, 21 below 2^12 (two a bucket), 16 at 2^16 and 8 at 2^24, and the larger
+// the table, the more half the bytes are worth.  2^24 queries in input order, entries
+// of 8 : 16 bytes, at the loads on either side of each line: V = 2^10 load 0.5, 67 : 51
+// us; 2^14 load 0.5 and 1, 84 : 85 and 99 : 92; 2^17 load 1.5 and 3, 118 : 120 and 167 :
+// 157; 2^21 load 5 and 6, 453 : 457 and 510 : 495; 2^24 load 8, 700 : 735 (its build 1981
+// : 1644).  Fewer queries, intersections and builds move with them.
+inline bool wide_entries(uint64_t n, uint64_t V) {
+    if (V < (1u << 12)) return true;
+    const uint64_t halves = V <= (1u << 16) ? 1 : V <= (1u << 18) ? 3 : V <= (1u << 22) ? 10 : 16;
+    return 2 * n > halves * V;
+}
+inline HeadFmt index_fmt(uint64_t n, uint64_t V, int key_bits) {
+    if (key_bits == 32 && !wide_entries(n, V)) return head_fmt(n, V, key_bits);
+    HeadFmt f;
+    f.bytes = 16;
+    return f;
+}
+
+// The most index memory that a build of up to n_cap keys and V_cap buckets needs: with
+// n_cap keys entries are wide up to some range, the smaller n the smaller it is.
+inline size_t index_bytes(uint64_t n_cap, uint64_t V_cap, int key_bits) {
+    if (key_bits == 64) return V_cap * 16;
+    uint64_t a = 1, b = V_cap;  // the last wide range of [1, V_cap]
+    while (a < b) {
+        const uint64_t m = a + (b - a + 1) / 2;
+        if (wide_entries(n_cap, m)) a = m;
+        else b = m - 1;
+    }
+    return a * 16 > V_cap * 8 ? a * 16 : V_cap * 8;
+}
 
 // Filter bit (of nf) of a quotient.
 __host__ __device__ inline uint32_t filter_bit(uint32_t q, uint32_t nf) {
@@ -385,10 +428,10 @@ __host__ __device__ inline uint64_t filter_bits64(uint64_t k) {
 // from st: runs are cumulative), and kperm[st .. st + len) lists the bucket's
 // ids grouped by key in run order, in bucket order inside each group.  A
 // bucket of one repeated key (R = 1) writes no kperm: its ids are the edge
-// array's own.  64-bit keys: the bucket's probe index entry is {len, st, R, 0},
-// and R = 0 marks a long bucket without runs (after an erase), which probes
-// scan.  32-bit keys (HeadFmt): run_end[st + len - 1] is R for R > 1 (when
-// R = len that is the last run's end, else the place is free).
+// array's own.  Wide entries hold R, and R = 0 marks a long bucket without runs
+// (after an erase), which probes scan.  Quotient entries (HeadFmt): run_end[st +
+// len - 1] is R for R > 1 (when R = len that is the last run's end, else the place
+// is free).
 struct RunsDev {
     void* run_key = nullptr;     // Key[n]
     uint32_t* run_end = nullptr; // [n]
@@ -449,7 +492,7 @@ hipError_t run_rare(const RareArgs& a, uint32_t* offsets, uint32_t* ids, Key* ek
                     typename KeyTraits<Key>::Params hp, const IndexOut& ix, Key* rkeys,
                     uint32_t* rids, void* ws, hipStream_t s);
 
-// ix.head (may be null): V probe index entries (head_fmt(n, V, key width)), one
+// ix.head (may be null): V probe index entries (index_fmt(n, V, key width)), one
 // per bucket, and the key-run summary of long buckets (IndexOut).  stable: ids ascend inside
 // every bucket (otherwise their order there is unspecified).
 template <typename Key>

@@ -3,8 +3,8 @@
 // HashGraph-Probe-Standard: each query is hashed with Eq. 1, the bucket's
 // segment [offsets[h], offsets[h+1]) of the edge array is scanned, and every
 // entry with an equal key is counted (all instances, not the first).  When
-// the V2 build wrote the per-bucket probe index, one entry of 4 or 8 bytes
-// (64-bit keys: 16) answers most queries instead (HeadFmt), so they cost one
+// the V2 build wrote the per-bucket probe index, one entry of 4, 8 or 16 bytes
+// answers most queries instead (HeadFmt, wide_entries), so they cost one
 // random read.  Each thread owns several queries (coalesced, strided by the
 // block) and issues all their entry or offset loads before using any, to keep
 // many random reads in flight.  Pairs are written in a second pass at
@@ -84,7 +84,7 @@ View<Key> view_of(const TableDev& t) {
 }
 
 // The template parameter W of the kernels: bytes of an index entry (4 or 8:
-// 32-bit keys, 16: 64-bit keys), 0 without the index.
+// quotients of 32-bit keys, 16: wide entries), 0 without the index.
 template <int W>
 struct EntryOf;
 template <>
@@ -185,7 +185,16 @@ template <typename Key, int W>
 __device__ __forceinline__ uint32_t count_settled(const View<Key>& t,
                                                   const typename EntryOf<W>::T& e, Key q,
                                                   uint32_t quot) {
-    if constexpr (W == 16) {
+    if constexpr (W == 16 && sizeof(Key) == 4) {
+        const uint32_t len = e.x;
+        if (len <= kWideKeys)
+            return (len >= 1 && e.y == q) + (len >= 2 && e.z == q) + (len >= 3 && e.w == q);
+        // {len, start, first key, its count | filter of the others}, or {len,
+        // start, runs, the key of a single run}
+        if (len > kRunBucket) return e.z != 1 ? kUnsettled : e.w == q ? len : 0u;
+        if (e.z == q) return e.w & 0xffu;
+        return (e.w >> (8 + filter_bit(q, 24))) & 1u ? kUnsettled : 0u;
+    } else if constexpr (W == 16) {
         const uint32_t len = e.x;
         const uint64_t f = (uint64_t)e.z | ((uint64_t)e.w << 32);
         if (len <= 1) return len == 1 && f == (uint64_t)q ? 1u : 0u;
@@ -210,6 +219,12 @@ __device__ __forceinline__ uint32_t count_settled(const View<Key>& t,
     }
 }
 
+// The keys of a wide entry of at most kWideKeys 32-bit keys that equal q, as a mask.
+__device__ __forceinline__ uint32_t wide_mask(const uint4& e, uint32_t q) {
+    return (e.x >= 1 && e.y == q ? 1u : 0u) | (e.x >= 2 && e.z == q ? 2u : 0u) |
+           (e.x >= 3 && e.w == q ? 4u : 0u);
+}
+
 // Matches of q in bucket h, whose entry e does not settle them.
 template <typename Key, int W>
 __device__ __forceinline__ uint32_t count_unsettled(const View<Key>& t,
@@ -217,7 +232,8 @@ __device__ __forceinline__ uint32_t count_unsettled(const View<Key>& t,
                                                     uint32_t h) {
     if constexpr (W == 16) {
         if (e.x > kRunBucket) return count_long(t, long_ref<Key, W>(t, h, e), q);
-        return count_in_bucket(t.keys, e.y, e.y + e.x, q);
+        // (32-bit keys: the first key is settled)
+        return count_in_bucket(t.keys, e.y + (sizeof(Key) == 4 ? 1u : 0u), e.y + e.x, q);
     } else {
         if (((uint32_t)e & 15u) == kCodeLong) return count_long(t, long_ref<Key, W>(t, h, e), q);
         const uint32_t lo = t.off[h];
@@ -292,6 +308,10 @@ __global__ __launch_bounds__(kProbeThreads) void k_probe_count(
                                          : 0u);
             }
         }
+        if constexpr (W == 16 && sizeof(Key) == 4) {
+            if (held && j < m)
+                held[j] = (uint16_t)(c && e[r].x <= kWideKeys ? 0x8000u | wide_mask(e[r], qq[r]) : 0u);
+        }
         sum += c;
     }
     if (total) {
@@ -333,7 +353,7 @@ __global__ __launch_bounds__(kProbeThreads) void k_probe_pairs(
         st[r] = 0;
         if (pos[r] == pend[r]) continue;
         if (!mask[r]) e[r] = entry_at<Key, W>(t, hh[r]);
-        if (W == 4 || W == 8) st[r] = t.off[hh[r]];
+        if (W && sizeof(Key) == 4) st[r] = t.off[hh[r]];
     }
 #pragma unroll
     for (int r = 0; r < kProbeItems; ++r) {
@@ -348,9 +368,14 @@ __global__ __launch_bounds__(kProbeThreads) void k_probe_pairs(
         } else {
             bool longb;
             if constexpr (W == 16) {
-                lo = e[r].y;
-                hi = lo + e[r].x;
                 longb = e[r].x > kRunBucket;
+                if constexpr (sizeof(Key) == 4) {
+                    if (!mk && e[r].x <= kWideKeys) mk = wide_mask(e[r], k);
+                    if (!mk) hi = lo + e[r].x;
+                } else {
+                    lo = e[r].y;
+                    hi = lo + e[r].x;
+                }
             } else {
                 const uint32_t code = (uint32_t)e[r] & 15u;
                 if (!mk && code <= kMaxHeld) {
@@ -488,7 +513,7 @@ __device__ __forceinline__ uint32_t count_by_offsets(const uint32_t* __restrict_
     return count_in_bucket(a_keys, lo, hi, k);
 }
 
-// With an index of 16-byte entries, which would cost more to stream than the two
+// With an index of wide entries, which would cost more to stream than the two
 // offsets: they are read for long buckets only.  One edge after the other, each
 // loaded and counted before the next: as a batch like the above, with the branch for
 // long buckets in it, 2^23 64-bit edges by 2^20 to 2^24 buckets of load 0.25 to 4 took
@@ -592,7 +617,8 @@ void with_entry(const TableDev& t, F&& f) {
     if (!t.head) f(std::integral_constant<int, 0>{});
     else if constexpr (sizeof(Key) == 8) f(std::integral_constant<int, 16>{});
     else if (t.fmt.bytes == 4) f(std::integral_constant<int, 4>{});
-    else f(std::integral_constant<int, 8>{});
+    else if (t.fmt.bytes == 8) f(std::integral_constant<int, 8>{});
+    else f(std::integral_constant<int, 16>{});
 }
 
 template <typename Key>

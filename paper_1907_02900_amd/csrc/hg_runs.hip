@@ -1039,9 +1039,11 @@ hipError_t run_build_one(const Key* keys, uint64_t n, uint32_t k, uint32_t V, ui
 HG_ONE_INST(uint32_t, false, 0)
 HG_ONE_INST(uint32_t, false, 4)
 HG_ONE_INST(uint32_t, false, 8)
+HG_ONE_INST(uint32_t, false, 16)
 HG_ONE_INST(uint32_t, true, 0)
 HG_ONE_INST(uint32_t, true, 4)
 HG_ONE_INST(uint32_t, true, 8)
+HG_ONE_INST(uint32_t, true, 16)
 HG_ONE_INST(uint64_t, false, 0)
 HG_ONE_INST(uint64_t, false, 16)
 HG_ONE_INST(uint64_t, true, 0)

@@ -639,7 +639,8 @@ void with_layout(bool any_order, const IndexOut& ix, F&& f) {
         if (!ix.head) f(any, std::integral_constant<int, 0>{});
         else if constexpr (sizeof(Key) == 8) f(any, std::integral_constant<int, 16>{});
         else if (ix.fmt.bytes == 4) f(any, std::integral_constant<int, 4>{});
-        else f(any, std::integral_constant<int, 8>{});
+        else if (ix.fmt.bytes == 8) f(any, std::integral_constant<int, 8>{});
+        else f(any, std::integral_constant<int, 16>{});
     };
     if (any_order) by_width(std::true_type{});
     else by_width(std::false_type{});
@@ -901,9 +902,9 @@ hipError_t set_smem_limits() {
                                    hipFuncAttributeMaxDynamicSharedMemorySize, lim));
         hipError_t le = hipSuccess;
         IndexOut ix{};
-        for (int i = 0; i < 6; ++i) {  // every layout and entry width
+        for (int i = 0; i < 8; ++i) {  // every layout and entry width
             ix.head = i / 2 ? &le : nullptr;
-            ix.fmt.bytes = i / 2 == 1 ? 4 : 8;
+            ix.fmt.bytes = 2u << (i / 2);
             with_layout<Key>(i & 1, ix, [&](auto any, auto width) {
                 const hipError_t e = hipFuncSetAttribute(
                     (const void*)k_local_light<Key, decltype(any)::value, decltype(width)::value>,
@@ -975,14 +976,14 @@ hipError_t run_build_v2(const Key* keys, uint64_t n, uint64_t V, uint64_t seed, 
     ix.k = 0;
     ix.bins = 0;
     if (n == 0) {
-        ix.fmt = head_fmt(0, V, sizeof(Key) * 8);
+        ix.fmt = index_fmt(0, V, sizeof(Key) * 8);
         if (ix.head) HG_TRY(fill_u32((uint32_t*)ix.head, ix.fmt.bytes / 4 * V, 0u, s));
         return fill_u32(offsets, V + 1, 0u, s);
     }
     const V2Plan p = plan_v2(n, V, sizeof(Key) * 8, bins_hint, !stable);
     ix.k = p.k;
     ix.bins = p.bins;
-    ix.fmt = head_fmt(n, V, sizeof(Key) * 8);
+    ix.fmt = index_fmt(n, V, sizeof(Key) * 8);
     ix.hp = make_hash_params(V, seed);
     V2Ws w;
     layout_v2(ws, p, sizeof(Key), &w);

@@ -320,12 +320,34 @@ __device__ __forceinline__ void store_word(const IndexOut& ix, uint32_t bucket, 
     else ((uint64_t*)ix.head)[bucket] = w;
 }
 
-// 64-bit keys: {len, start, low and high half of the key} for a bucket of at
-// most one key, {len, start, filter of all its keys (filter_bits64), low and
-// high half} for a longer one, so that most queries matching none of its keys
-// skip the edge array.  A bucket longer than kRunBucket later gets its
-// key-run summary in z.  `k` points at the bucket's first key.
-__device__ __forceinline__ uint4 head_entry64(uint32_t start, uint32_t end, const uint64_t* k) {
+// Wide entry of a bucket (wide_entries); one longer than kRunBucket later gets its
+// key-run summary in z and w.  `k` points at the bucket's first key.
+__device__ __forceinline__ uint4 wide_entry(uint32_t start, uint32_t end, const uint32_t* k) {
+    const uint32_t len = end - start;
+    if (len <= kWideKeys)
+        return make_uint4(len, len >= 1 ? k[0] : 0u, len >= 2 ? k[1] : 0u, len >= 3 ? k[2] : 0u);
+    const uint32_t k0 = k[0];
+    uint32_t c0 = 0, filt = 0;
+    if (len <= kRunBucket) {
+        c0 = 1;
+        // four keys per round, so that their loads overlap
+#pragma unroll 1
+        for (uint32_t i = 1; i < len; i += 4) {
+            uint32_t kv[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) kv[j] = i + j < len ? k[i + j] : k0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (i + j >= len) continue;
+                if (kv[j] == k0) ++c0;
+                else filt |= 1u << filter_bit(kv[j], 24);
+            }
+        }
+    }
+    return make_uint4(len, start, k0, c0 | filt << 8);
+}
+
+__device__ __forceinline__ uint4 wide_entry(uint32_t start, uint32_t end, const uint64_t* k) {
     const uint32_t len = end - start;
     uint64_t z = len == 1 ? k[0] : 0ull;
     if (len >= 2 && len <= kRunBucket) {
@@ -341,28 +363,38 @@ __device__ __forceinline__ uint4 head_entry64(uint32_t start, uint32_t end, cons
     return make_uint4(len, start, (uint32_t)z, (uint32_t)(z >> 32));
 }
 
+// Whether a table's entries are wide; W: their bytes where the caller knows them,
+// else 0.
+template <typename Key, int W>
+__device__ __forceinline__ bool is_wide(const IndexOut& ix) {
+    return sizeof(Key) == 8 || (W ? W == 16 : ix.fmt.bytes == 16);
+}
+
 // Writes the index entry of a bucket of at most kRunBucket entries, edge
 // positions [start, end), whose first key is at k (LDS or global).
-template <typename Key>
+template <typename Key, int W = 0>
 __device__ __forceinline__ void put_short(const IndexOut& ix, uint32_t bucket, uint32_t start,
                                           uint32_t end, const Key* k) {
-    if constexpr (sizeof(Key) == 4) {
+    if (is_wide<Key, W>(ix)) {
+        ((uint4*)ix.head)[bucket] = wide_entry(start, end, k);
+    } else if constexpr (sizeof(Key) == 4) {
         store_word(ix, bucket, short_word(ix.fmt, end - start, [&](uint32_t i) {
                        uint32_t h;
                        return KeyTraits<uint32_t>::quotient(k[i], ix.hp, h);
                    }));
-    } else {
-        ((uint4*)ix.head)[bucket] = head_entry64(start, end, k);
     }
 }
 
 // Writes the index entry of a long bucket of R key runs (R = 0: none), whose
-// first key `lead` clead entries equal, and (32-bit keys) R itself behind the
+// first key `lead` clead entries equal, and (quotient entries) R itself behind the
 // runs.
-template <typename Key>
+template <typename Key, int W = 0>
 __device__ __forceinline__ void put_long(const IndexOut& ix, uint32_t bucket, uint32_t len,
                                          uint32_t start, uint32_t R, Key lead, uint32_t clead) {
-    if constexpr (sizeof(Key) == 4) {
+    if (is_wide<Key, W>(ix)) {
+        ((uint4*)ix.head)[bucket] =
+            make_uint4(len, start, R, sizeof(Key) == 4 && R == 1 ? (uint32_t)lead : 0u);
+    } else if constexpr (sizeof(Key) == 4) {
         uint32_t h;
         const uint32_t room = 8 * ix.fmt.bytes - 6 - ix.fmt.qb;  // at least 17 bits
         uint64_t w = (uint64_t)KeyTraits<uint32_t>::quotient(lead, ix.hp, h) << 6 |
@@ -370,8 +402,6 @@ __device__ __forceinline__ void put_long(const IndexOut& ix, uint32_t bucket, ui
         if (R && (room >= 32 || clead >> room == 0)) w |= (uint64_t)clead << (6 + ix.fmt.qb);
         store_word(ix, bucket, w);
         if (R > 1) ix.runs.run_end[start + len - 1] = R;
-    } else {
-        ((uint4*)ix.head)[bucket] = make_uint4(len, start, R, 0u);
     }
 }
 
@@ -441,19 +471,19 @@ __device__ __forceinline__ void wave_sort_pairs(Key& k, uint32_t& p) {
     }
 }
 
-// Buckets whose index entry one lane builds key by key (32-bit keys: those
-// past the entry's capacity, whose quotients it hashes again).  Longer ones up
+// Buckets whose index entry one lane builds key by key (quotient entries: those
+// past the entry's capacity, whose keys it hashes again).  Longer ones up
 // to kRunBucket entries -- common only when keys repeat many times -- are
 // listed and built by groups of 32 lanes (bin_medium_heads) instead of one
 // lane walking them.
-template <typename Key>
-__host__ __device__ constexpr uint32_t head_lane_max() { return sizeof(Key) == 4 ? 8u : 16u; }
+template <int W>
+__host__ __device__ constexpr uint32_t head_lane_max() { return W == 16 ? 16u : 8u; }
 
 // Lists a bucket whose index entry is not one lane's work: the long buckets
 // (more than kRunBucket entries; their entries are written with their key
 // runs) and the medium ones (their entries are written by lane groups), med[]
 // packing lo | len << 13 | v << 19 (v = local bucket).  False: neither.
-template <typename Key>
+template <typename Key, int W>
 __device__ __forceinline__ bool list_bucket(const LongLds<Key>& lr, uint32_t* med, uint32_t v0,
                                             uint32_t v, uint32_t lo, uint32_t hi) {
     const uint32_t len = hi - lo;
@@ -463,7 +493,7 @@ __device__ __forceinline__ bool list_bucket(const LongLds<Key>& lr, uint32_t* me
         lr.bkt[t] = v0 + v;
         return true;
     }
-    if (len > head_lane_max<Key>()) {
+    if (len > head_lane_max<W>()) {
         med[atomicAdd(&lr.cnt[2], 1u)] = lo | (len << 13) | (v << 19);
         return true;
     }
@@ -498,7 +528,7 @@ __device__ __forceinline__ uint32_t group_or(uint32_t f, uint32_t g) {
 // most G: each wave takes 64 / G buckets at a time, lane s of group g holding
 // key s of its bucket; the first key's count is a ballot and the filter an
 // OR over the group -- the same entry put_short builds with one lane.
-template <typename Key, uint32_t G>
+template <typename Key, uint32_t G, int W>
 __device__ __forceinline__ void medium_heads_by(const IndexOut& ix, const uint32_t* list,
                                                 uint32_t n, const Key* skeys, uint32_t out,
                                                 uint32_t v0) {
@@ -517,11 +547,14 @@ __device__ __forceinline__ void medium_heads_by(const IndexOut& ix, const uint32
             // (listed buckets are longer than an entry's capacity)
             const uint64_t eq = ballot(in && kx == k0);
             const uint32_t c0 = (uint32_t)__popcll((eq >> (g * G)) & ((1ull << G) - 1ull));
-            uint32_t h;
-            const uint32_t q = KeyTraits<uint32_t>::quotient(kx, ix.hp, h);
+            uint32_t h, q = kx;
+            if (W != 16) q = KeyTraits<uint32_t>::quotient(kx, ix.hp, h);
+            const uint32_t nf = W == 16 ? 24u : ix.fmt.nf;
             const uint32_t f =
-                group_or<G>((in && kx != k0) ? (1u << filter_bit(q, ix.fmt.nf)) : 0u, g);
-            if (have && s == 0)  // lane 0's key is the first one
+                group_or<G>((in && kx != k0) ? (1u << filter_bit(q, nf)) : 0u, g);
+            if (have && s == 0 && W == 16)
+                ((uint4*)ix.head)[v0 + v] = make_uint4(len, out + lo, (uint32_t)k0, c0 | f << 8);
+            if (have && s == 0 && W != 16)  // lane 0's key is the first one
                 store_word(ix, v0 + v,
                            (uint64_t)kCodeMedium | (uint64_t)c0 << 4 | (uint64_t)q << 12 |
                                (uint64_t)f << (12 + ix.fmt.qb));
@@ -536,12 +569,12 @@ __device__ __forceinline__ void medium_heads_by(const IndexOut& ix, const uint32
 // Index entries of the bin's medium buckets (more than head_lane_max and at
 // most kRunBucket entries).  Called by whole waves after a barrier that
 // follows the list's construction.
-template <typename Key>
+template <typename Key, int W>
 __device__ __forceinline__ void bin_medium_heads(const IndexOut& ix, const LongLds<Key>& lr,
                                                  const uint32_t* med, const Key* skeys,
                                                  uint32_t out, uint32_t v0) {
     static_assert(kRunBucket <= 32u, "a medium bucket fits a group of 32 lanes");
-    medium_heads_by<Key, 32>(ix, med, lr.cnt[2], skeys, out, v0);
+    medium_heads_by<Key, 32, W>(ix, med, lr.cnt[2], skeys, out, v0);
 }
 
 // Key runs and index entry of one long bucket, by one wave: its entries are
@@ -552,7 +585,7 @@ __device__ __forceinline__ void bin_medium_heads(const IndexOut& ix, const LongL
 // slotted in among them.  bk / bp: the wave's 64-entry LDS buffers.  Returns
 // false, having written nothing, when more than 64 entries differ from the
 // lead key (uniform across the wave).
-template <typename Key>
+template <typename Key, int W = 0>
 __device__ __forceinline__ bool wave_bucket_runs(const IndexOut& ix, const Key* keys,
                                                  const uint32_t* ids_, uint32_t lo, uint32_t hi,
                                                  uint32_t st, uint32_t b, Key* bk, uint16_t* bp) {
@@ -580,7 +613,7 @@ __device__ __forceinline__ bool wave_bucket_runs(const IndexOut& ix, const Key* 
         if (lane == 0) {
             rkey[st] = lead;
             rend[st] = len;
-            put_long<Key>(ix, b, len, st, 1u, lead, len);
+            put_long<Key, W>(ix, b, len, st, 1u, lead, len);
         }
         return true;
     }
@@ -609,7 +642,7 @@ __device__ __forceinline__ bool wave_bucket_runs(const IndexOut& ix, const Key* 
     if (lane == 0) {
         rkey[st + rl] = lead;
         rend[st + rl] = nless + clead;
-        put_long<Key>(ix, b, len, st, (uint32_t)__popcll(fb) + 1u, lead, clead);
+        put_long<Key, W>(ix, b, len, st, (uint32_t)__popcll(fb) + 1u, lead, clead);
     }
     // the lead key's ids, in bucket order, after the smaller keys' runs
     uint32_t done = 0;
@@ -629,13 +662,13 @@ __device__ __forceinline__ bool wave_bucket_runs(const IndexOut& ix, const Key* 
 // when there are at most 64, are sorted across the wave's lanes and cut into
 // runs, and the lead run is slotted in among them.  A bucket with more other
 // keys is listed for the general pass.  Whole workgroup; barriers.
-template <typename Key>
+template <typename Key, int W>
 __device__ __forceinline__ void bin_long_runs(const IndexOut& ix, const LongLds<Key>& lr,
                                               const uint32_t* med, const Key* skeys,
                                               const uint32_t* sids, uint32_t out, uint32_t g,
                                               uint32_t v0) {
     __syncthreads();
-    bin_medium_heads<Key>(ix, lr, med, skeys, out, v0);
+    bin_medium_heads<Key, W>(ix, lr, med, skeys, out, v0);
     const uint32_t nl = lr.cnt[0];
     const uint32_t w = threadIdx.x / kWave, lane = lane_id();
     Key* bk = lr.wkey + w * kWave;
@@ -643,7 +676,7 @@ __device__ __forceinline__ void bin_long_runs(const IndexOut& ix, const LongLds<
     for (uint32_t j = w; j < nl; j += W_LOCAL) {
         const uint32_t lh = lr.lohi[j], lo = lh & 0xffffu, hi = lh >> 16;
         const uint32_t b = lr.bkt[j];
-        if (!wave_bucket_runs<Key>(ix, skeys, sids, lo, hi, out + lo, b, bk, bp) && lane == 0)
+        if (!wave_bucket_runs<Key, W>(ix, skeys, sids, lo, hi, out + lo, b, bk, bp) && lane == 0)
             ix.gen_list[gen_region(out, g) + atomicAdd(&lr.cnt[1], 1u)] = b;
     }
     __syncthreads();
@@ -697,8 +730,8 @@ __device__ __forceinline__ void words_of_bin(OrPart or_part, uint32_t* words, co
                 ((uint64_t*)ix.head)[v0 + v] = (uint64_t)words[v] << 32 | lo32[j] | len;
             else
                 ((uint32_t*)ix.head)[v0 + v] = words[v] | len;
-        } else if (!list_bucket<uint32_t>(lr, med, v0, v, lo, hi)) {
-            put_short<uint32_t>(ix, v0 + v, out + lo, out + hi, skeys + lo);
+        } else if (!list_bucket<uint32_t, W>(lr, med, v0, v, lo, hi)) {
+            put_short<uint32_t, W>(ix, v0 + v, out + lo, out + hi, skeys + lo);
         }
     }
 }
@@ -874,15 +907,15 @@ __device__ __forceinline__ void light_bin_body_by(const Key* __restrict__ src_ke
         for (uint32_t v = threadIdx.x; v < nb; v += kLocalThreads) {
             const uint32_t lo = cnt[v], hi = cnt[v + 1];
             offsets[v0 + v] = out + lo;
-            if (W && !list_bucket<Key>(lr, med, v0, v, lo, hi))
-                put_short<Key>(ix, v0 + v, out + lo, out + hi, skeys + lo);
+            if (W && !list_bucket<Key, W>(lr, med, v0, v, lo, hi))
+                put_short<Key, W>(ix, v0 + v, out + lo, out + hi, skeys + lo);
         }
     }
     for (uint32_t p = threadIdx.x; p < L; p += kLocalThreads) {
         ekeys[out + p] = skeys[p];
         ids[out + p] = sids[p];
     }
-    if constexpr (W != 0) bin_long_runs<Key>(ix, lr, med, skeys, sids, out, v0 >> k, v0);
+    if constexpr (W != 0) bin_long_runs<Key, W>(ix, lr, med, skeys, sids, out, v0 >> k, v0);
 }
 
 // The usual bin: buckets [v0, v0 + nb) of the table's hash function.
