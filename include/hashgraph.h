@@ -329,10 +329,12 @@ hg_status hg_probe(const hg_table *t, const void *d_queries, uint64_t m, uint32_
  *     counts are put back in input order.  Needs m * (key_bits / 8 + 7) bytes
  *     of workspace plus 2 KiB per 4096 queries (from the allocator,
  *     hg_set_allocator).
- *   HG_PROBE_GROUPED_UNLESS_SKEWED: the queries' histogram over the ranges
- *     is taken first and, on the device, a range holding more than 8 times
- *     its share of them (skewed queries, whose index lines stay cached
- *     anyway) keeps input order; else grouped.  Workspace as for grouped.
+ *   HG_PROBE_GROUPED_UNLESS_SKEWED: 2^14 of the queries are sampled first, on
+ *     the device; a range holding more than 8 times its share of them (skewed
+ *     queries, whose index lines stay cached anyway), or neighbouring queries
+ *     often in one range (3/8 of the neighbours below 2^26 buckets, 1/2 below
+ *     2^27, else 5/8: queries in runs or by bucket, which share index lines as
+ *     they come), keeps input order; else grouped.  Workspace as for grouped.
  *   HG_PROBE_AUTO: HG_PROBE_GROUPED_UNLESS_SKEWED when the table has a probe
  *     index, m >= 2^25, m >= hash_range / 2 and hash_range >= 2^22, the sizes
  *     from which grouping measured faster, and its workspace can be

@@ -475,16 +475,32 @@ __global__ __launch_bounds__(kUngroupThreads, 8) void k_ungroup_by_pos(
         if (sval[p] != 255u) dst[begin + p] = sval[p];
 }
 
+constexpr uint32_t kGroupBits = 9;  // ranges of a grouped probe: 2^kGroupBits at most
+
 // A range holding more than kGroupSkew times an even share of the sampled
 // queries keeps a probe in input order.
 constexpr uint32_t kGroupSkew = 8;
+
+// So does a share of more than this many eighths of sampled neighbours in one range:
+// such queries come in runs or already by bucket, and share the index lines that
+// grouping would bring together.  Of queries that repeat the one before with
+// probability f, input order was the faster from f = 0.3 at 2^23 buckets (load 4), 0.4
+// at 2^25, 0.46 at 2^26 and 0.63 at 2^28: 2^26 queries of 2^26 buckets in bucket order
+// take 0.24 ms in input order and 0.91 grouped, in runs of eight 0.24 and 0.85.
+uint32_t group_local_eighths(uint64_t V) {
+    return V < (1ull << 26) ? 3u : V < (1ull << 27) ? 4u : 5u;
+}
 
 // Whether grouping pays for these queries, from a sample: up to kGroupSample
 // queries, 16 neighbours (a line of them, one page) at each of 1024 places spread
 // evenly over the input, are hashed into the ranges, and when
 // one range holds more than kGroupSkew times an even share of them the probe
 // keeps input order (skewed queries read few index lines, which stay cached
-// anyway).  Writes the one segment of the grouping passes -- with no tiles
+// anyway); also when more than local / 8 of the neighbours share a range (not asked
+// below 2^kGroupBits ranges, where neighbours meet by chance).  Neighbours that equal
+// each other make the sample one of 1024 places: an even spread over 512 ranges then
+// leaves a range with 2 on average, and 17 of them, the line of kGroupSkew, has a
+// chance of 10^-10.  Writes the one segment of the grouping passes -- with no tiles
 // at all for input order, so that every grouping kernel returns at once --
 // and gate[0] = 1 (grouped) or 0 (input order).  One workgroup, bound by the
 // latency of its loads: 35 us at 2^28 queries with each sample on a page of its
@@ -497,11 +513,14 @@ __global__ __launch_bounds__(1024) void k_group_sample(const Key* __restrict__ q
                                                        typename KeyTraits<Key>::Params hp,
                                                        uint32_t shift, uint32_t bits, Segs g,
                                                        uint32_t ntiles, uint32_t nchunks,
+                                                       uint32_t local,
                                                        uint32_t* __restrict__ gate) {
     __shared__ uint32_t cnt[1u << kMaxDigitBits];
     __shared__ uint32_t wmax[1024 / kWave];
+    __shared__ uint32_t near;  // neighbours in one range
     const uint32_t D = 1u << bits;
     for (uint32_t d = threadIdx.x; d < D; d += 1024) cnt[d] = 0;
+    if (threadIdx.x == 0) near = 0;
     __syncthreads();
     const uint32_t S = m < kGroupSample ? (uint32_t)m : kGroupSample;
     constexpr int IT = kGroupSample / 1024;
@@ -515,7 +534,11 @@ __global__ __launch_bounds__(1024) void k_group_sample(const Key* __restrict__ q
 #pragma unroll
     for (int r = 0; r < IT; ++r) {
         const uint32_t i = r * 1024 + threadIdx.x;
-        if (i < S) atomicAdd(&cnt[(KeyTraits<Key>::bucket(k[r], hp) >> shift) & (D - 1)], 1u);
+        const uint32_t d = (KeyTraits<Key>::bucket(k[r], hp) >> shift) & (D - 1);
+        if (i < S) atomicAdd(&cnt[d], 1u);
+        const uint32_t next = (uint32_t)__shfl_down((int)d, 1, kWave);
+        const uint64_t same = ballot(i + 1 < S && i % kSampleRun != kSampleRun - 1 && next == d);
+        if (lane_id() == 0 && same) atomicAdd(&near, (uint32_t)__popcll(same));
     }
     __syncthreads();
     uint32_t mx = 0;
@@ -528,7 +551,9 @@ __global__ __launch_bounds__(1024) void k_group_sample(const Key* __restrict__ q
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int w = 1; w < 1024 / kWave; ++w) mx = wmax[w] > mx ? wmax[w] : mx;
-        const bool grouped = (uint64_t)mx * D <= (uint64_t)kGroupSkew * S;
+        const uint32_t pairs = S - 1 - (S - 1) / kSampleRun;
+        const bool apart = D < (1u << kGroupBits) || 8 * near <= local * pairs;
+        const bool grouped = apart && (uint64_t)mx * D <= (uint64_t)kGroupSkew * S;
         gate[0] = grouped ? 1u : 0u;
         g.seg_start[0] = 0;
         g.seg_start[1] = (uint32_t)m;
@@ -1131,8 +1156,6 @@ hipError_t scatter_perm(const uint32_t* ids, const uint32_t* vals, uint64_t n, u
 
 namespace {
 
-constexpr uint32_t kGroupBits = 9;
-
 struct GroupPlan {
     uint32_t bits, shift, tile, ntiles, ch, nchunks;
 };
@@ -1197,7 +1220,8 @@ hipError_t run_probe_grouped(const TableDev& t, const Key* queries, uint64_t m, 
     const uint32_t* gate = decide ? w.ctr : nullptr;  // ctr[0]: 1 grouped, 0 input order
     if (decide) {
         hipLaunchKernelGGL(k_group_sample<Key>, dim3(1), dim3(1024), 0, s, queries, m, hp,
-                           p.shift, p.bits, w.seg, p.ntiles, p.nchunks, w.ctr);
+                           p.shift, p.bits, w.seg, p.ntiles, p.nchunks,
+                           group_local_eighths(t.V), w.ctr);
         HG_TRY(hipGetLastError());
     } else {
         w.seg = one_segment(m, p.ntiles, p.nchunks, p.ch, p.tile);
