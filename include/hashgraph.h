@@ -143,7 +143,10 @@ uint32_t hg_version(void);
  * 1/64 of the device's memory mapped while any table or collection lives and
  * is emptied when the last one is freed or an allocation of the library runs
  * out of memory (hipMallocAsync / hipFreeAsync without such objects and under
- * stream capture); exactly one NULL is HG_ERR_INVALID_ARG.
+ * stream capture); exactly one NULL is HG_ERR_INVALID_ARG.  Every successful
+ * call, both functions NULL among them, also gives the device what the pools
+ * hold and no enqueued work uses: a caller whose own allocation fails calls it
+ * and tries again.
  * The setting is process-wide and takes effect for calls that start after
  * it; a block already handed out is returned to the functions that gave it.
  * The memory that tables, collections, batch plans and servers keep

@@ -476,10 +476,13 @@ uint32_t hg_version(void) { return 100; }
 
 hg_status hg_set_allocator(hg_alloc_fn alloc_fn, hg_free_fn free_fn, void* ctx) {
     if (!alloc_fn != !free_fn) return HG_ERR_INVALID_ARG;
-    std::lock_guard<std::mutex> lock(g_hook_mu);
-    g_hook.alloc = alloc_fn;
-    g_hook.free = free_fn;
-    g_hook.ctx = alloc_fn ? ctx : nullptr;
+    {
+        std::lock_guard<std::mutex> lock(g_hook_mu);
+        g_hook.alloc = alloc_fn;
+        g_hook.free = free_fn;
+        g_hook.ctx = alloc_fn ? ctx : nullptr;
+    }
+    empty_pools();
     return HG_OK;
 }
 

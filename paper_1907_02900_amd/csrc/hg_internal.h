@@ -70,8 +70,8 @@ WsHook ws_hook();  // the hook installed now (hg_api.hip)
 // next call: for 2^27 64-bit queries 3 to 50 ms a call, against 3 ms of kernels.
 // While tables or collections live, blocks therefore come from a pool of the
 // library's that keeps up to 1/64 of the device's memory (4.5 GiB of 288; 2^28
-// grouped queries take 2.8), and that is emptied when the last of them is freed
-// and when an allocation of the library fails.  Under stream capture, and for a
+// grouped queries take 2.8), and that is emptied when the last of them is freed,
+// when an allocation of the library fails and by hg_set_allocator.  Under stream capture, and for a
 // stream whose device is unknown, plain hipMallocAsync.
 hipError_t ws_alloc(void** p, size_t bytes, hipStream_t s);
 // hipMalloc and hipMallocAsync that empty the pools and try again when memory is

@@ -165,7 +165,8 @@ _hook = None  # the installed callbacks, kept alive while the library may call t
 def set_allocator(alloc=None, free=None):
     """hg_set_allocator: alloc(bytes, stream_handle) -> device address (0 on
     failure) and free(address, stream_handle) back the library's temporary
-    workspace; both None restores the library's own pool.  The functions are kept
+    workspace; both None restores the library's own pool.  Every call also gives
+    the device what the pool holds and no enqueued work uses.  The functions are kept
     referenced here until replaced."""
     global _hook
     L = lib()

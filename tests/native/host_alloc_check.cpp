@@ -128,10 +128,54 @@ static void failed_allocations_leave_nothing_half_done() {
     }
 }
 
+// The pool: used while tables live, emptied by hg_set_allocator, by an allocation that
+// fails, and with the last table; not used under capture.
+static void the_pool_is_given_back() {
+    uint64_t total = 0;
+    hg_table *a = nullptr, *b = nullptr;
+    CHECK(hg_build(kKeys, 1 << 20, 32, 1 << 20, 1, nullptr, nullptr, &a) == HG_OK, "build");
+    CHECK(st.kept > (8u << 20) && st.pools == 1, "the build's workspace: %zu kept", st.kept);
+    CHECK(hg_set_allocator(nullptr, nullptr, nullptr) == HG_OK, "set_allocator");
+    CHECK(st.kept == 0 && st.trims == 1, "%zu kept by hg_set_allocator", st.kept);
+    CHECK(hg_set_allocator([](size_t, hipStream_t, void*) -> void* { return nullptr; }, nullptr,
+                           nullptr) == HG_ERR_INVALID_ARG && st.trims == 1, "half an allocator");
+    // a call that needs what the pool holds
+    const uint64_t m = 1 << 21;
+    CHECK(hg_probe_ordered(a, kKeys, m, (uint32_t*)kKeys, &total, HG_PROBE_GROUPED, nullptr) == HG_OK,
+          "probe");
+    CHECK(st.kept > m * 11, "%zu kept by the probe", st.kept);
+    const size_t held = st.kept;
+    st.capacity = st.used + st.kept + (1 << 20);
+    CHECK(hg_table_create(1 << 18, 1 << 18, 32, &b) == HG_OK, "a table beside a full pool");
+    CHECK(st.kept == 0 && st.used + st.kept <= st.capacity, "%zu kept", st.kept);
+    CHECK(hg_table_create(held, 1 << 18, 32, &b) == HG_ERR_OOM, "a table too large");
+    st.capacity = ~(size_t)0;
+    // a call whose own pool block does not fit beside what the pool holds
+    CHECK(hg_probe_ordered(a, kKeys, m, (uint32_t*)kKeys, nullptr, HG_PROBE_GROUPED, nullptr) == HG_OK,
+          "probe");
+    st.fail_in = 0;
+    st.fail_times = 1;
+    CHECK(hg_probe_ordered(a, kKeys, 2 * m, (uint32_t*)kKeys, nullptr, HG_PROBE_GROUPED, nullptr) ==
+              HG_OK, "probe, second try");
+    st.fail_in = -1;
+    // under capture: no block of the pool
+    const size_t before = st.kept;
+    st.capturing = true;
+    CHECK(hg_probe_ordered(a, kKeys, 4 * m, (uint32_t*)kKeys, nullptr, HG_PROBE_GROUPED, nullptr) ==
+              HG_OK, "captured probe");
+    CHECK(st.kept == before, "captured probe took the pool");
+    st.capturing = false;
+    hg_table_free(a);
+    CHECK(st.kept == before, "a table is left");
+    hg_table_free(b);
+    CHECK(st.kept == 0 && st.live.empty(), "the last table");
+}
+
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "rebuilds") rebuilds_allocate_nothing();
     else if (what == "failures") failed_allocations_leave_nothing_half_done();
+    else if (what == "pool") the_pool_is_given_back();
     else return 2;
     printf("OK\n");
     return 0;

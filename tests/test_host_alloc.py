@@ -40,3 +40,7 @@ def test_rebuilds_within_the_capacity_allocate_nothing(check):
 
 def test_a_failed_allocation_leaves_nothing_half_done(check):
     check("failures")
+
+
+def test_the_pool_is_given_back(check):
+    check("pool")
