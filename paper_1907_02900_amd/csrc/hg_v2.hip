@@ -784,10 +784,9 @@ struct V2Ws {
     Segs s1, s2;
 };
 
-// One layout used both to size the workspace (base == nullptr) and to carve it.
-size_t layout_v2(void* ws, const V2Plan& p, size_t key_size, V2Ws* out) {
-    Carver c(ws);
-    V2Ws w{};
+// What the partition passes need: the reorganised entries, the [tile][digit] matrices
+// and their chunk sums, the segments.
+void layout_passes(Carver& c, const V2Plan& p, size_t key_size, V2Ws& w) {
     w.rkeys = c.take<char>(p.n * key_size);
     w.rids = c.take<uint32_t>(p.n);
     const uint32_t D1 = 1u << p.b1, D2 = 1u << p.b2;
@@ -804,6 +803,13 @@ size_t layout_v2(void* ws, const V2Plan& p, size_t key_size, V2Ws* out) {
         w.s2.ch = p.ch2;
         w.s2.tile = p.tile;
     }
+}
+
+// One layout used both to size a build's workspace (base == nullptr) and to carve it.
+size_t layout_v2(void* ws, const V2Plan& p, size_t key_size, V2Ws* out) {
+    Carver c(ws);
+    V2Ws w{};
+    layout_passes(c, p, key_size, w);
     w.bin_start = c.take<uint32_t>((size_t)p.bins + 1);
     w.heavy_list = c.take<uint32_t>((size_t)p.bins);
     w.ctr = c.take<uint32_t>(kCtrWords);
@@ -1094,10 +1100,9 @@ V2Plan perm_plan(uint64_t n) {
 
 size_t perm_layout(void* ws, const V2Plan& p, V2Ws* w, uint32_t** xv, uint32_t** xi) {
     Carver c(ws);
-    void* v2 = c.take<char>(layout_v2(nullptr, p, 4, nullptr));
+    layout_passes(c, p, 4, *w);
     *xv = c.take<uint32_t>(p.n);
     *xi = c.take<uint32_t>(p.n);
-    if (ws) layout_v2(v2, p, 4, w);
     return c.off + 256;
 }
 
@@ -1105,8 +1110,9 @@ size_t perm_layout(void* ws, const V2Plan& p, V2Ws* w, uint32_t** xv, uint32_t**
 
 size_t scatter_perm_ws_bytes(uint64_t n) {
     if (n <= kPermDirectMax) return 256;
+    V2Ws w{};
     uint32_t *xv, *xi;
-    return perm_layout(nullptr, perm_plan(n), nullptr, &xv, &xi);
+    return perm_layout(nullptr, perm_plan(n), &w, &xv, &xi);
 }
 
 hipError_t scatter_perm(const uint32_t* ids, const uint32_t* vals, uint64_t n, uint32_t* out,
@@ -1121,7 +1127,7 @@ hipError_t scatter_perm(const uint32_t* ids, const uint32_t* vals, uint64_t n, u
     }
     HG_TRY(set_smem_limits<uint32_t>());
     const V2Plan p = perm_plan(n);
-    V2Ws w;
+    V2Ws w{};
     uint32_t *xv, *xi;
     perm_layout(ws, p, &w, &xv, &xi);
     const auto hp = KeyTraits<uint32_t>::make(1, 0);  // unused: digits come from the ids

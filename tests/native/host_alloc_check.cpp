@@ -171,11 +171,34 @@ static void the_pool_is_given_back() {
     CHECK(st.kept == 0 && st.live.empty(), "the last table");
 }
 
+// Counts by input index (scattered by B's ids) take the entries twice and the passes'
+// matrices, not a build's workspace.
+static void intersections_take_no_builds_workspace() {
+    for (uint64_t n : {1ull << 21, 1ull << 25, (1ull << 25) + 12345, 1ull << 28}) {
+        hg_table *a = nullptr, *b = nullptr;
+        CHECK(hg_build(kKeys, n, 32, n, 1, nullptr, nullptr, &a) == HG_OK, "build");
+        CHECK(hg_build(kKeys, n, 32, n, 1, nullptr, nullptr, &b) == HG_OK, "build");
+        static size_t bytes;
+        CHECK(hg_set_allocator([](size_t nb, hipStream_t, void*) { bytes = nb; return (void*)4096; },
+                               [](void*, hipStream_t, void*) {}, nullptr) == HG_OK, "hook");
+        CHECK(hg_intersect(a, b, (uint32_t*)kKeys, nullptr, nullptr, 0, nullptr, nullptr) == HG_OK,
+              "intersect");
+        // edge counts, positions, two copies of (value, id); 1/8 of a byte to one byte an
+        // entry of matrices and scans
+        CHECK(bytes >= n * 28 && bytes < n * 29 + (4u << 20), "%llu edges: %zu bytes, %.2f an edge",
+              (unsigned long long)n, bytes, (double)bytes / (double)n);
+        CHECK(hg_set_allocator(nullptr, nullptr, nullptr) == HG_OK, "hook");
+        hg_table_free(a);
+        hg_table_free(b);
+    }
+}
+
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "rebuilds") rebuilds_allocate_nothing();
     else if (what == "failures") failed_allocations_leave_nothing_half_done();
     else if (what == "pool") the_pool_is_given_back();
+    else if (what == "scatter") intersections_take_no_builds_workspace();
     else return 2;
     printf("OK\n");
     return 0;

@@ -44,3 +44,7 @@ def test_a_failed_allocation_leaves_nothing_half_done(check):
 
 def test_the_pool_is_given_back(check):
     check("pool")
+
+
+def test_intersections_take_no_builds_workspace(check):
+    check("scatter")
