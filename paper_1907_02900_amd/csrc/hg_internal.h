@@ -449,7 +449,7 @@ __host__ __device__ inline uint32_t gen_region(uint32_t bin_start, uint32_t g) {
 inline uint64_t gen_list_cap(uint64_t n, uint64_t bins) { return n / (kRunBucket + 1) + bins + 1; }
 
 // Where a V2 build writes its probe index (head == null: none) and the
-// key-run summary of its long buckets.  k, bins, fmt and hp are set by the
+// key-run summary of its long buckets.  fmt, hp and the lists are set by the
 // build.
 struct IndexOut {
     void* head = nullptr;  // fmt.bytes per bucket
@@ -459,7 +459,6 @@ struct IndexOut {
     uint32_t* gen_list = nullptr;
     uint32_t* gen_cnt = nullptr;  // [bins]
     uint32_t* gen_any = nullptr;  // set when a bin held in LDS lists a bucket
-    uint32_t k = 0, bins = 0;
 };
 
 // The rare path of a build, after its per-bin kernel: bins too large for LDS

@@ -1004,16 +1004,12 @@ hipError_t run_build_v2(const Key* keys, uint64_t n, uint64_t V, uint64_t seed, 
                         uint32_t* ids, Key* ekeys, IndexOut& ix, void* ws,
                         uint32_t bins_hint, bool stable, hipStream_t s) {
     HG_TRY(set_smem_limits<Key>());
-    ix.k = 0;
-    ix.bins = 0;
     if (n == 0) {
         ix.fmt = index_fmt(0, V, sizeof(Key) * 8);
         if (ix.head) HG_TRY(fill_u32((uint32_t*)ix.head, ix.fmt.bytes / 4 * V, 0u, s));
         return fill_u32(offsets, V + 1, 0u, s);
     }
     const V2Plan p = plan_v2(n, V, sizeof(Key) * 8, bins_hint, !stable);
-    ix.k = p.k;
-    ix.bins = p.bins;
     ix.fmt = index_fmt(n, V, sizeof(Key) * 8);
     ix.hp = make_hash_params(V, seed);
     V2Ws w;

@@ -511,28 +511,29 @@ __device__ __forceinline__ uint32_t row_or16(uint32_t f) {
     return f;
 }
 
-// The OR of group g's lanes (groups of G = 16 or 32 lanes), from the rows'
-// ORs; uniform values, selected per lane.
-template <uint32_t G>
-__device__ __forceinline__ uint32_t group_or(uint32_t f, uint32_t g) {
+// The OR of half g's 32 lanes, from the rows' ORs; uniform values, selected per
+// lane.
+__device__ __forceinline__ uint32_t half_or(uint32_t f, uint32_t g) {
     const uint32_t r = row_or16(f);
     const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)r, 15);
     const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)r, 31);
     const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)r, 47);
     const uint32_t d = (uint32_t)__builtin_amdgcn_readlane((int)r, 63);
-    if constexpr (G == 16) return g == 0 ? a : g == 1 ? b : g == 2 ? c : d;
-    else return g == 0 ? (a | b) : (c | d);
+    return g == 0 ? (a | b) : (c | d);
 }
 
-// Index entries of the medium buckets in list[0, n), whose lengths are at
-// most G: each wave takes 64 / G buckets at a time, lane s of group g holding
-// key s of its bucket; the first key's count is a ballot and the filter an
-// OR over the group -- the same entry put_short builds with one lane.
-template <typename Key, uint32_t G, int W>
-__device__ __forceinline__ void medium_heads_by(const IndexOut& ix, const uint32_t* list,
-                                                uint32_t n, const Key* skeys, uint32_t out,
-                                                uint32_t v0) {
-    constexpr uint32_t PER = kWave / G;
+// Index entries of the bin's medium buckets (more than head_lane_max and at
+// most kRunBucket entries): each wave takes two buckets at a time, lane s of half g
+// holding key s of its bucket; the first key's count is a ballot and the filter an
+// OR over the half -- the same entry put_short builds with one lane.  Called by
+// whole waves after a barrier that follows the list's construction.
+template <typename Key, int W>
+__device__ __forceinline__ void bin_medium_heads(const IndexOut& ix, const LongLds<Key>& lr,
+                                                 const uint32_t* list, const Key* skeys,
+                                                 uint32_t out, uint32_t v0) {
+    constexpr uint32_t G = 32, PER = kWave / G;
+    static_assert(kRunBucket <= G, "a medium bucket fits a half wave");
+    const uint32_t n = lr.cnt[2];
     const uint32_t w = threadIdx.x / kWave, lane = lane_id();
     const uint32_t g = lane / G, s = lane % G;
     for (uint32_t j0 = w * PER; j0 < n; j0 += W_LOCAL * PER) {  // uniform per wave
@@ -551,7 +552,7 @@ __device__ __forceinline__ void medium_heads_by(const IndexOut& ix, const uint32
             if (W != 16) q = KeyTraits<uint32_t>::quotient(kx, ix.hp, h);
             const uint32_t nf = W == 16 ? 24u : ix.fmt.nf;
             const uint32_t f =
-                group_or<G>((in && kx != k0) ? (1u << filter_bit(q, nf)) : 0u, g);
+                half_or((in && kx != k0) ? (1u << filter_bit(q, nf)) : 0u, g);
             if (have && s == 0 && W == 16)
                 ((uint4*)ix.head)[v0 + v] = make_uint4(len, out + lo, (uint32_t)k0, c0 | f << 8);
             if (have && s == 0 && W != 16)  // lane 0's key is the first one
@@ -560,21 +561,10 @@ __device__ __forceinline__ void medium_heads_by(const IndexOut& ix, const uint32
                                (uint64_t)f << (12 + ix.fmt.qb));
         } else {
             const uint64_t z = in ? filter_bits64((uint64_t)kx) : 0ull;
-            const uint32_t zl = group_or<G>((uint32_t)z, g), zh = group_or<G>((uint32_t)(z >> 32), g);
+            const uint32_t zl = half_or((uint32_t)z, g), zh = half_or((uint32_t)(z >> 32), g);
             if (have && s == 0) ((uint4*)ix.head)[v0 + v] = make_uint4(len, out + lo, zl, zh);
         }
     }
-}
-
-// Index entries of the bin's medium buckets (more than head_lane_max and at
-// most kRunBucket entries).  Called by whole waves after a barrier that
-// follows the list's construction.
-template <typename Key, int W>
-__device__ __forceinline__ void bin_medium_heads(const IndexOut& ix, const LongLds<Key>& lr,
-                                                 const uint32_t* med, const Key* skeys,
-                                                 uint32_t out, uint32_t v0) {
-    static_assert(kRunBucket <= 32u, "a medium bucket fits a group of 32 lanes");
-    medium_heads_by<Key, 32, W>(ix, med, lr.cnt[2], skeys, out, v0);
 }
 
 // Key runs and index entry of one long bucket, by one wave: its entries are
