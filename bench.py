@@ -146,9 +146,13 @@ def group_matrix_bytes(m, V, tile=4096):
 def entry_format(n, V, kb):
     """(bytes, keys held) of the table's probe index entries: for 32-bit keys
     a field of bit_length((2^32 - 1) // V) bits per key beside a 4-bit code, in
-    4 bytes if they hold 2 + 2n/V keys, else 8; 64-bit keys 16 bytes, 1 key."""
+    4 bytes if they hold 2 + 2n/V keys, else 8, and past a load that rises with
+    V 16 bytes of keys; 64-bit keys 16 bytes, 1 key."""
     if kb == 8:
         return 16, 1
+    halves = 1 if V <= 1 << 16 else 3 if V <= 1 << 18 else 10 if V <= 1 << 22 else 16
+    if V < 1 << 12 or 2 * n > halves * V:
+        return 16, 3
     qb = max(((1 << 32) - 1) // V, 1).bit_length()
     cap = min(28 // qb, 13)
     if cap >= 3 and (cap - 2) * V >= 2 * n:
@@ -170,13 +174,9 @@ def index_bytes(name, n, m, V, kb, sum_tail):
 
 def v2_plan_bytes(hg, n, V, kb=4, any_order=False):
     """Tile x digit matrix bytes of each partition pass, from the library's
-    own plan (hg_build_plan, whose tiles are those of the stable order;
-    32-bit keys in any order take tiles of 8192)."""
-    p = hg.build_plan(n, V, 8 * kb)
-    tiles = list(p["tiles"])
-    if any_order and kb == 4:
-        rows = -(-n // 8192)
-        tiles = [rows, rows + (1 << p["digit_bits"][0]) if tiles[1] else 0]
+    own plan."""
+    p = hg.build_plan(n, V, 8 * kb, any_order=any_order)
+    tiles = p["tiles"]
     m1 = tiles[0] * (1 << p["digit_bits"][0]) * 4
     m2 = tiles[1] * (1 << p["digit_bits"][1]) * 4 if p["passes"] == 2 else 0
     return {"m1_bytes": m1, "m2_bytes": m2, "plan": p}
@@ -559,20 +559,22 @@ def main():
     blen = offl[h + 1] - offl[h]
     sum_len = int(blen.sum().item())
     # a bucket of up to `cap` keys is held whole in its index entry; a longer
-    # one holds its first key, that key's count and a filter of its other keys'
-    # quotients: a query equal to the first key, or whose filter bit no other
+    # one holds its first key, that key's count and a filter of its other keys
+    # (their quotients, but in 16-byte entries the keys): a query equal to the first key, or whose filter bit no other
     # key of the bucket sets, needs nothing more; other queries read the rest
     # of the bucket (a bucket of more than 32 keys is counted as read whole)
     ebytes, cap = entry_format(n, V, kb)
     qbits = max(((1 << 32) - 1) // V, 1).bit_length()
-    nf = min(8 * ebytes - 12 - qbits, 32)
+    nf = 24 if ebytes == 16 else min(8 * ebytes - 12 - qbits, 32)
     eku = ek.to(torch.int64) & 0xFFFFFFFF
     qu = dq.to(torch.int64) & 0xFFFFFFFF
     first = eku[offl[h].clamp(max=n - 1)]
     reads = (blen > cap) & (qu != first)
     sel = torch.nonzero(reads).squeeze(1)
     if sel.numel():
-        def fbit(x):  # the entry's filter bit of a key's quotient
+        def fbit(x):  # the entry's filter bit of a key
+            if ebytes == 16:
+                return (((x * 0x9E3779B1) & 0xFFFFFFFF) * nf) >> 32
             x = ((x ^ (x >> 16)) * 0x85EBCA6B) & 0xFFFFFFFF
             x = ((x ^ (x >> 13)) * 0xC2B2AE35) & 0xFFFFFFFF
             x = (x ^ (x >> 16)) // V

@@ -211,12 +211,18 @@ typedef struct hg_plan_info {
     uint32_t passes;          /* partition passes before the per-bin build     */
     uint32_t digit_bits[2];   /* digit width of each pass (0 if unused)        */
     uint32_t tiles[2];        /* partition tiles of each pass (second: bound)  */
-    uint32_t tile_keys;       /* keys per partition tile (stable order)        */
+    uint32_t tile_keys;       /* keys per partition tile                       */
     uint64_t workspace_bytes; /* device workspace of the build                 */
 } hg_plan_info;
 
 hg_status hg_build_plan(uint64_t n, uint64_t hash_range, int key_bits, uint32_t bins,
                         hg_plan_info *out);
+
+/* The same for a build with the given options (NULL: the defaults): bins and
+ * any_order are read, whose partition tiles differ.  hg_build_plan is the plan of
+ * the stable order.  HG_ERR_INVALID_ARG also for V1 and for stable with any_order. */
+hg_status hg_build_plan_opts(uint64_t n, uint64_t hash_range, int key_bits,
+                             const hg_build_opts *opts, hg_plan_info *out);
 
 /* Autotuner of a single build: chooses the launch parameters of
  * hg_build_opts for these keys by timing candidate builds of them on the

@@ -520,10 +520,19 @@ hg_status hg_exclusive_scan(const uint32_t* d_counts, uint64_t V, uint32_t* d_of
 
 hg_status hg_build_plan(uint64_t n, uint64_t hash_range, int key_bits, uint32_t bins,
                         hg_plan_info* out) {
+    hg_build_opts o{};
+    o.bins = bins;
+    return hg_build_plan_opts(n, hash_range, key_bits, &o, out);
+}
+
+hg_status hg_build_plan_opts(uint64_t n, uint64_t hash_range, int key_bits,
+                             const hg_build_opts* opts, hg_plan_info* out) {
+    const uint32_t bins = opts ? opts->bins : 0;
     if (!out || !valid_kb(key_bits) || !valid_range(hash_range) || n > kU32Max ||
-        (bins && bins > hash_range))
+        (bins && bins > hash_range) || (opts && opts->variant == HG_VARIANT_V1) ||
+        (opts && opts->stable && opts->any_order))
         return HG_ERR_INVALID_ARG;
-    const V2Plan p = plan_v2(n, hash_range, key_bits, bins, false);
+    const V2Plan p = plan_v2(n, hash_range, key_bits, bins, opts && opts->any_order);
     *out = hg_plan_info{};
     out->bucket_bits = p.k;
     out->bins = p.bins;

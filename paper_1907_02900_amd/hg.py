@@ -114,6 +114,8 @@ def lib():
                       ctypes.POINTER(vp)], i32),
         "hg_table_create": ([u64, u64, i32, ctypes.POINTER(vp)], i32),
         "hg_build_plan": ([u64, u64, i32, u32, ctypes.POINTER(PlanInfo)], i32),
+        "hg_build_plan_opts": ([u64, u64, i32, ctypes.POINTER(BuildOpts),
+                                ctypes.POINTER(PlanInfo)], i32),
         "hg_table_build": ([vp, vp, u64, u64, u64, ctypes.POINTER(BuildOpts), vp], i32),
         "hg_table_view": ([vp, ctypes.POINTER(TableInfo)], i32),
         "hg_table_export": ([vp, vp, vp, vp, vp], i32),
@@ -262,12 +264,18 @@ def hg_exclusive_scan(counts: torch.Tensor, out=None, stream=None):
 
 # ----------------------------------------------------------------- tables ---
 
-def build_plan(n: int, hash_range: int, key_bits: int = 32, bins: int = 0) -> dict:
+def build_plan(n: int, hash_range: int, key_bits: int = 32, bins: int = 0,
+               any_order: bool = False) -> dict:
     """The V2 plan (Alg. 2) the library follows for n keys over hash_range
     buckets (host only)."""
     p = PlanInfo()
-    _check(lib().hg_build_plan(int(n), int(hash_range), int(key_bits), int(bins),
-                               ctypes.byref(p)), "hg_build_plan")
+    if any_order:
+        o = _opts(bins=bins, any_order=True)
+        _check(lib().hg_build_plan_opts(int(n), int(hash_range), int(key_bits), ctypes.byref(o),
+                                        ctypes.byref(p)), "hg_build_plan_opts")
+    else:
+        _check(lib().hg_build_plan(int(n), int(hash_range), int(key_bits), int(bins),
+                                   ctypes.byref(p)), "hg_build_plan")
     return {"bucket_bits": p.bucket_bits, "bins": p.bins, "passes": p.passes,
             "digit_bits": list(p.digit_bits), "tiles": list(p.tiles),
             "tile_keys": p.tile_keys, "workspace_bytes": p.workspace_bytes}
