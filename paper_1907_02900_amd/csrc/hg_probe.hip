@@ -115,6 +115,14 @@ struct LongRef {
     uint32_t st, end, runs;
 };
 
+// Key runs of a long bucket with the entry e, which ends at edge position `end`.
+template <int W>
+__device__ __forceinline__ uint32_t runs_in(const typename EntryOf<W>::T& e,
+                                            const uint32_t* __restrict__ run_end, uint32_t end) {
+    if constexpr (W == 16) return e.z;
+    else return (e >> 5) & 1 ? 0u : (e >> 4) & 1 ? 1u : run_end[end - 1];
+}
+
 template <typename Key, int W>
 __device__ __forceinline__ LongRef long_ref(const View<Key>& t, uint32_t h,
                                             const typename EntryOf<W>::T& e) {
@@ -122,12 +130,11 @@ __device__ __forceinline__ LongRef long_ref(const View<Key>& t, uint32_t h,
     if constexpr (W == 16) {
         r.st = e.y;
         r.end = e.y + e.x;
-        r.runs = e.z;
     } else {
         r.st = t.off[h];
         r.end = t.bucket_end(h, r.st);
-        r.runs = (e >> 5) & 1 ? 0u : (e >> 4) & 1 ? 1u : t.runs.end[r.end - 1];
     }
+    r.runs = runs_in<W>(e, t.runs.end, r.end);
     return r;
 }
 
@@ -428,7 +435,7 @@ __device__ __forceinline__ bool stale(const View<Key>& b, uint64_t p, Key k) {
 // Alg. 3 over B's edges p: count the entries of A's bucket h(key_p) equal to
 // key_p.  A and B share hash parameters, so h is recomputed from B's key.
 //
-// With A's index (W = 4 or 8) or without one (W = 0).  A's buckets come in
+// With A's quotient entries (W = 4 or 8) or without its index (W = 0).  A's buckets come in
 // increasing order, so its index entries are streamed: they are smaller than its
 // offsets and keys together.  A thread's counts are stored after the last of its
 // loads, since a load waits for the stores before it: 2^23 edges by 2^20 to 2^24
@@ -496,32 +503,33 @@ __global__ __launch_bounds__(kProbeThreads) void k_intersect_count(
 
 // Matches of k in A's bucket h, by its offsets: a scan, or A's key runs when the
 // bucket is long and has them.
-template <typename Key>
+template <typename Key, int W>
 __device__ __forceinline__ uint32_t count_by_offsets(const uint32_t* __restrict__ a_off,
                                                      const uint32_t* __restrict__ a_len,
-                                                     const uint4* __restrict__ a_head,
+                                                     const void* __restrict__ a_head,
                                                      const Runs<Key>& runs,
                                                      const Key* __restrict__ a_keys, uint32_t h,
                                                      Key k) {
     const uint32_t lo = a_off[h], hi = a_len ? lo + a_len[h] : a_off[h + 1];
     if (hi - lo > kRunBucket) {
-        const uint4 e = a_head[h];
+        const auto e = ((const typename EntryOf<W>::T*)a_head)[h];
+        const uint32_t n = runs_in<W>(e, runs.end, hi);
         uint32_t gb, ge;
-        if (e.z != 0)
-            return run_group(LongRef{e.y, e.y + e.x, e.z}, runs, k, &gb, &ge) ? ge - gb : 0u;
+        if (n != 0) return run_group(LongRef{lo, hi, n}, runs, k, &gb, &ge) ? ge - gb : 0u;
     }
     return count_in_bucket(a_keys, lo, hi, k);
 }
 
 // With an index of wide entries, which would cost more to stream than the two
-// offsets: they are read for long buckets only.  One edge after the other, each
+// offsets, or of quotients that settle too few edges (scan_offsets): the entries are
+// read for long buckets only.  One edge after the other, each
 // loaded and counted before the next: as a batch like the above, with the branch for
 // long buckets in it, 2^23 64-bit edges by 2^20 to 2^24 buckets of load 0.25 to 4 took
 // 37 to 93 us, so 30 to 79.
-template <typename Key>
+template <typename Key, int W>
 __global__ __launch_bounds__(kProbeThreads) void k_intersect_scan(
     const uint32_t* __restrict__ a_off, const uint32_t* __restrict__ a_len,
-    const uint4* __restrict__ a_head, Runs<Key> runs, const Key* __restrict__ a_keys,
+    const void* __restrict__ a_head, Runs<Key> runs, const Key* __restrict__ a_keys,
     const uint32_t* __restrict__ b_off, const uint32_t* __restrict__ b_len,
     const Key* __restrict__ b_keys, const uint32_t* __restrict__ b_ids, uint64_t nb,
     typename KeyTraits<Key>::Params hp, uint32_t* __restrict__ edge_counts,
@@ -539,7 +547,7 @@ __global__ __launch_bounds__(kProbeThreads) void k_intersect_scan(
                 if (edge_counts) edge_counts[p] = 0;
                 continue;
             }
-            const uint32_t c = count_by_offsets(a_off, a_len, a_head, runs, a_keys, h, k);
+            const uint32_t c = count_by_offsets<Key, W>(a_off, a_len, a_head, runs, a_keys, h, k);
             if (edge_counts) edge_counts[p] = c;
             if (counts_by_input) counts_by_input[b_ids[p]] = c;
             sum += c;
@@ -611,6 +619,18 @@ uint64_t probe_total_slots(uint64_t m) {
     return 1 + (m ? 8 * (((uint64_t)grid_for(m, kProbeThreads * kProbeItems) + 7) / 8) : 0);
 }
 
+// Whether A's 8-byte entries are streamed, or its offsets scanned: past some load the
+// entries leave too many keys of B to the edge array, whose bucket then takes the
+// offsets as well.  Entries : offsets, at the lines: 2^18 and 2^19 buckets of load 1.5
+// 11 : 10 us, of load 1 9 : 9; 2^21 and 2^22 of load 4 by 2^22 edges 54 : 36 and 59 : 41,
+// of load 3 by half a table 23 : 24 and 31 : 32; 2^24 of load 4 by 2^24 edges 200 : 209.
+// (A few edges of B leave most of A's lines unread: 2^22 buckets of load 4 by 2^18 edges
+// 24 : 31.)
+bool scan_offsets(const TableDev& a, const TableDev& b) {
+    if (a.V <= (1u << 19)) return 2 * a.n >= 3 * a.V;
+    return a.V <= (1u << 23) && a.n >= 4 * a.V && 4 * b.n >= a.V;
+}
+
 // Calls f with the bytes of t's index entries (0: no index) as a constant.
 template <typename Key, typename F>
 void with_entry(const TableDev& t, F&& f) {
@@ -669,16 +689,20 @@ hipError_t run_intersect_counts(const TableDev& a, const TableDev& b, uint32_t* 
         HG_PROF("intersect_count", s);
         with_entry<Key>(a, [&](auto w) {
             constexpr int W = decltype(w)::value;
+            bool by_entry = W != 16;
+            if constexpr (W == 8) by_entry = !scan_offsets(a, b);
             if constexpr (W != 16)
-                hipLaunchKernelGGL((k_intersect_count<Key, W>), dim3(grid), dim3(kProbeThreads), 0, s,
-                                   view_of<Key>(a), view_of<Key>(b), b.n, edge_counts,
-                                   counts_by_input, d_total);
-            else
-                hipLaunchKernelGGL(k_intersect_scan<Key>, dim3(grid), dim3(kProbeThreads), 0, s,
-                                   a.offsets, a.len, (const uint4*)a.head, view_of<Key>(a).runs,
-                                   (const Key*)a.keys, b.offsets, b.len, (const Key*)b.keys, b.ids,
-                                   b.n, KeyTraits<Key>::make(a.V, a.seed), edge_counts,
-                                   counts_by_input, d_total);
+                if (by_entry)
+                    hipLaunchKernelGGL((k_intersect_count<Key, W>), dim3(grid),
+                                       dim3(kProbeThreads), 0, s, view_of<Key>(a), view_of<Key>(b),
+                                       b.n, edge_counts, counts_by_input, d_total);
+            if constexpr (W == 8 || W == 16)
+                if (!by_entry)
+                    hipLaunchKernelGGL((k_intersect_scan<Key, W>), dim3(grid), dim3(kProbeThreads),
+                                       0, s, a.offsets, a.len, a.head, view_of<Key>(a).runs,
+                                       (const Key*)a.keys, b.offsets, b.len, (const Key*)b.keys,
+                                       b.ids, b.n, KeyTraits<Key>::make(a.V, a.seed), edge_counts,
+                                       counts_by_input, d_total);
         });
     }
     HG_TRY(hipGetLastError());
