@@ -70,17 +70,19 @@ typedef struct hg_build_opts {
     int32_t no_index;  /* V2 also writes a probe index beside the CSR arrays:
                           one entry per bucket (32-bit keys: 4 or 8 bytes,
                           chosen from N and V, that identify every key of all
-                          but the longest buckets by its hash quotient;
-                          64-bit keys: 16 bytes, the bucket's length, start
-                          and its key or, of two or more, a filter), so most
-                          probes take one random read.  Buckets of more than
+                          but the longest buckets by its hash quotient, or, for
+                          small ranges and many keys per bucket, 16 bytes, three
+                          keys or the bucket's length, start, first key and a
+                          filter; 64-bit keys: 16 bytes, the bucket's length,
+                          start and its key or, of two or more, a filter), so
+                          most probes take one random read.  Buckets of more than
                           32 entries get a key-run summary as well (distinct
                           keys ascending, each with the end of its group of
                           ids), so probes and intersections of skewed tables
                           cost a binary search instead of a scan.  The whole
                           index is built on the device, in stream order: the
-                          build never waits for it.  Its arrays (8 or, 64-bit
-                          keys, 16 bytes per bucket of the range capacity, and
+                          build never waits for it.  Its arrays (8 to 16
+                          bytes per bucket of the range capacity, and
                           key + 8 bytes per entry of the key capacity for the
                           summary) are allocated by hg_table_create, or by
                           hg_build when it writes the index.  1 = skip the
@@ -679,8 +681,8 @@ hg_status hg_profile_get(uint32_t index, char *name, uint32_t name_cap, uint64_t
                          double *total_ms);
 
 /* Random-transaction micro-roofline: the ceiling of random-access kernels
- * (the probe makes one random 16-byte read per query, V1 one random atomic
- * add per key).  Allocates a zeroed buffer of footprint_bytes (a power of two,
+ * (the probe makes one random read of 4 to 16 bytes per query, V1 one random
+ * atomic add per key).  Allocates a zeroed buffer of footprint_bytes (a power of two,
  * >= 4096), runs `accesses` independent random accesses of the given kind
  * over it once to warm up and once timed (HIP events on `stream`), frees the
  * buffer and stores the timed run's milliseconds in *h_ms.  Waits for the

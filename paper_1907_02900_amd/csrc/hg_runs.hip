@@ -22,7 +22,7 @@
 // dominated by one key (skew), so the entries equal to the bucket's first key
 // (the lead key) form one run and the few others are sorted across a wave.
 // The rest, which the per-bin kernels list per bin:
-//   * buckets of up to light_cap keys (one workgroup each, in LDS): the
+//   * buckets of up to light_cap keys (k_listed_runs, in LDS): the
 //     others are gathered, sorted (bitonic network in LDS) and cut into runs;
 //   * longer buckets (from bins too large for LDS), in chunks of kChunk
 //     entries spread over the grid: per chunk the others and those below the
@@ -693,8 +693,9 @@ constexpr int kScanThreads = 1024;
 // The histograms of the split bins' slices in a kernel of their own, so that four
 // workgroups share a CU: with the oversize bins, which take 128 VGPRs and 50 KB of
 // LDS, the two ran 449 us at 2^26 Zipf(1.2) keys, apart 295 and 71.  Builds below
-// kSliceHistMin keys keep them in one kernel: the launch costs a build of 300 007 keys
-// 1.6 us of 49.5, and 1024 slices leave no such tail.
+// kSliceHistMin keys keep them in one kernel, where the launch costs more: whole builds
+// of Zipf(1.2) keys in one : in two, 2^22 372 : 376 us, 2^23 465 : 470, 2^24 737 : 724,
+// 2^26 2399 : 2289 (uniform keys 2^22 132 : 135, 2^24 335 : 336).
 constexpr uint64_t kSliceHistMin = 1ull << 24;
 
 template <typename Key>

@@ -169,7 +169,7 @@ __global__ __launch_bounds__(256) void k_colscan_reduce(const uint32_t* __restri
 // One workgroup per segment: digit totals, their exclusive scan, then chunk
 // sums become chunk bases.  It is one workgroup against memory latency (256
 // rows of 256 digits at 2^28 keys), so up to 16 row groups walk the chunks side
-// by side with eight loads in flight each: 78 -> 12 us at 2^28, 25 -> 6 us at
+// by side with eight loads in flight each: 78 -> 14 us at 2^28, 25 -> 6 us at
 // 300 007 keys, against one thread per digit walking all rows.
 // It knows where every digit of its segment starts, so the starts that the next
 // kernels need come from here as well, not from launches of their own.
@@ -638,8 +638,9 @@ __device__ void note_bin(const SegsOut& o, uint32_t b, uint32_t st, uint32_t nx)
 // One workgroup per final bin g (buckets [g*2^k, min((g+1)*2^k, V))) that
 // holds at most light_cap<Key>() keys.
 // ANY: any order inside a bucket; W: bytes of an index entry (0: none).
-// Both are constants so that an any-order bin carries no sorting network: with
-// them as arguments the kernel took 146 VGPRs, one workgroup per CU.
+// Both are constants so that a bin carries the code of its own layout only: 60 to 80
+// VGPRs in any order, 110 to 128 stable (whose bins with a bucket of more than kFixMax
+// keys are sorted in registers), and two workgroups per CU need 128.
 template <typename Key, bool ANY, int W>
 __global__ __launch_bounds__(kLocalThreads, 4) void k_local_light(
     const Key* __restrict__ src_keys, const uint32_t* __restrict__ src_ids,
