@@ -638,8 +638,8 @@ __device__ void note_bin(const SegsOut& o, uint32_t b, uint32_t st, uint32_t nx)
 // One workgroup per final bin g (buckets [g*2^k, min((g+1)*2^k, V))) that
 // holds at most light_cap<Key>() keys.
 // ANY: any order inside a bucket; W: bytes of an index entry (0: none).
-// Both are constants so that a bin carries the code of its own layout only: 60 to 80
-// VGPRs in any order, 110 to 128 stable (whose bins with a bucket of more than kFixMax
+// Both are constants so that a bin carries the code of its own layout only: 57 to 80
+// VGPRs in any order, 101 to 128 stable (whose bins with a bucket of more than kFixMax
 // keys are sorted in registers), and two workgroups per CU need 128.
 template <typename Key, bool ANY, int W>
 __global__ __launch_bounds__(kLocalThreads, 4) void k_local_light(
