@@ -36,7 +36,7 @@ def test_set_allocator_empties_the_pool(hg):
     time.sleep(0.5)
     assert free0 - torch.cuda.mem_get_info()[0] >= 11 * m - (64 << 20)  # the pool keeps it
     hg.set_allocator()
-    for _ in range(100):  # (the driver counts freed memory some time later)
+    for _ in range(100):  # (freed memory is counted some time later)
         if free0 - torch.cuda.mem_get_info()[0] < 64 << 20:
             break
         time.sleep(0.05)
